@@ -1,153 +1,321 @@
-// fp32 attention (correctness configuration): Algorithm 2's per-segment loop over a block list,
-// or Eq. 2 dense causal attention when no list is given.  Plain fp32 FMA flash loop, no reduced
-// precision anywhere: 32 query rows x 32 gathered key tokens per step.
+// fp32 attention: Algorithm 2's per-segment loop over a block list, or Eq. 2 dense causal attention when no list is
+// given.  fp32 operands, products and sums throughout (v_mfma_f32_16x16x4_f32 is an fp32 fused multiply-add).
+//
+// A workgroup owns 16 * RT query rows of one segment (sparse) or of the sequence (dense); its W waves split the KEYS:
+// wave w takes tiles w, w + W, ... of 16 keys, with a running max, sum and output of its own, and the W partial
+// results are merged through LDS at the end.  Per wave and tile:
+//
+//   S^T[key][q]  = K . Q^T      A = K rows, B = Q rows; both sides take the channels in the order 16*kk + 4*g + e
+//                               (g = lane group), so that one 16-byte load per lane feeds four MFMAs
+//   softmax                     one query per lane column, keys 4*g + r: in-lane, then over the four lane groups
+//   O^T[ch][q]  += V^T . P^T    B = P^T is the S^T accumulator as it stands (MFMA r contracts keys 4*g + r); A = V, whose
+//                               rows come in as 16-byte pieces: channel tile (half, e) holds channels 64*half + 4*i + e
+//
+// K and V go from memory straight to registers: the waves of a workgroup read different keys, so there is nothing to
+// share through LDS, and the fp32 matrix rate is a sixteenth of the bf16 one: 16 KB per 2048 * RT matrix cycles and wave
+// are 16 (RT = 2) to 32 (RT = 1) bytes per clock and compute unit, within what L2 delivers.  V of a tile is asked for
+// before its QK, K of the next tile before its softmax and PV.
+//
+// What bounds it: the fp32 matrix instructions, which share their units with the vector instructions (measured: a wave's
+// softmax and address arithmetic add their time to the MFMAs of all waves of the SIMD, at 2.0 vector instructions per MFMA
+// the pipe was busy 57 % of the time, at 0.5 82 %).  So the key loop keeps them few: tiles of 16 consecutive tokens with their
+// addresses on the scalar unit (MODE 1/2), one fma and one exp2 per weight, O rescaled only when a row's max has outgrown
+// its reference point.  Dense, 8 heads x 8192 tokens: 130 TFLOP/s of the 154 that a large library product reaches; 4 heads x
+// 2500 tokens: 530 -> 82 us, block-sparse 4 heads x 4096 tokens 203 -> 60 us, one head x 2048 tokens 80 -> 12.5 us against a
+// vector-FMA loop over 32 x 32 tiles in LDS (12 to 25 TFLOP/s).
 #include "kernels.h"
 
 namespace cp {
 namespace {
 
-constexpr int TQ = 32, TK = 32, PITCH = kHeadDim + 4;   // floats; 528 B rows keep float4 alignment
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 struct Args32 {
     const float* q; const float* k; const float* v; const int32_t* idx; const int32_t* cnt;
     float* out; float* lse;
-    int hq, hkv, n, s, b, n1, list_len, qtiles;   // qtiles: per segment (sparse) or per sequence (dense)
+    int batch, hq, hkv, n, s, b, n1, list_len, qtiles;   // qtiles: per segment (sparse) or per sequence (dense)
     int shared_lists;                             // lists are per (batch, KV head, segment) instead of per query head
-    float scale;
+    float scale_log2e;
     long long qs0, qs1, qs2, ks0, ks1, ks2, os0, os1, os2;
 };
 
-template <bool DENSE>
-__global__ __launch_bounds__(256) void attn_fp32_kernel(Args32 a) {
-    __shared__ __attribute__((aligned(16))) float Qs[TQ * PITCH];
-    __shared__ __attribute__((aligned(16))) float Ks[TK * PITCH];
-    __shared__ __attribute__((aligned(16))) float Vs[TK * PITCH];
-    __shared__ float Ps[TQ * (TK + 1)];
-    __shared__ int Tok[TK];
+constexpr float kLazyLog2 = 8.0f;
 
-    const int tid = threadIdx.x;
-    long long w = blockIdx.x;
-    const int qt = (int)(w % a.qtiles); w /= a.qtiles;
-    int j = 0;
-    if (!DENSE) { j = (int)(w % a.n1); w /= a.n1; }
-    const int h = (int)(w % a.hq); const int bb = (int)(w / a.hq);
-    const int g = h / (a.hq / a.hkv);
+__device__ __forceinline__ float group_max(float x) {               // over the four lane groups: lanes l, l^16, l^32, l^48
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 
-    const int q_lo = DENSE ? qt * TQ : j * a.s + qt * TQ;
-    const int q_end = DENSE ? a.n : min(a.n, (j + 1) * a.s);       // rows >= q_end do not exist
+typedef const __attribute__((address_space(4))) int32_t* scalar_list;   // read through scalar loads: wave-uniform addresses
+
+// MODE 0: any block size and any stride (dense if there is no list): every key of a tile has a token of its own.  MODE 1: sparse, block size a multiple of
+// 16: a tile is 16 consecutive tokens, described by its first token on the scalar unit.  MODE 2: dense.
+template <int MODE, int RT, int W>
+__global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kernel(Args32 a) {
+    constexpr bool RUN = MODE != 0;
+    constexpr int TQ = 16 * RT, TK = 16;
+    constexpr int kNoToken = 0x7fffffff;                            // a key that does not exist: after every query
+    const bool dense = MODE == 2 || (MODE == 0 && !a.idx);
+    __shared__ __attribute__((aligned(16))) float part_o[W * TQ * kHeadDim];   // 16-byte chunks XOR-swizzled by the row
+    __shared__ float part_m[W * TQ], part_l[W * TQ];
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c16 = lane & 15, g = lane >> 4;
+
+    // Consecutive workgroups walk the KV heads, so that a head's keys stay with few XCDs (workgroup id mod 8); the tiles
+    // with most keys, those at the end of the sequence, come first.
+    const int G = a.hq / a.hkv, bkv = a.batch * a.hkv;
+    const int x = blockIdx.x % bkv, y = blockIdx.x / bkv;
+    const int bb = x / a.hkv, kvh = x % a.hkv, h = kvh * G + y % G;
+    const int item = (dense ? a.qtiles : a.n1 * a.qtiles) - 1 - y / G;
+    const int j = dense ? 0 : item / a.qtiles;
+    const int q_lo = dense ? item * TQ : j * a.s + item % a.qtiles * TQ;
+    const int q_end = dense ? a.n : min(a.n, (j + 1) * a.s);       // rows >= q_end do not exist
     if (q_lo >= q_end) return;                                     // uniform: tile past a short segment
     const int q_last = min(q_end, q_lo + TQ) - 1;
-    const float* qp = a.q + bb * a.qs0 + h * a.qs1;
-    const float* kp = a.k + bb * a.ks0 + g * a.ks1;
-    const float* vp = a.v + bb * a.ks0 + g * a.ks1;
+    const float* kp = a.k + bb * a.ks0 + kvh * a.ks1;
+    const float* vp = a.v + bb * a.ks0 + kvh * a.ks1;
 
-    for (int x = tid; x < TQ * 32; x += 256) {
-        const int row = x >> 5, c4 = x & 31;
-        float4 val = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (q_lo + row < q_end) val = *(const float4*)(qp + (long long)(q_lo + row) * a.qs2 + c4 * 4);
-        *(float4*)(Qs + row * PITCH + c4 * 4) = val;
+    scalar_list list = nullptr; int count = 0;
+    if (!dense) {
+        const long long lrow = a.shared_lists ? ((long long)bb * a.hkv + kvh) * a.n1 + j : ((long long)bb * a.hq + h) * a.n1 + j;
+        list = (scalar_list)(unsigned long long)(a.idx + lrow * a.list_len);
+        count = min(max(((scalar_list)(unsigned long long)a.cnt)[lrow], 0), a.list_len);
     }
-
-    const int32_t* list = nullptr; int count = 0;
-    if (!DENSE) {
-        const long long lrow = a.shared_lists ? ((long long)bb * a.hkv + g) * a.n1 + j : ((long long)bb * a.hq + h) * a.n1 + j;
-        list = a.idx + lrow * a.list_len;
-        count = min(max(a.cnt[lrow], 0), a.list_len);
+    f32x4 qf[RT][8];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        const int row = q_lo + 16 * rt + c16;
+        const float* src = a.q + bb * a.qs0 + h * a.qs1 + (long long)min(row, q_last) * a.qs2 + 4 * g;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) qf[rt][kk] = *(const f32x4*)(src + 16 * kk);
     }
-    const long long total = DENSE ? (long long)q_last + 1 : (long long)count * a.b;   // virtual key positions
+    // positions 0 .. total-1 of the listed blocks laid end to end (host checks list_len * b < 2^31)
+    const unsigned total = dense ? (unsigned)q_last + 1u : (unsigned)count * (unsigned)a.b;
     const int ntiles = (int)((total + TK - 1) / TK);
 
-    const int qr = tid >> 3, sub = tid & 7;
-    const int qpos = q_lo + qr;
-    float m = -INFINITY, l = 0.f;
-    float o[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) o[e] = 0.f;
-    constexpr float kLog2e = 1.4426950408889634f;
+    // ---- MODE 1/2: first token of the wave's next tile, -1 past its last one; t: the dense tile --------------------
+    unsigned walk_e = 0, walk_off = 0;                              // list entry and offset inside its block of the next tile
+    if (MODE == 1) { walk_e = (unsigned)wave * TK / (unsigned)a.b; walk_off = (unsigned)wave * TK % (unsigned)a.b; }
+    const unsigned step_e = MODE == 1 ? W * TK / (unsigned)a.b : 0, step_off = MODE == 1 ? W * TK % (unsigned)a.b : 0;
+    const int n2 = MODE == 1 ? (a.n + a.b - 1) / a.b : 0;
+    auto next_base = [&](int t) -> int {                            // call in tile order: t = wave, wave + W, ...
+        if (MODE == 2) return t < ntiles ? t * TK : -1;
+        int base = -1;
+        while (base < 0 && walk_e < (unsigned)count) {              // entries outside the sequence have no tokens
+            const int blk = list[walk_e];
+            base = blk >= 0 && blk < n2 ? blk * a.b + (int)walk_off : -1;
+            if (base >= a.n) base = -1;
+            walk_e += step_e; walk_off += step_off;
+            if (walk_off >= (unsigned)a.b) { walk_off -= a.b; ++walk_e; }
+        }
+        return base;
+    };
+    // ---- MODE 0: token of the lane's key c16 of tile t ---------------------------------------------------------
+    auto key_token = [&](int t) -> int {
+        const unsigned p = (unsigned)t * TK + c16;
+        if (dense) return p < total ? (int)p : kNoToken;
+        const unsigned e = p / (unsigned)a.b;
+        const int blk = ((const int32_t*)(unsigned long long)list)[min(e, (unsigned)max(count - 1, 0))];
+        const long long tk = (long long)blk * a.b + p % (unsigned)a.b;
+        return t < ntiles && e < (unsigned)count && blk >= 0 && tk < a.n ? (int)tk : kNoToken;
+    };
 
-    for (int t = 0; t < ntiles; ++t) {
-        __syncthreads();                                   // previous tile fully consumed
-        for (int x = tid; x < TK * 32; x += 256) {
-            const int row = x >> 5, c4 = x & 31;
-            const long long p = (long long)t * TK + row;
-            int tok; bool valid;
-            if (DENSE) { tok = (int)p; valid = p < total; }
-            else {
-                const int e = (int)(p / a.b);
-                valid = e < count;
-                const long long blk = valid ? list[e] : 0;
-                const long long tk = blk * a.b + (p - (long long)e * a.b);
-                valid = valid && blk >= 0 && tk < a.n;             // entries outside the sequence are masked rows
-                tok = valid ? (int)tk : 0;
-            }
-            float4 kv = make_float4(0.f, 0.f, 0.f, 0.f), vv = kv;
-            if (valid) {
-                kv = *(const float4*)(kp + (long long)tok * a.ks2 + c4 * 4);
-                vv = *(const float4*)(vp + (long long)tok * a.ks2 + c4 * 4);
-            }
-            *(float4*)(Ks + row * PITCH + c4 * 4) = kv;
-            *(float4*)(Vs + row * PITCH + c4 * 4) = vv;
-            if (c4 == 0) Tok[row] = valid ? tok : 0x7fffffff;
+    f32x4 kf[8], vf[4][2];
+    auto load_k = [&](const float* rows, unsigned off) {            // 32-bit byte offset from a wave-uniform address (MODE 1/2)
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) kf[kk] = *(const f32x4*)((const char*)rows + off + 64 * kk);
+    };
+    auto load_v = [&](int r, const float* rows, unsigned off) {
+        vf[r][0] = *(const f32x4*)((const char*)rows + off);
+        vf[r][1] = *(const f32x4*)((const char*)rows + off + 256);
+    };
+    // MODE 1/2: the lane's offsets inside a tile of 16 existing tokens.  In the last, ragged tile of the sequence the rows
+    // past its end repeat the last token; they lie after every query and are masked.
+    const unsigned row_bytes = (unsigned)a.ks2 * 4u;
+    const unsigned k_full = c16 * row_bytes + 16 * g;
+    unsigned v_full[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v_full[r] = (4 * g + r) * row_bytes + 16 * c16;
+    auto load_k_run = [&](int base) {
+        const int b0 = max(base, 0);
+        unsigned off = k_full;
+        if (b0 + TK > a.n) off = min(c16, a.n - 1 - b0) * row_bytes + 16 * g;
+        load_k(kp + (long long)b0 * a.ks2, off);
+    };
+    auto load_v_run = [&](int base) {
+        unsigned off[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) off[r] = v_full[r];
+        if (base + TK > a.n) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) off[r] = min(4 * g + r, a.n - 1 - base) * row_bytes + 16 * c16;
         }
-        __syncthreads();
-        if (Tok[0] > q_last) break;                        // ascending lists: nothing visible from here on
-        // ---- S = scale * Q K^T : thread (qr, sub) owns keys sub, sub+8, sub+16, sub+24
-        float sc[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 8
-        for (int c = 0; c < kHeadDim; c += 4) {
-            const float4 qv = *(const float4*)(Qs + qr * PITCH + c);
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const float4 kv = *(const float4*)(Ks + (sub + 8 * x) * PITCH + c);
-                sc[x] = fmaf(qv.x, kv.x, sc[x]); sc[x] = fmaf(qv.y, kv.y, sc[x]);
-                sc[x] = fmaf(qv.z, kv.z, sc[x]); sc[x] = fmaf(qv.w, kv.w, sc[x]);
+        for (int r = 0; r < 4; ++r) load_v(r, vp + (long long)base * a.ks2, off[r]);
+    };
+    auto load_k_token = [&](int tok) { load_k(kp + (long long)(tok == kNoToken ? 0 : tok) * a.ks2 + 4 * g, 0u); };
+
+    f32x4 o[RT][2][4];
+    float m[RT], l[RT];                                             // m: running max in units of the exponent (log2)
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        m[rt] = -INFINITY; l[rt] = 0.f;
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[rt][hf][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    int base = -1, tok = kNoToken;
+    if (RUN) { base = next_base(wave); load_k_run(base); }
+    else { tok = key_token(wave); load_k_token(tok); }
+    // ascending lists: nothing is visible from the tile on whose first token is past the last row
+    auto more = [&](int t) -> bool {
+        if (RUN) return base >= 0 && base <= q_last;
+        const int first = __builtin_amdgcn_readfirstlane(tok);
+        return t < ntiles && (first <= q_last || first == kNoToken);
+    };
+    for (int t = wave; more(t); t += W) {
+        const int nbase = RUN ? next_base(t + W) : 0;
+        int ktok[4];                                                // MODE 0: the tokens of the accumulator rows 4*g + r
+        if (RUN) load_v_run(base);
+        else {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                ktok[r] = __shfl(tok, 4 * g + r);
+                load_v(r, vp + (long long)(ktok[r] == kNoToken ? 0 : ktok[r]) * a.ks2 + 4 * c16, 0u);
             }
         }
-        float mx = -INFINITY;
+        __builtin_amdgcn_sched_barrier(0);
+        f32x4 s[RT][2 / RT];                                        // two accumulator chains in flight
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            sc[x] = (Tok[sub + 8 * x] <= qpos) ? sc[x] * a.scale : -INFINITY;
-            mx = fmaxf(mx, sc[x]);
-        }
-        mx = fmaxf(mx, __shfl_xor(mx, 1)); mx = fmaxf(mx, __shfl_xor(mx, 2)); mx = fmaxf(mx, __shfl_xor(mx, 4));
-        const float m_new = fmaxf(m, mx);
-        const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-        const float alpha = exp2f((m - m_safe) * kLog2e);
-        float rs = 0.f;
+        for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const float p = exp2f((sc[x] - m_safe) * kLog2e);
-            Ps[qr * (TK + 1) + sub + 8 * x] = p;
-            rs += p;
-        }
-        rs += __shfl_xor(rs, 1); rs += __shfl_xor(rs, 2); rs += __shfl_xor(rs, 4);
-        l = l * alpha + rs;
-        m = m_new;
+            for (int i = 0; i < 2 / RT; ++i) s[rt][i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int e = 0; e < 16; ++e) o[e] *= alpha;
-        __syncthreads();
-        // ---- O += P V : thread (qr, sub) owns channels 4*sub + 32*x .. +3, x = 0..3
-#pragma unroll 4
-        for (int key = 0; key < TK; ++key) {
-            const float p = Ps[qr * (TK + 1) + key];
+        for (int kk = 0; kk < 8; ++kk)
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const float4 vv = *(const float4*)(Vs + key * PITCH + 4 * sub + 32 * x);
-                o[4 * x + 0] = fmaf(p, vv.x, o[4 * x + 0]); o[4 * x + 1] = fmaf(p, vv.y, o[4 * x + 1]);
-                o[4 * x + 2] = fmaf(p, vv.z, o[4 * x + 2]); o[4 * x + 3] = fmaf(p, vv.w, o[4 * x + 3]);
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int rt = 0; rt < RT; ++rt)
+                    s[rt][e % (2 / RT)] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kk][e], qf[rt][kk][e], s[rt][e % (2 / RT)], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        const bool hidden = RUN ? base + TK - 1 > q_lo : __ballot(tok > q_lo) != 0;      // by some row
+        const bool missing = !RUN && __ballot(tok == kNoToken) != 0;
+        if (RUN) load_k_run(nbase);
+        else { tok = key_token(t + W); load_k_token(tok); }
+        __builtin_amdgcn_sched_barrier(0);
+
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) {
+            if (RT == 1) s[rt][0] += s[rt][2 / RT - 1];
+            f32x4& z = s[rt][0];
+            if (hidden) {
+                const int qpos = q_lo + 16 * rt + c16;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if ((RUN ? base + 4 * g + r : ktok[r]) > qpos) z[r] = -INFINITY;
             }
+            float mx = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
+            mx = group_max(mx) * a.scale_log2e;
+            // the reference point moves only when the max has outgrown it by more than kLazyLog2 (see the bf16 kernel): P stays
+            // below 2^kLazyLog2, P, l and O carry one factor, and O is rescaled in the first tiles and then almost never
+            const float m_new = mx > m[rt] + kLazyLog2 ? mx : m[rt];
+            const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
+            const float alpha = __builtin_amdgcn_exp2f(m[rt] - m_safe);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z[r] = __builtin_amdgcn_exp2f(fmaf(z[r], a.scale_log2e, -m_safe));
+            l[rt] = l[rt] * alpha + ((z[0] + z[1]) + (z[2] + z[3]));   // the lane's own keys; the lane groups are added at the end
+            m[rt] = m_new;
+            if (__ballot(alpha != 1.0f) != 0) {
+#pragma unroll
+                for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[rt][hf][e] *= alpha;
+            }
+        }
+        if (missing) {                                              // 0 * V must be 0, whatever token 0 holds
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (ktok[r] == kNoToken) { vf[r][0] = f32x4{0.f, 0.f, 0.f, 0.f}; vf[r][1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+                        o[rt][hf][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][hf][e], s[rt][0][r], o[rt][hf][e], 0, 0, 0);
+        base = nbase;
+    }
+
+    // ---- merge the W partial results: out = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w ----------------------
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        l[rt] += __shfl_xor(l[rt], 16); l[rt] += __shfl_xor(l[rt], 32);
+        const int row = 16 * rt + c16;
+        if (g == 0) { part_m[wave * TQ + row] = m[rt]; part_l[wave * TQ + row] = l[rt]; }
+        float* dst = part_o + (wave * TQ + row) * kHeadDim;
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {                           // channels 64*hf + 16*g + 4*r .. +3
+                const int chunk = (16 * hf + 4 * g + r) ^ c16;
+                *(f32x4*)(dst + 4 * chunk) = f32x4{o[rt][hf][0][r], o[rt][hf][1][r], o[rt][hf][2][r], o[rt][hf][3][r]};
+            }
+    }
+    __syncthreads();
+    float* op = a.out + bb * a.os0 + h * a.os1;
+#pragma unroll
+    for (int c = 0; c < TQ * 32 / (64 * W); ++c) {
+        const int row = (c * 64 * W + tid) >> 5, chunk = tid & 31;
+        float M = -INFINITY, L = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) M = fmaxf(M, part_m[w * TQ + row]);
+        const float M_safe = (M == -INFINITY) ? 0.f : M;
+        f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const float f = __builtin_amdgcn_exp2f(part_m[w * TQ + row] - M_safe);
+            L += f * part_l[w * TQ + row];
+            sum += f * *(const f32x4*)(part_o + (w * TQ + row) * kHeadDim + 4 * (chunk ^ (row & 15)));
+        }
+        const int qpos = q_lo + row;
+        if (qpos < q_end) {
+            const float inv = L > 0.f ? 1.0f / L : 0.f;
+            *(f32x4*)(op + (long long)qpos * a.os2 + 4 * chunk) = sum * inv;
+            if (a.lse && chunk == 0)
+                a.lse[((long long)bb * a.hq + h) * a.n + qpos] = L > 0.f ? M * 0.6931471805599453f + logf(L) : -INFINITY;
         }
     }
-    if (qpos < q_end) {
-        const float inv = l > 0.f ? 1.0f / l : 0.f;
-        float* op = a.out + bb * a.os0 + h * a.os1 + (long long)qpos * a.os2;
-#pragma unroll
-        for (int x = 0; x < 4; ++x)
-            *(float4*)(op + 4 * sub + 32 * x) =
-                make_float4(o[4 * x] * inv, o[4 * x + 1] * inv, o[4 * x + 2] * inv, o[4 * x + 3] * inv);
-        if (a.lse && sub == 0)
-            a.lse[((long long)bb * a.hq + h) * a.n + qpos] = l > 0.f ? m + logf(l) : -INFINITY;
-    }
+}
+
+template <int MODE, int RT, int W>
+hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
+    a.qtiles = ((a.idx ? sh.s : sh.n) + 16 * RT - 1) / (16 * RT);
+    const long long grid = (long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1);
+    hipLaunchKernelGGL((attn_fp32_kernel<MODE, RT, W>), dim3((unsigned)grid), dim3(64 * W), 0, st, a);
+    return hipGetLastError();
+}
+
+// 32 rows per workgroup halve the K/V bytes and the softmax instructions per MFMA (130 against 115 TFLOP/s at 8 heads x 8192
+// tokens); 16 rows give twice the workgroups, and a short sequence needs them: one head x 2048 tokens 42 us at 16 rows, 74 at
+// 32; dense 4 heads x 2500 (316 workgroups of 32 rows) 82 / 90; 4 x 3300 (416) 128 / 117; 8 x 2000 (504) 95 / 85.  Eight waves
+// split a long row further and leave one workgroup to a compute unit, which evens out unequal rows (dense 8 x 4000: 285
+// against 306 us for four); four waves are better where rows are short (4 x 4096, 704 keys: 60 / 65) or workgroups many
+// (16 x 4096: 544 / 578).
+template <int MODE>
+hipError_t launch_tiled(const Shape& sh, Args32& a, hipStream_t st) {
+    const long long wide = (long long)sh.batch * sh.hq * (a.idx ? (long long)sh.n1 * ((sh.s + 31) / 32) : (sh.n + 31) / 32);
+    const long long keys = a.idx ? min((long long)sh.n, (long long)sh.list_len * sh.b) : sh.n;
+    if (wide < 384) return keys > 1024 ? launch<MODE, 1, 8>(sh, a, st) : launch<MODE, 1, 4>(sh, a, st);
+    return wide < 1536 && keys >= 1536 ? launch<MODE, 2, 8>(sh, a, st) : launch<MODE, 2, 4>(sh, a, st);
 }
 
 }  // namespace
@@ -157,22 +325,16 @@ hipError_t launch_attn_fp32(const Shape& sh, const void* q, const void* k, const
     Args32 a;
     a.q = (const float*)q; a.k = (const float*)k; a.v = (const float*)v; a.idx = idx; a.cnt = cnt;
     a.out = (float*)out; a.lse = lse;
-    a.hq = sh.hq; a.hkv = sh.hkv; a.n = sh.n; a.s = sh.s; a.b = sh.b; a.n1 = sh.n1; a.list_len = sh.list_len;
+    a.batch = sh.batch; a.hq = sh.hq; a.hkv = sh.hkv; a.n = sh.n; a.s = sh.s; a.b = sh.b; a.n1 = sh.n1; a.list_len = sh.list_len;
     a.shared_lists = shared_lists ? 1 : 0;
-    a.scale = sh.attn_scale;
+    a.scale_log2e = sh.attn_scale * 1.4426950408889634f;
     a.qs0 = sh.qs[0]; a.qs1 = sh.qs[1]; a.qs2 = sh.qs[2];
     a.ks0 = sh.kvs[0]; a.ks1 = sh.kvs[1]; a.ks2 = sh.kvs[2];
     a.os0 = sh.os[0]; a.os1 = sh.os[1]; a.os2 = sh.os[2];
-    if (idx) {
-        a.qtiles = (sh.s + TQ - 1) / TQ;
-        const long long grid = (long long)sh.batch * sh.hq * sh.n1 * a.qtiles;
-        hipLaunchKernelGGL(attn_fp32_kernel<false>, dim3((unsigned)grid), dim3(256), 0, st, a);
-    } else {
-        a.qtiles = (sh.n + TQ - 1) / TQ;
-        const long long grid = (long long)sh.batch * sh.hq * a.qtiles;
-        hipLaunchKernelGGL(attn_fp32_kernel<true>, dim3((unsigned)grid), dim3(256), 0, st, a);
-    }
-    return hipGetLastError();
+    const bool near = sh.kvs[2] < (1 << 26);                        // a tile's rows are within 32-bit byte offsets of its first
+    if (!idx && near) return launch_tiled<2>(sh, a, st);
+    if (idx && near && sh.b % 16 == 0) return launch_tiled<1>(sh, a, st);
+    return launch<0, 2, 4>(sh, a, st);
 }
 
 }  // namespace cp

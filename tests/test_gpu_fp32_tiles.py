@@ -1,0 +1,70 @@
+"""The fp32 attention kernel at the borders of its variants: 16 or 32 rows per workgroup, keys split over 4 or 8 waves,
+tiles of 16 consecutive tokens or one token per key.  Against the fp64 checker with the fp32 bars of the other tests
+(unit-variance inputs, so logits of a few units: 128 products and the weighted sum round to about 1e-6)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import critiprefill_oracle as O
+from paper_2409_12490_amd import binding as B
+from paper_2409_12490_amd import synth
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+SHAPES = [
+    # Hq Hkv   n     s    b    k  L
+    (1, 1, 1, 16, 16, 1, 0),              # one query, one key
+    (2, 1, 271, 128, 16, 3, 1),           # 16 rows, 4 waves, most of them without a tile; a last tile of 15 tokens
+    (2, 2, 1553, 288, 48, 40, 0),         # 16 rows, 8 waves; 48 does not divide 8 x 16 keys
+    (8, 4, 1601, 128, 32, 60, 1),         # 32 rows, 8 waves; a last row tile of one row
+    (8, 2, 2064, 256, 64, 4, 1),          # 32 rows: 4 waves for the short lists, 8 for dense
+    (16, 4, 3120, 512, 128, 16, 0),       # 32 rows, 4 waves: many workgroups
+    (3, 1, 500, 72, 24, 4, 1),            # blocks of 24: one token per key; segments no multiple of a row tile
+]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda c: "x".join(map(str, c)))
+def test_variants_against_checker(shape):
+    Hq, Hkv, n, s, b, k, L = shape
+    w = H.small_workload("fp32tiles", 1, Hq, Hkv, n, s, b, k, L, dtype="fp32", unit_variance=n > 1)
+    q, k_, v = synth.make_qkv(w, threads=8)
+    qf, kf, vf = (synth.to_f64(t) for t in (q, k_, v))
+    q, k_, v = q.to(DEV), k_.to(DEV), v.to(DEV)
+    g = np.random.default_rng(n)
+    Sd = g.random((1, Hq, w.n_segments, w.n_blocks), dtype=np.float32)
+    idx, cnt = O.select(Sd, s, b, k, L)
+    heads, segs = sorted({0, Hq - 1}), sorted({0, w.n_segments // 2, w.n_segments - 1})
+    todo = [(0, h, j) for h in heads for j in segs]
+    o_ref, lse_ref = O.sparse_attention(qf, kf, vf, idx, cnt, s, b, segments=todo)
+    out, lse = (t.cpu().numpy() for t in H.gpu_sparse(w, q, k_, v, torch.from_numpy(idx).to(DEV), torch.from_numpy(cnt).to(DEV)))
+    assert np.isfinite(out).all() and np.isfinite(lse).all()
+    for (_, h, j) in todo:
+        rows = slice(j * s, min(n, (j + 1) * s))
+        assert H.max_abs(out[0, h, rows], o_ref[0, h, rows]) <= H.TOL_OUT["fp32"], (h, j)
+        assert H.max_abs(lse[0, h, rows], lse_ref[0, h, rows]) <= 1e-4, (h, j)
+    rows = np.unique(np.concatenate([np.arange(min(n, 40)), np.arange(max(0, n - 40), n), g.integers(0, n, 40)]))
+    d_ref, dl_ref = O.dense_causal_attention(qf, kf, vf, rows=rows)
+    out, lse = (t.cpu().numpy() for t in H.gpu_dense(w, q, k_, v))
+    assert np.isfinite(out).all()
+    assert H.max_abs(out[:, :, rows], d_ref) <= H.TOL_OUT["fp32"]
+    assert H.max_abs(lse[:, :, rows], dl_ref) <= 1e-4
+
+
+def test_token_stride_beyond_32_bit_offsets():
+    """A token stride of 2^26 elements (256 MB): byte offsets inside a tile of 16 tokens no longer fit 32 bits."""
+    n, stride = 19, 1 << 26
+    w = H.small_workload("wide", 1, 1, 1, n, 16, 16, 1, 0, dtype="fp32", unit_variance=True)
+    q, k, v = synth.make_qkv(w)
+    rows = torch.empty((n - 1) * stride + 256, dtype=torch.float32, device=DEV)
+    kd = rows.as_strided((1, 1, n, 128), (0, 0, stride, 1), 0)
+    vd = rows.as_strided((1, 1, n, 128), (0, 0, stride, 1), 128)
+    kd.copy_(k); vd.copy_(v)
+    qd = q.to(DEV)
+    d_ref, _ = O.dense_causal_attention(synth.to_f64(q), synth.to_f64(k), synth.to_f64(v))
+    out, _ = H.gpu_dense(w, qd, kd, vd)
+    assert H.max_abs(out.cpu().numpy(), d_ref) <= H.TOL_OUT["fp32"]
+    idx, cnt = O.select(np.ones((1, 1, w.n_segments, w.n_blocks), np.float32), 16, 16, 1, 0)      # every block: dense again
+    out, _ = H.gpu_sparse(w, qd, kd, vd, torch.from_numpy(idx).to(DEV), torch.from_numpy(cnt).to(DEV))
+    assert H.max_abs(out.cpu().numpy(), d_ref) <= H.TOL_OUT["fp32"]
