@@ -27,132 +27,108 @@ struct PoolArgs {
     const void* q; const void* k; void* qrep; void* krep;
     int n, s, b, n1, n2, hq, hkv;
     long long q_groups, k_groups;          // B*Hq*n1, B*Hkv*n2
+    long long q_wgs;                       // workgroups that pool Q; the rest pool K
+    int q_split, k_split;                  // waves that share one group: 1, 2, 4 or 8
     long long qs0, qs1, qs2, ks0, ks1, ks2;
 };
 
-// One wavefront per group (a segment of Q or a block of K).  bf16: a lane owns 8 channels (16 B),
-// 16 lanes cover one 256 B token row, the wave covers 4 rows per load.
-__global__ __launch_bounds__(256) void pool_bf16_kernel(PoolArgs a) {
-    const int lane = threadIdx.x & 63;
-    const long long gid = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (gid >= a.q_groups + a.k_groups) return;
-    const uint16_t* src; uint16_t* dst; long long tok_stride; int t0, t1;
-    if (gid < a.q_groups) {
-        const int j = (int)(gid % a.n1); const long long bh = gid / a.n1;
-        const int h = (int)(bh % a.hq); const int bb = (int)(bh / a.hq);
-        src = (const uint16_t*)a.q + bb * a.qs0 + h * a.qs1; tok_stride = a.qs2;
-        t0 = j * a.s; t1 = min(a.n, t0 + a.s);
-        dst = (uint16_t*)a.qrep + gid * 2 * kHeadDim;
-    } else {
-        const long long g = gid - a.q_groups;
-        const int i = (int)(g % a.n2); const long long bh = g / a.n2;
-        const int h = (int)(bh % a.hkv); const int bb = (int)(bh / a.hkv);
-        src = (const uint16_t*)a.k + bb * a.ks0 + h * a.ks1; tok_stride = a.ks2;
-        t0 = i * a.b; t1 = min(a.n, t0 + a.b);
-        dst = (uint16_t*)a.krep + g * 2 * kHeadDim;
-    }
-    const int chunk = lane & 15, rsub = lane >> 4;
-    float hi[8], lo[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) { hi[e] = -INFINITY; lo[e] = INFINITY; }
-    const uint16_t* p = src + (long long)(t0 + rsub) * tok_stride + chunk * 8;
-    int t = t0 + rsub;
-    for (; t + 28 < t1; t += 32) {           // eight independent 16 B loads in flight
-        uint4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = load_once(p + (long long)(4 * u) * tok_stride);
-        p += 32 * tok_stride;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float x0 = bf16_lo(w[e]), x1 = bf16_hi(w[e]);
-                hi[2 * e] = fmaxf(hi[2 * e], x0); lo[2 * e] = fminf(lo[2 * e], x0);
-                hi[2 * e + 1] = fmaxf(hi[2 * e + 1], x1); lo[2 * e + 1] = fminf(lo[2 * e + 1], x1);
-            }
-        }
-    }
-    for (; t + 12 < t1; t += 16) {           // four independent 16 B loads in flight
-        uint4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = load_once(p + (long long)(4 * u) * tok_stride);
-        p += 16 * tok_stride;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float x0 = bf16_lo(w[e]), x1 = bf16_hi(w[e]);
-                hi[2 * e] = fmaxf(hi[2 * e], x0); lo[2 * e] = fminf(lo[2 * e], x0);
-                hi[2 * e + 1] = fmaxf(hi[2 * e + 1], x1); lo[2 * e + 1] = fminf(lo[2 * e + 1], x1);
-            }
-        }
-    }
-    for (; t < t1; t += 4) {
-        const uint4 v = load_once(p); p += 4 * tok_stride;
+constexpr int kPoolWaves = 8;
+
+// 16 bytes of one token row, as floats
+template <typename T> struct PoolVec;
+template <> struct PoolVec<uint16_t> {
+    static constexpr int kElems = 8;
+    static __device__ __forceinline__ void widen(const uint4& v, float (&x)[8]) {
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float x0 = bf16_lo(w[e]), x1 = bf16_hi(w[e]);
-            hi[2 * e] = fmaxf(hi[2 * e], x0); lo[2 * e] = fminf(lo[2 * e], x0);
-            hi[2 * e + 1] = fmaxf(hi[2 * e + 1], x1); lo[2 * e + 1] = fminf(lo[2 * e + 1], x1);
+        for (int e = 0; e < 4; ++e) { x[2 * e] = bf16_lo(w[e]); x[2 * e + 1] = bf16_hi(w[e]); }
+    }
+    static __device__ __forceinline__ uint4 narrow(const float (&x)[8]) {
+        return make_uint4(pack_bf16_exact(x[0], x[1]), pack_bf16_exact(x[2], x[3]), pack_bf16_exact(x[4], x[5]), pack_bf16_exact(x[6], x[7]));
+    }
+};
+template <> struct PoolVec<float> {
+    static constexpr int kElems = 4;
+    static __device__ __forceinline__ void widen(const uint4& v, float (&x)[4]) {
+        x[0] = __uint_as_float(v.x); x[1] = __uint_as_float(v.y); x[2] = __uint_as_float(v.z); x[3] = __uint_as_float(v.w);
+    }
+    static __device__ __forceinline__ uint4 narrow(const float (&x)[4]) {
+        return make_uint4(__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3]));
+    }
+};
+
+// A group is a segment of Q or a block of K; `split` waves of a workgroup share one and merge through LDS.  A lane owns 16 bytes
+// of a token row, kLanes lanes cover the row, a wave kRows rows per load with eight loads in flight (a batch).
+//
+// Bound by HBM for long sequences (1.34 GB at 32 + 8 heads x 128K tokens: 5.7 to 6.4 TB/s; a plain copy moves 5.2 here) and by
+// the latency of a wave's batches, one after another, for short ones: with a wave to a group, 2000 tokens took 11.7 us.
+template <typename T>
+__global__ __launch_bounds__(64 * kPoolWaves) void pool_kernel(PoolArgs a) {
+    constexpr int E = PoolVec<T>::kElems, kLanes = kHeadDim / E, kRows = 64 / kLanes, kLoads = 8, kBatch = kLoads * kRows;
+    __shared__ __attribute__((aligned(16))) float part[kPoolWaves][2][kHeadDim];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const bool is_q = (long long)blockIdx.x < a.q_wgs;
+    const int split = is_q ? a.q_split : a.k_split;
+    const int slot = wave / split, share = wave % split;
+    const long long gid = (is_q ? (long long)blockIdx.x : (long long)blockIdx.x - a.q_wgs) * (kPoolWaves / split) + slot;
+    const bool there = gid < (is_q ? a.q_groups : a.k_groups);
+    const int chunk = lane % kLanes, rsub = lane / kLanes;
+    float hi[E], lo[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) { hi[e] = -INFINITY; lo[e] = INFINITY; }
+    auto merge = [&](const uint4& v) {
+        float x[E];
+        PoolVec<T>::widen(v, x);
+#pragma unroll
+        for (int e = 0; e < E; ++e) { hi[e] = fmaxf(hi[e], x[e]); lo[e] = fminf(lo[e], x[e]); }
+    };
+    if (there) {
+        const int groups = is_q ? a.n1 : a.n2, heads = is_q ? a.hq : a.hkv, size = is_q ? a.s : a.b;
+        const int i = (int)(gid % groups); const long long bh = gid / groups;
+        const int h = (int)(bh % heads), bb = (int)(bh / heads);
+        const long long stride = is_q ? a.qs2 : a.ks2;
+        const T* src = (is_q ? (const T*)a.q + bb * a.qs0 + h * a.qs1 : (const T*)a.k + bb * a.ks0 + h * a.ks1) + chunk * E;
+        const int t0 = i * size, t1 = (int)min((long long)a.n, (long long)t0 + size);
+        int t = t0 + share * kBatch;
+        for (; t + kBatch <= t1; t += split * kBatch) {
+            const T* p = src + (long long)(t + rsub) * stride;
+            uint4 v[kLoads];
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) v[u] = load_once(p + (long long)(kRows * u) * stride);
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) merge(v[u]);
+        }
+        if (t < t1) {                          // the group's last, short batch: rows past the end repeat its last row
+            uint4 v[kLoads];
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) v[u] = load_once(src + (long long)min(t + kRows * u + rsub, t1 - 1) * stride);
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) merge(v[u]);
         }
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        hi[e] = fmaxf(hi[e], __shfl_xor(hi[e], 16)); hi[e] = fmaxf(hi[e], __shfl_xor(hi[e], 32));
-        lo[e] = fminf(lo[e], __shfl_xor(lo[e], 16)); lo[e] = fminf(lo[e], __shfl_xor(lo[e], 32));
-    }
-    if (rsub == 0) {
-        uint4 o;
-        o.x = pack_bf16_exact(hi[0], hi[1]); o.y = pack_bf16_exact(hi[2], hi[3]);
-        o.z = pack_bf16_exact(hi[4], hi[5]); o.w = pack_bf16_exact(hi[6], hi[7]);
-        *(uint4*)(dst + chunk * 8) = o;
-        o.x = pack_bf16_exact(lo[0], lo[1]); o.y = pack_bf16_exact(lo[2], lo[3]);
-        o.z = pack_bf16_exact(lo[4], lo[5]); o.w = pack_bf16_exact(lo[6], lo[7]);
-        *(uint4*)(dst + kHeadDim + chunk * 8) = o;
-    }
-}
-
-// fp32: a lane owns 4 channels (16 B), 32 lanes cover one 512 B row, the wave covers 2 rows per load.
-__global__ __launch_bounds__(256) void pool_fp32_kernel(PoolArgs a) {
-    const int lane = threadIdx.x & 63;
-    const long long gid = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (gid >= a.q_groups + a.k_groups) return;
-    const float* src; float* dst; long long tok_stride; int t0, t1;
-    if (gid < a.q_groups) {
-        const int j = (int)(gid % a.n1); const long long bh = gid / a.n1;
-        const int h = (int)(bh % a.hq); const int bb = (int)(bh / a.hq);
-        src = (const float*)a.q + bb * a.qs0 + h * a.qs1; tok_stride = a.qs2;
-        t0 = j * a.s; t1 = min(a.n, t0 + a.s);
-        dst = (float*)a.qrep + gid * 2 * kHeadDim;
-    } else {
-        const long long g = gid - a.q_groups;
-        const int i = (int)(g % a.n2); const long long bh = g / a.n2;
-        const int h = (int)(bh % a.hkv); const int bb = (int)(bh / a.hkv);
-        src = (const float*)a.k + bb * a.ks0 + h * a.ks1; tok_stride = a.ks2;
-        t0 = i * a.b; t1 = min(a.n, t0 + a.b);
-        dst = (float*)a.krep + g * 2 * kHeadDim;
-    }
-    const int chunk = lane & 31, rsub = lane >> 5;
-    float hi[4], lo[4];
+    for (int o = kLanes; o < 64; o *= 2)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { hi[e] = -INFINITY; lo[e] = INFINITY; }
-    for (int t = t0 + rsub; t < t1; t += 2) {
-        const float4 v = *(const float4*)(src + (long long)t * tok_stride + chunk * 4);
-        const float x[4] = {v.x, v.y, v.z, v.w};
+        for (int e = 0; e < E; ++e) { hi[e] = fmaxf(hi[e], __shfl_xor(hi[e], o)); lo[e] = fminf(lo[e], __shfl_xor(lo[e], o)); }
+    if (split > 1) {                           // uniform over the workgroup
+        if (rsub == 0) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { hi[e] = fmaxf(hi[e], x[e]); lo[e] = fminf(lo[e], x[e]); }
-    }
+            for (int e = 0; e < E; ++e) { part[wave][0][chunk * E + e] = hi[e]; part[wave][1][chunk * E + e] = lo[e]; }
+        }
+        __syncthreads();
+        if (share != 0) return;
+        for (int w = 1; w < split; ++w)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        hi[e] = fmaxf(hi[e], __shfl_xor(hi[e], 32));
-        lo[e] = fminf(lo[e], __shfl_xor(lo[e], 32));
+            for (int e = 0; e < E; ++e) {
+                hi[e] = fmaxf(hi[e], part[wave + w][0][chunk * E + e]);
+                lo[e] = fminf(lo[e], part[wave + w][1][chunk * E + e]);
+            }
     }
-    if (rsub == 0) {
-        *(float4*)(dst + chunk * 4) = make_float4(hi[0], hi[1], hi[2], hi[3]);
-        *(float4*)(dst + kHeadDim + chunk * 4) = make_float4(lo[0], lo[1], lo[2], lo[3]);
+    if (there && rsub == 0) {
+        T* dst = (T*)(is_q ? a.qrep : a.krep) + gid * 2 * kHeadDim;
+        *(uint4*)(dst + chunk * E) = PoolVec<T>::narrow(hi);
+        *(uint4*)(dst + kHeadDim + chunk * E) = PoolVec<T>::narrow(lo);
     }
 }
 
@@ -583,6 +559,17 @@ __global__ __launch_bounds__(64 * kScoreWaves, 4) void score_write_kernel(ScoreA
 
 }  // namespace
 
+// Every wave of a group gets at least one batch, and two where there are enough groups to fill the chip.  The whole estimate step
+// with 1 / 2 / 4 / 8 waves per segment: 32 heads x 2000 tokens 26.8 / 22.2 / 19.6 / 19.2 us, x 4096 35.7 / 26.4 / 21.3 / 20.3, x 128K
+// (512 tokens a segment) 280 / 269 / 271 / 267 and, with Q token-major, 315 / 273 / 275 / 274; two batches of 256-token segments
+// (batch 2, 64K) 364 at four waves, 375 at eight with one batch each.  fp32, 8 heads x 8192: 47 / 31 / 23 / 19.
+static int pool_split(const Shape& sh, int size, long long groups) {
+    const int batch = sh.dtype == 1 ? 32 : 16;
+    int split = 1;
+    while (split < kPoolWaves && 2 * split * batch <= size && (groups * split < 4096 || 4 * split * batch <= size)) split *= 2;
+    return split;
+}
+
 hipError_t launch_pool(const Shape& sh, const void* q, const void* k, void* qrep, void* krep, hipStream_t st) {
     PoolArgs a;
     a.q = q; a.k = k; a.qrep = qrep; a.krep = krep;
@@ -591,10 +578,11 @@ hipError_t launch_pool(const Shape& sh, const void* q, const void* k, void* qrep
     a.k_groups = (long long)sh.batch * sh.hkv * sh.n2;
     a.qs0 = sh.qs[0]; a.qs1 = sh.qs[1]; a.qs2 = sh.qs[2];
     a.ks0 = sh.kvs[0]; a.ks1 = sh.kvs[1]; a.ks2 = sh.kvs[2];
-    const long long groups = a.q_groups + a.k_groups;
-    const unsigned grid = (unsigned)((groups + 3) / 4);
-    if (sh.dtype == 1) hipLaunchKernelGGL(pool_bf16_kernel, dim3(grid), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL(pool_fp32_kernel, dim3(grid), dim3(256), 0, st, a);
+    a.q_split = pool_split(sh, sh.s, a.q_groups); a.k_split = pool_split(sh, sh.b, a.k_groups);
+    a.q_wgs = (a.q_groups * a.q_split + kPoolWaves - 1) / kPoolWaves;
+    const unsigned grid = (unsigned)(a.q_wgs + (a.k_groups * a.k_split + kPoolWaves - 1) / kPoolWaves);
+    if (sh.dtype == 1) hipLaunchKernelGGL(pool_kernel<uint16_t>, dim3(grid), dim3(64 * kPoolWaves), 0, st, a);
+    else hipLaunchKernelGGL(pool_kernel<float>, dim3(grid), dim3(64 * kPoolWaves), 0, st, a);
     return hipGetLastError();
 }
 

@@ -1,0 +1,23 @@
+"""The pooling kernel with 1, 2, 4 and 8 waves to a segment or block, and groups of every remainder of a batch (32 bf16 or 16 fp32
+rows): the scores of the estimate step against the fp64 checker, with the bar of the other score tests."""
+import numpy as np
+import pytest
+
+from oracle import critiprefill_oracle as O
+from paper_2409_12490_amd import synth
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("shape", [(1, 1, 1, 16, 16), (2, 1, 97, 32, 32), (2, 2, 1055, 128, 64), (3, 1, 1601, 512, 512), (1, 1, 3000, 1024, 8),
+                                   (32, 4, 8197, 64, 64)], ids=lambda c: "x".join(map(str, c)))
+def test_scores_for_every_split(shape, dtype):
+    Hq, Hkv, n, s, b = shape
+    w = H.small_workload("pool", 1, Hq, Hkv, n, s, b, 2, 0, dtype=dtype, unit_variance=n > 1)
+    q, k, v = synth.make_qkv(w, threads=8)
+    S_o = O.estimate(synth.to_f64(q), synth.to_f64(k), s, b)
+    S_g = H.gpu_estimate(w, q.to(DEV), k.to(DEV)).cpu().numpy()
+    np.testing.assert_allclose(S_g, S_o, rtol=2e-4, atol=1e-30)
