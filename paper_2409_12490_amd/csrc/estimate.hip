@@ -137,16 +137,19 @@ __global__ __launch_bounds__(64 * kPoolWaves) void pool_kernel(PoolArgs a) {
 // ---------------------------------------------------------------------------------------------
 struct ScoreArgs {
     const void* qrep; const void* krep; const float* prev; float* scores;
-    float* stats;                          // bf16 path: per-chunk softmax statistics (see score_stats_kernel)
+    float* stats;                          // bf16 path: per-chunk softmax statistics (see score_kernel)
     int hq, hkv, n1, n2, r, domain;
     int nchunk, n1_pad;
-    int parts;                             // bf16 path: waves that share 16 segments and split the tiles of a chunk (1, 2, 4, 8)
+    int parts;                             // bf16 path: waves that share a group and split the tiles of a chunk (1, 2, 4, 8)
+    int wg_groups;                         // bf16 path: groups of 16 * GPW segments per workgroup
     float scale, alpha;
 };
-constexpr int kScoreWaves = 8;             // waves per workgroup of the bf16 score kernels, 16 segments each
-constexpr int kScoreSegPerWg = 16 * kScoreWaves;
-constexpr int kScoreChunk = 256;           // blocks per workgroup
-constexpr int kScorePiece = 64;            // blocks per LDS buffer (32 KiB of representatives), two buffers
+constexpr int kScoreWaves = 8;             // waves per workgroup of the bf16 score kernel
+constexpr int kTileBlocks = 32;            // blocks per MFMA tile
+constexpr int kTileBytes = kTileBlocks * 2 * kHeadDim * 2;   // max row + min row per block, bf16
+constexpr int kChunkTiles = 8;             // tiles per workgroup, all of them in LDS (128 KiB)
+constexpr int kScoreChunk = kChunkTiles * kTileBlocks;
+constexpr int kScoreWgs = 256;             // workgroups that fill the chip, one to a compute unit
 
 __device__ __forceinline__ float block_reduce_max(float v, float* red) {
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
@@ -232,22 +235,33 @@ __global__ __launch_bounds__(256) void score_valu_kernel(ScoreArgs a) {
 // score, bf16: the four representative products as bf16 MFMA GEMMs (representatives are exact bf16
 // values, so every product is exact and only the fp32 accumulation rounds).
 //
-// The blocks of a (batch, head) are cut into chunks of 256; a workgroup = 8 waves takes one chunk and 128
-// segments, wave w the segments 16w .. 16w+15.  Z^T = K_rep . Q_rep^T: the A operand is a tile of 32 blocks
-// of K_max (then K_min); the chunk's representatives go global -> LDS once for all eight waves in four
-// pieces of 64 blocks (global_load_lds, no register staging, two 32 KiB buffers: the next piece lands while
-// the current one is used; two workgroups per compute unit); the B operand, column n = (segment n >> 1, representative n & 1), stays in
-// registers.  A lane then holds, for its column, 16 blocks of the tile in registers: the softmax
-// statistics over blocks are in-lane reductions plus one exchange between the wave halves, and the two
-// query representatives of a segment sit in neighbouring lanes (one DPP exchange per score).
+// The blocks of a (batch, head) are cut into tiles of 32 and the tiles into chunks of eight; a workgroup keeps the K
+// representatives of one chunk in LDS (128 KiB, copied once by global_load_lds, 16-byte pieces XOR-swizzled by the block) and
+// its 8 waves walk groups of 16 * GPW segments over them, with no further barrier.  Z^T = K_rep . Q_rep^T: the A operand is
+// a tile of 32 blocks of K_max (then K_min), the B operand, column = (segment, max/min representative), stays in registers.
+// A lane then holds, for its column, 16 blocks of the tile in registers: the softmax statistics over blocks are in-lane
+// reductions plus one exchange between the wave halves, and the two query representatives of a segment sit in neighbouring lanes
+// (one DPP exchange per score).  A short sequence has fewer groups than waves: `parts` waves then share a group and split
+// its tiles.
 //
-//   score_stats_kernel   per chunk and column: max and sum of 2^(c z - max) of the two products  -> stats
-//   score_write_kernel   merges the chunk statistics, recomputes the products of its chunk, normalises,
-//                        combines (S1+S3)/2 vs (S2+S4)/2, masks, fuses, stores.  Chunks that lie wholly
-//                        after every segment of the workgroup are written without any product.
+//   PASS 0   per chunk and column: max and sum of 2^(c z - max) of the two products  -> stats
+//   PASS 1   merges the chunk statistics, recomputes the products of its chunk, normalises, combines (S1+S3)/2 vs
+//            (S2+S4)/2, masks, fuses, stores.  Tiles that lie wholly after a group are written without any product.
+//   PASS 2   both in one launch, for rows of a single chunk (n2 <= 256): the statistics stay in LDS.
+//
+// A chunk is four tiles from the front of the row and the four that mirror them from its end, so that every workgroup has the
+// same share of the causal half.
+//
+// What bounds it: PASS 0 the vector unit (171 vector instructions, 34 of them exponentials, per 16 segments and tile: 53K of
+// the 106K busy cycles of a compute unit at 2 x 32 heads x 64K tokens, the MFMAs beside them) and the 5 to 7 us until a chunk has
+// landed; PASS 1 the latency of S' and of the stores (2.7 TB/s there).  Against eight waves that streamed their chunk
+// through two 32 KiB buffers, with a barrier per 64 blocks and 128 segments of one chunk to a workgroup, the estimate step takes,
+// same pooling: 32 heads x 2000 tokens 19.2 -> 13.7 us (one launch less), x 4096 20.3 -> 16.1, x 16K 48.4 -> 37.6, 2 x 2 heads x 84K
+// 57 -> 37, 32 x 128K 268 -> 263, 2 x 32 x 64K with fusion 373 -> 356, 8 x 128K in blocks of 16 with fusion 351 -> 320.
 // ---------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 #define SCORE_LDS(T, off) ((__attribute__((address_space(3))) T*)(uintptr_t)(off))
 
@@ -269,288 +283,321 @@ __device__ __forceinline__ float neighbour(float x) {      // the value of lane 
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, true));
 }
 
-struct ScoreTile {
-    static constexpr int kTileBlocks = 32;                  // blocks per MFMA tile
-    static constexpr int kTileBytes = kTileBlocks * 2 * kHeadDim * 2;   // max row + min row per block, bf16
-};
-
-// The part both kernels share: the workgroup's coordinates, the B operand, the staged A tiles.
-struct ScoreCtx {
-    int lane, wave, l32, hh;
-    int part;                                               // tiles nt = part (mod parts) of the chunk are this wave's
-    int chunk, j0, seg, rep, h, bb_;
-    int i_begin, i_end, ntile;                              // blocks of the chunk, tiles of 32
-    long long qrow0;                                        // row of segment 0 of this (batch, head) in scores
-    const uint16_t* ksrc;                                   // K representatives of block 0 of this KV head
-    int vis;                                                // first block wholly after the lane's segment
-    int vis_wg;                                             // ... after the last segment of the workgroup
-    int vis_wave, vis_wave_max;                             // ... after the first / last segment of the wave
-    bf16x8 qf[8];
-    unsigned lds0;
-};
-
-__device__ __forceinline__ void score_setup(const ScoreArgs& a, ScoreCtx& c, unsigned lds0) {
-    const int tid = threadIdx.x;
-    c.lane = tid & 63; c.wave = tid >> 6; c.l32 = c.lane & 31; c.hh = c.lane >> 5;
-    c.chunk = blockIdx.x;
-    // a short sequence has fewer than 8 x 16 segments: waves then share their 16 segments and split the tiles
-    const int seg_waves = kScoreWaves / a.parts;
-    c.part = c.wave / seg_waves;
-    c.j0 = blockIdx.y * kScoreSegPerWg + 16 * (c.wave % seg_waves);
-    c.h = blockIdx.z % a.hq; c.bb_ = blockIdx.z / a.hq;
-    c.seg = c.j0 + (c.l32 >> 1); c.rep = c.l32 & 1;
-    c.i_begin = c.chunk * kScoreChunk; c.i_end = min(a.n2, c.i_begin + kScoreChunk);
-    c.ntile = (c.i_end - c.i_begin + ScoreTile::kTileBlocks - 1) / ScoreTile::kTileBlocks;
-    c.qrow0 = ((long long)c.bb_ * a.hq + c.h) * a.n1;
-    const int g = c.h / (a.hq / a.hkv);
-    c.ksrc = (const uint16_t*)a.krep + ((long long)c.bb_ * a.hkv + g) * a.n2 * 2 * kHeadDim;
-    c.vis = min(a.n2, (min(c.seg, a.n1 - 1) + 1) * a.r);
-    c.vis_wg = min(a.n2, min(a.n1, (int)(blockIdx.y + 1) * kScoreSegPerWg) * a.r);
-    c.vis_wave = min(a.n2, (min(c.j0, a.n1 - 1) + 1) * a.r);
-    c.vis_wave_max = min(a.n2, min(a.n1, c.j0 + 16) * a.r);
-    c.lds0 = lds0;
-    const uint16_t* src = (const uint16_t*)a.qrep + ((c.qrow0 + min(c.seg, a.n1 - 1)) * 2 + c.rep) * kHeadDim + 8 * c.hh;
+// z[gg][b2][r] = K_rep(b2)[block 8*(r>>2) + 4*hh + (r&3) of the tile] . Q_rep[column of group gg]; tile: its LDS address.
+// The two products alternate; every fragment feeds GPW MFMAs and is read kAhead of them ahead.
+template <int GPW>
+__device__ __forceinline__ void score_tile(unsigned tile, int l32, int hh, const bf16x8 (&qf)[GPW][8], f32x16 (&z)[GPW][2]) {
+    constexpr int kAhead = 4;
+    const unsigned base = tile + l32 * 512;
+    const int sw = l32 & 15;
+    auto read = [&](int j) { return as_bf16x8(*SCORE_LDS(const u32x4, base + (j & 1) * 256 + (((2 * (j >> 1) + hh) ^ sw) << 4))); };
+    bf16x8 kf[kAhead];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) c.qf[ks] = as_bf16x8(*(const uint4*)(src + 16 * ks));
-}
-// Piece p of the chunk, global -> LDS buffer p & 1: instruction x of wave w (X instructions each) writes the
-// 1 KiB at 1024 * (X w + x) = rows 4 (X w + x) .. +3 of the piece (row = 2 * block + representative, 256 B); a
-// lane's 16 bytes land at lane * 16 inside that KiB, so the XOR swizzle of the 16-byte chunks by the block
-// index (which spreads the 32 row reads of a fragment over all banks) is applied to the global address.
-// Blocks past the last one repeat it.
-__device__ __forceinline__ void score_load_piece(const ScoreArgs& a, const ScoreCtx& c, int p) {
-    const unsigned long long pv = (unsigned long long)c.ksrc;
-    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)pv);
-    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(pv >> 32));
-    const void* sbase = (const void*)(((unsigned long long)hi << 32) | lo);
-    constexpr int kPerWave = kScorePiece / 2 / kScoreWaves;  // 1 KiB instructions per wave
-    constexpr unsigned kPieceBytes = kScorePiece * 2 * kHeadDim * 2;
+    for (int gg = 0; gg < GPW; ++gg)
 #pragma unroll
-    for (int x = 0; x < kPerWave; ++x) {
-        const int row = 4 * (kPerWave * c.wave + x) + (c.lane >> 4);
-        const int blk = min(c.i_begin + p * kScorePiece + (row >> 1), a.n2 - 1);
-        const int lc = (c.lane & 15) ^ ((row >> 1) & 15);
-        const unsigned voff = (unsigned)(((blk * 2 + (row & 1)) * kHeadDim + lc * 8) * 2);
-        const unsigned dst =
-            __builtin_amdgcn_readfirstlane(c.lds0 + (p & 1) * kPieceBytes + 1024u * (kPerWave * c.wave + x));
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff), "s"(sbase)
-                     : "memory");   // m0: reserved for the compiler, which sets it anew before each use of its own
+        for (int b2 = 0; b2 < 2; ++b2)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) z[gg][b2][r] = 0.f;
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) kf[j] = read(j);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+#pragma unroll
+        for (int gg = 0; gg < GPW; ++gg)
+            z[gg][j & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[j % kAhead], qf[gg][j >> 1], z[gg][j & 1], 0, 0, 0);
+        if (j + kAhead < 16) kf[j % kAhead] = read(j + kAhead);
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
-// every load of this wave has landed, every wave has arrived (and is done with the buffer that is filled next)
-__device__ __forceinline__ void score_chunk_ready() {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-}
-// z[b2][r] = K_rep(b2)[block 8*(r>>2) + 4*hh + (r&3) of the tile] . Q_rep[column]
-__device__ __forceinline__ void score_tile(const ScoreCtx& c, int nt, f32x16 (&z)[2]) {   // tile nt of the chunk
-    const unsigned base = c.lds0 + (nt & 3) * ScoreTile::kTileBytes + c.l32 * 512;
-    const int sw = c.l32 & 15;
-#pragma unroll
-    for (int b2 = 0; b2 < 2; ++b2) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) z[b2][r] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            const bf16x8 kf = as_bf16x8(*SCORE_LDS(const u32x4, base + b2 * 256 + (((2 * ks + c.hh) ^ sw) << 4)));
-            z[b2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, c.qf[ks], z[b2], 0, 0, 0);
-        }
-    }
-}
-// statistics of chunk part cc (= chunk * parts + part), product b2, column col:
-// stats[(((bh * nchunk * parts + cc) * 2 + b2) * 2 + which) * cols + col]
-__device__ __forceinline__ long long stats_index(const ScoreArgs& a, const ScoreCtx& c, int cc, int b2, int which) {
-    const long long cols = 2LL * a.n1_pad;
-    return ((((long long)blockIdx.z * (a.nchunk * a.parts) + cc) * 2 + b2) * 2 + which) * cols + 2 * c.seg + c.rep;
-}
 
-__global__ __launch_bounds__(64 * kScoreWaves, 4) void score_stats_kernel(ScoreArgs a) {
-    __shared__ __attribute__((aligned(1024))) unsigned char tiles[2 * kScorePiece * 2 * kHeadDim * 2];
-    ScoreCtx c;
-    score_setup(a, c, (unsigned)(uintptr_t)tiles);
-    if (a.domain == 1 && c.i_begin >= c.vis_wg) return;     // uniform: no visible block for any segment here
+template <int PASS, int GPW>
+__global__ __launch_bounds__(64 * kScoreWaves, 2) void score_kernel(ScoreArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char score_lds[];
+    const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)score_lds;
+    constexpr unsigned kRed = kChunkTiles * kTileBytes;     // behind the tiles: (max, sum) [wave][product][column], PASS 2
     constexpr float kLog2e = 1.4426950408889634f;
-    const float cs = a.scale * kLog2e;                      // logits in log2 units
-    const int dom = a.domain == 0 ? a.n2 : c.vis;
-    const int dom_wave = a.domain == 0 ? a.n2 : c.vis_wave; // blocks below it count for every column of the wave
-    float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};
-    score_load_piece(a, c, 0);
-    for (int nt = 0; nt < c.ntile; ++nt) {
-        if ((nt & 1) == 0) {                                // a new piece: wait for it, start the next one
-            score_chunk_ready();
-            if (nt + 2 < c.ntile) score_load_piece(a, c, (nt >> 1) + 1);
-        }
-        if ((nt & (a.parts - 1)) != c.part) continue;       // another wave's tile
-        f32x16 z[2];
-        score_tile(c, nt, z);
-        const int i0 = c.i_begin + nt * ScoreTile::kTileBlocks + 4 * c.hh;
-        if (cs > 0.f && c.i_begin + (nt + 1) * ScoreTile::kTileBlocks <= dom_wave) {
-            // every block of the tile counts for every column of the wave: no masks, the scale folded into one fma
-#pragma unroll
-            for (int b2 = 0; b2 < 2; ++b2) {
-                float mt = fmaxf(z[b2][0], z[b2][1]);
-#pragma unroll
-                for (int r = 2; r < 16; r += 2) mt = fmaxf(fmaxf(z[b2][r], z[b2][r + 1]), mt);
-                mt = halves_max(mt) * cs;
-                const float mn = fmaxf(m[b2], mt);
-                float sum = 0.f;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(fmaf(z[b2][r], cs, -mn));
-                l[b2] = l[b2] * __builtin_amdgcn_exp2f(m[b2] - mn) + sum;
-                m[b2] = mn;
-            }
-            continue;
-        }
-#pragma unroll
-        for (int b2 = 0; b2 < 2; ++b2) {
-            float v[16];
-            float mt = -INFINITY;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                v[r] = (i0 + 8 * (r >> 2) + (r & 3) < dom) ? z[b2][r] * cs : -INFINITY;
-                mt = fmaxf(mt, v[r]);
-            }
-            mt = halves_max(mt);
-            const float mn = fmaxf(m[b2], mt);
-            const float ms = (mn == -INFINITY) ? 0.f : mn;
-            float sum = 0.f;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) sum += exp2f(v[r] - ms);
-            l[b2] = l[b2] * exp2f(m[b2] - ms) + sum;        // per-half partial sums under a common max
-            m[b2] = mn;
-        }
-    }
-#pragma unroll
-    for (int b2 = 0; b2 < 2; ++b2) {
-        const float lt = halves_sum(l[b2]);
-        if (c.hh == 0) {
-            a.stats[stats_index(a, c, c.chunk * a.parts + c.part, b2, 0)] = m[b2];
-            a.stats[stats_index(a, c, c.chunk * a.parts + c.part, b2, 1)] = lt;
-        }
-    }
-}
-
-__global__ __launch_bounds__(64 * kScoreWaves, 4) void score_write_kernel(ScoreArgs a) {
-    __shared__ __attribute__((aligned(1024))) unsigned char tiles[2 * kScorePiece * 2 * kHeadDim * 2];
-    ScoreCtx c;
-    score_setup(a, c, (unsigned)(uintptr_t)tiles);
-    const bool vec = (a.n2 & 3) == 0;                       // rows of scores are 16-byte aligned
-    auto finish = [&](float sc, long long off) {            // fusion and the subnormal flush
-        if (a.prev) sc = a.alpha * sc + (1.0f - a.alpha) * a.prev[off];
-        if (fabsf(sc) < 1.17549435e-38f) sc = 0.f;
-        return sc;
-    };
-    if (c.i_begin >= c.vis_wg) {                            // uniform: nothing of this chunk is visible
-        const int width = c.i_end - c.i_begin;
-        for (int x = threadIdx.x; x < kScoreSegPerWg * width; x += 64 * kScoreWaves) {
-            const int j = blockIdx.y * kScoreSegPerWg + x / width;
-            if (j >= a.n1) break;
-            const long long off = (c.qrow0 + j) * a.n2 + c.i_begin + x % width;
-            a.scores[off] = finish(0.f, off);
-        }
-        return;
-    }
-    constexpr float kLog2e = 1.4426950408889634f;
-    const float cs = a.scale * kLog2e;
-    const int dom = a.domain == 0 ? a.n2 : c.vis;
-    score_load_piece(a, c, 0);                              // the merge below runs while the piece lands
-    // merge the chunk statistics of the lane's column: the lane does the product b2 = hh, the same column's
-    // lane in the other wave half does the other one (domain 1: chunks past the workgroup's last visible
-    // block were never written)
-    const int ncc = (a.domain == 0 ? a.nchunk : (c.vis_wg + kScoreChunk - 1) / kScoreChunk) * a.parts;
-    float mx[2], inv[2];
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int chunk = blockIdx.x, h = blockIdx.z % a.hq, bb = blockIdx.z / a.hq;
+    const int col_waves = kScoreWaves / a.parts, part = wave / col_waves;
+    const int g_first = blockIdx.y * a.wg_groups + wave % col_waves;
+    const int g_end = min((a.n1 + 16 * GPW - 1) / (16 * GPW), (int)(blockIdx.y + 1) * a.wg_groups);
+    const long long qrow0 = ((long long)bb * a.hq + h) * a.n1;   // row of segment 0 of this (batch, head) in scores
+    // first block of tile lt of the chunk
+    auto tile_begin = [&](int lt) { return kTileBlocks * (lt < kChunkTiles / 2 ? chunk * (kChunkTiles / 2) + lt
+                                                          : a.nchunk * kChunkTiles - 1 - (chunk * (kChunkTiles / 2) + lt - kChunkTiles / 2)); };
+    // first block wholly after segment j (of those that exist)
+    auto seen_end = [&](int j) { return min(a.n2, (min(j, a.n1 - 1) + 1) * a.r); };
+    // ---- K representatives -> LDS: wave w copies tile w, row = 2 * block + representative, 256 B; blocks past the last one repeat
+    // it; a tile that nobody needs is left out
     {
-        float M = -INFINITY, L = 0.f;
-        const long long step = stats_index(a, c, 1, 0, 0) - stats_index(a, c, 0, 0, 0);
-        const float* sm_ = a.stats + stats_index(a, c, 0, c.hh, 0);
-        const float* sl_ = a.stats + stats_index(a, c, 0, c.hh, 1);
-#pragma unroll 4
-        for (int cc = 0; cc < ncc; ++cc) {
-            const float mc = sm_[cc * step], lc = sl_[cc * step];
-            const float mn = fmaxf(M, mc);
-            const float ms = (mn == -INFINITY) ? 0.f : mn;
-            L = L * exp2f(M - ms) + lc * exp2f(mc - ms);
-            M = mn;
+        static_assert(kScoreWaves == kChunkTiles, "a wave copies a tile");
+        const int b0 = tile_begin(wave);
+        if (b0 < (PASS == 1 || a.domain == 1 ? seen_end(g_end * 16 * GPW - 1) : a.n2)) {
+            const uint16_t* ksrc = (const uint16_t*)a.krep + ((long long)bb * a.hkv + h / (a.hq / a.hkv)) * a.n2 * 2 * kHeadDim;
+            const unsigned long long pv = (unsigned long long)ksrc;
+            const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)pv);
+            const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(pv >> 32));
+            const void* sbase = (const void*)(((unsigned long long)hi << 32) | lo);
+#pragma unroll
+            for (int x = 0; x < 16; ++x) {
+                const int row = 4 * x + (lane >> 4);
+                const int blk = min(b0 + (row >> 1), a.n2 - 1);
+                const int lc = (lane & 15) ^ ((row >> 1) & 15);
+                const unsigned voff = (unsigned)(((blk * 2 + (row & 1)) * kHeadDim + lc * 8) * 2);
+                const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + wave * kTileBytes + 1024u * x);
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff), "s"(sbase)
+                             : "memory");   // m0: reserved for the compiler, which sets it anew before each use of its own
+            }
         }
-        const float own_m = (M == -INFINITY) ? 0.f : M;
-        const float own_i = L > 0.f ? 1.0f / L : 0.f;
-        const auto rm = __builtin_amdgcn_permlane32_swap(__float_as_uint(own_m), __float_as_uint(own_m), false, false);
-        const auto ri = __builtin_amdgcn_permlane32_swap(__float_as_uint(own_i), __float_as_uint(own_i), false, false);
-        const float oth_m = __uint_as_float(c.hh ? rm[0] : rm[1]);   // the value of lane l ^ 32
-        const float oth_i = __uint_as_float(c.hh ? ri[0] : ri[1]);
-        mx[0] = c.hh ? oth_m : own_m; mx[1] = c.hh ? own_m : oth_m;
-        inv[0] = c.hh ? oth_i : own_i; inv[1] = c.hh ? own_i : oth_i;
     }
-    // 2^(c z + fold) = 2^(c z - max) / sum / 2; usable when every column of the wave has a positive sum
-    float fold[2];
-    fold[0] = -mx[0] + __log2f(inv[0]) - 1.0f; fold[1] = -mx[1] + __log2f(inv[1]) - 1.0f;
-    const bool l_pos = __builtin_amdgcn_ballot_w64(inv[0] > 0.f && inv[1] > 0.f) == ~0ull;
-    for (int nt = 0; nt < c.ntile; ++nt) {
-        if ((nt & 1) == 0) {                                // a new piece: wait for it, start the next one
-            score_chunk_ready();
-            if (nt + 2 < c.ntile) score_load_piece(a, c, (nt >> 1) + 1);
+    const float cs = a.scale * kLog2e;                      // logits in log2 units
+    const bool vec = (a.n2 & 3) == 0;                       // rows of scores are 16-byte aligned
+    const int rep = l32 & 1;
+    bool landed = false;
+    // Every wave takes the body at least once and meets the barriers in it: with parts > 1 or PASS 2 it has at most one group (the
+    // host sees to that), else there is only the first one, behind which all copies have landed
+    const bool joint = PASS == 2 || a.parts > 1;
+    for (int g = g_first; g < g_end || !landed; g += col_waves) {
+        const bool active = g < g_end;                      // wave-uniform
+        const int j0 = g * 16 * GPW;
+        const int vis_hi = seen_end(j0 + 16 * GPW - 1);     // first block after the last segment of the group
+        int seg[GPW], vis[GPW];
+        bf16x8 qf[GPW][8];
+#pragma unroll
+        for (int gg = 0; gg < GPW; ++gg) {
+            seg[gg] = j0 + 16 * gg + (l32 >> 1);
+            vis[gg] = seen_end(seg[gg]);
+            const uint16_t* src = (const uint16_t*)a.qrep + ((qrow0 + min(seg[gg], a.n1 - 1)) * 2 + rep) * kHeadDim + 8 * hh;
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) qf[gg][ks] = as_bf16x8(*(const uint4*)(src + 16 * ks));
         }
-        if ((nt & (a.parts - 1)) != c.part) continue;       // another wave's tile
-        f32x16 z[2];
-        const bool unseen = c.i_begin + nt * ScoreTile::kTileBlocks >= c.vis_wave_max;   // by every segment of the wave
-        if (!unseen) score_tile(c, nt, z);
-        const int i0 = c.i_begin + nt * ScoreTile::kTileBlocks + 4 * c.hh;
-        // S1 = (max,max), S2 = (max,min), S3 = (min,max), S4 = (min,min): the lane has the products of its
-        // query representative with K_max (b2 = 0) and K_min (b2 = 1), its neighbour those of the other one
-        float sc[16];
-        const int tile_end = c.i_begin + (nt + 1) * ScoreTile::kTileBlocks;
-        if (unseen) {
+        // statistics of product b2, column col: stats[((bh * nchunk + chunk) * 2 + b2) * 2 + (0: max, 1: sum)][col]
+        const long long cols = 2LL * a.n1_pad, chunk_step = 4 * cols;
+        float* stats = a.stats + (long long)blockIdx.z * a.nchunk * chunk_step;
+        float mx[GPW][2], inv[GPW][2];
+        if (PASS == 1) {                                    // merge: the lane does product b2 = hh, its column's other lane the other one
 #pragma unroll
-            for (int r = 0; r < 16; ++r) sc[r] = 0.f;
-        } else if (cs > 0.f && tile_end <= c.vis_wave && l_pos) {
-            // every block of the tile is visible to every segment of the wave: 1/sum and the 1/2 of the average
-            // are folded into the exponent
+            for (int gg = 0; gg < GPW; ++gg) {
+                float M = -INFINITY, L = 0.f;
+                const float* from = stats + 2 * hh * cols + 2 * min(seg[gg], a.n1_pad - 1) + rep;
+                constexpr int kAhead = 8;
+                for (int c0 = 0; c0 < a.nchunk; c0 += kAhead) {
+                    float mc[kAhead], lc[kAhead];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float p0 = __builtin_amdgcn_exp2f(fmaf(z[0][r], cs, fold[0]));
-                const float p1 = __builtin_amdgcn_exp2f(fmaf(z[1][r], cs, fold[1]));
-                sc[r] = fmaxf(p0 + neighbour(p0), p1 + neighbour(p1));
-            }
-        } else {
+                    for (int u = 0; u < kAhead; ++u) {
+                        const float* at = from + min(c0 + u, a.nchunk - 1) * chunk_step;
+                        mc[u] = at[0]; lc[u] = at[cols];
+                    }
+                    float mn = M;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int i = i0 + 8 * (r >> 2) + (r & 3);
-                const bool in_dom = i < dom;
-                const float p0 = in_dom ? exp2f(z[0][r] * cs - mx[0]) * inv[0] : 0.f;
-                const float p1 = in_dom ? exp2f(z[1][r] * cs - mx[1]) * inv[1] : 0.f;
-                const float t0 = p0 + neighbour(p0), t1 = p1 + neighbour(p1);
-                sc[r] = (i < c.vis) ? fmaxf(t0, t1) * 0.5f : 0.f;
+                    for (int u = 0; u < kAhead; ++u) {
+                        if (c0 + u >= a.nchunk) { mc[u] = -INFINITY; lc[u] = 0.f; }
+                        mn = fmaxf(mn, mc[u]);
+                    }
+                    const float ms = (mn == -INFINITY) ? 0.f : mn;
+                    L *= exp2f(M - ms);
+#pragma unroll
+                    for (int u = 0; u < kAhead; ++u) L += lc[u] * exp2f(mc[u] - ms);
+                    M = mn;
+                }
+                const float own_m = (M == -INFINITY) ? 0.f : M;
+                const float own_i = L > 0.f ? 1.0f / L : 0.f;
+                const auto rm = __builtin_amdgcn_permlane32_swap(__float_as_uint(own_m), __float_as_uint(own_m), false, false);
+                const auto ri = __builtin_amdgcn_permlane32_swap(__float_as_uint(own_i), __float_as_uint(own_i), false, false);
+                const float oth_m = __uint_as_float(hh ? rm[0] : rm[1]);   // the value of lane l ^ 32
+                const float oth_i = __uint_as_float(hh ? ri[0] : ri[1]);
+                mx[gg][0] = hh ? oth_m : own_m; mx[gg][1] = hh ? own_m : oth_m;
+                inv[gg][0] = hh ? oth_i : own_i; inv[gg][1] = hh ? own_i : oth_i;
             }
         }
-        // both lanes of a pair hold the segment's 16 scores: representative 0 stores blocks 0-7 and 16-23 of
-        // the lane half's 16, representative 1 the rest, four consecutive blocks at a time
-        if (c.seg < a.n1) {
+        // S' of the lane's eight scores of a tile and group, asked for one tile ahead
+        float4 pv[GPW][2];
+        const bool fused4 = PASS != 0 && a.prev && vec && active;
+        auto fetch_prev = [&](int lt) {
 #pragma unroll
-            for (int g2 = 0; g2 < 2; ++g2) {
-                const int g = 2 * g2 + c.rep;               // wave-varying but only two values: both compiled
-                const int i = i0 + 8 * g;
-                const long long off = (c.qrow0 + c.seg) * a.n2 + i;
-                float w[4];
+            for (int gg = 0; gg < GPW; ++gg)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = c.rep ? sc[4 * (2 * g2 + 1) + e] : sc[4 * (2 * g2) + e];
-                if (vec) {
-                    if (i < a.n2) {
-                        float4 o;
-                        if (a.prev) {
-                            const float4 pv = *(const float4*)(a.prev + off);
-                            o.x = a.alpha * w[0] + (1.0f - a.alpha) * pv.x; o.y = a.alpha * w[1] + (1.0f - a.alpha) * pv.y;
-                            o.z = a.alpha * w[2] + (1.0f - a.alpha) * pv.z; o.w = a.alpha * w[3] + (1.0f - a.alpha) * pv.w;
-                        } else { o.x = w[0]; o.y = w[1]; o.z = w[2]; o.w = w[3]; }
-                        if (fabsf(o.x) < 1.17549435e-38f) o.x = 0.f;
-                        if (fabsf(o.y) < 1.17549435e-38f) o.y = 0.f;
-                        if (fabsf(o.z) < 1.17549435e-38f) o.z = 0.f;
-                        if (fabsf(o.w) < 1.17549435e-38f) o.w = 0.f;
-                        *(float4*)(a.scores + off) = o;
+                for (int g2 = 0; g2 < 2; ++g2) {
+                    const int i = lt < kChunkTiles ? tile_begin(lt) + 4 * hh + 8 * (2 * g2 + rep) : a.n2;
+                    if (fused4 && i < a.n2 && seg[gg] < a.n1) pv[gg][g2] = *(const float4*)(a.prev + (qrow0 + seg[gg]) * a.n2 + i);
+                }
+        };
+        if (PASS != 0) fetch_prev(part);
+        if (!landed) {                                      // every wave's copies are in LDS
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+            landed = true;
+        }
+        if (PASS != 1) {
+            float m[GPW][2], l[GPW][2];
+#pragma unroll
+            for (int gg = 0; gg < GPW; ++gg)
+#pragma unroll
+                for (int b2 = 0; b2 < 2; ++b2) { m[gg][b2] = -INFINITY; l[gg][b2] = 0.f; }
+            for (int lt = part; lt < kChunkTiles; lt += a.parts) {
+                const int b0 = tile_begin(lt);
+                if (!active || b0 >= (a.domain == 0 ? a.n2 : vis_hi)) continue;
+                f32x16 z[GPW][2];
+                score_tile<GPW>(lds0 + lt * kTileBytes, l32, hh, qf, z);
+#pragma unroll
+                for (int gg = 0; gg < GPW; ++gg) {
+                    const int dom = a.domain == 0 ? a.n2 : vis[gg];
+                    const int dom_lo = a.domain == 0 ? a.n2 : seen_end(j0 + 16 * gg);
+                    if (cs > 0.f && b0 + kTileBlocks <= dom_lo) {
+                        // every block of the tile counts for every column: no masks, the scale folded into one fma
+#pragma unroll
+                        for (int b2 = 0; b2 < 2; ++b2) {
+                            const f32x16& x = z[gg][b2];
+                            float mt = fmaxf(x[0], x[1]);
+#pragma unroll
+                            for (int r = 2; r < 16; r += 2) mt = fmaxf(fmaxf(x[r], x[r + 1]), mt);
+                            mt = halves_max(mt) * cs;
+                            const float mn = fmaxf(m[gg][b2], mt);
+                            float sum = 0.f;
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(fmaf(x[r], cs, -mn));
+                            l[gg][b2] = l[gg][b2] * __builtin_amdgcn_exp2f(m[gg][b2] - mn) + sum;
+                            m[gg][b2] = mn;
+                        }
+                        continue;
+                    }
+#pragma unroll
+                    for (int b2 = 0; b2 < 2; ++b2) {
+                        float v[16];
+                        float mt = -INFINITY;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            v[r] = (b0 + 4 * hh + 8 * (r >> 2) + (r & 3) < dom) ? z[gg][b2][r] * cs : -INFINITY;
+                            mt = fmaxf(mt, v[r]);
+                        }
+                        mt = halves_max(mt);
+                        const float mn = fmaxf(m[gg][b2], mt);
+                        const float ms = (mn == -INFINITY) ? 0.f : mn;
+                        float sum = 0.f;
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) sum += exp2f(v[r] - ms);
+                        l[gg][b2] = l[gg][b2] * exp2f(m[gg][b2] - ms) + sum;        // per-half partial sums under a common max
+                        m[gg][b2] = mn;
+                    }
+                }
+            }
+#pragma unroll
+            for (int gg = 0; gg < GPW; ++gg)
+#pragma unroll
+                for (int b2 = 0; b2 < 2; ++b2) l[gg][b2] = halves_sum(l[gg][b2]);
+            if (joint) {                                    // merge the parts of the group (the host keeps GPW at 1 here)
+#pragma unroll
+                for (int b2 = 0; b2 < 2; ++b2)
+                    if (hh == 0) *SCORE_LDS(f32x2, lds0 + kRed + ((wave * 2 + b2) * 32 + l32) * 8) = f32x2{m[0][b2], l[0][b2]};
+                __syncthreads();
+#pragma unroll
+                for (int b2 = 0; b2 < 2; ++b2) {
+                    float M = -INFINITY, L = 0.f;
+                    for (int x = 0; x < a.parts; ++x)
+                        M = fmaxf(M, (*SCORE_LDS(const f32x2, lds0 + kRed + (((x * col_waves + wave % col_waves) * 2 + b2) * 32 + l32) * 8))[0]);
+                    const float ms = (M == -INFINITY) ? 0.f : M;
+                    for (int x = 0; x < a.parts; ++x) {
+                        const f32x2 e = *SCORE_LDS(const f32x2, lds0 + kRed + (((x * col_waves + wave % col_waves) * 2 + b2) * 32 + l32) * 8);
+                        L += e[1] * exp2f(e[0] - ms);
+                    }
+                    m[0][b2] = M; l[0][b2] = L;
+                }
+            }
+            if (PASS == 0) {
+                if (hh == 0 && part == 0 && active) {
+#pragma unroll
+                    for (int gg = 0; gg < GPW; ++gg)
+#pragma unroll
+                        for (int b2 = 0; b2 < 2; ++b2) {
+                            float* at = stats + chunk * chunk_step + 2 * b2 * cols + 2 * seg[gg] + rep;
+                            at[0] = m[gg][b2]; at[cols] = l[gg][b2];
+                        }
+                }
+                continue;
+            }
+#pragma unroll
+            for (int gg = 0; gg < GPW; ++gg)
+#pragma unroll
+                for (int b2 = 0; b2 < 2; ++b2) {
+                    mx[gg][b2] = (m[gg][b2] == -INFINITY) ? 0.f : m[gg][b2];
+                    inv[gg][b2] = l[gg][b2] > 0.f ? 1.0f / l[gg][b2] : 0.f;
+                }
+        }
+        if (!active) continue;
+        // 2^(c z + fold) = 2^(c z - max) / sum / 2; usable when every column of the wave has a positive sum
+        float fold[GPW][2];
+        bool folds[GPW];
+#pragma unroll
+        for (int gg = 0; gg < GPW; ++gg) {
+#pragma unroll
+            for (int b2 = 0; b2 < 2; ++b2) fold[gg][b2] = -mx[gg][b2] + __log2f(inv[gg][b2]) - 1.0f;
+            folds[gg] = cs > 0.f && __builtin_amdgcn_ballot_w64(inv[gg][0] > 0.f && inv[gg][1] > 0.f) == ~0ull;
+        }
+        for (int lt = part; lt < kChunkTiles; lt += a.parts) {
+            const int b0 = tile_begin(lt);
+            float4 now[GPW][2];
+#pragma unroll
+            for (int gg = 0; gg < GPW; ++gg)
+#pragma unroll
+                for (int g2 = 0; g2 < 2; ++g2) now[gg][g2] = pv[gg][g2];
+            fetch_prev(lt + a.parts);
+            if (b0 >= a.n2) continue;
+            const int i0 = b0 + 4 * hh;
+            f32x16 z[GPW][2];
+            if (b0 < vis_hi) score_tile<GPW>(lds0 + lt * kTileBytes, l32, hh, qf, z);
+#pragma unroll
+            for (int gg = 0; gg < GPW; ++gg) {
+                // S1 = (max,max), S2 = (max,min), S3 = (min,max), S4 = (min,min): the lane has the products of its
+                // query representative with K_max (b2 = 0) and K_min (b2 = 1), its neighbour those of the other one
+                float sc[16];
+                const bool full = b0 + kTileBlocks <= seen_end(j0 + 16 * gg);       // visible to every segment of the sixteen
+                if (b0 >= seen_end(j0 + 16 * gg + 15)) {                            // to none
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+                } else if (folds[gg] && full) {                                     // 1/sum and the 1/2 of the average are in the exponent
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const float p0 = __builtin_amdgcn_exp2f(fmaf(z[gg][0][r], cs, fold[gg][0]));
+                        const float p1 = __builtin_amdgcn_exp2f(fmaf(z[gg][1][r], cs, fold[gg][1]));
+                        sc[r] = fmaxf(p0 + neighbour(p0), p1 + neighbour(p1));
                     }
                 } else {
+                    const int dom = a.domain == 0 ? a.n2 : vis[gg];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (i + e < a.n2) a.scores[off + e] = finish(w[e], off + e);
+                    for (int r = 0; r < 16; ++r) {
+                        const int i = i0 + 8 * (r >> 2) + (r & 3);
+                        const bool in_dom = i < dom;
+                        const float p0 = in_dom ? exp2f(z[gg][0][r] * cs - mx[gg][0]) * inv[gg][0] : 0.f;
+                        const float p1 = in_dom ? exp2f(z[gg][1][r] * cs - mx[gg][1]) * inv[gg][1] : 0.f;
+                        const float t0 = p0 + neighbour(p0), t1 = p1 + neighbour(p1);
+                        sc[r] = (i < vis[gg]) ? fmaxf(t0, t1) * 0.5f : 0.f;
+                    }
+                }
+                // both lanes of a pair hold the segment's 16 scores: representative 0 stores blocks 0-7 and 16-23 of
+                // the lane half's 16, representative 1 the rest, four consecutive blocks at a time
+                if (seg[gg] < a.n1) {
+                    const long long row = (qrow0 + seg[gg]) * a.n2;
+#pragma unroll
+                    for (int g2 = 0; g2 < 2; ++g2) {
+                        const int i = i0 + 8 * (2 * g2 + rep);  // wave-varying but only two values: both compiled
+                        float w[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) w[e] = rep ? sc[4 * (2 * g2 + 1) + e] : sc[4 * (2 * g2) + e];
+                        const float old[4] = {now[gg][g2].x, now[gg][g2].y, now[gg][g2].z, now[gg][g2].w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            if (a.prev) w[e] = a.alpha * w[e] + (1.0f - a.alpha) * (vec ? old[e] : i + e < a.n2 ? a.prev[row + i + e] : 0.f);
+                            if (fabsf(w[e]) < 1.17549435e-38f) w[e] = 0.f;
+                        }
+                        if (vec) {
+                            if (i < a.n2) *(float4*)(a.scores + row + i) = make_float4(w[0], w[1], w[2], w[3]);
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if (i + e < a.n2) a.scores[row + i + e] = w[e];
+                        }
+                    }
                 }
             }
         }
@@ -586,15 +633,24 @@ hipError_t launch_pool(const Shape& sh, const void* q, const void* k, void* qrep
     return hipGetLastError();
 }
 
-// waves of a score workgroup that share their segments: all eight take different segments unless the sequence
-// has too few of them
-static int score_parts(int n1) { return n1 <= 16 ? 8 : n1 <= 32 ? 4 : n1 <= 64 ? 2 : 1; }
-
+// Scratch for the statistics of every chunk, padded to 128 segments.  A single chunk keeps them in LDS; the factor for short
+// sequences leaves room for up to eight partial statistics per chunk, which the kernel merges in LDS now: callers may hold
+// buffers of this size, so it stays.
 size_t score_stats_bytes(const Shape& sh) {
     if (sh.dtype != 1) return 0;
-    const size_t nchunk = (size_t)((sh.n2 + kScoreChunk - 1) / kScoreChunk) * score_parts(sh.n1);
-    const size_t n1_pad = (size_t)((sh.n1 + kScoreSegPerWg - 1) / kScoreSegPerWg) * kScoreSegPerWg;
+    const size_t room = sh.n1 <= 16 ? 8 : sh.n1 <= 32 ? 4 : sh.n1 <= 64 ? 2 : 1;
+    const size_t nchunk = (size_t)((sh.n2 + kScoreChunk - 1) / kScoreChunk) * room;
+    const size_t n1_pad = (size_t)((sh.n1 + 127) / 128) * 128;
     return (size_t)sh.batch * sh.hq * nchunk * 2 * 2 * (2 * n1_pad) * sizeof(float);
+}
+
+template <int PASS, int GPW>
+static hipError_t launch_score_pass(const ScoreArgs& a, dim3 grid, hipStream_t st) {
+    constexpr int smem = kChunkTiles * kTileBytes + (PASS == 1 ? 0 : kScoreWaves * 2 * 32 * 8);
+    const hipError_t e = hipFuncSetAttribute((const void*)score_kernel<PASS, GPW>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((score_kernel<PASS, GPW>), grid, dim3(64 * kScoreWaves), smem, st, a);
+    return hipGetLastError();
 }
 
 hipError_t launch_score(const Shape& sh, const void* qrep, const void* krep, const float* prev, float* scores,
@@ -604,16 +660,27 @@ hipError_t launch_score(const Shape& sh, const void* qrep, const void* krep, con
     a.hq = sh.hq; a.hkv = sh.hkv; a.n1 = sh.n1; a.n2 = sh.n2; a.r = sh.r; a.domain = sh.softmax_domain;
     a.scale = sh.score_scale; a.alpha = sh.alpha;
     a.nchunk = (sh.n2 + kScoreChunk - 1) / kScoreChunk;
-    a.n1_pad = (sh.n1 + kScoreSegPerWg - 1) / kScoreSegPerWg * kScoreSegPerWg;
-    a.parts = score_parts(sh.n1);
+    a.n1_pad = (sh.n1 + 127) / 128 * 128;
+    a.parts = 1; a.wg_groups = kScoreWaves;
     if (sh.dtype == 1) {
-        if ((long long)sh.batch * sh.hq > 65535) return hipErrorInvalidValue;
-        dim3 grid_m(a.nchunk, a.n1_pad / kScoreSegPerWg, sh.batch * sh.hq);
-        hipLaunchKernelGGL(score_stats_kernel, grid_m, dim3(64 * kScoreWaves), 0, st, a);
-        hipError_t e = hipGetLastError();
+        const long long heads = (long long)sh.batch * sh.hq;
+        if (heads > 65535) return hipErrorInvalidValue;
+        // Few segments: as many workgroups as the chip holds, the waves without a group of their own sharing one.  Many: pairs
+        // of groups per wave, which halve the LDS reads per MFMA (estimate at 32 heads x 128K 263 against 271 us, 8 x 128K in
+        // blocks of 16 320 / 349), and, with more than four workgroups to a compute unit, more groups to a workgroup,
+        // so that a chunk is copied less often.
+        const int sixteens = (sh.n1 + 15) / 16;
+        auto wgs = [&](int groups) { return heads * a.nchunk * ((groups + a.wg_groups - 1) / a.wg_groups); };
+        const bool pairs = a.nchunk > 1 && sixteens > kScoreWaves && heads * a.nchunk * ((sixteens + 2 * kScoreWaves - 1) / (2 * kScoreWaves)) >= kScoreWgs;
+        const int groups = pairs ? (sixteens + 1) / 2 : sixteens;
+        if (!pairs)
+            while (a.parts < kChunkTiles && (a.wg_groups / 2 >= groups || wgs(groups) < kScoreWgs)) { a.parts *= 2; a.wg_groups /= 2; }
+        while (a.parts == 1 && a.nchunk > 1 && a.wg_groups < groups && wgs(groups) >= 4 * kScoreWgs) a.wg_groups *= 2;
+        const dim3 grid(a.nchunk, (groups + a.wg_groups - 1) / a.wg_groups, (unsigned)heads);
+        if (a.nchunk == 1) return launch_score_pass<2, 1>(a, grid, st);
+        const hipError_t e = pairs ? launch_score_pass<0, 2>(a, grid, st) : launch_score_pass<0, 1>(a, grid, st);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(score_write_kernel, grid_m, dim3(64 * kScoreWaves), 0, st, a);
-        return hipGetLastError();
+        return pairs ? launch_score_pass<1, 2>(a, grid, st) : launch_score_pass<1, 1>(a, grid, st);
     }
     const size_t smem = (2 * kHeadDim + 4 + 4 * (size_t)sh.n2) * sizeof(float);
     dim3 grid(sh.n1, sh.hq, sh.batch);
