@@ -9,14 +9,15 @@ from concurrent.futures import ThreadPoolExecutor
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libcritiprefill.so")
-SOURCES = ["api.hip", "estimate.hip", "select.hip", "attn_fp32.hip", "attn_bf16.hip"]
+SOURCES = ["api.hip", "estimate.hip", "select.hip", "attn_fp32.hip", "attn_bf16.hip", "attn_bf16_rows.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# attn_bf16: MFMA results stay in architectural VGPRs (S^T feeds the softmax VALU code directly; the
+# bf16 attention: MFMA results stay in architectural VGPRs (S^T feeds the softmax VALU code directly; the
 # operands that only MFMA touches live in AGPRs), and fmaxf needs no NaN-quieting pre-pass (the kernel
 # never produces NaN: masked logits are -inf and the running max is guarded).
-EXTRA = {"attn_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fno-honor-nans", "-mno-amdgpu-ieee"]}
+_BF16_ATTN = ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fno-honor-nans", "-mno-amdgpu-ieee"]
+EXTRA = {"attn_bf16.hip": _BF16_ATTN, "attn_bf16_rows.hip": _BF16_ATTN}
 
 
 def _compile(src: str, objdir: str) -> str:

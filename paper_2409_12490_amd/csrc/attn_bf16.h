@@ -1,0 +1,71 @@
+// What the two bf16 attention kernels share: vector types, argument block, lane exchanges, the copy from memory to LDS.
+#pragma once
+#include "kernels.h"
+
+namespace cp {
+
+struct ArgsB {
+    const uint16_t* q; const uint16_t* k; const uint16_t* v; const int32_t* idx; const int32_t* cnt;
+    uint16_t* out; float* lse;
+    int batch, hq, hkv, n, s, b, n1, list_len, qtiles;
+    int shared_lists;                     // lists are per (batch, KV head, segment) instead of per query head
+    float scale_log2e, scale;
+    long long qs0, qs1, qs2, ks0, ks1, ks2, os0, os1, os2;
+};
+
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 v4bf16_lds;
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+typedef __attribute__((ext_vector_type(4))) int i32x4;
+typedef __attribute__((ext_vector_type(2))) int i32x2;
+#define LDS_PTR(T, off) ((__attribute__((address_space(3))) T*)(uintptr_t)(off))
+
+constexpr float kLazyLog2 = 8.0f;        // how far a row's max may outgrow its reference point before O is rescaled
+
+__device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
+    union { uint4 u; bf16x8 b; } c; c.u = v; return c.b;
+}
+__device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
+    union { u32x4 u; bf16x8 b; } c; c.u = v; return c.b;
+}
+// Keep a value computed at this point of the program (stops a load from staying pending into the loop).
+__device__ __forceinline__ void pin(const bf16x8& v) { asm volatile("" ::"v"(v)); }
+
+// 16 bytes per lane from global memory (uniform base + per-lane byte offset) straight into LDS at
+// (lds_base + lane * 16); lds_base is wave-uniform.  Issued through inline asm so the compiler does not
+// serialise later LDS reads of OTHER ring slots behind it; the matching s_waitcnt vmcnt is placed by hand
+// before the tile barrier.  m0 is written here and not named as a clobber: it is a reserved register for the
+// compiler, which keeps no value in it across statements and sets it anew before each use of its own (naming it
+// only draws "clobber list contains reserved registers").
+__device__ __forceinline__ void dma16(const void* sbase, unsigned voff, unsigned lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(voff), "s"(sbase)
+                 : "memory");
+}
+
+__device__ __forceinline__ const uint16_t* uniform_ptr(const uint16_t* p) {   // into SGPRs
+    const unsigned long long v = (unsigned long long)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v);
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+    return (const uint16_t*)(((unsigned long long)hi << 32) | lo);
+}
+
+__device__ __forceinline__ float half_max(float x) {      // max over lanes l and l^32
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float half_sum(float x) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+}  // namespace
+
+// Attention with 32-row workgroups whose waves split the keys; fills in qtiles.
+hipError_t launch_attn_bf16_rows(const Shape& sh, ArgsB a, hipStream_t st);
+
+}  // namespace cp

@@ -27,20 +27,10 @@
 // and the transposed 8 B reads of V free of bank conflicts.  The block list of the segment is copied to
 // LDS once, so the key loop itself issues no other global loads and the only vmcnt waits in it are the
 // hand-placed ones that pace the ring.
-#include "kernels.h"
+#include "attn_bf16.h"
 
 namespace cp {
 namespace {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 v4bf16_lds;
-typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-typedef __attribute__((ext_vector_type(2))) int i32x2;
-#define LDS_PTR(T, off) ((__attribute__((address_space(3))) T*)(uintptr_t)(off))
 
 constexpr int TQ = 256;               // query rows per workgroup
 constexpr int WQ = 32;                // query rows per wave
@@ -51,55 +41,9 @@ constexpr int kTokOff = 0;                            // [NBUF][TK] token positi
 constexpr int kVOff = 1024;                           // [NBUF] V tiles
 constexpr int kKOff = kVOff + NBUF * kTileBytes;      // [NBUF] K tiles
 constexpr int kListOff = kKOff + NBUF * kTileBytes;   // the segment's block list (sparse only)
-constexpr float kLazyLog2 = 8.0f;        // see the softmax phase: how far a row's max may outgrow its reference point
 constexpr int kOutPitch = 272;                        // epilogue staging: one output row + 16 B, in bytes
 static_assert(kListOff + kMaxListBf16 * 4 <= 160 * 1024, "LDS budget");
 static_assert(8 * WQ * kOutPitch <= 2 * NBUF * kTileBytes, "epilogue staging reuses the tile rings");
-
-struct ArgsB {
-    const uint16_t* q; const uint16_t* k; const uint16_t* v; const int32_t* idx; const int32_t* cnt;
-    uint16_t* out; float* lse;
-    int batch, hq, hkv, n, s, b, n1, list_len, qtiles;
-    int shared_lists;                     // lists are per (batch, KV head, segment) instead of per query head
-    float scale_log2e, scale;
-    long long qs0, qs1, qs2, ks0, ks1, ks2, os0, os1, os2;
-};
-
-__device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
-    union { uint4 u; bf16x8 b; } c; c.u = v; return c.b;
-}
-__device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) {
-    union { u32x4 u; bf16x8 b; } c; c.u = v; return c.b;
-}
-// Keep a value computed at this point of the program (stops a load from staying pending into the loop).
-__device__ __forceinline__ void pin(const bf16x8& v) { asm volatile("" ::"v"(v)); }
-
-// 16 bytes per lane from global memory (uniform base + per-lane byte offset) straight into LDS at
-// (lds_base + lane * 16); lds_base is wave-uniform.  Issued through inline asm so the compiler does not
-// serialise later LDS reads of OTHER ring slots behind it; the matching s_waitcnt vmcnt is placed by hand
-// before the tile barrier.  m0 is written here and not named as a clobber: it is a reserved register for the
-// compiler, which keeps no value in it across statements and sets it anew before each use of its own (naming it
-// only draws "clobber list contains reserved registers").
-__device__ __forceinline__ void dma16(const void* sbase, unsigned voff, unsigned lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(voff), "s"(sbase)
-                 : "memory");
-}
-
-__device__ __forceinline__ const uint16_t* uniform_ptr(const uint16_t* p) {   // into SGPRs
-    const unsigned long long v = (unsigned long long)p;
-    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v);
-    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
-    return (const uint16_t*)(((unsigned long long)hi << 32) | lo);
-}
-
-__device__ __forceinline__ float half_max(float x) {      // max over lanes l and l^32
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float half_sum(float x) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 
 // MODE 0: sparse, any block size (row tokens of every tile kept in LDS); MODE 1: sparse, block size a
 // multiple of 64 (every tile is 64 consecutive tokens, described by its first token alone); MODE 2: dense;
@@ -719,6 +663,11 @@ hipError_t launch_attn_bf16(const Shape& sh, const void* q, const void* k, const
     a.qs0 = sh.qs[0]; a.qs1 = sh.qs[1]; a.qs2 = sh.qs[2];
     a.ks0 = sh.kvs[0]; a.ks1 = sh.kvs[1]; a.ks2 = sh.kvs[2];
     a.os0 = sh.os[0]; a.os1 = sh.os[1]; a.os2 = sh.os[2];
+    // Few query rows: 256 of them to a workgroup leave compute units idle, 32 do not.  The lines lie where the two kernels meet
+    // (256-row against 32-row kernel).  Block-sparse, 16384 rows: 32 heads x 512 20.4 / 13.9 to 22.6 / 15.4 us, 8 x 2048 25.7 / 21.1 to 55 / 35, 1 x
+    // 16K 26.3 / 22.3 to 69 / 56; 24576 rows: 26.5 / 26.7 and 26.9 / 25.5, 26.1 / 30.2 to 69 / 59, 27.6 / 33.7 to 72 / 85.  Dense, 32768 rows:
+    // 32 x 1024 30.9 / 30.5, 8 x 4096 98 / 86, 1 x 32K 722 / 590; 40960 rows: 37 / 40, 123 / 126, 903 / 938.
+    if ((long long)sh.batch * sh.hq * sh.n <= (idx ? 16384 : 32768)) return launch_attn_bf16_rows(sh, a, st);
     hipError_t e;
     if (idx) {
         if (sh.list_len > kMaxListBf16) return hipErrorInvalidValue;
