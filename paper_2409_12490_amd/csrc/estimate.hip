@@ -133,7 +133,7 @@ __global__ __launch_bounds__(64 * kPoolWaves) void pool_kernel(PoolArgs a) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// score, fp32 (correctness configuration): one workgroup per (batch, head, segment) row of S, plain fp32 FMA.
+// score, fp32: fp32 MFMAs, whole rows of logits in LDS.
 // ---------------------------------------------------------------------------------------------
 struct ScoreArgs {
     const void* qrep; const void* krep; const float* prev; float* scores;
@@ -141,7 +141,7 @@ struct ScoreArgs {
     int hq, hkv, n1, n2, r, domain;
     int nchunk, n1_pad;
     int parts;                             // bf16 path: waves that share a group and split the tiles of a chunk (1, 2, 4, 8)
-    int wg_groups;                         // bf16 path: groups of 16 * GPW segments per workgroup
+    int wg_groups;                         // groups of 16 * GPW segments (bf16) or segments (fp32) per workgroup
     float scale, alpha;
 };
 constexpr int kScoreWaves = 8;             // waves per workgroup of the bf16 score kernel
@@ -151,82 +151,83 @@ constexpr int kChunkTiles = 8;             // tiles per workgroup, all of them i
 constexpr int kScoreChunk = kChunkTiles * kTileBlocks;
 constexpr int kScoreWgs = 256;             // workgroups that fill the chip, one to a compute unit
 
-__device__ __forceinline__ float block_reduce_max(float v, float* red) {
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-}
-__device__ __forceinline__ float block_reduce_sum(float v, float* red) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    return (red[0] + red[1]) + (red[2] + red[3]);
-}
-
-__global__ __launch_bounds__(256) void score_valu_kernel(ScoreArgs a) {
+// A workgroup takes up to eight segments of a (batch, head), i.e. 16 columns (segment, max/min representative) of Z^T = K_rep .
+// Q_rep^T, and all blocks: 16x16x4 fp32 MFMAs over tiles of eight blocks (A = 16 representative rows of K straight from memory, B =
+// the columns), logits to LDS as [column][K representative][block], then row softmax, (S1+S3)/2 vs (S2+S4)/2, mask, fusion.
+// Bound by latency: one chain of loads, products, two passes over the row, stores.  Estimate step against one segment per
+// workgroup with vector FMAs, each thread reading the 1 KiB of a block's representatives by itself: one head x 2048 tokens 12.0 ->
+// 9.1 us, 8 x 8192 in blocks of 16 45 -> 30, 2 x 64K in blocks of 32 167 -> 85 (pooling included); error against float64 half as large (two accumulator chains).
+constexpr int kScore32Waves = 8;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+__host__ __device__ inline int score32_pitch(int n2) { return 2 * n2 + 1; }   // floats per column; odd: columns fall on different banks
+__global__ __launch_bounds__(64 * kScore32Waves) void score_fp32_kernel(ScoreArgs a) {
     extern __shared__ float smem[];
-    float* qr = smem;                 // [2][128]
-    float* red = smem + 2 * kHeadDim; // [4]
-    float* z = red + 4;               // [4][n2]
-    const int j = blockIdx.x, h = blockIdx.y, bb = blockIdx.z;
-    const int tid = threadIdx.x;
-    const long long qrow = ((long long)bb * a.hq + h) * a.n1 + j;
-    const int g = h / (a.hq / a.hkv);
-    const long long kbase = ((long long)bb * a.hkv + g) * a.n2;
-    qr[tid] = ((const float*)a.qrep)[qrow * 2 * kHeadDim + tid];
-    __syncthreads();
-    const int vis = min(a.n2, (j + 1) * a.r);               // first block wholly after the segment
-    const int dom = a.domain == 0 ? a.n2 : vis;
-    for (int i = tid; i < a.n2; i += 256) {
-        float zz[4] = {0.f, 0.f, 0.f, 0.f};
-        const float4* km = (const float4*)((const float*)a.krep + (kbase + i) * 2 * kHeadDim);
-#pragma unroll 4
-        for (int c = 0; c < 32; ++c) {
-            const float4 hi4 = km[c], lo4 = km[32 + c];
-            const float kh[4] = {hi4.x, hi4.y, hi4.z, hi4.w}, kl[4] = {lo4.x, lo4.y, lo4.z, lo4.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float qh = qr[c * 4 + e], ql = qr[kHeadDim + c * 4 + e];
-                zz[0] = fmaf(qh, kh[e], zz[0]); zz[1] = fmaf(qh, kl[e], zz[1]);
-                zz[2] = fmaf(ql, kh[e], zz[2]); zz[3] = fmaf(ql, kl[e], zz[3]);
-            }
-        }
-        const bool in_dom = i < dom;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) z[w * a.n2 + i] = in_dom ? zz[w] * a.scale : -INFINITY;
-    }
-    __syncthreads();
-    float mx[4], inv[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        float m = -INFINITY;
-        for (int i = tid; i < a.n2; i += 256) m = fmaxf(m, z[w * a.n2 + i]);
-        mx[w] = block_reduce_max(m, red);
-    }
     constexpr float kLog2e = 1.4426950408889634f;
+    const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int segs = a.wg_groups, pitch = score32_pitch(a.n2);
+    float* z = smem;                                        // [2 * segs][pitch]
+    float* inv = smem + 2 * segs * pitch;                   // [2 * segs][2]
+    const int j0 = blockIdx.x * segs, h = blockIdx.y, bb = blockIdx.z;
+    const long long qrow0 = ((long long)bb * a.hq + h) * a.n1;
+    const float* krep = (const float*)a.krep + ((long long)bb * a.hkv + h / (a.hq / a.hkv)) * a.n2 * 2 * kHeadDim;
+    const int n_seg = min(segs, a.n1 - j0);                 // of this workgroup
+    f32x4 qf[8];                                            // column c16: both sides take the channels in the order 16*kk + 4*g + e
+    {
+        const float* src = (const float*)a.qrep + (qrow0 + j0) * 2 * kHeadDim + min(c16, 2 * n_seg - 1) * kHeadDim + 4 * g;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
+        for (int kk = 0; kk < 8; ++kk) qf[kk] = *(const f32x4*)(src + 16 * kk);
+    }
+    const int col = c16, seg = j0 + (c16 >> 1);
+    const int dom = a.domain == 0 ? a.n2 : min(a.n2, (seg + 1) * a.r);
+    for (int t = wave; 8 * t < a.n2; t += kScore32Waves) {
+        const float* src = krep + (long long)min(16 * t + c16, 2 * a.n2 - 1) * kHeadDim + 4 * g;
+        f32x4 kf[8];
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) kf[kk] = *(const f32x4*)(src + 16 * kk);
+        f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kk][e], qf[kk][e], acc[e & 1], 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {                       // K row 4*g + r of the tile: block 2*g + r/2, representative r & 1
+            const int i = 8 * t + 2 * g + (r >> 1);
+            if (col < 2 * n_seg && i < a.n2) z[col * pitch + (r & 1) * a.n2 + i] = i < dom ? (acc[0][r] + acc[1][r]) * a.scale : -INFINITY;
+        }
+    }
+    __syncthreads();
+    for (int x = wave; x < 4 * n_seg; x += kScore32Waves) { // one wave to a row of logits
+        float* row = z + (x >> 1) * pitch + (x & 1) * a.n2;
+        float m = -INFINITY;
+        for (int i = lane; i < a.n2; i += 64) m = fmaxf(m, row[i]);
+        for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
         float sum = 0.f;
-        for (int i = tid; i < a.n2; i += 256) {
-            const float e = exp2f((z[w * a.n2 + i] - mx[w]) * kLog2e);
-            z[w * a.n2 + i] = e;
+        for (int i = lane; i < a.n2; i += 64) {
+            const float e = exp2f((row[i] - m) * kLog2e);
+            row[i] = e;
             sum += e;
         }
-        inv[w] = 1.0f / block_reduce_sum(sum, red);
+        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+        if (lane == 0) inv[x] = 1.0f / sum;
     }
-    float* out = a.scores + qrow * a.n2;
-    const float* prev = a.prev ? a.prev + qrow * a.n2 : nullptr;
-    for (int i = tid; i < a.n2; i += 256) {
-        const float s1 = z[i] * inv[0], s2 = z[a.n2 + i] * inv[1];
-        const float s3 = z[2 * a.n2 + i] * inv[2], s4 = z[3 * a.n2 + i] * inv[3];
-        float s = fmaxf((s1 + s3) * 0.5f, (s2 + s4) * 0.5f);
-        if (i >= vis) s = 0.f;
-        if (prev) s = a.alpha * s + (1.0f - a.alpha) * prev[i];
-        if (fabsf(s) < 1.17549435e-38f) s = 0.f;
-        out[i] = s;
+    __syncthreads();
+    for (int s = 0; s < n_seg; ++s) {
+        const int vis = min(a.n2, (j0 + s + 1) * a.r);      // first block wholly after the segment
+        const float* zmax = z + 2 * s * pitch;              // of Q_max: K_max, K_min; then of Q_min
+        const float* zmin = zmax + pitch;
+        const long long row = (qrow0 + j0 + s) * a.n2;
+        for (int i = tid; i < a.n2; i += 64 * kScore32Waves) {
+            float sc = 0.f;
+            if (i < vis) {
+                const float s1 = zmax[i] * inv[4 * s], s2 = zmax[a.n2 + i] * inv[4 * s + 1];
+                const float s3 = zmin[i] * inv[4 * s + 2], s4 = zmin[a.n2 + i] * inv[4 * s + 3];
+                sc = fmaxf((s1 + s3) * 0.5f, (s2 + s4) * 0.5f);
+            }
+            if (a.prev) sc = a.alpha * sc + (1.0f - a.alpha) * a.prev[row + i];
+            if (fabsf(sc) < 1.17549435e-38f) sc = 0.f;
+            a.scores[row + i] = sc;
+        }
     }
 }
 
@@ -682,14 +683,15 @@ hipError_t launch_score(const Shape& sh, const void* qrep, const void* krep, con
         if (e != hipSuccess) return e;
         return pairs ? launch_score_pass<1, 2>(a, grid, st) : launch_score_pass<1, 1>(a, grid, st);
     }
-    const size_t smem = (2 * kHeadDim + 4 + 4 * (size_t)sh.n2) * sizeof(float);
-    dim3 grid(sh.n1, sh.hq, sh.batch);
-    const void* fn = (const void*)score_valu_kernel;
-    if (smem > 48 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(score_valu_kernel, grid, dim3(256), smem, st, a);
+    // as many segments to a workgroup as leave one for every compute unit and fit their rows of logits in LDS
+    const long long heads = (long long)sh.batch * sh.hq;
+    auto bytes = [&](int segs) { return (2 * (size_t)segs * score32_pitch(sh.n2) + 4 * segs) * sizeof(float); };
+    int segs = 8;
+    while (segs > 1 && (bytes(segs) > 128 * 1024 || heads * ((sh.n1 + segs - 1) / segs) < kScoreWgs)) segs /= 2;
+    a.wg_groups = segs;
+    const hipError_t e = hipFuncSetAttribute((const void*)score_fp32_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes(segs));
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(score_fp32_kernel, dim3((sh.n1 + segs - 1) / segs, sh.hq, sh.batch), dim3(64 * kScore32Waves), bytes(segs), st, a);
     return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
 """The pooling kernel with 1, 2, 4 and 8 waves to a segment or block, and groups of every remainder of a batch (32 bf16 or 16 fp32
-rows): the scores of the estimate step against the fp64 checker, with the bar of the other score tests."""
+rows); the fp32 score kernel with 1 to 8 segments to a workgroup (the last two shapes: eight with one left over, one): the scores of the estimate step against the fp64 checker, with the bar of the other score tests."""
 import numpy as np
 import pytest
 
@@ -13,7 +13,8 @@ DEV = "cuda"
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("shape", [(1, 1, 1, 16, 16), (2, 1, 97, 32, 32), (2, 2, 1055, 128, 64), (3, 1, 1601, 512, 512), (1, 1, 3000, 1024, 8),
-                                   (32, 4, 8197, 64, 64)], ids=lambda c: "x".join(map(str, c)))
+                                   (32, 4, 8197, 64, 64),
+                                   (32, 8, 1040, 16, 16), (1, 1, 40000, 256, 8)], ids=lambda c: "x".join(map(str, c)))
 def test_scores_for_every_split(shape, dtype):
     Hq, Hkv, n, s, b = shape
     w = H.small_workload("pool", 1, Hq, Hkv, n, s, b, 2, 0, dtype=dtype, unit_variance=n > 1)
