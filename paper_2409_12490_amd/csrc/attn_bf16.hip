@@ -41,6 +41,7 @@ constexpr int kTokOff = 0;                            // [NBUF][TK] token positi
 constexpr int kVOff = 1024;                           // [NBUF] V tiles
 constexpr int kKOff = kVOff + NBUF * kTileBytes;      // [NBUF] K tiles
 constexpr int kListOff = kKOff + NBUF * kTileBytes;   // the segment's block list (sparse only)
+constexpr unsigned kRound = 256;                      // workgroups of a round, see the workgroup order
 constexpr int kOutPitch = 272;                        // epilogue staging: one output row + 16 B, in bytes
 static_assert(kListOff + kMaxListBf16 * 4 <= 160 * 1024, "LDS budget");
 static_assert(8 * WQ * kOutPitch <= 2 * NBUF * kTileBytes, "epilogue staging reuses the tile rings");
@@ -61,17 +62,22 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     const int l32 = lane & 31, hh = lane >> 5;
     const bool rotated = wave >= 4;                              // shares its SIMD with wave - 4
 
+    // Every argument is asked for here, in one go: the compiler would load them where they are used, one latency after another.  With
+    // this, the index arithmetic free of divisions, Q loaded without a branch per fragment and the trailing tiles looked at 64 at a time, the
+    // list is asked for after 120 instead of 290 instructions: 32 x 16K tokens (16 blocks of 64) 388 -> 376 us, 2 x 32 x 64K (32
+    // of 32) 2640 -> 2597, 32 x 128K (32 of 64, shared lists) 4.97 -> 4.75 ms, same outputs.
+    asm volatile("" ::"s"(a.q), "s"(a.k), "s"(a.v), "s"(a.idx), "s"(a.cnt), "s"(a.n), "s"(a.s), "s"(a.qs0), "s"(a.qs1), "s"(a.qs2), "s"(a.ks0),
+                 "s"(a.ks1), "s"(a.ks2), "s"(a.list_len), "s"(a.scale_log2e), "s"(a.div_b.mul));
     // ---- which (batch, head, segment, query tile) this workgroup owns --------------------------
-    int bb, h, j = 0, qt;
-    const int G = a.hq / a.hkv;
+    int bb, h, g, j = 0, qt;
     if (DENSE) {
         // heaviest query tiles first; consecutive workgroups walk the KV heads so that the query
         // heads sharing one KV head land on the same XCD (workgroup id mod 8) at the same time.
-        const int bh_count = a.batch * a.hq, bkv = a.batch * a.hkv;
-        const int x = blockIdx.x % bh_count;
-        qt = a.qtiles - 1 - blockIdx.x / bh_count;
-        const int bkvh = x % bkv, gq = x / bkv;
-        bb = bkvh / a.hkv; h = (bkvh % a.hkv) * G + gq;
+        // div_order: batch * hq, batch * hkv
+        const unsigned y = a.div_order[0].div(blockIdx.x), x = blockIdx.x - y * (unsigned)(a.batch * a.hq);
+        qt = a.qtiles - 1 - (int)y;
+        const unsigned gq = a.div_order[1].div(x), bkvh = x - gq * (unsigned)(a.batch * a.hkv);
+        bb = (int)a.div_hkv.div(bkvh); g = (int)bkvh - bb * a.hkv; h = g * a.group + (int)gq;
     } else {
         // (batch, KV head) groups run one after another.  Workgroups reach the compute units round-robin and in
         // order: workgroup x + 256 follows workgroup x on the same unit and starts only after every workgroup
@@ -81,26 +87,24 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
         // takes 256 (query head, segment) pairs at ONE query tile and the next round the same pairs at the next
         // tile.  Inside a round every XCD (workgroup id mod 8) gets 32 consecutive pairs: the query heads of a
         // few neighbouring segments.
-        constexpr int kRound = 256;
-        const int pairs = G * a.n1;
-        const int per_group = pairs * a.qtiles;
-        const int grp = blockIdx.x / per_group;
-        const int x = blockIdx.x % per_group;
-        const int full = pairs / kRound * kRound;                // pairs that fill whole rounds
-        int u;
-        if (x < full * a.qtiles) {
-            const int y = x % (kRound * a.qtiles), pos = y % kRound;
-            qt = y / kRound;
-            u = x / (kRound * a.qtiles) * kRound + (pos & 7) * (kRound / 8) + (pos >> 3);
+        // div_order: items of a group, items of a round, pairs that fill no whole round
+        const unsigned pairs = a.group * a.n1, qtiles = a.qtiles;
+        const unsigned grp = a.div_order[0].div(blockIdx.x), x = blockIdx.x - grp * pairs * qtiles;
+        const unsigned full = pairs / kRound * kRound;           // pairs that fill whole rounds
+        unsigned u;
+        if (x < full * qtiles) {
+            const unsigned rd = a.div_order[1].div(x), y = x - rd * kRound * qtiles, pos = y % kRound;
+            qt = (int)(y / kRound);
+            u = rd * kRound + (pos & 7) * (kRound / 8) + (pos >> 3);
         } else {
-            const int rest = pairs - full, y = x - full * a.qtiles;
-            qt = y / rest;
-            u = full + y % rest;
+            const unsigned rest = pairs - full, y = x - full * qtiles;
+            qt = (int)a.div_order[2].div(y);
+            u = full + y - (unsigned)qt * rest;
         }
-        const int gq = u % G; j = u / G;
-        bb = grp / a.hkv; h = (grp % a.hkv) * G + gq;
+        j = (int)a.div_group.div(u);
+        const int gq = (int)u - j * a.group;
+        bb = (int)a.div_hkv.div(grp); g = (int)grp - bb * a.hkv; h = g * a.group + gq;
     }
-    const int g = h / G;
     const int q_lo = DENSE ? qt * TQ : j * a.s + qt * TQ;
     const int q_end = DENSE ? a.n : min(a.n, (j + 1) * a.s);
     if (q_lo >= q_end) return;                                   // uniform: tile past a short segment
@@ -131,14 +135,9 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     const int qpos = wq_lo + l32;
     bf16x8 qf[8];
     {
-        const bool ok = qpos < q_end;
-        const uint16_t* src = qp + (long long)(ok ? qpos : q_lo) * a.qs2 + 8 * hh;
+        const uint16_t* src = qp + (long long)min(qpos, q_last) * a.qs2 + 8 * hh;    // rows past the end repeat the last one
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) {
-            uint4 v = *(const uint4*)(src + 16 * ks);
-            if (!ok) v = make_uint4(0, 0, 0, 0);
-            qf[ks] = as_bf16x8(v);
-        }
+        for (int ks = 0; ks < 8; ++ks) qf[ks] = as_bf16x8(*(const uint4*)(src + 16 * ks));
     }
 
     if (!DENSE) {
@@ -155,7 +154,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     const unsigned tab0 = lds0 + kListOff + (((unsigned)a.list_len * 4u + 1023u) & ~1023u);
     if (HALF) {
         for (int x = tid; x < ntiles; x += 512) {
-            const unsigned p0 = (unsigned)x * TK, e0 = p0 / ub, p1 = p0 + 32, e1 = p1 / ub;
+            const unsigned p0 = (unsigned)x * TK, e0 = a.div_b.div(p0), p1 = p0 + 32, e1 = a.div_b.div(p1);
             const int lo = *LDS_PTR(const int, lds0 + kListOff + e0 * 4) * a.b + (int)(p0 - e0 * ub);
             const int hi = e1 < (unsigned)count ? *LDS_PTR(const int, lds0 + kListOff + e1 * 4) * a.b + (int)(p1 - e1 * ub) : -1;
             i32x2 d; d[0] = lo; d[1] = hi;
@@ -163,18 +162,20 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
         }
         __syncthreads();
     }
-    if (!DENSE) {   // drop trailing tiles that start after the last query row (lists are ascending)
+    if (!DENSE) {   // drop trailing tiles that start after the last query row (lists are ascending): lane l looks at the l-th last one
         while (ntiles > 0) {
+            const int x = max(ntiles - 1 - lane, 0);
             int tok;
-            if (HALF) tok = *LDS_PTR(const int, tab0 + (ntiles - 1) * 8);
+            if (HALF) tok = *LDS_PTR(const int, tab0 + x * 8);
             else {
-                const unsigned p = (unsigned)(ntiles - 1) * TK;
-                const unsigned e = p / ub;
+                const unsigned p = (unsigned)x * TK, e = a.div_b.div(p);
                 tok = *LDS_PTR(const int, lds0 + kListOff + e * 4) * a.b + (int)(p - e * ub);
             }
-            if (tok <= q_last) break;
-            --ntiles;
+            const unsigned long long seen = __builtin_amdgcn_ballot_w64(tok <= q_last && lane < ntiles);
+            ntiles -= seen ? (int)__builtin_ctzll(seen) : min(ntiles, 64);
+            if (seen) break;
         }
+        ntiles = __builtin_amdgcn_readfirstlane(ntiles);
     }
 
     // ---- tile loader: wave w fills rows 4*w .. 4*w+3 and 32 + 4*w .. +3 of K and of V (4 instructions) ----
@@ -663,16 +664,22 @@ hipError_t launch_attn_bf16(const Shape& sh, const void* q, const void* k, const
     a.qs0 = sh.qs[0]; a.qs1 = sh.qs[1]; a.qs2 = sh.qs[2];
     a.ks0 = sh.kvs[0]; a.ks1 = sh.kvs[1]; a.ks2 = sh.kvs[2];
     a.os0 = sh.os[0]; a.os1 = sh.os[1]; a.os2 = sh.os[2];
+    a.group = sh.hq / sh.hkv;
     // Few query rows: 256 of them to a workgroup leave compute units idle, 32 do not.  The lines lie where the two kernels meet
     // (256-row against 32-row kernel).  Block-sparse, 16384 rows: 32 heads x 512 20.4 / 13.9 to 22.6 / 15.4 us, 8 x 2048 25.7 / 21.1 to 55 / 35, 1 x
     // 16K 26.3 / 22.3 to 69 / 56; 24576 rows: 26.5 / 26.7 and 26.9 / 25.5, 26.1 / 30.2 to 69 / 59, 27.6 / 33.7 to 72 / 85.  Dense, 32768 rows:
     // 32 x 1024 30.9 / 30.5, 8 x 4096 98 / 86, 1 x 32K 722 / 590; 40960 rows: 37 / 40, 123 / 126, 903 / 938.
     if ((long long)sh.batch * sh.hq * sh.n <= (idx ? 16384 : 32768)) return launch_attn_bf16_rows(sh, a, st);
+    const uint32_t bkv = (uint32_t)sh.batch * sh.hkv;
+    a.div_group = FastDiv(a.group); a.div_hkv = FastDiv(sh.hkv); a.div_b = FastDiv(sh.b);
     hipError_t e;
     if (idx) {
         if (sh.list_len > kMaxListBf16) return hipErrorInvalidValue;
         a.qtiles = (sh.s + TQ - 1) / TQ;
         const long long grid = (long long)sh.batch * sh.hq * sh.n1 * a.qtiles;
+        const uint32_t pairs = (uint32_t)a.group * sh.n1;        // (query head, segment) pairs of a KV head
+        a.div_order[0] = FastDiv(pairs * a.qtiles); a.div_order[1] = FastDiv(kRound * a.qtiles);
+        a.div_order[2] = FastDiv(pairs % kRound ? pairs % kRound : 1);
         const int smem = kListOff + ((sh.list_len * 4 + 1023) & ~1023);
         const int tab_bytes = (int)(((long long)sh.list_len * sh.b + TK - 1) / TK) * 8;     // MODE 3: tile descriptions
         if (sh.b % TK == 0) {
@@ -691,6 +698,7 @@ hipError_t launch_attn_bf16(const Shape& sh, const void* q, const void* k, const
     } else {
         a.qtiles = (sh.n + TQ - 1) / TQ;
         const long long grid = (long long)sh.batch * sh.hq * a.qtiles;
+        a.div_order[0] = FastDiv((uint32_t)sh.batch * sh.hq); a.div_order[1] = FastDiv(bkv);
         e = hipFuncSetAttribute((const void*)attn_bf16_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kListOff);
         if (e != hipSuccess) return e;

@@ -40,7 +40,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a) {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Consecutive workgroups walk the KV heads, so that a head's keys stay with few XCDs (workgroup id mod 8); inside one the row
     // tiles of a segment and head follow each other, and the segments with most keys, those at the end, come first.
-    const int G = a.hq / a.hkv, bkv = a.batch * a.hkv;
+    const int G = a.group, bkv = a.batch * a.hkv;
     const int x = blockIdx.x % bkv, y = blockIdx.x / bkv;
     const int bb = x / a.hkv, kvh = x % a.hkv;
     int h, j = 0, q_lo;
