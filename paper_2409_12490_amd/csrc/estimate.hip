@@ -142,6 +142,7 @@ struct ScoreArgs {
     int nchunk, n1_pad;
     int parts;                             // bf16 path: waves that share a group and split the tiles of a chunk (1, 2, 4, 8)
     int wg_groups;                         // groups of 16 * GPW segments (bf16) or segments (fp32) per workgroup
+    int wg_heads;                          // bf16 path: query heads of one KV head whose groups are numbered through
     float scale, alpha;
 };
 constexpr int kScoreWaves = 8;             // waves per workgroup of the bf16 score kernel
@@ -319,11 +320,11 @@ __global__ __launch_bounds__(64 * kScoreWaves, 2) void score_kernel(ScoreArgs a)
     constexpr float kLog2e = 1.4426950408889634f;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int chunk = blockIdx.x, h = blockIdx.z % a.hq, bb = blockIdx.z / a.hq;
+    const int chunk = blockIdx.x, bh0 = blockIdx.z * a.wg_heads, h0 = bh0 % a.hq, bb = bh0 / a.hq;
     const int col_waves = kScoreWaves / a.parts, part = wave / col_waves;
     const int g_first = blockIdx.y * a.wg_groups + wave % col_waves;
-    const int g_end = min((a.n1 + 16 * GPW - 1) / (16 * GPW), (int)(blockIdx.y + 1) * a.wg_groups);
-    const long long qrow0 = ((long long)bb * a.hq + h) * a.n1;   // row of segment 0 of this (batch, head) in scores
+    const int head_groups = (a.n1 + 16 * GPW - 1) / (16 * GPW);
+    const int g_end = min(head_groups * a.wg_heads, (int)(blockIdx.y + 1) * a.wg_groups);
     // first block of tile lt of the chunk
     auto tile_begin = [&](int lt) { return kTileBlocks * (lt < kChunkTiles / 2 ? chunk * (kChunkTiles / 2) + lt
                                                           : a.nchunk * kChunkTiles - 1 - (chunk * (kChunkTiles / 2) + lt - kChunkTiles / 2)); };
@@ -334,8 +335,9 @@ __global__ __launch_bounds__(64 * kScoreWaves, 2) void score_kernel(ScoreArgs a)
     {
         static_assert(kScoreWaves == kChunkTiles, "a wave copies a tile");
         const int b0 = tile_begin(wave);
-        if (b0 < (PASS == 1 || a.domain == 1 ? seen_end(g_end * 16 * GPW - 1) : a.n2)) {
-            const uint16_t* ksrc = (const uint16_t*)a.krep + ((long long)bb * a.hkv + h / (a.hq / a.hkv)) * a.n2 * 2 * kHeadDim;
+        const int last = a.wg_heads > 1 ? a.n1 - 1 : g_end * 16 * GPW - 1;      // (several heads: the last segment is among them)
+        if (b0 < (PASS == 1 || a.domain == 1 ? seen_end(last) : a.n2)) {
+            const uint16_t* ksrc = (const uint16_t*)a.krep + ((long long)bb * a.hkv + h0 / (a.hq / a.hkv)) * a.n2 * 2 * kHeadDim;
             const unsigned long long pv = (unsigned long long)ksrc;
             const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)pv);
             const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(pv >> 32));
@@ -361,7 +363,9 @@ __global__ __launch_bounds__(64 * kScoreWaves, 2) void score_kernel(ScoreArgs a)
     const bool joint = PASS == 2 || a.parts > 1;
     for (int g = g_first; g < g_end || !landed; g += col_waves) {
         const bool active = g < g_end;                      // wave-uniform
-        const int j0 = g * 16 * GPW;
+        const int head = min(g, g_end - 1) / head_groups;   // of this workgroup
+        const int j0 = (g - head * head_groups) * 16 * GPW;
+        const long long qrow0 = (long long)(bh0 + head) * a.n1;  // row of segment 0 of this (batch, head) in scores
         const int vis_hi = seen_end(j0 + 16 * GPW - 1);     // first block after the last segment of the group
         int seg[GPW], vis[GPW];
         bf16x8 qf[GPW][8];
@@ -375,7 +379,7 @@ __global__ __launch_bounds__(64 * kScoreWaves, 2) void score_kernel(ScoreArgs a)
         }
         // statistics of product b2, column col: stats[((bh * nchunk + chunk) * 2 + b2) * 2 + (0: max, 1: sum)][col]
         const long long cols = 2LL * a.n1_pad, chunk_step = 4 * cols;
-        float* stats = a.stats + (long long)blockIdx.z * a.nchunk * chunk_step;
+        float* stats = a.stats + (long long)(bh0 + head) * a.nchunk * chunk_step;
         float mx[GPW][2], inv[GPW][2];
         if (PASS == 1) {                                    // merge: the lane does product b2 = hh, its column's other lane the other one
 #pragma unroll
@@ -662,7 +666,7 @@ hipError_t launch_score(const Shape& sh, const void* qrep, const void* krep, con
     a.scale = sh.score_scale; a.alpha = sh.alpha;
     a.nchunk = (sh.n2 + kScoreChunk - 1) / kScoreChunk;
     a.n1_pad = (sh.n1 + 127) / 128 * 128;
-    a.parts = 1; a.wg_groups = kScoreWaves;
+    a.parts = 1; a.wg_groups = kScoreWaves; a.wg_heads = 1;
     if (sh.dtype == 1) {
         const long long heads = (long long)sh.batch * sh.hq;
         if (heads > 65535) return hipErrorInvalidValue;
@@ -677,7 +681,12 @@ hipError_t launch_score(const Shape& sh, const void* qrep, const void* krep, con
         if (!pairs)
             while (a.parts < kChunkTiles && (a.wg_groups / 2 >= groups || wgs(groups) < kScoreWgs)) { a.parts *= 2; a.wg_groups /= 2; }
         while (a.parts == 1 && a.nchunk > 1 && a.wg_groups < groups && wgs(groups) >= 4 * kScoreWgs) a.wg_groups *= 2;
-        const dim3 grid(a.nchunk, (groups + a.wg_groups - 1) / a.wg_groups, (unsigned)heads);
+        // One workgroup holds all groups of a head and there are still two for every compute unit: the heads of a KV head share a
+        // copied chunk (estimate, 2 x 32 heads x 64K 330 -> 319 us without S', 359 with it either way; 32 x 128K in blocks of 32 407 -> 402).
+        while (pairs && a.wg_groups >= groups * a.wg_heads && (a.hq / a.hkv) % (2 * a.wg_heads) == 0 && heads / a.wg_heads * a.nchunk >= 2 * kScoreWgs) {
+            a.wg_heads *= 2; a.wg_groups *= 2;
+        }
+        const dim3 grid(a.nchunk, (groups * a.wg_heads + a.wg_groups - 1) / a.wg_groups, (unsigned)(heads / a.wg_heads));
         if (a.nchunk == 1) return launch_score_pass<2, 1>(a, grid, st);
         const hipError_t e = pairs ? launch_score_pass<0, 2>(a, grid, st) : launch_score_pass<0, 1>(a, grid, st);
         if (e != hipSuccess) return e;
