@@ -99,14 +99,15 @@ constexpr int kPrefilterMaxK = 128;                     // and is used for k up 
 // in index order into the wave's LDS region (at most 4 per lane) and the exact search runs on them: the same list,
 // ties included, with a fraction of the compares.  A row with more than 256 keys >= T (many equal scores) is
 // searched in full.
+// merged: the row's keys in LDS (SHARED), else they come from the scores.
 template <int PER_LANE, bool SHARED>
-__device__ __forceinline__ int select_row(const SelectArgs& a, long long row, int j, int n_cand, int kj, int lane,
-                                          int32_t* out, uint2* cand) {
+__device__ __forceinline__ int select_row(const SelectArgs& a, long long row, int n_cand, int kj, int lane,
+                                          int32_t* out, uint2* cand, const uint32_t* merged) {
     uint32_t key[PER_LANE];
 #pragma unroll
     for (int m = 0; m < PER_LANE; ++m) {
         const int i = m * 64 + lane;
-        const uint32_t kx = row_key<SHARED>(a, row, j, min(i, a.n2 - 1));   // unconditional load: no per-element exec masks to keep
+        const uint32_t kx = SHARED ? merged[min(i, n_cand - 1)] : row_key<false>(a, row, 0, min(i, a.n2 - 1));   // unconditional load: no per-element exec masks to keep
         key[m] = (i < n_cand) ? kx : 0u;                   // 0 is below every trial threshold: never counted
     }
     if (PER_LANE > kCandPerLane && kj <= kPrefilterMaxK) {
@@ -145,12 +146,15 @@ __device__ __forceinline__ int select_row(const SelectArgs& a, long long row, in
     return take_largest<PER_LANE>(key, thr, kj, (n_cand + 63) / 64, lane, out, [&](int m) { return m * 64 + lane; });
 }
 
+// SHARED: a workgroup per list, since there are only as many as KV heads: its four waves merge the scores of the group's query heads
+// into LDS (several loads of a head's row in flight), then one of them searches.  With one wave per list, its loads head after head,
+// 32 query heads x 128K tokens in blocks of 64 took 44 us for 8 KV heads and 71 us for 4; now 15 and 14 (67 MB of scores).
 // MAX_PER_LANE: 64 * MAX_PER_LANE >= n2, a multiple of 8.  A row early in the sequence has few candidates: the
 // search is compiled for eight row lengths (eighths of the maximum) and a wave takes the shortest that holds its row.
 template <int MAX_PER_LANE, bool SHARED>
 __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
     const int lane = threadIdx.x & 63;
-    const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const long long row = SHARED ? (long long)blockIdx.x : (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= a.rows) return;
     const int j = (int)(row % a.n1);
     const int diag_lo = j * a.r;
@@ -159,22 +163,42 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
     const int n_cand = diag_lo - n_local;
     const int kj = min(a.budget, n_cand);
     int32_t* out = a.idx + row * a.list_len;
-    __shared__ uint2 cand_all[4][64 * kCandPerLane];
-    uint2* cand = cand_all[threadIdx.x >> 6];
+    __shared__ uint2 cand_all[SHARED ? 1 : 4][64 * kCandPerLane];
+    uint2* cand = cand_all[SHARED ? 0 : threadIdx.x >> 6];
+    __shared__ uint32_t merged[SHARED ? 64 * MAX_PER_LANE : 1];
+    if (SHARED) {                                              // the whole workgroup merges the group's scores, one wave searches
+        const float* src = a.scores + ((row / a.n1 * a.group) * a.n1 + j) * a.n2;
+        const long long step = (long long)a.n1 * a.n2;         // to the next head's row
+        for (int i = threadIdx.x; i < n_cand && kj > 0; i += 256) {
+            uint32_t kx = 0;
+            int g2 = 0;
+            for (; g2 + 4 <= a.group; g2 += 4) {
+                float x[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[u] = src[(g2 + u) * step + i];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) kx = max(kx, ordered_key(x[u]));
+            }
+            for (; g2 < a.group; ++g2) kx = max(kx, ordered_key(src[g2 * step + i]));
+            merged[i] = kx;
+        }
+        __syncthreads();
+        if (threadIdx.x >= 64) return;
+    }
 
     int written = 0;
     if (kj > 0) {
         constexpr int E = MAX_PER_LANE / 8;
         const int eighths = (n_cand + 64 * E - 1) / (64 * E);          // wave-uniform, 1 .. 8
         switch (eighths) {
-            case 1: written = select_row<1 * E, SHARED>(a, row, j, n_cand, kj, lane, out, cand); break;
-            case 2: written = select_row<2 * E, SHARED>(a, row, j, n_cand, kj, lane, out, cand); break;
-            case 3: written = select_row<3 * E, SHARED>(a, row, j, n_cand, kj, lane, out, cand); break;
-            case 4: written = select_row<4 * E, SHARED>(a, row, j, n_cand, kj, lane, out, cand); break;
-            case 5: written = select_row<5 * E, SHARED>(a, row, j, n_cand, kj, lane, out, cand); break;
-            case 6: written = select_row<6 * E, SHARED>(a, row, j, n_cand, kj, lane, out, cand); break;
-            case 7: written = select_row<7 * E, SHARED>(a, row, j, n_cand, kj, lane, out, cand); break;
-            default: written = select_row<8 * E, SHARED>(a, row, j, n_cand, kj, lane, out, cand); break;
+            case 1: written = select_row<1 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            case 2: written = select_row<2 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            case 3: written = select_row<3 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            case 4: written = select_row<4 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            case 5: written = select_row<5 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            case 6: written = select_row<6 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            case 7: written = select_row<7 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            default: written = select_row<8 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
         }
     }
     // local blocks then the segment's own blocks
@@ -278,7 +302,7 @@ hipError_t launch_select_impl(const Shape& sh, const float* scores, int32_t* idx
     a.rows = (long long)sh.batch * (SHARED ? sh.hkv : sh.hq) * sh.n1;
     a.group = sh.hq / sh.hkv;
     a.n1 = sh.n1; a.n2 = sh.n2; a.r = sh.r; a.budget = sh.budget; a.local = sh.local; a.list_len = sh.list_len;
-    const unsigned grid = (unsigned)((a.rows + 3) / 4);
+    const unsigned grid = (unsigned)(SHARED ? a.rows : (a.rows + 3) / 4);
     if (sh.n2 <= 64 * 8) hipLaunchKernelGGL((select_kernel<8, SHARED>), dim3(grid), dim3(256), 0, st, a);
     else if (sh.n2 <= 64 * 32) hipLaunchKernelGGL((select_kernel<32, SHARED>), dim3(grid), dim3(256), 0, st, a);
     else if (sh.n2 <= 64 * 64) hipLaunchKernelGGL((select_kernel<64, SHARED>), dim3(grid), dim3(256), 0, st, a);
