@@ -140,9 +140,11 @@ struct ScoreArgs {
     float* stats;                          // bf16 path: per-chunk softmax statistics (see score_kernel)
     int hq, hkv, n1, n2, r, domain;
     int nchunk, n1_pad;
-    int parts;                             // bf16 path: waves that share a group and split the tiles of a chunk (1, 2, 4, 8)
-    int wg_groups;                         // groups of 16 * GPW segments (bf16) or segments (fp32) per workgroup
-    int wg_heads;                          // bf16 path: query heads of one KV head whose groups are numbered through
+    // bf16 path: the sixteens of segments of a KV head's query heads are dealt to gridDim.y workgroups: share_least each, the first
+    // share_more one more
+    int group, share_least, share_more;
+    FastDiv div_chunks, div_groups;        // nchunk; sixteens of a head
+    int segs;                              // fp32 path: segments per workgroup
     float scale, alpha;
 };
 constexpr int kScoreWaves = 8;             // waves per workgroup of the bf16 score kernel
@@ -151,6 +153,7 @@ constexpr int kTileBytes = kTileBlocks * 2 * kHeadDim * 2;   // max row + min ro
 constexpr int kChunkTiles = 8;             // tiles per workgroup, all of them in LDS (128 KiB)
 constexpr int kScoreChunk = kChunkTiles * kTileBlocks;
 constexpr int kScoreWgs = 256;             // workgroups that fill the chip, one to a compute unit
+constexpr unsigned kMaxGridYZ = 65535;     // the largest second and third extent of a grid
 
 // A workgroup takes up to eight segments of a (batch, head), i.e. 16 columns (segment, max/min representative) of Z^T = K_rep .
 // Q_rep^T, and all blocks: 16x16x4 fp32 MFMAs over tiles of eight blocks (A = 16 representative rows of K straight from memory, B =
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(64 * kScore32Waves) void score_fp32_kernel(ScoreArg
     constexpr float kLog2e = 1.4426950408889634f;
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int segs = a.wg_groups, pitch = score32_pitch(a.n2);
+    const int segs = a.segs, pitch = score32_pitch(a.n2);
     float* z = smem;                                        // [2 * segs][pitch]
     float* inv = smem + 2 * segs * pitch;                   // [2 * segs][2]
     const int j0 = blockIdx.x * segs, h = blockIdx.y, bb = blockIdx.z;
@@ -237,14 +240,13 @@ __global__ __launch_bounds__(64 * kScore32Waves) void score_fp32_kernel(ScoreArg
 // score, bf16: the four representative products as bf16 MFMA GEMMs (representatives are exact bf16
 // values, so every product is exact and only the fp32 accumulation rounds).
 //
-// The blocks of a (batch, head) are cut into tiles of 32 and the tiles into chunks of eight; a workgroup keeps the K
+// The blocks of a (batch, KV head) are cut into tiles of 32 and the tiles into chunks of eight; a workgroup keeps the K
 // representatives of one chunk in LDS (128 KiB, copied once by global_load_lds, 16-byte pieces XOR-swizzled by the block) and
-// its 8 waves walk groups of 16 * GPW segments over them, with no further barrier.  Z^T = K_rep . Q_rep^T: the A operand is
-// a tile of 32 blocks of K_max (then K_min), the B operand, column = (segment, max/min representative), stays in registers.
+// its 8 waves take groups of 16 segments, of any of the KV head's query heads, one each per round.  Z^T = K_rep . Q_rep^T: the A operand
+// is a tile of 32 blocks of K_max (then K_min), the B operand, column = (segment, max/min representative), stays in registers.
 // A lane then holds, for its column, 16 blocks of the tile in registers: the softmax statistics over blocks are in-lane
 // reductions plus one exchange between the wave halves, and the two query representatives of a segment sit in neighbouring lanes
-// (one DPP exchange per score).  A short sequence has fewer groups than waves: `parts` waves then share a group and split
-// its tiles.
+// (one DPP exchange per score).  In a last round of at most four groups `parts` waves share a group and split its tiles.
 //
 //   PASS 0   per chunk and column: max and sum of 2^(c z - max) of the two products  -> stats
 //   PASS 1   merges the chunk statistics, recomputes the products of its chunk, normalises, combines (S1+S3)/2 vs
@@ -252,18 +254,20 @@ __global__ __launch_bounds__(64 * kScore32Waves) void score_fp32_kernel(ScoreArg
 //   PASS 2   both in one launch, for rows of a single chunk (n2 <= 256): the statistics stay in LDS.
 //
 // A chunk is four tiles from the front of the row and the four that mirror them from its end, so that every workgroup has the
-// same share of the causal half.
+// same share of the causal half.  Rows of scores start at any multiple of 4 bytes; 16 bytes of one go in one access all the same.
 //
-// What bounds it: PASS 0 the vector unit (171 vector instructions, 34 of them exponentials, per 16 segments and tile: 53K of
-// the 106K busy cycles of a compute unit at 2 x 32 heads x 64K tokens, the MFMAs beside them) and the 5 to 7 us until a chunk has
-// landed; PASS 1 the latency of S' and of the stores (2.7 TB/s there).  Against eight waves that streamed their chunk
-// through two 32 KiB buffers, with a barrier per 64 blocks and 128 segments of one chunk to a workgroup, the estimate step takes,
-// same pooling: 32 heads x 2000 tokens 19.2 -> 13.7 us (one launch less), x 4096 20.3 -> 16.1, x 16K 48.4 -> 37.6, 2 x 2 heads x 84K
-// 57 -> 37, 32 x 128K 268 -> 263, 2 x 32 x 64K with fusion 373 -> 356, 8 x 128K in blocks of 16 with fusion 351 -> 320.
+// What bounds it: PASS 0 the vector unit (171 vector instructions, 34 of them exponentials, per 16 segments and tile) and the 5 to 7
+// us until a chunk has landed; PASS 1 the latency of S' and of the stores.  With one workgroup to a compute unit, what the groups leave
+// over after whole rounds of whole workgroups decides (score_shares).  The two passes, in us, against (a) eight waves that streamed
+// their chunk through two 32 KiB buffers, 128 segments of one head and chunk to a workgroup, and (b) this kernel with groups of one head in
+// fixed eights: 32 / 8 heads x 66000 tokens, segments of 256, blocks of 32: (a) 101, (b) 138, now 71; segments of 128, blocks of 16,
+// with S': 561, 825, 340; x 131072 (512, 64): 60, 60, 60, with S' 63, 67, 65; 2 x 32 x 65536 (256, 32) with S' 153, 146, 127;
+// 8 x 131072 (128, 16) 199, 214, 196; x 16384 (256, 32) 24, 15.6, 15.0.
 // ---------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_row;   // four scores of a row, which starts anywhere
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 #define SCORE_LDS(T, off) ((__attribute__((address_space(3))) T*)(uintptr_t)(off))
 
@@ -285,60 +289,58 @@ __device__ __forceinline__ float neighbour(float x) {      // the value of lane 
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, true));
 }
 
-// z[gg][b2][r] = K_rep(b2)[block 8*(r>>2) + 4*hh + (r&3) of the tile] . Q_rep[column of group gg]; tile: its LDS address.
-// The two products alternate; every fragment feeds GPW MFMAs and is read kAhead of them ahead.
-template <int GPW>
-__device__ __forceinline__ void score_tile(unsigned tile, int l32, int hh, const bf16x8 (&qf)[GPW][8], f32x16 (&z)[GPW][2]) {
+// z[b2][r] = K_rep(b2)[block 8*(r>>2) + 4*hh + (r&3) of the tile] . Q_rep[column]; tile: its LDS address.
+// The two products alternate; every fragment is read kAhead MFMAs ahead.
+__device__ __forceinline__ void score_tile(unsigned tile, int l32, int hh, const bf16x8 (&qf)[8], f32x16 (&z)[2]) {
     constexpr int kAhead = 4;
     const unsigned base = tile + l32 * 512;
     const int sw = l32 & 15;
     auto read = [&](int j) { return as_bf16x8(*SCORE_LDS(const u32x4, base + (j & 1) * 256 + (((2 * (j >> 1) + hh) ^ sw) << 4))); };
     bf16x8 kf[kAhead];
 #pragma unroll
-    for (int gg = 0; gg < GPW; ++gg)
+    for (int b2 = 0; b2 < 2; ++b2)
 #pragma unroll
-        for (int b2 = 0; b2 < 2; ++b2)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) z[gg][b2][r] = 0.f;
+        for (int r = 0; r < 16; ++r) z[b2][r] = 0.f;
 #pragma unroll
     for (int j = 0; j < kAhead; ++j) kf[j] = read(j);
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-#pragma unroll
-        for (int gg = 0; gg < GPW; ++gg)
-            z[gg][j & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[j % kAhead], qf[gg][j >> 1], z[gg][j & 1], 0, 0, 0);
+        z[j & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[j % kAhead], qf[j >> 1], z[j & 1], 0, 0, 0);
         if (j + kAhead < 16) kf[j % kAhead] = read(j + kAhead);
         __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-template <int PASS, int GPW>
+template <int PASS>
 __global__ __launch_bounds__(64 * kScoreWaves, 2) void score_kernel(ScoreArgs a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char score_lds[];
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)score_lds;
-    constexpr unsigned kRed = kChunkTiles * kTileBytes;     // behind the tiles: (max, sum) [wave][product][column], PASS 2
+    constexpr unsigned kRed = kChunkTiles * kTileBytes;     // behind the tiles: (max, sum) [wave][product][column], PASS 0 and 2
     constexpr float kLog2e = 1.4426950408889634f;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int chunk = blockIdx.x, bh0 = blockIdx.z * a.wg_heads, h0 = bh0 % a.hq, bb = bh0 / a.hq;
-    const int col_waves = kScoreWaves / a.parts, part = wave / col_waves;
-    const int g_first = blockIdx.y * a.wg_groups + wave % col_waves;
-    const int head_groups = (a.n1 + 16 * GPW - 1) / (16 * GPW);
-    const int g_end = min(head_groups * a.wg_heads, (int)(blockIdx.y + 1) * a.wg_groups);
-    // first block of tile lt of the chunk
-    auto tile_begin = [&](int lt) { return kTileBlocks * (lt < kChunkTiles / 2 ? chunk * (kChunkTiles / 2) + lt
-                                                          : a.nchunk * kChunkTiles - 1 - (chunk * (kChunkTiles / 2) + lt - kChunkTiles / 2)); };
+    // grid (x, shares, z): unit x + X z is a chunk of a (batch, KV head)
+    const unsigned unit = blockIdx.z * gridDim.x + blockIdx.x;
+    const int share = blockIdx.y, shares = gridDim.y;
+    const int kv = (int)a.div_chunks.div(unit), chunk = (int)unit - kv * a.nchunk;
+    // the sixteens of segments of the KV head's query heads, numbered through; this workgroup has every shares-th one
+    const int head_groups = (a.n1 + 15) / 16;
+    const int mine = a.share_least + (share < a.share_more ? 1 : 0);
+    // first block of tile lt of the chunk; four tiles (f) come from the front of the row, four (b) from its end, in the order f b f b b f b f,
+    // of which 1, 2 or 4 waves that take every first, second or fourth tile get equal shares
+    auto tile_begin = [&](int lt) {
+        const int x = chunk * (kChunkTiles / 2) + (lt >> 1);
+        return kTileBlocks * (((lt ^ (lt >> 2)) & 1) ? a.nchunk * kChunkTiles - 1 - x : x);
+    };
     // first block wholly after segment j (of those that exist)
     auto seen_end = [&](int j) { return min(a.n2, (min(j, a.n1 - 1) + 1) * a.r); };
     // ---- K representatives -> LDS: wave w copies tile w, row = 2 * block + representative, 256 B; blocks past the last one repeat
-    // it; a tile that nobody needs is left out
+    // it; a tile without a block is left out
     {
         static_assert(kScoreWaves == kChunkTiles, "a wave copies a tile");
         const int b0 = tile_begin(wave);
-        const int last = a.wg_heads > 1 ? a.n1 - 1 : g_end * 16 * GPW - 1;      // (several heads: the last segment is among them)
-        if (b0 < (PASS == 1 || a.domain == 1 ? seen_end(last) : a.n2)) {
-            const uint16_t* ksrc = (const uint16_t*)a.krep + ((long long)bb * a.hkv + h0 / (a.hq / a.hkv)) * a.n2 * 2 * kHeadDim;
-            const unsigned long long pv = (unsigned long long)ksrc;
+        if (b0 < a.n2) {
+            const unsigned long long pv = (unsigned long long)((const uint16_t*)a.krep + (long long)kv * a.n2 * 2 * kHeadDim);
             const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)pv);
             const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(pv >> 32));
             const void* sbase = (const void*)(((unsigned long long)hi << 32) | lo);
@@ -355,255 +357,228 @@ __global__ __launch_bounds__(64 * kScoreWaves, 2) void score_kernel(ScoreArgs a)
         }
     }
     const float cs = a.scale * kLog2e;                      // logits in log2 units
-    const bool vec = (a.n2 & 3) == 0;                       // rows of scores are 16-byte aligned
     const int rep = l32 & 1;
-    bool landed = false;
-    // Every wave takes the body at least once and meets the barriers in it: with parts > 1 or PASS 2 it has at most one group (the
-    // host sees to that), else there is only the first one, behind which all copies have landed
-    const bool joint = PASS == 2 || a.parts > 1;
-    for (int g = g_first; g < g_end || !landed; g += col_waves) {
-        const bool active = g < g_end;                      // wave-uniform
-        const int head = min(g, g_end - 1) / head_groups;   // of this workgroup
-        const int j0 = (g - head * head_groups) * 16 * GPW;
-        const long long qrow0 = (long long)(bh0 + head) * a.n1;  // row of segment 0 of this (batch, head) in scores
-        const int vis_hi = seen_end(j0 + 16 * GPW - 1);     // first block after the last segment of the group
-        int seg[GPW], vis[GPW];
-        bf16x8 qf[GPW][8];
+    for (int first = 0; first < mine; first += kScoreWaves) {       // every wave takes every round and meets the barriers in it
+        const int left = mine - first;                      // parts: waves that share a group of the last round and split its tiles
+        const int parts = left > 4 ? 1 : left > 2 ? 2 : left > 1 ? 4 : 8;
+        const int col_waves = kScoreWaves / parts, part = wave / col_waves, slot = wave % col_waves;
+        const bool active = slot < left;                    // wave-uniform
+        const int g = share + (first + min(slot, left - 1)) * shares, gh = (int)a.div_groups.div(g);
+        const int bh = kv * a.group + gh, j0 = (g - gh * head_groups) * 16;
+        const long long qrow0 = (long long)bh * a.n1;       // row of segment 0 of this (batch, head) in scores
+        const int vis_lo = seen_end(j0), vis_hi = seen_end(j0 + 15);    // first block after the first / last segment of the group
+        const int seg = j0 + (l32 >> 1), vis = seen_end(seg);
+        const long long row = (qrow0 + seg) * a.n2;
+        bf16x8 qf[8];
+        {
+            const uint16_t* src = (const uint16_t*)a.qrep + ((qrow0 + min(seg, a.n1 - 1)) * 2 + rep) * kHeadDim + 8 * hh;
 #pragma unroll
-        for (int gg = 0; gg < GPW; ++gg) {
-            seg[gg] = j0 + 16 * gg + (l32 >> 1);
-            vis[gg] = seen_end(seg[gg]);
-            const uint16_t* src = (const uint16_t*)a.qrep + ((qrow0 + min(seg[gg], a.n1 - 1)) * 2 + rep) * kHeadDim + 8 * hh;
-#pragma unroll
-            for (int ks = 0; ks < 8; ++ks) qf[gg][ks] = as_bf16x8(*(const uint4*)(src + 16 * ks));
+            for (int ks = 0; ks < 8; ++ks) qf[ks] = as_bf16x8(*(const uint4*)(src + 16 * ks));
         }
         // statistics of product b2, column col: stats[((bh * nchunk + chunk) * 2 + b2) * 2 + (0: max, 1: sum)][col]
         const long long cols = 2LL * a.n1_pad, chunk_step = 4 * cols;
-        float* stats = a.stats + (long long)(bh0 + head) * a.nchunk * chunk_step;
-        float mx[GPW][2], inv[GPW][2];
+        float* stats = a.stats + (long long)bh * a.nchunk * chunk_step;
+        float mx[2], inv[2];
         if (PASS == 1) {                                    // merge: the lane does product b2 = hh, its column's other lane the other one
+            float M = -INFINITY, L = 0.f;
+            const float* from = stats + 2 * hh * cols + 2 * seg + rep;
+            constexpr int kAhead = 8;
+            for (int c0 = 0; c0 < a.nchunk; c0 += kAhead) {
+                float mc[kAhead], lc[kAhead];
 #pragma unroll
-            for (int gg = 0; gg < GPW; ++gg) {
-                float M = -INFINITY, L = 0.f;
-                const float* from = stats + 2 * hh * cols + 2 * min(seg[gg], a.n1_pad - 1) + rep;
-                constexpr int kAhead = 8;
-                for (int c0 = 0; c0 < a.nchunk; c0 += kAhead) {
-                    float mc[kAhead], lc[kAhead];
-#pragma unroll
-                    for (int u = 0; u < kAhead; ++u) {
-                        const float* at = from + min(c0 + u, a.nchunk - 1) * chunk_step;
-                        mc[u] = at[0]; lc[u] = at[cols];
-                    }
-                    float mn = M;
-#pragma unroll
-                    for (int u = 0; u < kAhead; ++u) {
-                        if (c0 + u >= a.nchunk) { mc[u] = -INFINITY; lc[u] = 0.f; }
-                        mn = fmaxf(mn, mc[u]);
-                    }
-                    const float ms = (mn == -INFINITY) ? 0.f : mn;
-                    L *= exp2f(M - ms);
-#pragma unroll
-                    for (int u = 0; u < kAhead; ++u) L += lc[u] * exp2f(mc[u] - ms);
-                    M = mn;
+                for (int u = 0; u < kAhead; ++u) {
+                    const float* at = from + min(c0 + u, a.nchunk - 1) * chunk_step;
+                    mc[u] = at[0]; lc[u] = at[cols];
                 }
-                const float own_m = (M == -INFINITY) ? 0.f : M;
-                const float own_i = L > 0.f ? 1.0f / L : 0.f;
-                const auto rm = __builtin_amdgcn_permlane32_swap(__float_as_uint(own_m), __float_as_uint(own_m), false, false);
-                const auto ri = __builtin_amdgcn_permlane32_swap(__float_as_uint(own_i), __float_as_uint(own_i), false, false);
-                const float oth_m = __uint_as_float(hh ? rm[0] : rm[1]);   // the value of lane l ^ 32
-                const float oth_i = __uint_as_float(hh ? ri[0] : ri[1]);
-                mx[gg][0] = hh ? oth_m : own_m; mx[gg][1] = hh ? own_m : oth_m;
-                inv[gg][0] = hh ? oth_i : own_i; inv[gg][1] = hh ? own_i : oth_i;
+                float mn = M;
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) {
+                    if (c0 + u >= a.nchunk) { mc[u] = -INFINITY; lc[u] = 0.f; }
+                    mn = fmaxf(mn, mc[u]);
+                }
+                const float ms = (mn == -INFINITY) ? 0.f : mn;
+                L *= exp2f(M - ms);
+#pragma unroll
+                for (int u = 0; u < kAhead; ++u) L += lc[u] * exp2f(mc[u] - ms);
+                M = mn;
             }
+            const float own_m = (M == -INFINITY) ? 0.f : M;
+            const float own_i = L > 0.f ? 1.0f / L : 0.f;
+            const auto rm = __builtin_amdgcn_permlane32_swap(__float_as_uint(own_m), __float_as_uint(own_m), false, false);
+            const auto ri = __builtin_amdgcn_permlane32_swap(__float_as_uint(own_i), __float_as_uint(own_i), false, false);
+            const float oth_m = __uint_as_float(hh ? rm[0] : rm[1]);   // the value of lane l ^ 32
+            const float oth_i = __uint_as_float(hh ? ri[0] : ri[1]);
+            mx[0] = hh ? oth_m : own_m; mx[1] = hh ? own_m : oth_m;
+            inv[0] = hh ? oth_i : own_i; inv[1] = hh ? own_i : oth_i;
         }
-        // S' of the lane's eight scores of a tile and group, asked for one tile ahead
-        float4 pv[GPW][2];
-        const bool fused4 = PASS != 0 && a.prev && vec && active;
-        auto fetch_prev = [&](int lt) {
+        // S' of the lane's eight scores of tile lt, asked for two tiles ahead
+        struct Prev { f32x4_row v[2]; } prev[2];
+        auto fetch_prev = [&](int lt, Prev& to) {
+            if (!a.prev || !active || seg >= a.n1 || lt >= kChunkTiles) return;
 #pragma unroll
-            for (int gg = 0; gg < GPW; ++gg)
+            for (int g2 = 0; g2 < 2; ++g2) {
+                const int i = tile_begin(lt) + 4 * hh + 8 * (2 * g2 + rep);
+                const float* at = a.prev + row + i;
+                if (i + 4 <= a.n2) to.v[g2] = *(const f32x4_row*)at;
+                else {
 #pragma unroll
-                for (int g2 = 0; g2 < 2; ++g2) {
-                    const int i = lt < kChunkTiles ? tile_begin(lt) + 4 * hh + 8 * (2 * g2 + rep) : a.n2;
-                    if (fused4 && i < a.n2 && seg[gg] < a.n1) pv[gg][g2] = *(const float4*)(a.prev + (qrow0 + seg[gg]) * a.n2 + i);
+                    for (int e = 0; e < 4; ++e) if (i + e < a.n2) to.v[g2][e] = at[e];
                 }
+            }
         };
-        if (PASS != 0) fetch_prev(part);
-        if (!landed) {                                      // every wave's copies are in LDS
+        if (PASS != 0) { fetch_prev(part, prev[0]); fetch_prev(part + parts, prev[1]); }
+        if (first == 0) {                                   // every wave's copies are in LDS
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            landed = true;
         }
         if (PASS != 1) {
-            float m[GPW][2], l[GPW][2];
-#pragma unroll
-            for (int gg = 0; gg < GPW; ++gg)
-#pragma unroll
-                for (int b2 = 0; b2 < 2; ++b2) { m[gg][b2] = -INFINITY; l[gg][b2] = 0.f; }
-            for (int lt = part; lt < kChunkTiles; lt += a.parts) {
+            float m[2] = {-INFINITY, -INFINITY}, l[2] = {0.f, 0.f};
+            const int dom = a.domain == 0 ? a.n2 : vis, dom_lo = a.domain == 0 ? a.n2 : vis_lo, dom_hi = a.domain == 0 ? a.n2 : vis_hi;
+            for (int lt = part; lt < kChunkTiles; lt += parts) {
                 const int b0 = tile_begin(lt);
-                if (!active || b0 >= (a.domain == 0 ? a.n2 : vis_hi)) continue;
-                f32x16 z[GPW][2];
-                score_tile<GPW>(lds0 + lt * kTileBytes, l32, hh, qf, z);
-#pragma unroll
-                for (int gg = 0; gg < GPW; ++gg) {
-                    const int dom = a.domain == 0 ? a.n2 : vis[gg];
-                    const int dom_lo = a.domain == 0 ? a.n2 : seen_end(j0 + 16 * gg);
-                    if (cs > 0.f && b0 + kTileBlocks <= dom_lo) {
-                        // every block of the tile counts for every column: no masks, the scale folded into one fma
-#pragma unroll
-                        for (int b2 = 0; b2 < 2; ++b2) {
-                            const f32x16& x = z[gg][b2];
-                            float mt = fmaxf(x[0], x[1]);
-#pragma unroll
-                            for (int r = 2; r < 16; r += 2) mt = fmaxf(fmaxf(x[r], x[r + 1]), mt);
-                            mt = halves_max(mt) * cs;
-                            const float mn = fmaxf(m[gg][b2], mt);
-                            float sum = 0.f;
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(fmaf(x[r], cs, -mn));
-                            l[gg][b2] = l[gg][b2] * __builtin_amdgcn_exp2f(m[gg][b2] - mn) + sum;
-                            m[gg][b2] = mn;
-                        }
-                        continue;
-                    }
+                if (!active || b0 >= dom_hi) continue;
+                f32x16 z[2];
+                score_tile(lds0 + lt * kTileBytes, l32, hh, qf, z);
+                if (cs > 0.f && b0 + kTileBlocks <= dom_lo) {
+                    // every block of the tile counts for every column: no masks, the scale folded into one fma
 #pragma unroll
                     for (int b2 = 0; b2 < 2; ++b2) {
-                        float v[16];
-                        float mt = -INFINITY;
+                        const f32x16& x = z[b2];
+                        float mt = fmaxf(x[0], x[1]);
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            v[r] = (b0 + 4 * hh + 8 * (r >> 2) + (r & 3) < dom) ? z[gg][b2][r] * cs : -INFINITY;
-                            mt = fmaxf(mt, v[r]);
-                        }
-                        mt = halves_max(mt);
-                        const float mn = fmaxf(m[gg][b2], mt);
-                        const float ms = (mn == -INFINITY) ? 0.f : mn;
+                        for (int r = 2; r < 16; r += 2) mt = fmaxf(fmaxf(x[r], x[r + 1]), mt);
+                        mt = halves_max(mt) * cs;
+                        const float mn = fmaxf(m[b2], mt);
                         float sum = 0.f;
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) sum += exp2f(v[r] - ms);
-                        l[gg][b2] = l[gg][b2] * exp2f(m[gg][b2] - ms) + sum;        // per-half partial sums under a common max
-                        m[gg][b2] = mn;
+                        for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(fmaf(x[r], cs, -mn));
+                        l[b2] = l[b2] * __builtin_amdgcn_exp2f(m[b2] - mn) + sum;
+                        m[b2] = mn;
                     }
+                    continue;
+                }
+#pragma unroll
+                for (int b2 = 0; b2 < 2; ++b2) {
+                    float v[16];
+                    float mt = -INFINITY;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        v[r] = (b0 + 4 * hh + 8 * (r >> 2) + (r & 3) < dom) ? z[b2][r] * cs : -INFINITY;
+                        mt = fmaxf(mt, v[r]);
+                    }
+                    mt = halves_max(mt);
+                    const float mn = fmaxf(m[b2], mt);
+                    const float ms = (mn == -INFINITY) ? 0.f : mn;
+                    float sum = 0.f;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sum += exp2f(v[r] - ms);
+                    l[b2] = l[b2] * exp2f(m[b2] - ms) + sum;            // per-half partial sums under a common max
+                    m[b2] = mn;
                 }
             }
 #pragma unroll
-            for (int gg = 0; gg < GPW; ++gg)
-#pragma unroll
-                for (int b2 = 0; b2 < 2; ++b2) l[gg][b2] = halves_sum(l[gg][b2]);
-            if (joint) {                                    // merge the parts of the group (the host keeps GPW at 1 here)
+            for (int b2 = 0; b2 < 2; ++b2) l[b2] = halves_sum(l[b2]);
+            if (parts > 1) {                                // merge the parts of the group
+                auto red = [&](int w, int b2) { return SCORE_LDS(f32x2, lds0 + kRed + ((w * 2 + b2) * 32 + l32) * 8); };
 #pragma unroll
                 for (int b2 = 0; b2 < 2; ++b2)
-                    if (hh == 0) *SCORE_LDS(f32x2, lds0 + kRed + ((wave * 2 + b2) * 32 + l32) * 8) = f32x2{m[0][b2], l[0][b2]};
+                    if (hh == 0) *red(wave, b2) = f32x2{m[b2], l[b2]};
                 __syncthreads();
 #pragma unroll
                 for (int b2 = 0; b2 < 2; ++b2) {
                     float M = -INFINITY, L = 0.f;
-                    for (int x = 0; x < a.parts; ++x)
-                        M = fmaxf(M, (*SCORE_LDS(const f32x2, lds0 + kRed + (((x * col_waves + wave % col_waves) * 2 + b2) * 32 + l32) * 8))[0]);
+                    for (int x = 0; x < parts; ++x) M = fmaxf(M, (*red(x * col_waves + slot, b2))[0]);
                     const float ms = (M == -INFINITY) ? 0.f : M;
-                    for (int x = 0; x < a.parts; ++x) {
-                        const f32x2 e = *SCORE_LDS(const f32x2, lds0 + kRed + (((x * col_waves + wave % col_waves) * 2 + b2) * 32 + l32) * 8);
+                    for (int x = 0; x < parts; ++x) {
+                        const f32x2 e = *red(x * col_waves + slot, b2);
                         L += e[1] * exp2f(e[0] - ms);
                     }
-                    m[0][b2] = M; l[0][b2] = L;
+                    m[b2] = M; l[b2] = L;
                 }
             }
             if (PASS == 0) {
                 if (hh == 0 && part == 0 && active) {
 #pragma unroll
-                    for (int gg = 0; gg < GPW; ++gg)
-#pragma unroll
-                        for (int b2 = 0; b2 < 2; ++b2) {
-                            float* at = stats + chunk * chunk_step + 2 * b2 * cols + 2 * seg[gg] + rep;
-                            at[0] = m[gg][b2]; at[cols] = l[gg][b2];
-                        }
+                    for (int b2 = 0; b2 < 2; ++b2) {
+                        float* at = stats + chunk * chunk_step + 2 * b2 * cols + 2 * seg + rep;
+                        at[0] = m[b2]; at[cols] = l[b2];
+                    }
                 }
                 continue;
             }
 #pragma unroll
-            for (int gg = 0; gg < GPW; ++gg)
-#pragma unroll
-                for (int b2 = 0; b2 < 2; ++b2) {
-                    mx[gg][b2] = (m[gg][b2] == -INFINITY) ? 0.f : m[gg][b2];
-                    inv[gg][b2] = l[gg][b2] > 0.f ? 1.0f / l[gg][b2] : 0.f;
-                }
+            for (int b2 = 0; b2 < 2; ++b2) {
+                mx[b2] = (m[b2] == -INFINITY) ? 0.f : m[b2];
+                inv[b2] = l[b2] > 0.f ? 1.0f / l[b2] : 0.f;
+            }
         }
         if (!active) continue;
         // 2^(c z + fold) = 2^(c z - max) / sum / 2; usable when every column of the wave has a positive sum
-        float fold[GPW][2];
-        bool folds[GPW];
+        float fold[2];
 #pragma unroll
-        for (int gg = 0; gg < GPW; ++gg) {
+        for (int b2 = 0; b2 < 2; ++b2) fold[b2] = -mx[b2] + __log2f(inv[b2]) - 1.0f;
+        const bool folds = cs > 0.f && __builtin_amdgcn_ballot_w64(inv[0] > 0.f && inv[1] > 0.f) == ~0ull;
+        auto write_tile = [&](int lt, const Prev& old) {
+            const int b0 = tile_begin(lt), i0 = b0 + 4 * hh;
+            if (b0 >= a.n2) return;
+            // S1 = (max,max), S2 = (max,min), S3 = (min,max), S4 = (min,min): the lane has the products of its
+            // query representative with K_max (b2 = 0) and K_min (b2 = 1), its neighbour those of the other one
+            float sc[16];
+            if (b0 >= vis_hi) {                             // visible to no segment of the sixteen
 #pragma unroll
-            for (int b2 = 0; b2 < 2; ++b2) fold[gg][b2] = -mx[gg][b2] + __log2f(inv[gg][b2]) - 1.0f;
-            folds[gg] = cs > 0.f && __builtin_amdgcn_ballot_w64(inv[gg][0] > 0.f && inv[gg][1] > 0.f) == ~0ull;
-        }
-        for (int lt = part; lt < kChunkTiles; lt += a.parts) {
-            const int b0 = tile_begin(lt);
-            float4 now[GPW][2];
-#pragma unroll
-            for (int gg = 0; gg < GPW; ++gg)
-#pragma unroll
-                for (int g2 = 0; g2 < 2; ++g2) now[gg][g2] = pv[gg][g2];
-            fetch_prev(lt + a.parts);
-            if (b0 >= a.n2) continue;
-            const int i0 = b0 + 4 * hh;
-            f32x16 z[GPW][2];
-            if (b0 < vis_hi) score_tile<GPW>(lds0 + lt * kTileBytes, l32, hh, qf, z);
-#pragma unroll
-            for (int gg = 0; gg < GPW; ++gg) {
-                // S1 = (max,max), S2 = (max,min), S3 = (min,max), S4 = (min,min): the lane has the products of its
-                // query representative with K_max (b2 = 0) and K_min (b2 = 1), its neighbour those of the other one
-                float sc[16];
-                const bool full = b0 + kTileBlocks <= seen_end(j0 + 16 * gg);       // visible to every segment of the sixteen
-                if (b0 >= seen_end(j0 + 16 * gg + 15)) {                            // to none
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) sc[r] = 0.f;
-                } else if (folds[gg] && full) {                                     // 1/sum and the 1/2 of the average are in the exponent
+                for (int r = 0; r < 16; ++r) sc[r] = 0.f;
+            } else {
+                f32x16 z[2];
+                score_tile(lds0 + lt * kTileBytes, l32, hh, qf, z);
+                if (folds && b0 + kTileBlocks <= vis_lo) {  // to every one: 1/sum and the 1/2 of the average are in the exponent
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        const float p0 = __builtin_amdgcn_exp2f(fmaf(z[gg][0][r], cs, fold[gg][0]));
-                        const float p1 = __builtin_amdgcn_exp2f(fmaf(z[gg][1][r], cs, fold[gg][1]));
+                        const float p0 = __builtin_amdgcn_exp2f(fmaf(z[0][r], cs, fold[0]));
+                        const float p1 = __builtin_amdgcn_exp2f(fmaf(z[1][r], cs, fold[1]));
                         sc[r] = fmaxf(p0 + neighbour(p0), p1 + neighbour(p1));
                     }
                 } else {
-                    const int dom = a.domain == 0 ? a.n2 : vis[gg];
+                    const int dom = a.domain == 0 ? a.n2 : vis;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
                         const int i = i0 + 8 * (r >> 2) + (r & 3);
                         const bool in_dom = i < dom;
-                        const float p0 = in_dom ? exp2f(z[gg][0][r] * cs - mx[gg][0]) * inv[gg][0] : 0.f;
-                        const float p1 = in_dom ? exp2f(z[gg][1][r] * cs - mx[gg][1]) * inv[gg][1] : 0.f;
+                        const float p0 = in_dom ? exp2f(z[0][r] * cs - mx[0]) * inv[0] : 0.f;
+                        const float p1 = in_dom ? exp2f(z[1][r] * cs - mx[1]) * inv[1] : 0.f;
                         const float t0 = p0 + neighbour(p0), t1 = p1 + neighbour(p1);
-                        sc[r] = (i < vis[gg]) ? fmaxf(t0, t1) * 0.5f : 0.f;
+                        sc[r] = (i < vis) ? fmaxf(t0, t1) * 0.5f : 0.f;
                     }
                 }
-                // both lanes of a pair hold the segment's 16 scores: representative 0 stores blocks 0-7 and 16-23 of
-                // the lane half's 16, representative 1 the rest, four consecutive blocks at a time
-                if (seg[gg] < a.n1) {
-                    const long long row = (qrow0 + seg[gg]) * a.n2;
+            }
+            // both lanes of a pair hold the segment's 16 scores: representative 0 stores blocks 0-7 and 16-23 of
+            // the lane half's 16, representative 1 the rest, four consecutive blocks at a time
+            if (seg < a.n1) {
 #pragma unroll
-                    for (int g2 = 0; g2 < 2; ++g2) {
-                        const int i = i0 + 8 * (2 * g2 + rep);  // wave-varying but only two values: both compiled
-                        float w[4];
+                for (int g2 = 0; g2 < 2; ++g2) {
+                    const int i = i0 + 8 * (2 * g2 + rep);  // wave-varying but only two values: both compiled
+                    f32x4_row w;
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) w[e] = rep ? sc[4 * (2 * g2 + 1) + e] : sc[4 * (2 * g2) + e];
-                        const float old[4] = {now[gg][g2].x, now[gg][g2].y, now[gg][g2].z, now[gg][g2].w};
+                    for (int e = 0; e < 4; ++e) {
+                        w[e] = rep ? sc[4 * (2 * g2 + 1) + e] : sc[4 * (2 * g2) + e];
+                        if (a.prev) w[e] = a.alpha * w[e] + (1.0f - a.alpha) * old.v[g2][e];
+                        if (fabsf(w[e]) < 1.17549435e-38f) w[e] = 0.f;
+                    }
+                    float* to = a.scores + row + i;
+                    if (i + 4 <= a.n2) *(f32x4_row*)to = w;
+                    else {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            if (a.prev) w[e] = a.alpha * w[e] + (1.0f - a.alpha) * (vec ? old[e] : i + e < a.n2 ? a.prev[row + i + e] : 0.f);
-                            if (fabsf(w[e]) < 1.17549435e-38f) w[e] = 0.f;
-                        }
-                        if (vec) {
-                            if (i < a.n2) *(float4*)(a.scores + row + i) = make_float4(w[0], w[1], w[2], w[3]);
-                        } else {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (i + e < a.n2) a.scores[row + i + e] = w[e];
-                        }
+                        for (int e = 0; e < 4; ++e)
+                            if (i + e < a.n2) to[e] = w[e];
                     }
                 }
+            }
+        };
+        for (int lt = part; lt < kChunkTiles; lt += 2 * parts) {
+            write_tile(lt, prev[0]);
+            fetch_prev(lt + 2 * parts, prev[0]);
+            if (lt + parts < kChunkTiles) {
+                write_tile(lt + parts, prev[1]);
+                fetch_prev(lt + 3 * parts, prev[1]);
             }
         }
     }
@@ -638,9 +613,9 @@ hipError_t launch_pool(const Shape& sh, const void* q, const void* k, void* qrep
     return hipGetLastError();
 }
 
-// Scratch for the statistics of every chunk, padded to 128 segments.  A single chunk keeps them in LDS; the factor for short
-// sequences leaves room for up to eight partial statistics per chunk, which the kernel merges in LDS now: callers may hold
-// buffers of this size, so it stays.
+// Scratch for the statistics of every chunk, padded to 128 segments.  The kernel needs none for a single chunk and `room` times less
+// for a short sequence (the partial statistics of its waves are merged in LDS).  The size is part of the interface: it decides which calls
+// critiprefill_estimate_static refuses, and those stay the same.
 size_t score_stats_bytes(const Shape& sh) {
     if (sh.dtype != 1) return 0;
     const size_t room = sh.n1 <= 16 ? 8 : sh.n1 <= 32 ? 4 : sh.n1 <= 64 ? 2 : 1;
@@ -649,12 +624,30 @@ size_t score_stats_bytes(const Shape& sh) {
     return (size_t)sh.batch * sh.hq * nchunk * 2 * 2 * (2 * n1_pad) * sizeof(float);
 }
 
-template <int PASS, int GPW>
+// Workgroups that the groups of a KV head's query heads are dealt to.  A workgroup copies its chunk (about 0.6 of a round: 6 us, rounds of
+// 8 in PASS 0 and 15 in PASS 1), takes its rounds of eight groups and shares out the rest, 1, 1/2, 1/4 or 1/8 of a round; the chip runs
+// kScoreWgs of them at a time.  Taken: the number with the least time by this account, among those that give a workgroup up to
+// six whole rounds and a rest of 1, 2, 4 or 8.
+static int score_shares(int groups, long long chunks) {        // chunks: of all (batch, KV head)
+    int best = 1;
+    double least = 1e30;
+    for (int rounds = 0; rounds <= 6; ++rounds)
+        for (int rest = 1; rest <= kScoreWaves; rest *= 2) {
+            const int share = min(groups, rounds * kScoreWaves + rest), n = (groups + share - 1) / share;
+            const int mine = (groups + n - 1) / n, left = mine % kScoreWaves;
+            const double time = 0.6 + mine / kScoreWaves + (left == 0 ? 0.0 : left > 4 ? 1.0 : left > 2 ? 0.5 : left > 1 ? 0.25 : 0.125);
+            const double all = time * (double)((chunks * n + kScoreWgs - 1) / kScoreWgs);
+            if (all < least && n <= (int)kMaxGridYZ) { least = all; best = n; }
+        }
+    return best;
+}
+
+template <int PASS>
 static hipError_t launch_score_pass(const ScoreArgs& a, dim3 grid, hipStream_t st) {
     constexpr int smem = kChunkTiles * kTileBytes + (PASS == 1 ? 0 : kScoreWaves * 2 * 32 * 8);
-    const hipError_t e = hipFuncSetAttribute((const void*)score_kernel<PASS, GPW>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    const hipError_t e = hipFuncSetAttribute((const void*)score_kernel<PASS>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((score_kernel<PASS, GPW>), grid, dim3(64 * kScoreWaves), smem, st, a);
+    hipLaunchKernelGGL(score_kernel<PASS>, grid, dim3(64 * kScoreWaves), smem, st, a);
     return hipGetLastError();
 }
 
@@ -666,38 +659,26 @@ hipError_t launch_score(const Shape& sh, const void* qrep, const void* krep, con
     a.scale = sh.score_scale; a.alpha = sh.alpha;
     a.nchunk = (sh.n2 + kScoreChunk - 1) / kScoreChunk;
     a.n1_pad = (sh.n1 + 127) / 128 * 128;
-    a.parts = 1; a.wg_groups = kScoreWaves; a.wg_heads = 1;
     if (sh.dtype == 1) {
-        const long long heads = (long long)sh.batch * sh.hq;
-        if (heads > 65535) return hipErrorInvalidValue;
-        // Few segments: as many workgroups as the chip holds, the waves without a group of their own sharing one.  Many: pairs
-        // of groups per wave, which halve the LDS reads per MFMA (estimate at 32 heads x 128K 263 against 271 us, 8 x 128K in
-        // blocks of 16 320 / 349), and, with more than four workgroups to a compute unit, more groups to a workgroup,
-        // so that a chunk is copied less often.
-        const int sixteens = (sh.n1 + 15) / 16;
-        auto wgs = [&](int groups) { return heads * a.nchunk * ((groups + a.wg_groups - 1) / a.wg_groups); };
-        const bool pairs = a.nchunk > 1 && sixteens > kScoreWaves && heads * a.nchunk * ((sixteens + 2 * kScoreWaves - 1) / (2 * kScoreWaves)) >= kScoreWgs;
-        const int groups = pairs ? (sixteens + 1) / 2 : sixteens;
-        if (!pairs)
-            while (a.parts < kChunkTiles && (a.wg_groups / 2 >= groups || wgs(groups) < kScoreWgs)) { a.parts *= 2; a.wg_groups /= 2; }
-        while (a.parts == 1 && a.nchunk > 1 && a.wg_groups < groups && wgs(groups) >= 4 * kScoreWgs) a.wg_groups *= 2;
-        // One workgroup holds all groups of a head and there are still two for every compute unit: the heads of a KV head share a
-        // copied chunk (estimate, 2 x 32 heads x 64K 330 -> 319 us without S', 359 with it either way; 32 x 128K in blocks of 32 407 -> 402).
-        while (pairs && a.wg_groups >= groups * a.wg_heads && (a.hq / a.hkv) % (2 * a.wg_heads) == 0 && heads / a.wg_heads * a.nchunk >= 2 * kScoreWgs) {
-            a.wg_heads *= 2; a.wg_groups *= 2;
-        }
-        const dim3 grid(a.nchunk, (groups * a.wg_heads + a.wg_groups - 1) / a.wg_groups, (unsigned)(heads / a.wg_heads));
-        if (a.nchunk == 1) return launch_score_pass<2, 1>(a, grid, st);
-        const hipError_t e = pairs ? launch_score_pass<0, 2>(a, grid, st) : launch_score_pass<0, 1>(a, grid, st);
-        if (e != hipSuccess) return e;
-        return pairs ? launch_score_pass<1, 2>(a, grid, st) : launch_score_pass<1, 1>(a, grid, st);
+        if ((long long)sh.batch * sh.hq > 65535) return hipErrorInvalidValue;
+        const unsigned units = (unsigned)sh.batch * sh.hkv * a.nchunk;
+        const int head_groups = (sh.n1 + 15) / 16, groups = sh.hq / sh.hkv * head_groups;
+        const int shares = score_shares(groups, units);
+        a.group = sh.hq / sh.hkv; a.share_least = groups / shares; a.share_more = groups % shares;
+        a.div_chunks = FastDiv(a.nchunk); a.div_groups = FastDiv(head_groups);
+        // workgroups that copy the same chunk on one XCD (workgroup id mod 8) where that leaves no XCD short
+        const unsigned across = units % 8 == 0 && units / 8 <= kMaxGridYZ ? 8 : units;
+        const dim3 grid(across, shares, units / across);
+        if (a.nchunk == 1) return launch_score_pass<2>(a, grid, st);
+        const hipError_t e = launch_score_pass<0>(a, grid, st);
+        return e != hipSuccess ? e : launch_score_pass<1>(a, grid, st);
     }
-    // as many segments to a workgroup as leave one for every compute unit and fit their rows of logits in LDS
     const long long heads = (long long)sh.batch * sh.hq;
+    // as many segments to a workgroup as leave one for every compute unit and fit their rows of logits in LDS
     auto bytes = [&](int segs) { return (2 * (size_t)segs * score32_pitch(sh.n2) + 4 * segs) * sizeof(float); };
     int segs = 8;
     while (segs > 1 && (bytes(segs) > 128 * 1024 || heads * ((sh.n1 + segs - 1) / segs) < kScoreWgs)) segs /= 2;
-    a.wg_groups = segs;
+    a.segs = segs;
     const hipError_t e = hipFuncSetAttribute((const void*)score_fp32_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes(segs));
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(score_fp32_kernel, dim3((sh.n1 + segs - 1) / segs, sh.hq, sh.batch), dim3(64 * kScore32Waves), bytes(segs), st, a);
