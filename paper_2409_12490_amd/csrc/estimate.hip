@@ -6,6 +6,8 @@
 //                 element-wise max, block causal mask, layer fusion.
 #include "kernels.h"
 
+#include <type_traits>
+
 namespace cp {
 namespace {
 
@@ -26,9 +28,11 @@ __device__ __forceinline__ uint4 load_once(const void* p) {
 struct PoolArgs {
     const void* q; const void* k; void* qrep; void* krep;
     int n, s, b, n1, n2, hq, hkv;
-    long long q_groups, k_groups;          // B*Hq*n1, B*Hkv*n2
-    long long q_wgs;                       // workgroups that pool Q; the rest pool K
-    int q_split, k_split;                  // waves that share one group: 1, 2, 4 or 8
+    unsigned q_groups, k_groups;           // B*Hq*n1, B*Hkv*n2
+    unsigned q_wgs;                        // workgroups that pool Q; the rest pool K
+    int q_split, k_split;                  // log2 of the waves that share one group
+    int q_across, k_across;                // consecutive groups: 0 along a head, 1 across the heads (see launch_pool)
+    FastDiv div_n1, div_n2, div_hq, div_hkv;
     long long qs0, qs1, qs2, ks0, ks1, ks2;
 };
 
@@ -60,19 +64,31 @@ template <> struct PoolVec<float> {
 // A group is a segment of Q or a block of K; `split` waves of a workgroup share one and merge through LDS.  A lane owns 16 bytes
 // of a token row, kLanes lanes cover the row, a wave kRows rows per load with eight loads in flight (a batch).
 //
-// Bound by HBM for long sequences (1.34 GB at 32 + 8 heads x 128K tokens: 5.7 to 6.4 TB/s; a plain copy moves 5.2 here) and by
-// the latency of a wave's batches, one after another, for short ones: with a wave to a group, 2000 tokens took 11.7 us.
+// Bound by HBM for long sequences (1.34 GB at 32 + 8 heads x 128K tokens: 202 to 215 us, 6.2 to 6.6 TB/s; a plain copy moves 5.2
+// here) and by the latency of a wave's batches, one after another, for short ones: with a wave to a group, 2000 tokens took 11.7 us.
 template <typename T>
 __global__ __launch_bounds__(64 * kPoolWaves) void pool_kernel(PoolArgs a) {
     constexpr int E = PoolVec<T>::kElems, kLanes = kHeadDim / E, kRows = 64 / kLanes, kLoads = 8, kBatch = kLoads * kRows;
     __shared__ __attribute__((aligned(16))) float part[kPoolWaves][2][kHeadDim];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const bool is_q = (long long)blockIdx.x < a.q_wgs;
-    const int split = is_q ? a.q_split : a.k_split;
-    const int slot = wave / split, share = wave % split;
-    const long long gid = (is_q ? (long long)blockIdx.x : (long long)blockIdx.x - a.q_wgs) * (kPoolWaves / split) + slot;
+    const bool is_q = blockIdx.x < a.q_wgs;
+    const int log_split = is_q ? a.q_split : a.k_split, split = 1 << log_split;
+    const int slot = wave >> log_split, share = wave & (split - 1);
+    const unsigned gid = (is_q ? blockIdx.x : blockIdx.x - a.q_wgs) * (kPoolWaves >> log_split) + slot;
     const bool there = gid < (is_q ? a.q_groups : a.k_groups);
+    const int groups = is_q ? a.n1 : a.n2, heads = is_q ? a.hq : a.hkv;
+    int i = 0, h = 0, bb = 0;
+    if (there) {
+        const FastDiv by_group = is_q ? a.div_n1 : a.div_n2, by_head = is_q ? a.div_hq : a.div_hkv;
+        if (is_q ? a.q_across : a.k_across) {
+            const unsigned x = by_head.div(gid);
+            h = (int)(gid - x * heads); bb = (int)by_group.div(x); i = (int)(x - (unsigned)bb * groups);
+        } else {
+            const unsigned x = by_group.div(gid);
+            i = (int)(gid - x * groups); bb = (int)by_head.div(x); h = (int)(x - (unsigned)bb * heads);
+        }
+    }
     const int chunk = lane % kLanes, rsub = lane / kLanes;
     float hi[E], lo[E];
 #pragma unroll
@@ -84,9 +100,7 @@ __global__ __launch_bounds__(64 * kPoolWaves) void pool_kernel(PoolArgs a) {
         for (int e = 0; e < E; ++e) { hi[e] = fmaxf(hi[e], x[e]); lo[e] = fminf(lo[e], x[e]); }
     };
     if (there) {
-        const int groups = is_q ? a.n1 : a.n2, heads = is_q ? a.hq : a.hkv, size = is_q ? a.s : a.b;
-        const int i = (int)(gid % groups); const long long bh = gid / groups;
-        const int h = (int)(bh % heads), bb = (int)(bh / heads);
+        const int size = is_q ? a.s : a.b;
         const long long stride = is_q ? a.qs2 : a.ks2;
         const T* src = (is_q ? (const T*)a.q + bb * a.qs0 + h * a.qs1 : (const T*)a.k + bb * a.ks0 + h * a.ks1) + chunk * E;
         const int t0 = i * size, t1 = (int)min((long long)a.n, (long long)t0 + size);
@@ -99,13 +113,18 @@ __global__ __launch_bounds__(64 * kPoolWaves) void pool_kernel(PoolArgs a) {
 #pragma unroll
             for (int u = 0; u < kLoads; ++u) merge(v[u]);
         }
-        if (t < t1) {                          // the group's last, short batch: rows past the end repeat its last row
-            uint4 v[kLoads];
+        // the group's last, short batch: rows past the end repeat its last row.  Half a batch has a form of its own, or the smallest groups
+        // would ask for everything twice (32 heads x 9000 tokens in groups of 16: 20.3 against 17.6 us)
+        auto last = [&](auto loads) {
+            constexpr int N = decltype(loads)::value;
+            uint4 v[N];
 #pragma unroll
-            for (int u = 0; u < kLoads; ++u) v[u] = load_once(src + (long long)min(t + kRows * u + rsub, t1 - 1) * stride);
+            for (int u = 0; u < N; ++u) v[u] = load_once(src + (long long)min(t + kRows * u + rsub, t1 - 1) * stride);
 #pragma unroll
-            for (int u = 0; u < kLoads; ++u) merge(v[u]);
-        }
+            for (int u = 0; u < N; ++u) merge(v[u]);
+        };
+        if (t + kBatch / 2 < t1) last(std::integral_constant<int, kLoads>());
+        else if (t < t1) last(std::integral_constant<int, kLoads / 2>());
     }
 #pragma unroll
     for (int o = kLanes; o < 64; o *= 2)
@@ -126,7 +145,7 @@ __global__ __launch_bounds__(64 * kPoolWaves) void pool_kernel(PoolArgs a) {
             }
     }
     if (there && rsub == 0) {
-        T* dst = (T*)(is_q ? a.qrep : a.krep) + gid * 2 * kHeadDim;
+        T* dst = (T*)(is_q ? a.qrep : a.krep) + (((long long)bb * heads + h) * groups + i) * 2 * kHeadDim;
         *(uint4*)(dst + chunk * E) = PoolVec<T>::narrow(hi);
         *(uint4*)(dst + kHeadDim + chunk * E) = PoolVec<T>::narrow(lo);
     }
@@ -587,27 +606,33 @@ __global__ __launch_bounds__(64 * kScoreWaves, 2) void score_kernel(ScoreArgs a)
 }  // namespace
 
 // Every wave of a group gets at least one batch, and two where there are enough groups to fill the chip.  The whole estimate step
-// with 1 / 2 / 4 / 8 waves per segment: 32 heads x 2000 tokens 26.8 / 22.2 / 19.6 / 19.2 us, x 4096 35.7 / 26.4 / 21.3 / 20.3, x 128K
-// (512 tokens a segment) 280 / 269 / 271 / 267 and, with Q token-major, 315 / 273 / 275 / 274; two batches of 256-token segments
-// (batch 2, 64K) 364 at four waves, 375 at eight with one batch each.  fp32, 8 heads x 8192: 47 / 31 / 23 / 19.
-static int pool_split(const Shape& sh, int size, long long groups) {
+// with 1 / 2 / 4 / 8 waves per segment, at the time the split came in: 32 heads x 2000 tokens 26.8 / 22.2 / 19.6 / 19.2 us, x 4096 35.7 /
+// 26.4 / 21.3 / 20.3, x 128K (512 tokens a segment) 280 / 269 / 271 / 267; two batches of 256-token segments (batch 2, 64K) 364
+// at four waves, 375 at eight with one batch each.  fp32, 8 heads x 8192: 47 / 31 / 23 / 19.
+static int pool_split(const Shape& sh, int size, long long groups) {    // log2 of the waves
     const int batch = sh.dtype == 1 ? 32 : 16;
-    int split = 1;
-    while (split < kPoolWaves && 2 * split * batch <= size && (groups * split < 4096 || 4 * split * batch <= size)) split *= 2;
-    return split;
+    int x = 0;
+    while ((1 << x) < kPoolWaves && (2 << x) * batch <= size && (groups << x < 4096 || (4 << x) * batch <= size)) ++x;
+    return x;
 }
 
 hipError_t launch_pool(const Shape& sh, const void* q, const void* k, void* qrep, void* krep, hipStream_t st) {
     PoolArgs a;
     a.q = q; a.k = k; a.qrep = qrep; a.krep = krep;
     a.n = sh.n; a.s = sh.s; a.b = sh.b; a.n1 = sh.n1; a.n2 = sh.n2; a.hq = sh.hq; a.hkv = sh.hkv;
-    a.q_groups = (long long)sh.batch * sh.hq * sh.n1;
-    a.k_groups = (long long)sh.batch * sh.hkv * sh.n2;
+    a.q_groups = (unsigned)sh.batch * sh.hq * sh.n1;                // below 2^31: make_shape, and n2 <= 8192 here
+    a.k_groups = (unsigned)sh.batch * sh.hkv * sh.n2;
     a.qs0 = sh.qs[0]; a.qs1 = sh.qs[1]; a.qs2 = sh.qs[2];
     a.ks0 = sh.kvs[0]; a.ks1 = sh.kvs[1]; a.ks2 = sh.kvs[2];
     a.q_split = pool_split(sh, sh.s, a.q_groups); a.k_split = pool_split(sh, sh.b, a.k_groups);
-    a.q_wgs = (a.q_groups * a.q_split + kPoolWaves - 1) / kPoolWaves;
-    const unsigned grid = (unsigned)(a.q_wgs + (a.k_groups * a.k_split + kPoolWaves - 1) / kPoolWaves);
+    // Token-major tensors (the heads of a token lie together) are walked across the heads: along a head the waves in flight, a few heads
+    // of many, all read at strides of a whole token.  Pooling along / across them, 32 / 8 heads x 66000 tokens, 512 a segment, 132 / 108
+    // us, x 33000 60 / 55, x 128K 211 / 213; 2 x 32 / 4 x 66000 227 / 190.
+    a.q_across = sh.qs[1] < sh.qs[2]; a.k_across = sh.kvs[1] < sh.kvs[2];
+    a.div_n1 = FastDiv(sh.n1); a.div_n2 = FastDiv(sh.n2); a.div_hq = FastDiv(sh.hq); a.div_hkv = FastDiv(sh.hkv);
+    const unsigned q_slots = kPoolWaves >> a.q_split, k_slots = kPoolWaves >> a.k_split;
+    a.q_wgs = (a.q_groups + q_slots - 1) / q_slots;
+    const unsigned grid = a.q_wgs + (a.k_groups + k_slots - 1) / k_slots;
     if (sh.dtype == 1) hipLaunchKernelGGL(pool_kernel<uint16_t>, dim3(grid), dim3(64 * kPoolWaves), 0, st, a);
     else hipLaunchKernelGGL(pool_kernel<float>, dim3(grid), dim3(64 * kPoolWaves), 0, st, a);
     return hipGetLastError();

@@ -2,6 +2,7 @@
 rows); the fp32 score kernel with 1 to 8 segments to a workgroup (the last two shapes: eight with one left over, one): the scores of the estimate step against the fp64 checker, with the bar of the other score tests."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import critiprefill_oracle as O
 from paper_2409_12490_amd import synth
@@ -22,3 +23,19 @@ def test_scores_for_every_split(shape, dtype):
     S_o = O.estimate(synth.to_f64(q), synth.to_f64(k), s, b)
     S_g = H.gpu_estimate(w, q.to(DEV), k.to(DEV)).cpu().numpy()
     np.testing.assert_allclose(S_g, S_o, rtol=2e-4, atol=1e-30)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("size", [1, 15, 16, 17, 31, 33, 100])
+def test_token_major_and_head_major_agree(size, dtype):
+    """Groups are walked along a head or, where the heads of a token lie together, across the heads: the same maxima and minima, hence the
+    same scores bit for bit.  Batches, odd head counts, groups around half a batch (16 bf16 or 8 fp32 rows) and a whole one."""
+    for Bt, Hq, Hkv, groups in ((2, 6, 3, 5), (3, 5, 5, 9)):
+        w = H.small_workload("walk", Bt, Hq, Hkv, groups * size - size // 2, size, size, 1, 0, dtype=dtype, unit_variance=size > 1)
+        q, k, _ = (t.to(DEV) for t in synth.make_qkv(w, threads=4))
+        plain = H.gpu_estimate(w, q, k)
+        for turn_q, turn_k in ((True, True), (True, False), (False, True)):
+            qt, kt = (t.transpose(1, 2).contiguous().transpose(1, 2) if turn else t for t, turn in ((q, turn_q), (k, turn_k)))
+            assert torch.equal(H.gpu_estimate(w, qt, kt), plain)
+        S_o = O.estimate(synth.to_f64(q.cpu()), synth.to_f64(k.cpu()), size, size)
+        np.testing.assert_allclose(plain.cpu().numpy(), S_o, rtol=2e-4, atol=1e-30)
