@@ -280,8 +280,8 @@ __global__ __launch_bounds__(64 * kScore32Waves) void score_fp32_kernel(ScoreArg
 // over after whole rounds of whole workgroups decides (score_shares).  The two passes, in us, against (a) eight waves that streamed
 // their chunk through two 32 KiB buffers, 128 segments of one head and chunk to a workgroup, and (b) this kernel with groups of one head in
 // fixed eights: 32 / 8 heads x 66000 tokens, segments of 256, blocks of 32: (a) 101, (b) 138, now 71; segments of 128, blocks of 16,
-// with S': 561, 825, 340; x 131072 (512, 64): 60, 60, 60, with S' 63, 67, 65; 2 x 32 x 65536 (256, 32) with S' 153, 146, 127;
-// 8 x 131072 (128, 16) 199, 214, 196; x 16384 (256, 32) 24, 15.6, 15.0.
+// with S': 560, 824, 346; x 131072 (512, 64): 60, 60, 52, with S' 63, 66, 58; 2 x 32 x 65536 (256, 32) with S' 155, 146, 123;
+// 8 x 131072 (128, 16) 199, 214, 189; x 16384 (256, 32) 25, 16, 15.6.
 // ---------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -342,9 +342,11 @@ __global__ __launch_bounds__(64 * kScoreWaves, 2) void score_kernel(ScoreArgs a)
     const unsigned unit = blockIdx.z * gridDim.x + blockIdx.x;
     const int share = blockIdx.y, shares = gridDim.y;
     const int kv = (int)a.div_chunks.div(unit), chunk = (int)unit - kv * a.nchunk;
-    // the sixteens of segments of the KV head's query heads, numbered through; this workgroup has every shares-th one
+    // the sixteens of segments of the KV head's query heads, numbered through: dealt in eights to and fro, so that rows lie together and
+    // nobody has all the late segments, which see most blocks (one by one, every shares-th, PASS 1 takes 125 instead of 94 us at
+    // 32 / 4 heads x 128K, 256 a segment, blocks of 32, and 36 instead of 28 at 32 / 8 (512, 64)), the rest one by one
     const int head_groups = (a.n1 + 15) / 16;
-    const int mine = a.share_least + (share < a.share_more ? 1 : 0);
+    const int mine = a.share_least + (share < a.share_more ? 1 : 0), whole = a.share_least / kScoreWaves * kScoreWaves;
     // first block of tile lt of the chunk; four tiles (f) come from the front of the row, four (b) from its end, in the order f b f b b f b f,
     // of which 1, 2 or 4 waves that take every first, second or fourth tile get equal shares
     auto tile_begin = [&](int lt) {
@@ -382,7 +384,9 @@ __global__ __launch_bounds__(64 * kScoreWaves, 2) void score_kernel(ScoreArgs a)
         const int parts = left > 4 ? 1 : left > 2 ? 2 : left > 1 ? 4 : 8;
         const int col_waves = kScoreWaves / parts, part = wave / col_waves, slot = wave % col_waves;
         const bool active = slot < left;                    // wave-uniform
-        const int g = share + (first + min(slot, left - 1)) * shares, gh = (int)a.div_groups.div(g);
+        const int g = first < whole ? first * shares + (first & kScoreWaves ? shares - 1 - share : share) * kScoreWaves + slot
+                                    : whole * shares + share + min(slot, left - 1) * shares;
+        const int gh = (int)a.div_groups.div(g);
         const int bh = kv * a.group + gh, j0 = (g - gh * head_groups) * 16;
         const long long qrow0 = (long long)bh * a.n1;       // row of segment 0 of this (batch, head) in scores
         const int vis_lo = seen_end(j0), vis_hi = seen_end(j0 + 15);    // first block after the first / last segment of the group
