@@ -16,13 +16,17 @@
 // are 16 (RT = 2) to 32 (RT = 1) bytes per clock and compute unit, within what L2 delivers.  V of a tile is asked for
 // before its QK, K of the next tile before its softmax and PV.
 //
+// Values: a wave takes its weights relative to the true max of the row among its keys, so they are at most 1, and weights down to
+// the smallest subnormal count; O overflows for |V| above 3.4e38 / (number of keys) at the earliest.  (A max that may outgrow its
+// reference by 2^8, as in the bf16 kernel, saves most rescalings of O, 4 % of the time, and overflows 256 times earlier.)
+//
 // What bounds it: the fp32 matrix instructions, which share their units with the vector instructions (measured: a wave's
 // softmax and address arithmetic add their time to the MFMAs of all waves of the SIMD, at 2.0 vector instructions per MFMA
 // the pipe was busy 57 % of the time, at 0.5 82 %).  So the key loop keeps them few: tiles of 16 consecutive tokens with their
-// addresses on the scalar unit (MODE 1/2), one fma and one exp2 per weight, O rescaled only when a row's max has outgrown
-// its reference point.  Dense, 8 heads x 8192 tokens: 130 TFLOP/s of the 154 that a large library product reaches; 4 heads x
-// 2500 tokens: 530 -> 82 us, block-sparse 4 heads x 4096 tokens 203 -> 60 us, one head x 2048 tokens 80 -> 12.5 us against a
-// vector-FMA loop over 32 x 32 tiles in LDS (12 to 25 TFLOP/s).
+// addresses on the scalar unit (MODE 1/2), O rescaled only in tiles where some row's max moves.  Dense, 8 heads x 8192 tokens: 126
+// TFLOP/s of the 154 that a large library product reaches (1090 us); 4 heads x 2500 tokens: 519 -> 81 us, block-sparse 4 heads x 4096
+// tokens (704 keys) 183 -> 56 us, one head x 2048 tokens (384 keys) 85 -> 13.7 us against a vector-FMA loop over 32 x 32 tiles in LDS
+// (12 to 25 TFLOP/s).
 #include "kernels.h"
 
 namespace cp {
@@ -35,11 +39,9 @@ struct Args32 {
     float* out; float* lse;
     int batch, hq, hkv, n, s, b, n1, list_len, qtiles;   // qtiles: per segment (sparse) or per sequence (dense)
     int shared_lists;                             // lists are per (batch, KV head, segment) instead of per query head
-    float scale_log2e;
+    float scale_log2e, scale;
     long long qs0, qs1, qs2, ks0, ks1, ks2, os0, os1, os2;
 };
-
-constexpr float kLazyLog2 = 8.0f;
 
 __device__ __forceinline__ float group_max(float x) {               // over the four lane groups: lanes l, l^16, l^32, l^48
     auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -160,7 +162,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
     auto load_k_token = [&](int tok) { load_k(kp + (long long)(tok == kNoToken ? 0 : tok) * a.ks2 + 4 * g, 0u); };
 
     f32x4 o[RT][2][4];
-    float m[RT], l[RT];                                             // m: running max in units of the exponent (log2)
+    float m[RT], l[RT];                                             // m: running max of the raw logits
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         m[rt] = -INFINITY; l[rt] = 0.f;
@@ -221,14 +223,21 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
                     if ((RUN ? base + 4 * g + r : ktok[r]) > qpos) z[r] = -INFINITY;
             }
             float mx = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
-            mx = group_max(mx) * a.scale_log2e;
-            // the reference point moves only when the max has outgrown it by more than kLazyLog2 (see the bf16 kernel): P stays
-            // below 2^kLazyLog2, P, l and O carry one factor, and O is rescaled in the first tiles and then almost never
-            const float m_new = mx > m[rt] + kLazyLog2 ? mx : m[rt];
+            // weights are taken from the row's true max, so that no P is above 1 and O grows no faster than the sum of |V|
+            const float m_new = fmaxf(m[rt], group_max(mx));
             const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-            const float alpha = __builtin_amdgcn_exp2f(m[rt] - m_safe);
+            float alpha = (m[rt] - m_safe) * a.scale_log2e;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) z[r] = __builtin_amdgcn_exp2f(fmaf(z[r], a.scale_log2e, -m_safe));
+            for (int r = 0; r < 4; ++r) z[r] = (z[r] - m_safe) * a.scale_log2e;
+            if (__ballot(fminf(fminf(fminf(z[0], z[1]), fminf(z[2], z[3])), alpha) < -126.f) == 0) {
+                alpha = __builtin_amdgcn_exp2f(alpha);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z[r] = __builtin_amdgcn_exp2f(z[r]);
+            } else {                                                // v_exp_f32 has no subnormal results, exp2f does
+                alpha = exp2f(alpha);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) z[r] = exp2f(z[r]);
+            }
             l[rt] = l[rt] * alpha + ((z[0] + z[1]) + (z[2] + z[3]));   // the lane's own keys; the lane groups are added at the end
             m[rt] = m_new;
             if (__ballot(alpha != 1.0f) != 0) {
@@ -282,7 +291,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
         f32x4 sum = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-            const float f = __builtin_amdgcn_exp2f(part_m[w * TQ + row] - M_safe);
+            const float f = exp2f((part_m[w * TQ + row] - M_safe) * a.scale_log2e);
             L += f * part_l[w * TQ + row];
             sum += f * *(const f32x4*)(part_o + (w * TQ + row) * kHeadDim + 4 * (chunk ^ (row & 15)));
         }
@@ -291,7 +300,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
             const float inv = L > 0.f ? 1.0f / L : 0.f;
             *(f32x4*)(op + (long long)qpos * a.os2 + 4 * chunk) = sum * inv;
             if (a.lse && chunk == 0)
-                a.lse[((long long)bb * a.hq + h) * a.n + qpos] = L > 0.f ? M * 0.6931471805599453f + logf(L) : -INFINITY;
+                a.lse[((long long)bb * a.hq + h) * a.n + qpos] = L > 0.f ? M * a.scale + logf(L) : -INFINITY;
         }
     }
 }
@@ -327,7 +336,7 @@ hipError_t launch_attn_fp32(const Shape& sh, const void* q, const void* k, const
     a.out = (float*)out; a.lse = lse;
     a.batch = sh.batch; a.hq = sh.hq; a.hkv = sh.hkv; a.n = sh.n; a.s = sh.s; a.b = sh.b; a.n1 = sh.n1; a.list_len = sh.list_len;
     a.shared_lists = shared_lists ? 1 : 0;
-    a.scale_log2e = sh.attn_scale * 1.4426950408889634f;
+    a.scale = sh.attn_scale; a.scale_log2e = sh.attn_scale * 1.4426950408889634f;
     a.qs0 = sh.qs[0]; a.qs1 = sh.qs[1]; a.qs2 = sh.qs[2];
     a.ks0 = sh.kvs[0]; a.ks1 = sh.kvs[1]; a.ks2 = sh.kvs[2];
     a.os0 = sh.os[0]; a.os1 = sh.os[1]; a.os2 = sh.os[2];

@@ -68,3 +68,40 @@ def test_token_stride_beyond_32_bit_offsets():
     idx, cnt = O.select(np.ones((1, 1, w.n_segments, w.n_blocks), np.float32), 16, 16, 1, 0)      # every block: dense again
     out, _ = H.gpu_sparse(w, qd, kd, vd, torch.from_numpy(idx).to(DEV), torch.from_numpy(cnt).to(DEV))
     assert H.max_abs(out.cpu().numpy(), d_ref) <= H.TOL_OUT["fp32"]
+
+
+def _logits(row):
+    """K of one head whose logits with an all-ones first channel of Q are ``row`` (the scale 1/sqrt(128) taken out)."""
+    k = torch.zeros((1, 1, len(row), 128), dtype=torch.float32)
+    k[0, 0, :, 0] = torch.tensor(row, dtype=torch.float32) * 128 ** 0.5
+    return k
+
+
+@pytest.mark.parametrize("b", [16, 24, 0], ids=["runs", "tokens", "dense"])
+@pytest.mark.parametrize("case", ["large_values", "subnormal_weights"])
+def test_value_range(case, b):
+    """Weights stay at most 1 and count down to the subnormals.  large_values: keys with V = 3e37 in the tiles of one wave, the later ones
+    with a logit 5 above the first (a factor of 148); a weight above 11 would overflow.  subnormal_weights: keys whose weight is exp(-90) = 8e-40 beside one
+    of weight 1 and V = 0, with V = 2^118. The logits are exact up to one rounding, 90 * 2^-24 = 5e-6 relative in a weight; a
+    subnormal of 8e-40 is known to 2^-19 = 2e-6."""
+    n = 300
+    row = [-20.0 if case == "large_values" else -90.0] * n
+    v = torch.full((1, 1, n, 128), 1.0 if case == "large_values" else 2.0 ** 118, dtype=torch.float32)
+    row[0] = 0.0
+    if case == "large_values":
+        row[64] = row[128] = 5.0                                  # later tiles of the same wave, with four waves and with eight
+        v[0, 0, [0, 64, 128]] = 3e37
+    else:
+        v[0, 0, 0] = 0.0
+    k, q = _logits(row), torch.zeros((1, 1, n, 128), dtype=torch.float32)
+    q[..., 0] = 1.0
+    w = H.small_workload("range", 1, 1, 1, n, b * 25 or 16, b or 16, 25, 0, dtype="fp32")
+    qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+    if b:
+        idx, cnt = O.select(np.ones((1, 1, w.n_segments, w.n_blocks), np.float32), b * 25, b, 25, 0)    # every block
+        out, lse = H.gpu_sparse(w, qd, kd, vd, torch.from_numpy(idx).to(DEV), torch.from_numpy(cnt).to(DEV))
+    else:
+        out, lse = H.gpu_dense(w, qd, kd, vd)
+    ref, lse_ref = O.dense_causal_attention(synth.to_f64(q), synth.to_f64(k), synth.to_f64(v))
+    np.testing.assert_allclose(out.cpu().numpy(), ref, rtol=2e-5)
+    np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=0, atol=2e-5)
