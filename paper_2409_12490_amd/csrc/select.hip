@@ -146,8 +146,8 @@ __device__ __forceinline__ int select_row(const SelectArgs& a, long long row, in
     return take_largest<PER_LANE>(key, thr, kj, (n_cand + 63) / 64, lane, out, [&](int m) { return m * 64 + lane; });
 }
 
-// SHARED: a workgroup per list, since there are only as many as KV heads: its four waves merge the scores of the group's query heads
-// into LDS (several loads of a head's row in flight), then one of them searches.  With one wave per list, its loads head after head,
+// SHARED: a workgroup per list: its four waves merge the scores of the group's query heads into LDS,
+// several loads of a head's row in flight, then one of them searches.  With one wave per list, its loads head after head,
 // 32 query heads x 128K tokens in blocks of 64 took 44 us for 8 KV heads and 71 us for 4; now 15 and 14 (67 MB of scores).
 // MAX_PER_LANE: 64 * MAX_PER_LANE >= n2, a multiple of 8.  A row early in the sequence has few candidates: the
 // search is compiled for eight row lengths (eighths of the maximum) and a wave takes the shortest that holds its row.
@@ -313,8 +313,13 @@ hipError_t launch_select_impl(const Shape& sh, const float* scores, int32_t* idx
     return hipGetLastError();
 }
 
+// A KV head with one query head has that head's list: the per-head kernel, four rows to a workgroup, unless the lists are long and so few that
+// a workgroup each fits the chip twice (128K tokens in blocks of 32, a workgroup / a wave per list: 256 lists 13 / 17 us, 512 14 /
+// 17, 2048 34 / 25, 8192 129 / 83; in blocks of 64: 256 lists 8.7 / 7.8, 8192 42 / 20).
 hipError_t launch_select(const Shape& sh, const float* scores, int32_t* idx, int32_t* cnt, bool shared, hipStream_t st) {
-    return shared ? launch_select_impl<true>(sh, scores, idx, cnt, st) : launch_select_impl<false>(sh, scores, idx, cnt, st);
+    const bool few = sh.n2 > 64 * 32 && sh.n2 <= 64 * 64 && (long long)sh.batch * sh.hkv * sh.n1 <= 512;
+    return shared && (sh.hq != sh.hkv || few) ? launch_select_impl<true>(sh, scores, idx, cnt, st)
+                                              : launch_select_impl<false>(sh, scores, idx, cnt, st);
 }
 
 }  // namespace cp

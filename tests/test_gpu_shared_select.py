@@ -26,3 +26,15 @@ def test_lists_bit_exact(n_blocks, group, budget):
     k = torch.empty((1, 2, w.seq_len, 128), dtype=torch.bfloat16, device=DEV)
     idx_g, cnt_g = H.gpu_select_shared(w, q, k, torch.from_numpy(S).to(DEV))
     H.check_selection(Sg, idx_o, cnt_o, idx_g, cnt_g, w, exact=True)
+
+
+@pytest.mark.parametrize("n_blocks,heads", [(300, 3), (2049, 1), (4096, 5), (4099, 2)])
+def test_one_query_head_per_kv_head(n_blocks, heads):
+    """With as many KV heads as query heads the shared lists are the per-head lists, whichever kernel makes them."""
+    b = 16
+    w = H.small_workload("single", 2, heads, heads, n_blocks * b, 512, b, 33, 1)
+    S = torch.rand((2, heads, w.n_segments, w.n_blocks), generator=torch.Generator().manual_seed(n_blocks)).to(DEV)
+    S[..., ::5] = 0.5                                                  # ties
+    q = torch.empty((2, heads, w.seq_len, 128), dtype=torch.bfloat16, device=DEV)
+    for mine, theirs in zip(H.gpu_select_shared(w, q, q, S), H.gpu_select(w, q, q, S)):
+        assert torch.equal(mine, theirs)
