@@ -19,6 +19,8 @@
 // faster than this one.
 #include "attn_bf16.h"
 
+#include <algorithm>
+
 namespace cp {
 namespace {
 
@@ -307,7 +309,8 @@ static hipError_t launch_waves(const Shape& sh, const ArgsB& a, unsigned grid, h
 // 32) and 15.3 / 17.1 (64), 2 x 8192 58 / 54 and 26 / 22; dense, one head x 16K 160 / 211, 2 x 8192 88 / 109, 2 x 16K 306 / 315,
 // 8 x 2048 29 / 33, 8 x 4096 91 / 86, 32 x 512 15.3 / 13.1.
 hipError_t launch_attn_bf16_rows(const Shape& sh, ArgsB a, hipStream_t st) {
-    a.qtiles = ((a.idx ? sh.s : sh.n) + kRowsTQ - 1) / kRowsTQ;
+    const int longest = a.idx ? std::min(sh.s, sh.n) : sh.n;          // a segment may be set longer than the sequence
+    a.qtiles = (longest + kRowsTQ - 1) / kRowsTQ;
     const unsigned grid = (unsigned)((long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1));
     const long long rows = (long long)sh.batch * sh.hq * sh.n;
     const bool eight = rows <= 8192 || (!a.idx && ((sh.n >= 2048 && rows <= 16384) || sh.n >= 8192));

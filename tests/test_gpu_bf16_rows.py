@@ -27,6 +27,8 @@ SHAPES = [
     (24, 8, 1399, 64, 16, 5, 2),         # 256-row kernel, a token per key; 33576 rows: 256-row dense
     (32, 8, 2100, 192, 96, 3, 1),        # 256-row kernel, blocks of 96
     (2, 1, 8200, 512, 64, 4, 1),         # 16400 rows of 8200 keys: dense with eight waves
+    (3, 1, 77, 4096, 64, 2, 1),          # a segment longer than the sequence
+    (24, 8, 800, 4096, 16, 2, 1),        # the same in the 256-row kernel
 ]
 
 
