@@ -67,7 +67,8 @@ __device__ __forceinline__ float half_sum(float x) {
 
 }  // namespace
 
-// Attention with 32-row workgroups whose waves split the keys; fills in qtiles.
+// Attention with 32-row workgroups whose waves split the keys, and whether it is the better one here.
+bool attn_bf16_rows_better(const Shape& sh, bool sparse);
 hipError_t launch_attn_bf16_rows(const Shape& sh, ArgsB a, hipStream_t st);
 
 }  // namespace cp

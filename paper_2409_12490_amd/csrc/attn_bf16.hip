@@ -665,11 +665,7 @@ hipError_t launch_attn_bf16(const Shape& sh, const void* q, const void* k, const
     a.ks0 = sh.kvs[0]; a.ks1 = sh.kvs[1]; a.ks2 = sh.kvs[2];
     a.os0 = sh.os[0]; a.os1 = sh.os[1]; a.os2 = sh.os[2];
     a.group = sh.hq / sh.hkv;
-    // Few query rows: 256 of them to a workgroup leave compute units idle, 32 do not.  The lines lie where the two kernels meet
-    // (256-row against 32-row kernel).  Block-sparse, 16384 rows: 32 heads x 512 20.4 / 13.9 to 22.6 / 15.4 us, 8 x 2048 25.7 / 21.1 to 55 / 35, 1 x
-    // 16K 26.3 / 22.3 to 69 / 56; 24576 rows: 26.5 / 26.7 and 26.9 / 25.5, 26.1 / 30.2 to 69 / 59, 27.6 / 33.7 to 72 / 85.  Dense, 32768 rows:
-    // 32 x 1024 30.9 / 30.5, 8 x 4096 98 / 86, 1 x 32K 722 / 590; 40960 rows: 37 / 40, 123 / 126, 903 / 938.
-    if ((long long)sh.batch * sh.hq * sh.n <= (idx ? 16384 : 32768)) return launch_attn_bf16_rows(sh, a, st);
+    if (attn_bf16_rows_better(sh, idx != nullptr)) return launch_attn_bf16_rows(sh, a, st);
     const uint32_t bkv = (uint32_t)sh.batch * sh.hkv;
     a.div_group = FastDiv(a.group); a.div_hkv = FastDiv(sh.hkv); a.div_b = FastDiv(sh.b);
     hipError_t e;

@@ -304,16 +304,45 @@ static hipError_t launch_waves(const Shape& sh, const ArgsB& a, unsigned grid, h
     return sh.b % 32 == 0 ? launch<1, W>(a, grid, st) : launch<0, W>(a, grid, st);
 }
 
+// Row tiles that exist: a segment's last tile may be short.
+static long long row_tiles(const Shape& sh, bool sparse, int rows) {
+    const int s = sparse ? sh.s : sh.n, rest = sh.n % s;
+    return (long long)sh.batch * sh.hq * ((long long)(sh.n / s) * ((s + rows - 1) / rows) + (rest + rows - 1) / rows);
+}
+
+static long long listed_keys(const Shape& sh) { return std::min((long long)sh.n, (long long)sh.list_len * sh.b); }
+
+// Few query rows: 256 of them to a workgroup leave compute units idle, 32 do not.  The lines lie where the two kernels meet (256-row against
+// 32-row kernel).
+//   block-sparse, blocks of 64 or 16: 16384 rows: 32 heads x 512 20.4 / 13.9 to 22.6 / 15.4 us, 8 x 2048 25.7 / 21.1 to 55 / 35, 1 x 16K
+//   26.3 / 22.3 to 69 / 56; 24576 rows: 26.5 / 26.7 and 26.9 / 25.5, 26.1 / 30.2 to 69 / 59, 27.6 / 33.7 to 72 / 85.
+//   dense, 32768 rows: 32 x 1024 30.9 / 30.5, 8 x 4096 98 / 86, 1 x 32K 722 / 590; 40960 rows: 37 / 40, 123 / 126, 903 / 938.
+// Two 32-row workgroups fit a compute unit, and segments that are no multiple of 32 rows make more of them out of 16384 rows than the 512
+// that fit the chip.  A second round costs as much as the first where all lists are as long, and more than the 256-row kernel takes
+// where they are short: 16384 x 1 head, segments of 240 (552 workgroups), 6 blocks of 48 24.0 / 30.4, 10 of 40 27.4 / 33.7, 20 of
+// 24 29.0 / 34.4, 40 of 48 67 / 62; 290 x 56 (616) 16.2 / 18.5; but 680 x 24 (552) 23.0 / 18.5, 2720 x 6 (546), 40 of 48 65 / 42; up
+// to 540 workgroups (a short last tile per head) the 32-row kernel is never slower.  Segments of 48: more than 256 workgroups of
+// 256 rows, 46 / 30.
+bool attn_bf16_rows_better(const Shape& sh, bool sparse) {
+    const long long rows = (long long)sh.batch * sh.hq * sh.n;
+    if (!sparse) return rows <= 32768;
+    if (rows > 16384) return false;
+    const long long keys = listed_keys(sh);
+    return row_tiles(sh, true, kRowsTQ) <= 540 || row_tiles(sh, true, 256) > 256 || keys >= 1536 || (keys >= 340 && sh.n <= 2 * keys);
+}
+
 // Eight waves where the workgroups are too few to give every compute unit two, and for dense rows of thousands of keys; four
 // otherwise, two workgroups to a unit.  Eight against four waves: block-sparse, 8 heads x 1024 tokens 13.6 / 14.4 us (blocks of
-// 32) and 15.3 / 17.1 (64), 2 x 8192 58 / 54 and 26 / 22; dense, one head x 16K 160 / 211, 2 x 8192 88 / 109, 2 x 16K 306 / 315,
-// 8 x 2048 29 / 33, 8 x 4096 91 / 86, 32 x 512 15.3 / 13.1.
+// 32) and 15.3 / 17.1 (64), 2 x 8192 58 / 54 and 26 / 22; more than 256 workgroups out of 8192 rows: 8192 x 1, segments of 240, 60 blocks of 40
+// 32 / 42, but 256 x 32 16.0 / 13.2; dense, one head x 16K 160 / 211, 2 x 8192 88 / 109, 2 x 16K 306 / 315, 8 x 2048 29 / 33, 8 x
+// 4096 91 / 86, 32 x 512 15.3 / 13.1.
 hipError_t launch_attn_bf16_rows(const Shape& sh, ArgsB a, hipStream_t st) {
     const int longest = a.idx ? std::min(sh.s, sh.n) : sh.n;          // a segment may be set longer than the sequence
     a.qtiles = (longest + kRowsTQ - 1) / kRowsTQ;
     const unsigned grid = (unsigned)((long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1));
     const long long rows = (long long)sh.batch * sh.hq * sh.n;
-    const bool eight = rows <= 8192 || (!a.idx && ((sh.n >= 2048 && rows <= 16384) || sh.n >= 8192));
+    const bool eight = a.idx ? rows <= 8192 && (row_tiles(sh, true, kRowsTQ) <= 270 || listed_keys(sh) >= 340)
+                             : rows <= 8192 || (sh.n >= 2048 && rows <= 16384) || sh.n >= 8192;
     return eight ? launch_waves<8>(sh, a, grid, st) : launch_waves<4>(sh, a, grid, st);
 }
 
