@@ -3,22 +3,12 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fast_div.h"
+
 namespace cp {
 
 constexpr int kHeadDim = 128;
 constexpr int kMaxListBf16 = 6144;    // block-list entries the bf16 attention kernel keeps in LDS
-
-// n / d for 0 <= n < 2^31 by a multiplication (the divisors of the index arithmetic are known to the host; a division in the kernel
-// is some forty dependent instructions)
-struct FastDiv {
-    uint32_t mul, shift;
-    FastDiv() : mul(1), shift(0) {}
-    explicit FastDiv(uint32_t d) : shift(0) {                         // 1 <= d < 2^31
-        while ((1ull << shift) < d) ++shift;
-        mul = (uint32_t)(((((1ull << shift) - d) << 32) / d) + 1);
-    }
-    __device__ __forceinline__ uint32_t div(uint32_t n) const { return ((uint32_t)(((unsigned long long)mul * n) >> 32) + n) >> shift; }
-};
 
 struct Shape {
     int batch, hq, hkv, n, s, b, r, n1, n2;   // r = s / b
