@@ -27,9 +27,9 @@ SHAPES = [
     (24, 8, 1399, 64, 16, 5, 2),         # 256-row kernel, a token per key; 33576 rows: 256-row dense
     (32, 8, 2100, 192, 96, 3, 1),        # 256-row kernel, blocks of 96
     (2, 1, 8200, 512, 64, 4, 1),         # 16400 rows of 8200 keys: dense with eight waves
-    (1, 1, 16001, 240, 48, 5, 1),        # 540 row tiles of 32: 32-row, one more makes it 256-row
-    (1, 1, 16321, 240, 48, 5, 1),        # 545 of them, short lists: 256-row kernel below 16384 rows
-    (1, 1, 16321, 240, 48, 40, 0),       # and with long lists: 32-row
+    (1, 1, 16001, 240, 48, 5, 1),        # 534 row tiles of 32: 32-row
+    (1, 1, 16321, 240, 48, 5, 1),        # 545 row tiles, short lists: 256-row kernel below 16384 rows
+    (1, 1, 16321, 240, 48, 40, 0),       # 545 row tiles, long lists: 32-row
     (32, 8, 250, 240, 48, 6, 0),         # 8000 rows in 288 tiles, 250 keys: 32-row, four waves
     (3, 1, 77, 4096, 64, 2, 1),          # a segment longer than the sequence
     (24, 8, 800, 4096, 16, 2, 1),        # the same in the 256-row kernel

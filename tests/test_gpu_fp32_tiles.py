@@ -105,3 +105,23 @@ def test_value_range(case, b):
     ref, lse_ref = O.dense_causal_attention(synth.to_f64(q), synth.to_f64(k), synth.to_f64(v))
     np.testing.assert_allclose(out.cpu().numpy(), ref, rtol=2e-5)
     np.testing.assert_allclose(lse.cpu().numpy(), lse_ref, rtol=0, atol=2e-5)
+
+
+@pytest.mark.parametrize("b,s", [(32, 128), (24, 72)], ids=["runs", "tokens"])
+def test_batches(b, s):
+    """Batch and head offsets of block-sparse (a run of tokens per tile, a token per key), shared and dense attention: three batches, groups of
+    two heads, token-major storage, every row of every head."""
+    w = H.small_workload("fp32batch", 3, 6, 3, 307, s, b, 3, 1, dtype="fp32", unit_variance=True)
+    q, k, v = synth.make_qkv(w, threads=4)
+    qf, kf, vf = (synth.to_f64(t) for t in (q, k, v))
+    qd, kd, vd = (t.to(DEV).transpose(1, 2).contiguous().transpose(1, 2) for t in (q, k, v))
+    Sd = np.random.default_rng(b).random((3, 6, w.n_segments, w.n_blocks), dtype=np.float32)
+    idx, cnt = O.select(Sd, s, b, 3, 1)
+    runs = [(O.sparse_attention(qf, kf, vf, idx, cnt, s, b), H.gpu_sparse(w, qd, kd, vd, torch.from_numpy(idx).to(DEV), torch.from_numpy(cnt).to(DEV))),
+            (O.dense_causal_attention(qf, kf, vf), H.gpu_dense(w, qd, kd, vd))]
+    idx, cnt = O.select(O.shared_group_scores(Sd, 3), s, b, 3, 1)
+    runs.append((O.sparse_attention(qf, kf, vf, *O.expand_shared_lists(idx, cnt, 6), s, b),
+                 H.gpu_sparse_shared(w, qd, kd, vd, torch.from_numpy(idx).to(DEV), torch.from_numpy(cnt).to(DEV))))
+    for (o_ref, lse_ref), (out, lse) in runs:
+        assert H.max_abs(out.cpu().numpy(), o_ref) <= H.TOL_OUT["fp32"]
+        assert H.max_abs(lse.cpu().numpy(), lse_ref) <= 1e-4
