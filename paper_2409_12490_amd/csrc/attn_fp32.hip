@@ -313,12 +313,13 @@ hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// 32 rows per workgroup halve the K/V bytes and the softmax instructions per MFMA (130 against 115 TFLOP/s at 8 heads x 8192
-// tokens); 16 rows give twice the workgroups, and a short sequence needs them: one head x 2048 tokens 42 us at 16 rows, 74 at
-// 32; dense 4 heads x 2500 (316 workgroups of 32 rows) 82 / 90; 4 x 3300 (416) 128 / 117; 8 x 2000 (504) 95 / 85.  Eight waves
-// split a long row further and leave one workgroup to a compute unit, which evens out unequal rows (dense 8 x 4000: 285
-// against 306 us for four); four waves are better where rows are short (4 x 4096, 704 keys: 60 / 65) or workgroups many
-// (16 x 4096: 544 / 578).
+// 32 rows per workgroup halve the K/V bytes and the softmax instructions per MFMA, 16 rows give twice the workgroups, and a short sequence
+// needs them; eight waves split a long row further and leave one workgroup to a compute unit, which evens out unequal rows, four
+// waves are better where rows are short or workgroups many.  Attention alone, us, rows x waves 16x4 / 16x8 / 32x4 / 32x8 (workgroups
+// of 32 rows in brackets): dense 1 head x 2048 tokens (64) 43 / 41 / 77 / 73, 4 x 2500 (316) 88 / 78 / 106 / 88, 4 x 3300 (416) 127 /
+// 120 / 157 / 115, 8 x 2000 (504) 90 / 95 / 104 / 86, 8 x 4000 (1000) 306 / 320 / 303 / 292, 8 x 8192 (2048) 1174 / 1223 / 1092 / 1126,
+// 16 x 4096 (2048) 605 / 658 / 562 / 595; block-sparse 1 x 2048, 416 keys (64) 13.9 / 14.7 / 23 / 23, 4 x 4096, 704 keys (512) 68 / 69 / 56 /
+// 61, 8 x 8192, 704 keys (2048) 202 / 254 / 198 / 224.
 template <int MODE>
 hipError_t launch_tiled(const Shape& sh, Args32& a, hipStream_t st) {
     const long long wide = (long long)sh.batch * sh.hq * (a.idx ? (long long)sh.n1 * ((sh.s + 31) / 32) : (sh.n + 31) / 32);
