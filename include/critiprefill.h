@@ -88,7 +88,7 @@ int critiprefill_estimate(const critiprefill_params *p, const void *q, const voi
  * the same result, bit for bit, with the scratch in a fixed array inside the library's device image
  * instead of a caller workspace.  Calls no allocating routine.
  * Limit: critiprefill_workspace_bytes(p) must not exceed CRITIPREFILL_STATIC_SCRATCH_BYTES (32 MiB; the five
- * benchmark configurations need 1 to 28 MiB), otherwise CP_ERR_WORKSPACE and nothing is launched.
+ * benchmark configurations need 0.1 to 28 MiB), otherwise CP_ERR_WORKSPACE and nothing is launched.
  * Every GPU the library runs on holds its own copy of the array until the process ends; the device that is
  * current at the call is used (it must be the device of hip_stream).  All calls on one GPU share the array:
  * two calls whose kernels may overlap (different streams, or threads) race; calls on one stream are ordered.

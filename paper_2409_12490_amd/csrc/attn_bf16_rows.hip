@@ -14,7 +14,7 @@
 //
 // What bounds it: up to a few hundred workgroups the latency of a tile (16 KB asked for one tile ahead; 1.5 us per tile and wave at 4
 // heads x 3000 tokens), beyond that the caches: every 32 rows read their keys anew, eight times the bytes of the 256-row kernel
-// (10 to 14 TB/s reached).  Dense 2 heads x 600 tokens 20.6 -> 9.6 us, 4 x 3000 72.7 -> 32.7, 2 x 8192 185 -> 88; block-sparse 2 x
+// (9 to 12 TB/s reached).  Dense 2 heads x 600 tokens 20.6 -> 9.6 us, 4 x 3000 72.7 -> 32.7, 2 x 8192 185 -> 88; block-sparse 2 x
 // 5632 32.2 -> 25.7 (against the 256-row kernel, with 6 to 64 workgroups there); where that kernel fills the chip it is 2.4 times
 // faster than this one.
 #include "attn_bf16.h"

@@ -22,7 +22,7 @@
 //
 // What bounds it: the fp32 matrix instructions, which share their units with the vector instructions (measured: a wave's
 // softmax and address arithmetic add their time to the MFMAs of all waves of the SIMD, at 2.0 vector instructions per MFMA
-// the pipe was busy 57 % of the time, at 0.5 82 %).  So the key loop keeps them few: tiles of 16 consecutive tokens with their
+// the pipe was busy 57 % of the time, at 1.0, now with long rows, 80 %; 47 % at 4 heads x 2500).  So the key loop keeps them few: tiles of 16 consecutive tokens with their
 // addresses on the scalar unit (MODE 1/2), O rescaled only in tiles where some row's max moves.  Dense, 8 heads x 8192 tokens: 126
 // TFLOP/s of the 154 that a large library product reaches (1090 us); 4 heads x 2500 tokens: 519 -> 81 us, block-sparse 4 heads x 4096
 // tokens (704 keys) 183 -> 56 us, one head x 2048 tokens (384 keys) 85 -> 13.7 us against a vector-FMA loop over 32 x 32 tiles in LDS

@@ -64,7 +64,7 @@ template <> struct PoolVec<float> {
 // A group is a segment of Q or a block of K; `split` waves of a workgroup share one and merge through LDS.  A lane owns 16 bytes
 // of a token row, kLanes lanes cover the row, a wave kRows rows per load with eight loads in flight (a batch).
 //
-// Bound by HBM for long sequences (1.34 GB at 32 + 8 heads x 128K tokens: 202 to 215 us, 6.2 to 6.6 TB/s; a plain copy moves 5.2
+// Bound by HBM for long sequences (1.34 GB at 32 + 8 heads x 128K tokens: 194 to 215 us, 6.2 to 6.9 TB/s; a plain copy moves 5.2
 // here) and by the latency of a wave's batches, one after another, for short ones: with a wave to a group, 2000 tokens took 11.7 us.
 template <typename T>
 __global__ __launch_bounds__(64 * kPoolWaves) void pool_kernel(PoolArgs a) {
@@ -279,9 +279,9 @@ __global__ __launch_bounds__(64 * kScore32Waves) void score_fp32_kernel(ScoreArg
 // us until a chunk has landed; PASS 1 the latency of S' and of the stores.  With one workgroup to a compute unit, what the groups leave
 // over after whole rounds of whole workgroups decides (score_shares).  The two passes, in us, against (a) eight waves that streamed
 // their chunk through two 32 KiB buffers, 128 segments of one head and chunk to a workgroup, and (b) this kernel with groups of one head in
-// fixed eights: 32 / 8 heads x 66000 tokens, segments of 256, blocks of 32: (a) 101, (b) 138, now 71; segments of 128, blocks of 16,
-// with S': 560, 824, 346; x 131072 (512, 64): 60, 60, 52, with S' 63, 66, 58; 2 x 32 x 65536 (256, 32) with S' 155, 146, 123;
-// 8 x 131072 (128, 16) 199, 214, 189; x 16384 (256, 32) 25, 16, 15.6.
+// fixed eights: 32 / 8 heads x 66000 tokens, segments of 256, blocks of 32: (a) 104, (b) 139, now 72; segments of 128, blocks of 16,
+// with S': 551, 822, 342; x 131072 (512, 64): 60, 60, 53, with S' 61, 66, 58; 2 x 32 x 65536 (256, 32) with S' 154, 146, 121;
+// 8 x 131072 (128, 16) 195, 209, 183; x 16384 (512, 64) 20, 9.8, 9.6.
 // ---------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
