@@ -57,7 +57,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = thread_id(), lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hh = lane >> 5;
     const bool rotated = wave >= 4;                              // shares its SIMD with wave - 4
@@ -69,12 +69,13 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     asm volatile("" ::"s"(a.q), "s"(a.k), "s"(a.v), "s"(a.idx), "s"(a.cnt), "s"(a.n), "s"(a.s), "s"(a.qs0), "s"(a.qs1), "s"(a.qs2), "s"(a.ks0),
                  "s"(a.ks1), "s"(a.ks2), "s"(a.list_len), "s"(a.scale_log2e), "s"(a.div_b.mul));
     // ---- which (batch, head, segment, query tile) this workgroup owns --------------------------
+    const unsigned wg = workgroup_id();
     int bb, h, g, j = 0, qt;
     if (DENSE) {
         // heaviest query tiles first; consecutive workgroups walk the KV heads so that the query
         // heads sharing one KV head land on the same XCD (workgroup id mod 8) at the same time.
         // div_order: batch * hq, batch * hkv
-        const unsigned y = a.div_order[0].div(blockIdx.x), x = blockIdx.x - y * (unsigned)(a.batch * a.hq);
+        const unsigned y = a.div_order[0].div(wg), x = wg - y * (unsigned)(a.batch * a.hq);
         qt = a.qtiles - 1 - (int)y;
         const unsigned gq = a.div_order[1].div(x), bkvh = x - gq * (unsigned)(a.batch * a.hkv);
         bb = (int)a.div_hkv.div(bkvh); g = (int)bkvh - bb * a.hkv; h = g * a.group + (int)gq;
@@ -89,7 +90,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
         // few neighbouring segments.
         // div_order: items of a group, items of a round, pairs that fill no whole round
         const unsigned pairs = a.group * a.n1, qtiles = a.qtiles;
-        const unsigned grp = a.div_order[0].div(blockIdx.x), x = blockIdx.x - grp * pairs * qtiles;
+        const unsigned grp = a.div_order[0].div(wg), x = wg - grp * pairs * qtiles;
         const unsigned full = pairs / kRound * kRound;           // pairs that fill whole rounds
         unsigned u;
         if (x < full * qtiles) {
@@ -109,7 +110,10 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     const int q_end = DENSE ? a.n : min(a.n, (j + 1) * a.s);
     if (q_lo >= q_end) return;                                   // uniform: tile past a short segment
     const int q_last = min(q_end, q_lo + TQ) - 1;
-    const int wq_lo = q_lo + WQ * wave;
+    // A vector register for a value that is the same in all lanes: the loop's branches on what this wave sees then stay predicated
+    // code.  As branches on scalars the compiler threads them through the loop, with copies of O, S and P and 41 to 56 spilled registers.
+    int wq_lo = q_lo + WQ * wave;
+    asm("" : "+v"(wq_lo));
     const int wq_last = min(q_end, wq_lo + WQ) - 1;              // < wq_lo when the wave has no rows
 
     const uint16_t* qp = a.q + bb * a.qs0 + h * a.qs1;
@@ -237,7 +241,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
         for (int i = 0; i < 2; ++i) {
             const int tok = ent[i] * a.b + eoff[i];
             const bool valid = ent[i] >= 0 && (unsigned)tok < (unsigned)a.n;   // also rejects entries whose token index wrapped
-            const unsigned base = __umul24(valid ? (unsigned)tok : 0u, tok_bytes);  // invalid rows read token 0, masked later
+            const unsigned base = mul24(valid ? (unsigned)tok : 0u, tok_bytes);  // invalid rows read token 0, masked later
             koff[i] = base + kch * 16;
             voff[i] = base + vch * 16;
             tokv[i] = valid ? tok : 0x7fffffff;
@@ -289,7 +293,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
                 const int base = i ? hi : lo;
                 const int tok = base + 4 * wave + r4;
                 const bool valid = base >= 0 && (unsigned)tok < (unsigned)a.n;
-                const unsigned sb = __umul24(valid ? (unsigned)tok : 0u, tok_bytes);
+                const unsigned sb = mul24(valid ? (unsigned)tok : 0u, tok_bytes);
                 koff[i] = sb + kch * 16; voff[i] = sb + vch * 16;
             }
         }
@@ -306,7 +310,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
             for (int i = 0; i < 2; ++i) {
                 const int tok = base + 32 * i + 4 * wave + r4;
                 const bool valid = base >= 0 && (unsigned)tok < (unsigned)a.n;
-                const unsigned sb = __umul24(valid ? (unsigned)tok : 0u, tok_bytes);
+                const unsigned sb = mul24(valid ? (unsigned)tok : 0u, tok_bytes);
                 koff[i] = sb + kch * 16; voff[i] = sb + vch * 16;
             }
         }
@@ -450,14 +454,16 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     };
     // MODE 1/2: the tile holds tokens base .. base+63; key row kr is visible iff base + kr <= min(qpos, n-1)
     auto mask_base = [&](f32x16 (&s)[2], int base) {
-        const int lim = min(qpos, a.n - 1) - base - 4 * hh;
+        int lim = min(qpos, a.n - 1) - base - 4 * hh;
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
             for (int gg = 0; gg < 4; ++gg)
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < 4; ++i) {
                     if (32 * kt + 8 * gg + i > lim) s[kt][4 * gg + i] = -INFINITY;
+                    asm("" : "+v"(lim));                     // or each comparison is built on the others, 32 scalar pairs at once
+                }
     };
     // MODE 3: key row 32*kt + kr of the tile is token (kt ? hi : lo) + kr; a missing half (-1) is masked whole
     auto mask_halves = [&](f32x16 (&s)[2], int lo, int hi) {
@@ -465,12 +471,14 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt) {
             const int base = kt ? hi : lo;
-            const int lim = base < 0 ? -1 : top - base;
+            int lim = base < 0 ? -1 : top - base;
 #pragma unroll
             for (int gg = 0; gg < 4; ++gg)
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < 4; ++i) {
                     if (8 * gg + i > lim) s[kt][4 * gg + i] = -INFINITY;
+                    asm("" : "+v"(lim));
+                }
         }
     };
     // S^T tile -> P^T fragments; running max / sum; O rescaled when any row's max moved

@@ -38,12 +38,12 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a) {
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
     constexpr unsigned kStat = W * 2 * kSlotBytes;                  // behind the slots: (max, sum) [wave][row]
 
-    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
+    const int tid = thread_id(), lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Consecutive workgroups walk the KV heads, so that a head's keys stay with few XCDs (workgroup id mod 8); inside one the row
     // tiles of a segment and head follow each other, and the segments with most keys, those at the end, come first.
     const int G = a.group, bkv = a.batch * a.hkv;
-    const int x = blockIdx.x % bkv, y = blockIdx.x / bkv;
+    const int wg = (int)workgroup_id(), x = wg % bkv, y = wg / bkv;
     const int bb = x / a.hkv, kvh = x % a.hkv;
     int h, j = 0, q_lo;
     if (DENSE) { h = kvh * G + y % G; q_lo = (a.qtiles - 1 - y / G) * kRowsTQ; }

@@ -372,8 +372,10 @@ __global__ __launch_bounds__(64 * kScoreWaves, 2) void score_kernel(ScoreArgs a)
                 const int lc = (lane & 15) ^ ((row >> 1) & 15);
                 const unsigned voff = (unsigned)(((blk * 2 + (row & 1)) * kHeadDim + lc * 8) * 2);
                 const unsigned dst = __builtin_amdgcn_readfirstlane(lds0 + wave * kTileBytes + 1024u * x);
-                asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff), "s"(sbase)
-                             : "memory");   // m0: reserved for the compiler, which sets it anew before each use of its own
+                // m0: reserved for the compiler, which sets it anew before each use of its own.  The wait: one state after m0, five after
+                // the v_readfirstlane behind sbase, which the compiler does not see in here
+                asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(dst), "v"(voff), "s"(sbase)
+                             : "memory");
             }
         }
     }
