@@ -26,6 +26,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(2))) int i32x2;
 #define LDS_PTR(T, off) ((__attribute__((address_space(3))) T*)(uintptr_t)(off))
+typedef const __attribute__((address_space(4))) int32_t* scalar_list;   // read through scalar loads: wave-uniform addresses
 
 constexpr float kLazyLog2 = 8.0f;        // how far a row's max may outgrow its reference point before O is rescaled
 
@@ -48,6 +49,10 @@ __device__ __forceinline__ void pin(const bf16x8& v) { asm volatile("" ::"v"(v))
 // compiler keeps a scalar in a vector register) has written sbase, so the asm waits for both itself.
 __device__ __forceinline__ void dma16(const void* sbase, unsigned voff, unsigned lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(voff), "s"(sbase)
+                 : "memory");
+}
+__device__ __forceinline__ void dma4(const void* sbase, unsigned voff, unsigned lds_base) {   // the same with 4 bytes per lane
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_base), "v"(voff), "s"(sbase)
                  : "memory");
 }
 

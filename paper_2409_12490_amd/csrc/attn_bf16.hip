@@ -54,6 +54,7 @@ constexpr int kFragLook = 3;               // depth of the LDS fragment ring, se
 template <int MODE, int KLOOK = kFragLook>
 __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     constexpr bool DENSE = MODE == 2, FAST = MODE != 0, HALF = MODE == 3;
+    constexpr bool EARLY = MODE == 1 || HALF;                    // the first tiles are asked for before the list is in LDS
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
 
@@ -127,12 +128,33 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     // not needed before those tiles have landed.
     int count = 0, list_first = -1;
     const int32_t* list = nullptr;
+    int head_tok[8];                                             // EARLY: first tokens of tiles 0-3 (MODE 3: of their halves), -1 past the end
     if (!DENSE) {
         const long long lrow = a.shared_lists ? ((long long)bb * a.hkv + g) * a.n1 + j : ((long long)bb * a.hq + h) * a.n1 + j;
-        list = a.idx + lrow * a.list_len;
+        list = uniform_ptr(a.idx + lrow * a.list_len);
         // the whole row (its pitch is list_len) is copied, so that its loads do not wait for the count
-        if (tid < a.list_len) list_first = list[tid];
-        count = min(max(a.cnt[lrow], 0), a.list_len);             // a bad count must not run past the list's LDS region
+        if (EARLY) {
+            // The tiles that are asked for first come from scalar loads: no copy in LDS, no barrier and no walk on the way to them.  And
+            // V of tile 1 and K of tile 2 are asked for once Q is there: the wait for Q is one for all loads.  32 x 128K (32 blocks of 64)
+            // 4.83 -> 4.71 ms a layer, shared lists 4.52 -> 4.40, 2 x 32 x 64K (32 of 32) 2504 -> 2470 us; x 16K within the noise.
+            constexpr int kFirst = HALF ? 8 : 4, kRun = HALF ? 32 : TK;
+            const scalar_list entries = (scalar_list)(unsigned long long)list;
+            const int cnt = *(scalar_list)(unsigned long long)uniform_ptr(a.cnt + lrow);
+            int entry[kFirst]; unsigned at[kFirst];
+#pragma unroll
+            for (int x = 0; x < kFirst; ++x) {
+                at[x] = a.div_b.div((unsigned)(x * kRun));
+                entry[x] = entries[min(at[x], (unsigned)a.list_len - 1u)];
+            }
+            for (int x = 64 * wave; x < a.list_len; x += 512)     // lanes past the row's end repeat its last entry
+                dma4(list, (unsigned)min(x + lane, a.list_len - 1) * 4u, lds0 + kListOff + x * 4);
+            count = min(max(cnt, 0), a.list_len);
+#pragma unroll
+            for (int x = 0; x < kFirst; ++x) head_tok[x] = at[x] < (unsigned)count ? entry[x] * a.b + (int)(x * kRun - at[x] * a.b) : -1;
+        } else {
+            if (tid < a.list_len) list_first = list[tid];
+            count = min(max(a.cnt[lrow], 0), a.list_len);         // a bad count must not run past the list's LDS region
+        }
         __builtin_amdgcn_sched_barrier(0);
     }
     // ---- Q fragments (B operand: column = query l32, 8 channels at 16*ks + 8*hh) ---------------
@@ -144,43 +166,9 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
         for (int ks = 0; ks < 8; ++ks) qf[ks] = as_bf16x8(*(const uint4*)(src + 16 * ks));
     }
 
-    if (!DENSE) {
-        if (tid < a.list_len) *LDS_PTR(int, lds0 + kListOff + tid * 4) = list_first;
-        for (int x = tid + 512; x < a.list_len; x += 512) *LDS_PTR(int, lds0 + kListOff + x * 4) = list[x];
-    }
-    __syncthreads();
-    // positions 0 .. total-1 of the listed blocks laid end to end (host checks count * b < 2^31)
-    const unsigned total = DENSE ? (unsigned)q_last + 1u : (unsigned)count * (unsigned)a.b;
     const unsigned ub = (unsigned)a.b;
-    int ntiles = (int)((total + TK - 1) / TK);
-    // MODE 3: the first tokens of the two halves of every tile, worked out once by all threads and kept in LDS
-    // behind the list (8 bytes per tile), so that the key loop reads a tile's description instead of walking the list
-    const unsigned tab0 = lds0 + kListOff + (((unsigned)a.list_len * 4u + 1023u) & ~1023u);
-    if (HALF) {
-        for (int x = tid; x < ntiles; x += 512) {
-            const unsigned p0 = (unsigned)x * TK, e0 = a.div_b.div(p0), p1 = p0 + 32, e1 = a.div_b.div(p1);
-            const int lo = *LDS_PTR(const int, lds0 + kListOff + e0 * 4) * a.b + (int)(p0 - e0 * ub);
-            const int hi = e1 < (unsigned)count ? *LDS_PTR(const int, lds0 + kListOff + e1 * 4) * a.b + (int)(p1 - e1 * ub) : -1;
-            i32x2 d; d[0] = lo; d[1] = hi;
-            *LDS_PTR(i32x2, tab0 + x * 8) = d;
-        }
-        __syncthreads();
-    }
-    if (!DENSE) {   // drop trailing tiles that start after the last query row (lists are ascending): lane l looks at the l-th last one
-        while (ntiles > 0) {
-            const int x = max(ntiles - 1 - lane, 0);
-            int tok;
-            if (HALF) tok = *LDS_PTR(const int, tab0 + x * 8);
-            else {
-                const unsigned p = (unsigned)x * TK, e = a.div_b.div(p);
-                tok = *LDS_PTR(const int, lds0 + kListOff + e * 4) * a.b + (int)(p - e * ub);
-            }
-            const unsigned long long seen = __builtin_amdgcn_ballot_w64(tok <= q_last && lane < ntiles);
-            ntiles -= seen ? (int)__builtin_ctzll(seen) : min(ntiles, 64);
-            if (seen) break;
-        }
-        ntiles = __builtin_amdgcn_readfirstlane(ntiles);
-    }
+    const unsigned tab0 = lds0 + kListOff + (((unsigned)a.list_len * 4u + 1023u) & ~1023u);   // MODE 3: the tile table, see the prologue
+    int ntiles = 0;                                          // set in the prologue
 
     // ---- tile loader: wave w fills rows 4*w .. 4*w+3 and 32 + 4*w .. +3 of K and of V (4 instructions) ----
     const int r4 = lane >> 4;                                // row inside the wave's 4-row group
@@ -549,13 +537,59 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
         if (!FAST) describe_next(slot);                      // writes the row tokens into the vacated slot
     };
 
-    // ---- prologue: K of tiles 0-2 and V of tiles 0-1 in flight; tiles up to 3 described -------------
-    if (ntiles > 0) {
+    // ---- prologue: K and V of tile 0 and K of tile 1 are asked for, the list arrives and is counted, then V of tile 1 and K of tile 2
+    auto describe_first = [&](int x) __attribute__((always_inline)) {    // EARLY: tile x of the first four
+        nb[x] = head_tok[HALF ? 2 * x : x];
+        if (HALF) { nb2[x] = head_tok[2 * x + 1]; half_offsets(nb[x], nb2[x]); }
+        else base_offsets(nb[x]);
+    };
+    if (EARLY) {
+        describe_first(0); issue_k(0); issue_v(0, true);
+        describe_first(1); issue_k(1);
+        voff_issue[0] = voff[0]; voff_issue[1] = voff[1];
+        // the list has landed: 8 loads of Q and the 6 above are younger
+        asm volatile("s_waitcnt vmcnt(14)" ::: "memory");
+    } else if (!DENSE) {
+        if (tid < a.list_len) *LDS_PTR(int, lds0 + kListOff + tid * 4) = list_first;
+        for (int x = tid + 512; x < a.list_len; x += 512) *LDS_PTR(int, lds0 + kListOff + x * 4) = list[x];
+    }
+    __syncthreads();
+    // positions 0 .. total-1 of the listed blocks laid end to end (host checks count * b < 2^31)
+    const unsigned total = DENSE ? (unsigned)q_last + 1u : (unsigned)count * (unsigned)a.b;
+    ntiles = (int)((total + TK - 1) / TK);
+    // MODE 3: the first tokens of the two halves of every tile, worked out once by all threads and kept in LDS
+    // behind the list (8 bytes per tile), so that the key loop reads a tile's description instead of walking the list
+    if (HALF) {
+        for (int x = tid; x < ntiles; x += 512) {
+            const unsigned p0 = (unsigned)x * TK, e0 = a.div_b.div(p0), p1 = p0 + 32, e1 = a.div_b.div(p1);
+            const int lo = *LDS_PTR(const int, lds0 + kListOff + e0 * 4) * a.b + (int)(p0 - e0 * ub);
+            const int hi = e1 < (unsigned)count ? *LDS_PTR(const int, lds0 + kListOff + e1 * 4) * a.b + (int)(p1 - e1 * ub) : -1;
+            i32x2 d; d[0] = lo; d[1] = hi;
+            *LDS_PTR(i32x2, tab0 + x * 8) = d;
+        }
+        __syncthreads();
+    }
+    if (!DENSE) {   // drop trailing tiles that start after the last query row (lists are ascending): lane l looks at the l-th last one
+        while (ntiles > 0) {
+            const int x = max(ntiles - 1 - lane, 0);
+            int tok;
+            if (HALF) tok = *LDS_PTR(const int, tab0 + x * 8);
+            else {
+                const unsigned p = (unsigned)x * TK, e = a.div_b.div(p);
+                tok = *LDS_PTR(const int, lds0 + kListOff + e * 4) * a.b + (int)(p - e * ub);
+            }
+            const unsigned long long seen = __builtin_amdgcn_ballot_w64(tok <= q_last && lane < ntiles);
+            ntiles -= seen ? (int)__builtin_ctzll(seen) : min(ntiles, 64);
+            if (seen) break;
+        }
+        ntiles = __builtin_amdgcn_readfirstlane(ntiles);
+    }
+
+    if (!EARLY && ntiles > 0) {
         if (!FAST) fetch_entries();
 #pragma unroll
         for (int s3 = 0; s3 < 4; ++s3) {
-            if (HALF) { next_halves(nb[s3], nb2[s3]); half_offsets(nb[s3], nb2[s3]); }
-            else if (FAST) { nb[s3] = next_base(); base_offsets(nb[s3]); }
+            if (FAST) { nb[s3] = next_base(); base_offsets(nb[s3]); }
             else { tile_offsets(); fetch_entries(); put_tok(s3); }
             if (s3 == 0) { issue_k(0); issue_v(0, true); }
             if (s3 == 1) { issue_k(1); }                     // K0 V0 K1 first: they are needed at once
@@ -567,7 +601,15 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     }
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) pin(qf[ks]);                      // Q has arrived: no wait for it is left in the key loop
-    if (ntiles > 0) dma_wait(4);                                     // K0, V0, K1 have landed
+    if (EARLY) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // and K0, V0, K1
+        if (HALF) walk_t = 4;
+        else { walk_e = (int)a.div_b.div(4 * TK); walk_off = 4 * TK - walk_e * a.b; }
+        describe_first(2);
+        if (ntiles > 0) { issue_v(1, false); issue_k(2); }
+        voff_issue[0] = voff[0]; voff_issue[1] = voff[1];
+        describe_first(3);
+    } else if (ntiles > 0) dma_wait(4);                              // K0, V0, K1 have landed
     __syncthreads();
     // from here on: koff = K offsets of tile 3, voff_issue = V offsets of tile 2, voff = V offsets of tile 3
 

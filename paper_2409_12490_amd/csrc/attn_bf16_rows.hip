@@ -27,8 +27,6 @@ namespace {
 constexpr int kRowsTQ = 32, kRowsTK = 32, kSlotBytes = kRowsTK * 256;
 constexpr int kNoToken = 0x7fffffff;              // a key that does not exist: after every query
 
-typedef const __attribute__((address_space(4))) int32_t* scalar_list;   // read through scalar loads: wave-uniform addresses
-
 // MODE 0: sparse, any block size: every key of a tile has a token of its own.  MODE 1: sparse, block size a multiple of 32: a
 // tile is 32 consecutive tokens, described by its first token on the scalar unit.  MODE 2: dense.
 template <int MODE, int W>
