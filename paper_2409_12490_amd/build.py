@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libcritiprefill.so")
-SOURCES = ["api.hip", "estimate.hip", "select.hip", "attn_fp32.hip", "attn_bf16.hip", "attn_bf16_rows.hip"]
+SOURCES = ["api.hip", "estimate.hip", "select.hip", "attn_fp32.hip", "attn_fp32_split.hip", "attn_bf16.hip", "attn_bf16_rows.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

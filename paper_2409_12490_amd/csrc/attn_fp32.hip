@@ -13,35 +13,23 @@
 //
 // K and V go from memory straight to registers: the waves of a workgroup read different keys, so there is nothing to
 // share through LDS, and the fp32 matrix rate is a sixteenth of the bf16 one: 16 KB per 2048 * RT matrix cycles and wave
-// are 16 (RT = 2) to 32 (RT = 1) bytes per clock and compute unit, within what L2 delivers.  V of a tile is asked for
+// are 16 (RT = 2, MODE 0) to 32 (RT = 1) bytes per clock and compute unit, within what L2 delivers.  V of a tile is asked for
 // before its QK, K of the next tile before its softmax and PV.
 //
 // Values: a wave takes its weights relative to the true max of the row among its keys, so they are at most 1, and weights down to
 // the smallest subnormal count; O overflows for |V| above 3.4e38 / (number of keys) at the earliest.  (A max that may outgrow its
 // reference by 2^8, as in the bf16 kernel, saves most rescalings of O, 4 % of the time, and overflows 256 times earlier.)
 //
-// What bounds it: the fp32 matrix instructions, which share their units with the vector instructions (measured: a wave's
-// softmax and address arithmetic add their time to the MFMAs of all waves of the SIMD, at 2.0 vector instructions per MFMA
-// the pipe was busy 57 % of the time, at 1.0, now with long rows, 80 %; 47 % at 4 heads x 2500).  So the key loop keeps them few: tiles of 16 consecutive tokens with their
-// addresses on the scalar unit (MODE 1/2), O rescaled only in tiles where some row's max moves.  Dense, 8 heads x 8192 tokens: 126
-// TFLOP/s of the 154 that a large library product reaches (1090 us); 4 heads x 2500 tokens: 519 -> 81 us, block-sparse 4 heads x 4096
-// tokens (704 keys) 183 -> 56 us, one head x 2048 tokens (384 keys) 85 -> 13.7 us against a vector-FMA loop over 32 x 32 tiles in LDS
-// (12 to 25 TFLOP/s).
-#include "kernels.h"
+// This kernel takes the launches that are too small for attn_fp32_split.hip, and the block sizes and strides that are not for it.
+//
+// What bounds it: latency, where few workgroups fill the chip (one head x 2048 tokens, 384 keys: 13.7 us, against 85 of a vector-FMA loop over
+// 32 x 32 tiles in LDS), and the fp32 matrix instructions, which share their units with the vector instructions (measured: a wave's softmax and address
+// arithmetic add their time to the MFMAs of all waves of the SIMD).  So the key loop keeps them few: tiles of 16 consecutive tokens with their
+// addresses on the scalar unit (MODE 1/2), O rescaled only in tiles where some row's max moves.
+#include "attn_fp32.h"
 
 namespace cp {
 namespace {
-
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
-struct Args32 {
-    const float* q; const float* k; const float* v; const int32_t* idx; const int32_t* cnt;
-    float* out; float* lse;
-    int batch, hq, hkv, n, s, b, n1, list_len, qtiles;   // qtiles: per segment (sparse) or per sequence (dense)
-    int shared_lists;                             // lists are per (batch, KV head, segment) instead of per query head
-    float scale_log2e, scale;
-    long long qs0, qs1, qs2, ks0, ks1, ks2, os0, os1, os2;
-};
 
 __device__ __forceinline__ float group_max(float x) {               // over the four lane groups: lanes l, l^16, l^32, l^48
     auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -49,8 +37,6 @@ __device__ __forceinline__ float group_max(float x) {               // over the 
     r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-
-typedef const __attribute__((address_space(4))) int32_t* scalar_list;   // read through scalar loads: wave-uniform addresses
 
 // MODE 0: any block size and any stride (dense if there is no list): every key of a tile has a token of its own.  MODE 1: sparse, block size a multiple of
 // 16: a tile is 16 consecutive tokens, described by its first token on the scalar unit.  MODE 2: dense.
@@ -313,19 +299,13 @@ hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// 32 rows per workgroup halve the K/V bytes and the softmax instructions per MFMA, 16 rows give twice the workgroups, and a short sequence
-// needs them; eight waves split a long row further and leave one workgroup to a compute unit, which evens out unequal rows, four
-// waves are better where rows are short or workgroups many.  Attention alone, us, rows x waves 16x4 / 16x8 / 32x4 / 32x8 (workgroups
-// of 32 rows in brackets): dense 1 head x 2048 tokens (64) 43 / 41 / 77 / 73, 4 x 2500 (316) 88 / 78 / 106 / 88, 4 x 3300 (416) 127 /
-// 120 / 157 / 115, 8 x 2000 (504) 90 / 95 / 104 / 86, 8 x 4000 (1000) 306 / 320 / 303 / 292, 8 x 8192 (2048) 1174 / 1223 / 1092 / 1126,
-// 16 x 4096 (2048) 605 / 658 / 562 / 595; block-sparse 1 x 2048, 416 keys (64) 13.9 / 14.7 / 23 / 23, 4 x 4096, 704 keys (512) 68 / 69 / 56 /
-// 61, 8 x 8192, 704 keys (2048) 202 / 254 / 198 / 224.
+// 16 rows to a workgroup: what is left to this kernel are launches that 32 rows would not fill the chip with (attn_fp32_split_better).  Eight waves
+// split a long row further, four are better where rows are short.  Attention alone, us, four / eight waves (workgroups of 32 rows in brackets): dense 1 head
+// x 2048 tokens (64) 43 / 41; block-sparse 1 x 2048, 416 keys (64) 13.9 / 14.7.
 template <int MODE>
 hipError_t launch_tiled(const Shape& sh, Args32& a, hipStream_t st) {
-    const long long wide = (long long)sh.batch * sh.hq * (a.idx ? (long long)sh.n1 * ((sh.s + 31) / 32) : (sh.n + 31) / 32);
     const long long keys = a.idx ? min((long long)sh.n, (long long)sh.list_len * sh.b) : sh.n;
-    if (wide < 384) return keys > 1024 ? launch<MODE, 1, 8>(sh, a, st) : launch<MODE, 1, 4>(sh, a, st);
-    return wide < 1536 && keys >= 1536 ? launch<MODE, 2, 8>(sh, a, st) : launch<MODE, 2, 4>(sh, a, st);
+    return keys > 1024 ? launch<MODE, 1, 8>(sh, a, st) : launch<MODE, 1, 4>(sh, a, st);
 }
 
 }  // namespace
@@ -342,6 +322,7 @@ hipError_t launch_attn_fp32(const Shape& sh, const void* q, const void* k, const
     a.ks0 = sh.kvs[0]; a.ks1 = sh.kvs[1]; a.ks2 = sh.kvs[2];
     a.os0 = sh.os[0]; a.os1 = sh.os[1]; a.os2 = sh.os[2];
     const bool near = sh.kvs[2] < (1 << 26);                        // a tile's rows are within 32-bit byte offsets of its first
+    if (attn_fp32_split_better(sh, idx != nullptr)) return launch_attn_fp32_split(sh, a, st);
     if (!idx && near) return launch_tiled<2>(sh, a, st);
     if (idx && near && sh.b % 16 == 0) return launch_tiled<1>(sh, a, st);
     return launch<0, 2, 4>(sh, a, st);
