@@ -51,6 +51,9 @@ __device__ __forceinline__ void dma16(const void* sbase, unsigned voff, unsigned
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(voff), "s"(sbase)
                  : "memory");
 }
+__device__ __forceinline__ void dma16_far(const void* src, unsigned lds_base) {   // the same from an address per lane
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(src) : "memory");
+}
 __device__ __forceinline__ void dma4(const void* sbase, unsigned voff, unsigned lds_base) {   // the same with 4 bytes per lane
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_base), "v"(voff), "s"(sbase)
                  : "memory");

@@ -122,48 +122,57 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     const uint16_t* vp = uniform_ptr(a.v + bb * a.ks0 + g * a.ks1);
 
     // ---- the virtual token list --------------------------------------------------------------
-    // Its loads are issued before those of Q (the scheduling barrier keeps the compiler from hoisting Q's loads
-    // above them): loads return in order, the list row comes from L2 / Infinity Cache (the selection has just
-    // written it) and the first K/V tiles cannot be asked for before it is here, while Q comes from HBM and is
-    // not needed before those tiles have landed.
-    int count = 0, list_first = -1;
-    const int32_t* list = nullptr;
+    // Asked for before Q: loads return in order, the list row comes from L2 / Infinity Cache (the selection has just written it) and the first
+    // K/V tiles cannot be asked for before it is here, while Q comes from HBM and is not needed before those tiles have landed.
+    int count = 0;
     int head_tok[8];                                             // EARLY: first tokens of tiles 0-3 (MODE 3: of their halves), -1 past the end
     if (!DENSE) {
         const long long lrow = a.shared_lists ? ((long long)bb * a.hkv + g) * a.n1 + j : ((long long)bb * a.hq + h) * a.n1 + j;
-        list = uniform_ptr(a.idx + lrow * a.list_len);
-        // the whole row (its pitch is list_len) is copied, so that its loads do not wait for the count
+        const int32_t* list = uniform_ptr(a.idx + lrow * a.list_len);
+        const int cnt = *(scalar_list)(unsigned long long)uniform_ptr(a.cnt + lrow);
+        // The tiles that are asked for first come from scalar loads: no copy in LDS, no barrier and no walk on the way to them.  And
+        // V of tile 1 and K of tile 2 are asked for once Q is there: the wait for Q is one for all loads.  32 x 128K (32 blocks of 64)
+        // 4.83 -> 4.71 ms a layer, shared lists 4.52 -> 4.40, 2 x 32 x 64K (32 of 32) 2504 -> 2470 us; x 16K within the noise.
+        constexpr int kFirst = HALF ? 8 : 4, kRun = HALF ? 32 : TK;
+        int entry[kFirst]; unsigned at[kFirst];
         if (EARLY) {
-            // The tiles that are asked for first come from scalar loads: no copy in LDS, no barrier and no walk on the way to them.  And
-            // V of tile 1 and K of tile 2 are asked for once Q is there: the wait for Q is one for all loads.  32 x 128K (32 blocks of 64)
-            // 4.83 -> 4.71 ms a layer, shared lists 4.52 -> 4.40, 2 x 32 x 64K (32 of 32) 2504 -> 2470 us; x 16K within the noise.
-            constexpr int kFirst = HALF ? 8 : 4, kRun = HALF ? 32 : TK;
             const scalar_list entries = (scalar_list)(unsigned long long)list;
-            const int cnt = *(scalar_list)(unsigned long long)uniform_ptr(a.cnt + lrow);
-            int entry[kFirst]; unsigned at[kFirst];
 #pragma unroll
             for (int x = 0; x < kFirst; ++x) {
                 at[x] = a.div_b.div((unsigned)(x * kRun));
                 entry[x] = entries[min(at[x], (unsigned)a.list_len - 1u)];
             }
-            for (int x = 64 * wave; x < a.list_len; x += 512)     // lanes past the row's end repeat its last entry
-                dma4(list, (unsigned)min(x + lane, a.list_len - 1) * 4u, lds0 + kListOff + x * 4);
-            count = min(max(cnt, 0), a.list_len);
+        }
+        // the whole row (its pitch is list_len) is copied, so that its loads do not wait for the count; lanes past its end repeat its last entry
+        for (int x = 64 * wave; x < a.list_len; x += 512)
+            dma4(list, (unsigned)min(x + lane, a.list_len - 1) * 4u, lds0 + kListOff + x * 4);
+        count = min(max(cnt, 0), a.list_len);                     // a bad count must not run past the list's LDS region
+        if (EARLY) {
 #pragma unroll
             for (int x = 0; x < kFirst; ++x) head_tok[x] = at[x] < (unsigned)count ? entry[x] * a.b + (int)(x * kRun - at[x] * a.b) : -1;
-        } else {
-            if (tid < a.list_len) list_first = list[tid];
-            count = min(max(a.cnt[lrow], 0), a.list_len);         // a bad count must not run past the list's LDS region
         }
         __builtin_amdgcn_sched_barrier(0);
     }
-    // ---- Q fragments (B operand: column = query l32, 8 channels at 16*ks + 8*hh) ---------------
-    const int qpos = wq_lo + l32;
-    bf16x8 qf[8];
+    // ---- Q: the wave's 32 rows as whole rows to LDS, where tiles 2 and 3 come later, and from there into registers, swizzled like K.  A lane
+    // per row straight from memory asks the address unit for 4096 pieces of 16 bytes per workgroup, 2 us that the first tiles wait behind.  Now
+    // 1024 of 64 bytes: 2 x 32 x 64K 2466 -> 2433 us, 32 x 128K 4.76 -> 4.73 ms a layer, shared lists 4.45 -> 4.38, 32 x 16K 357 -> 355 us, dense 32 x 2048 51.7 -> 51.2.
+    const int qpos = wq_lo + l32;                                 // B operand: column = query l32, 8 channels at 16*ks + 8*hh
+    const unsigned q_lds = lds0 + (wave < 4 ? kVOff : kKOff) + 2 * kTileBytes + (wave & 3) * (WQ * 256);
+    const int r4 = lane >> 4;                                // row inside the wave's 4-row group
+    const int pch = lane & 15;                               // physical chunk the lane's 16 bytes land in
     {
-        const uint16_t* src = qp + (long long)min(qpos, q_last) * a.qs2 + 8 * hh;    // rows past the end repeat the last one
+        const int first = q_lo + WQ * wave;
+        const unsigned chunk = (unsigned)(pch ^ r4) << 4;    // of row 4 * i + r4: logical chunk pch ^ (row & 15)
+        if (first + WQ - 1 <= q_last && a.qs2 < (1 << 28)) {
+            const char* rows = (const char*)uniform_ptr(qp + (long long)first * a.qs2);
+            const unsigned row_off = (unsigned)r4 * (unsigned)a.qs2 * 2u;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) qf[ks] = as_bf16x8(*(const uint4*)(src + 16 * ks));
+            for (int i = 0; i < 8; ++i) dma16(rows + (long long)i * a.qs2 * 8, row_off + (chunk ^ (64 * (i & 3))), q_lds + i * 1024);
+        } else {                                             // rows past the end repeat the last one
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                dma16_far((const char*)(qp + (long long)min(first + 4 * i + r4, q_last) * a.qs2) + (chunk ^ (64 * (i & 3))), q_lds + i * 1024);
+        }
     }
 
     const unsigned ub = (unsigned)a.b;
@@ -171,8 +180,6 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     int ntiles = 0;                                          // set in the prologue
 
     // ---- tile loader: wave w fills rows 4*w .. 4*w+3 and 32 + 4*w .. +3 of K and of V (4 instructions) ----
-    const int r4 = lane >> 4;                                // row inside the wave's 4-row group
-    const int pch = lane & 15;                               // physical chunk the lane's 16 bytes land in
     const int kch = pch ^ ((4 * wave + r4) & 15);            // K: logical chunk, swizzle = row & 15
     const int vch = pch ^ (4 * r4);                          // V: logical chunk, swizzle = 4 * (row & 3)
     const unsigned tok_bytes = (unsigned)a.ks2 * 2u;         // host checks n * tok_bytes < 2^32, both < 2^24
@@ -332,6 +339,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
         v_addr[dt] = lds0 + kVOff + (4 * hh + (i16 >> 2)) * 256 +
                      ((((unsigned)(dt ^ (i16 >> 2)) << 2) + 2 * gbit + ((i16 & 3) >> 1)) << 4) + (i16 & 1) * 8;
 
+    bf16x8 qf[8];
     f32x16 o[4];
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
@@ -537,23 +545,21 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
         if (!FAST) describe_next(slot);                      // writes the row tokens into the vacated slot
     };
 
-    // ---- prologue: K and V of tile 0 and K of tile 1 are asked for, the list arrives and is counted, then V of tile 1 and K of tile 2
-    auto describe_first = [&](int x) __attribute__((always_inline)) {    // EARLY: tile x of the first four
-        nb[x] = head_tok[HALF ? 2 * x : x];
-        if (HALF) { nb2[x] = head_tok[2 * x + 1]; half_offsets(nb[x], nb2[x]); }
-        else base_offsets(nb[x]);
+    // ---- prologue: K and V of tile 0 and K of tile 1 are asked for, the list arrives and is counted, Q goes to registers, then V of tile 1
+    // and K of tile 2
+    if (!FAST) { asm volatile("s_waitcnt vmcnt(8)" ::: "memory"); __syncthreads(); fetch_entries(); }   // the list has landed, Q is younger
+    auto describe_first = [&](int x) __attribute__((always_inline)) {    // tile x of the first four
+        if (EARLY) {
+            nb[x] = head_tok[HALF ? 2 * x : x];
+            if (HALF) { nb2[x] = head_tok[2 * x + 1]; half_offsets(nb[x], nb2[x]); }
+            else base_offsets(nb[x]);
+        } else if (DENSE) { nb[x] = x * TK <= q_last ? x * TK : -1; base_offsets(nb[x]); }
+        else { tile_offsets(); put_tok(x); fetch_entries(); }
     };
-    if (EARLY) {
-        describe_first(0); issue_k(0); issue_v(0, true);
-        describe_first(1); issue_k(1);
-        voff_issue[0] = voff[0]; voff_issue[1] = voff[1];
-        // the list has landed: 8 loads of Q and the 6 above are younger
-        asm volatile("s_waitcnt vmcnt(14)" ::: "memory");
-    } else if (!DENSE) {
-        if (tid < a.list_len) *LDS_PTR(int, lds0 + kListOff + tid * 4) = list_first;
-        for (int x = tid + 512; x < a.list_len; x += 512) *LDS_PTR(int, lds0 + kListOff + x * 4) = list[x];
-    }
-    __syncthreads();
+    describe_first(0); issue_k(0); issue_v(0, true);
+    describe_first(1); issue_k(1);
+    voff_issue[0] = voff[0]; voff_issue[1] = voff[1];
+    if (EARLY) { asm volatile("s_waitcnt vmcnt(14)" ::: "memory"); __syncthreads(); }    // 8 copies of Q and the 6 above are younger than the list's
     // positions 0 .. total-1 of the listed blocks laid end to end (host checks count * b < 2^31)
     const unsigned total = DENSE ? (unsigned)q_last + 1u : (unsigned)count * (unsigned)a.b;
     ntiles = (int)((total + TK - 1) / TK);
@@ -585,32 +591,20 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
         ntiles = __builtin_amdgcn_readfirstlane(ntiles);
     }
 
-    if (!EARLY && ntiles > 0) {
-        if (!FAST) fetch_entries();
+    asm volatile("s_waitcnt vmcnt(6)" ::: "memory");                 // the wave's Q is in LDS
 #pragma unroll
-        for (int s3 = 0; s3 < 4; ++s3) {
-            if (FAST) { nb[s3] = next_base(); base_offsets(nb[s3]); }
-            else { tile_offsets(); fetch_entries(); put_tok(s3); }
-            if (s3 == 0) { issue_k(0); issue_v(0, true); }
-            if (s3 == 1) { issue_k(1); }                     // K0 V0 K1 first: they are needed at once
-            if (s3 == 1 || s3 == 2) {
-                if (s3 == 2) { issue_v(1, false); issue_k(2); }
-                voff_issue[0] = voff[0]; voff_issue[1] = voff[1];
-            }
-        }
-    }
+    for (int ks = 0; ks < 8; ++ks) qf[ks] = as_bf16x8(*LDS_PTR(const u32x4, q_lds + l32 * 256 + (((2 * ks + hh) ^ (l32 & 15)) << 4)));
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) pin(qf[ks]);                      // Q has arrived: no wait for it is left in the key loop
-    if (EARLY) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // and K0, V0, K1
-        if (HALF) walk_t = 4;
-        else { walk_e = (int)a.div_b.div(4 * TK); walk_off = 4 * TK - walk_e * a.b; }
-        describe_first(2);
-        if (ntiles > 0) { issue_v(1, false); issue_k(2); }
-        voff_issue[0] = voff[0]; voff_issue[1] = voff[1];
-        describe_first(3);
-    } else if (ntiles > 0) dma_wait(4);                              // K0, V0, K1 have landed
-    __syncthreads();
+    for (int ks = 0; ks < 8; ++ks) pin(qf[ks]);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // and K0, V0, K1
+    __syncthreads();                                                 // everybody's, and nobody reads Q in LDS any more
+    if (HALF) walk_t = 4;
+    else if (EARLY) { walk_e = (int)a.div_b.div(4 * TK); walk_off = 4 * TK - walk_e * a.b; }
+    else if (DENSE) dense_tile = 4;
+    describe_first(2);
+    if (ntiles > 0) { issue_v(1, false); issue_k(2); }
+    voff_issue[0] = voff[0]; voff_issue[1] = voff[1];
+    describe_first(3);
     // from here on: koff = K offsets of tile 3, voff_issue = V offsets of tile 2, voff = V offsets of tile 3
 
     f32x16 s[2]; bf16x8 pf[4];
