@@ -3,20 +3,18 @@
 // rounded values) in another split: a workgroup owns 32 query rows and its W waves split the KEYS.  Wave w takes tiles w, w + W, ...
 // of 32 keys, with a running max, sum and output of its own, and the W partial results are merged through LDS at the end.
 //
-//   S^T[key][q]   = K . Q^T     32x32x16 MFMA, A = K rows straight from memory to registers (a wave's keys are its own: nothing to
-//                               share), B = Q fragments that stay in registers
+//   S^T[key][q]   = K . Q^T     32x32x16 MFMA, A = K rows from LDS, B = Q fragments that stay in registers
 //   softmax                     one query per lane column
-//   O^T[ch][q]   += V^T . P^T   A = V through the transposing LDS read, from a tile of the wave's own that global_load_lds fills
-//                               (two slots of 8 KiB); B = P^T, the S^T accumulators as they stand
+//   O^T[ch][q]   += V^T . P^T   A = V through the transposing LDS read; B = P^T, the S^T accumulators as they stand
 //
-// There is no barrier in the key loop.  V and then K of the next tile are asked for between QK and the softmax: loads
-// return in order, so a wave whose K is there has its V too.
+// K and V tiles of the wave's own (8 KiB each) come by global_load_lds as whole rows.  There is no barrier in the key loop: K of the next tile is asked
+// for when QK has read this one, V when PV has; each has half a tile's time to land, and loads return in order, so the other may be on its way.
 //
-// What bounds it: up to a few hundred workgroups the latency of a tile (16 KB asked for one tile ahead; 1.5 us per tile and wave at 4
-// heads x 3000 tokens), beyond that the caches: every 32 rows read their keys anew, eight times the bytes of the 256-row kernel
-// (9 to 12 TB/s reached).  Dense 2 heads x 600 tokens 20.6 -> 9.6 us, 4 x 3000 72.7 -> 32.7, 2 x 8192 185 -> 88; block-sparse 2 x
-// 5632 32.2 -> 25.7 (against the 256-row kernel, with 6 to 64 workgroups there); where that kernel fills the chip it is 2.4 times
-// faster than this one.
+// What bounds it: K as A operands straight from memory, a lane per row, asked the address unit of a compute unit for 512 pieces of 16 bytes a tile and Q for 512
+// more per wave, one a cycle: that bound the kernel (640 of them a tile, 2560 of the 3000 cycles that four waves take).  By whole rows it is 256 pieces of 64
+// bytes: dense 2 heads x 600 tokens 9.9 -> 7.3 us, 4 x 3000 32.4 -> 20.5, 2 x 8192 88 -> 53; block-sparse 4 x 4000 (blocks of 16) 28.7 -> 18.6, 2 x 5632 24.7 ->
+// 17.5, 8 x 1024 14.4 -> 10.6.  What is left is latency up to a few hundred workgroups, beyond that the caches: every 32 rows read their keys
+// anew, eight times the bytes of the 256-row kernel.
 #include "attn_bf16.h"
 
 #include <algorithm>
@@ -27,14 +25,15 @@ namespace {
 constexpr int kRowsTQ = 32, kRowsTK = 32, kSlotBytes = kRowsTK * 256;
 constexpr int kNoToken = 0x7fffffff;              // a key that does not exist: after every query
 
-// MODE 0: sparse, any block size: every key of a tile has a token of its own.  MODE 1: sparse, block size a multiple of 32: a
-// tile is 32 consecutive tokens, described by its first token on the scalar unit.  MODE 2: dense.
+// MODE 0: sparse, any block size: every key of a tile has a token of its own.  MODE 1: sparse, block size a multiple of 16: a
+// tile is two runs of 16 consecutive tokens, described by their first tokens on the scalar unit.  MODE 2: dense.
 template <int MODE, int W>
 __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a) {
     constexpr bool DENSE = MODE == 2, RUN = MODE != 0;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
-    constexpr unsigned kStat = W * 2 * kSlotBytes;                  // behind the slots: (max, sum) [wave][row]
+    constexpr unsigned kQ = W * 2 * kSlotBytes;                     // behind the waves' K and V slots: Q
+    constexpr unsigned kStat = kQ + kRowsTQ * 256;                  // (max, sum) [wave][row]
 
     const int tid = thread_id(), lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -63,34 +62,44 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a) {
         count = min(max(((scalar_list)(unsigned long long)a.cnt)[lrow], 0), a.list_len);
     }
     const int qpos = q_lo + l32;
-    bf16x8 qf[8];
-    {
-        const uint16_t* src = a.q + bb * a.qs0 + h * a.qs1 + (long long)min(qpos, q_last) * a.qs2 + 8 * hh;
+    // ---- Q, as whole rows to LDS by all waves, from there to the registers of each: a lane per row straight from memory, by every wave for
+    // itself, asks the address unit for 512 * W pieces of 16 bytes
+    const int r4 = lane >> 4, pch = lane & 15;                      // row inside a copy's four rows, chunk the lane's 16 bytes land in
+    const uint16_t* qp = a.q + bb * a.qs0 + h * a.qs1;
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) qf[ks] = as_bf16x8(*(const uint4*)(src + 16 * ks));
+    for (int i = 0; i < 8 / W; ++i) {
+        const int row = 4 * (wave * (8 / W) + i) + r4;              // rows past the end repeat the last one; 16-byte chunks swizzled by the row
+        dma16_far((const char*)(qp + (long long)min(q_lo + row, q_last) * a.qs2) + ((pch ^ (row & 15)) << 4), lds0 + kQ + (wave * (8 / W) + i) * 1024);
     }
     // positions 0 .. total-1 of the listed blocks laid end to end (host checks list_len * b < 2^31)
     const unsigned total = DENSE ? (unsigned)q_last + 1u : (unsigned)count * (unsigned)a.b;
     const int ntiles = (int)((total + kRowsTK - 1) / kRowsTK);
 
-    // ---- MODE 1/2: first token of the wave's next tile, -1 past its last one; t: the dense tile --------------------
+    // ---- MODE 1/2: first tokens of the two runs of the wave's next tile, -1: no such tokens; call in tile order
     unsigned walk_e = 0, walk_off = 0, step_e = 0, step_off = 0;    // list entry and offset inside its block of the next tile
     if (MODE == 1) {
         walk_e = (unsigned)wave * kRowsTK / (unsigned)a.b; walk_off = (unsigned)wave * kRowsTK % (unsigned)a.b;
         step_e = W * kRowsTK / (unsigned)a.b; step_off = W * kRowsTK % (unsigned)a.b;
     }
     const int n2 = MODE == 1 ? (a.n + a.b - 1) / a.b : 0;
-    auto next_base = [&](int t) -> int {                            // call in tile order: t = wave, wave + W, ...
-        if (DENSE) return t < ntiles ? t * kRowsTK : -1;
-        int base = -1;
-        while (base < 0 && walk_e < (unsigned)count) {              // entries outside the sequence have no tokens
-            const int blk = list[walk_e];
-            base = blk >= 0 && blk < n2 ? blk * a.b + (int)walk_off : -1;
-            if (base >= a.n) base = -1;
+    auto run_at = [&](unsigned e, unsigned off) -> int {
+        if (e >= (unsigned)count) return -1;
+        const int blk = list[e];
+        const int at = blk >= 0 && blk < n2 ? blk * a.b + (int)off : -1;    // entries outside the sequence have no tokens
+        return at < a.n ? at : -1;
+    };
+    int base0 = -1, base1 = -1;
+    auto next_tile = [&](int t) {
+        if (DENSE) {
+            base0 = t < ntiles ? t * kRowsTK : -1;
+            base1 = base0 >= 0 && base0 + 16 < a.n ? base0 + 16 : -1;
+        } else {
+            base0 = __builtin_amdgcn_readfirstlane(run_at(walk_e, walk_off));
+            const bool over = walk_off + 16 >= (unsigned)a.b;
+            base1 = __builtin_amdgcn_readfirstlane(run_at(walk_e + (over ? 1 : 0), over ? 0 : walk_off + 16));
             walk_e += step_e; walk_off += step_off;
             if (walk_off >= (unsigned)a.b) { walk_off -= a.b; ++walk_e; }
         }
-        return base;
     };
     // ---- MODE 0: token of key l32 of tile t --------------------------------------------------------------------
     auto key_token = [&](int t) -> int {
@@ -100,47 +109,50 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a) {
         return t < ntiles && e < (unsigned)count && blk >= 0 && tk < a.n ? (int)tk : kNoToken;
     };
 
-    // ---- loads: V rows 4*x + r4 into the slot (16-byte chunks swizzled by the row), K row l32 into registers ---------
+    // ---- copies: rows 4*i + r4 of K and V into the wave's two slots, 16-byte chunks swizzled by the row (K: row & 15, V: 4 * (row & 3))
     const unsigned tok_bytes = (unsigned)a.ks2 * 2u;                // host checks n * tok_bytes < 2^32, both < 2^24
-    const int r4 = lane >> 4, vch = (lane & 15) ^ (4 * r4);
-    const unsigned k_full = (unsigned)l32 * tok_bytes + hh * 16, v_full = (unsigned)r4 * tok_bytes + vch * 16;
-    typedef const __attribute__((address_space(1))) char* global_bytes;
-    bf16x8 kf[8];
-    auto load_k = [&](const uint16_t* rows, unsigned off) {
+    const unsigned vch = (unsigned)(pch ^ (4 * r4)) << 4, kch = (unsigned)(pch ^ r4) << 4;   // K: of rows 16*x + r4, the others by the row's bits 2 and 3
+    const unsigned k_slot = lds0 + wave * 2 * kSlotBytes, v_slot = k_slot + kSlotBytes;
+    unsigned k_run[4], v_run[4];                                    // byte offsets of the lane's pieces of a run of 16 rows
 #pragma unroll
-        for (int ks = 0; ks < 8; ++ks) kf[ks] = as_bf16x8(*(const __attribute__((address_space(1))) u32x4*)((global_bytes)(unsigned long long)rows + off + 32 * ks));
-    };
-    auto load_tile = [&](int base, int tok, unsigned slot) {        // MODE 1/2: base; MODE 0: tok
+    for (int i = 0; i < 4; ++i) {
+        k_run[i] = (unsigned)(4 * i + r4) * tok_bytes + (kch ^ (64 * i));
+        v_run[i] = (unsigned)(4 * i + r4) * tok_bytes + vch;
+    }
+    int tok = kNoToken;                                             // MODE 0: of the lane's key of the next tile
+    auto copy = [&](const uint16_t* from, bool is_k) {              // the next tile's; the reads of the tile before are done
+        const unsigned slot = is_k ? k_slot : v_slot;
+        auto chunk = [&](int i) { return is_k ? kch ^ (64 * (i & 3)) : vch; };
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         if (RUN) {
-            const uint16_t* vrow = uniform_ptr(vp + (long long)base * a.ks2);
-            unsigned koff = k_full;
-            if (base + kRowsTK <= a.n) {
+            const int first = max(base0, base1);                    // rows without a token repeat some of the tile's: masked
 #pragma unroll
-                for (int i = 0; i < 8; ++i) dma16(uniform_ptr(vrow + (long long)(4 * i) * a.ks2), v_full, slot + i * 1024);
-            } else {                                                // rows past the end repeat the last token: after every query, masked
-                const int top = a.n - 1 - base;
+            for (int run = 0; run < 2; ++run) {
+                const int at = run ? base1 : base0, from_tok = max(at >= 0 ? at : first, 0);
+                const uint16_t* rows = uniform_ptr(from + (long long)from_tok * a.ks2);
+                if (from_tok + 16 <= a.n) dma16x4(rows, is_k ? k_run : v_run, slot + run * 4096);
+                else {                                            // past the end the last token: after every query, masked
+                    const int top = a.n - 1 - from_tok;
 #pragma unroll
-                for (int i = 0; i < 8; ++i) dma16(vrow, (unsigned)min(4 * i + r4, top) * tok_bytes + vch * 16, slot + i * 1024);
-                koff = (unsigned)min(l32, top) * tok_bytes + hh * 16;
+                    for (int i = 0; i < 4; ++i) dma16(rows, (unsigned)min(4 * i + r4, top) * tok_bytes + chunk(i), slot + (4 * run + i) * 1024);
+                }
             }
-            load_k(uniform_ptr(kp + (long long)base * a.ks2), koff);
         } else {                                                    // keys without a token read token 0 and are masked
             const unsigned row = (tok == kNoToken ? 0u : (unsigned)tok) * tok_bytes;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) dma16(vp, (unsigned)__shfl((int)row, 4 * i + r4) + vch * 16, slot + i * 1024);
-            load_k(kp, row + hh * 16);
+            for (int i = 0; i < 8; ++i) dma16(from, (unsigned)__shfl((int)row, 4 * i + r4) + chunk(i), slot + i * 1024);
         }
     };
+    const unsigned k_base = (k_slot + l32 * 256) | (unsigned)(((l32 & 15) ^ hh) << 4);   // K row l32, channels 16*ks + 8*hh: k_base ^ 32*ks
     // V (transposed read, 16-lane groups): lane supplies row 4*hh + (i16 >> 2) (+16*t4, +8) and the 8-byte unit of channels
     // 32*dt + 16*gbit + 4*(i16 & 3); physical chunk = logical chunk ^ 4*(row & 3)
-    const unsigned slot0 = lds0 + wave * 2 * kSlotBytes;
     const int i16 = lane & 15, gbit = (lane >> 4) & 1;
     unsigned va[4];
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt)
         va[dt] = (4 * hh + (i16 >> 2)) * 256 + ((((unsigned)(dt ^ (i16 >> 2)) << 2) + 2 * gbit + ((i16 & 3) >> 1)) << 4) + (i16 & 1) * 8;
-    auto read_v = [&](unsigned slot, int t4, int dt) -> bf16x8 {
-        const unsigned ad = slot + va[dt] + t4 * 16 * 256;
+    auto read_v = [&](int t4, int dt) -> bf16x8 {
+        const unsigned ad = v_slot + va[dt] + t4 * 16 * 256;
         const v4bf16_lds lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(LDS_PTR(v4bf16_lds, ad));
         const v4bf16_lds hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(LDS_PTR(v4bf16_lds, ad + 8 * 256));
         bf16x8 f;
@@ -157,37 +169,52 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a) {
     float m_run = -INFINITY, l_run = 0.f;
     const float c = a.scale_log2e, lazy_raw = kLazyLog2 / c;
 
-    int base = -1, tok = kNoToken;
     // ascending lists: nothing is visible from the tile on whose first token is past the last row
     auto more = [&](int t) -> bool {
-        if (RUN) return base >= 0 && base <= q_last;
+        if (RUN) return t < ntiles && base0 <= q_last;
         const int first = __builtin_amdgcn_readfirstlane(tok);
         return t < ntiles && (first <= q_last || first == kNoToken);
     };
-    if (RUN) base = __builtin_amdgcn_readfirstlane(next_base(wave)); else tok = key_token(wave);
-    if (more(wave)) load_tile(base, tok, slot0);
-    unsigned slot = slot0;
-    for (int t = wave; more(t); t += W) {
-        const int this_base = base, this_tok = tok;
-        if (RUN) base = __builtin_amdgcn_readfirstlane(next_base(t + W)); else tok = key_token(t + W);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // V and K of this tile
+    if (RUN) next_tile(wave); else tok = key_token(wave);
+    bool go = more(wave);
+    if (go) {
+        copy(kp, true); copy(vp, false);
+        asm volatile("s_waitcnt vmcnt(16)" ::: "memory");           // the wave's share of Q has landed
+    } else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    bf16x8 qf[8];
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qf[ks] = as_bf16x8(*LDS_PTR(const u32x4, lds0 + kQ + l32 * 256 + (((2 * ks + hh) ^ (l32 & 15)) << 4)));
+    for (int t = wave; go; t += W) {
+        const int this0 = base0, this1 = base1, this_tok = tok;
+        if (RUN) next_tile(t + W); else tok = key_token(t + W);
+        const bool next = more(t + W);
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");            // K of this tile; its V may be on the way
         f32x16 s;
 #pragma unroll
         for (int r = 0; r < 16; ++r) s[r] = 0.f;
+        bf16x8 kf[8];
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) kf[ks] = as_bf16x8(*LDS_PTR(const u32x4, k_base ^ (unsigned)(32 * ks)));
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], s, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
-        const unsigned next_slot = slot ^ kSlotBytes;               // its last reads fed the PV of the tile before
-        if (more(t + W)) load_tile(base, tok, next_slot);
+        if (next) copy(kp, true);
         __builtin_amdgcn_sched_barrier(0);
 
         // ---- softmax: see the 256-row kernel
         if (RUN) {
-            if (this_base + kRowsTK - 1 > q_lo) {
-                const int lim = qpos - this_base - 4 * hh;
+            if (max(this0, this1) + 15 > q_lo || this0 < 0 || this1 < 0) {   // hidden from some row, or not there
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (8 * (r >> 2) + (r & 3) > lim) s[r] = -INFINITY;
+                for (int run = 0; run < 2; ++run) {
+                    const int at = run ? this1 : this0;
+                    int lim = at < 0 ? -1 : qpos - at - 4 * hh;
+#pragma unroll
+                    for (int r = 0; r < 8; ++r) {
+                        if (8 * (r >> 2) + (r & 3) > lim) s[8 * run + r] = -INFINITY;
+                        asm("" : "+v"(lim));                        // see the 256-row kernel
+                    }
+                }
             }
         } else if (__builtin_amdgcn_ballot_w64(this_tok > q_lo) != 0) {
 #pragma unroll
@@ -224,12 +251,16 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
         }
+        if (next) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");  // V of this tile; K of the next may be on the way
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
         for (int t4 = 0; t4 < 2; ++t4)
 #pragma unroll
             for (int dt = 0; dt < 4; ++dt)
-                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_v(slot, t4, dt), pf[t4], o[dt], 0, 0, 0);
-        slot = next_slot;
+                o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_v(t4, dt), pf[t4], o[dt], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (next) copy(vp, false);
+        go = next;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // no copy is in flight when the slots are written below
 
@@ -248,7 +279,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a) {
             u32x4 w;
 #pragma unroll
             for (int e = 0; e < 4; ++e) w[e] = __float_as_uint(o[dt][4 * gg + e]);
-            *LDS_PTR(u32x4, slot0 + l32 * 512 + chunk * 16) = w;
+            *LDS_PTR(u32x4, k_slot + l32 * 512 + chunk * 16) = w;
         }
     __syncthreads();
     uint16_t* ob = a.out + bb * a.os0 + h * a.os1;
@@ -287,7 +318,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a) {
 
 template <int MODE, int W>
 hipError_t launch(const ArgsB& a, unsigned grid, hipStream_t st) {
-    constexpr int smem = W * 2 * kSlotBytes + 2 * W * 32 * 4;
+    constexpr int smem = W * 2 * kSlotBytes + kRowsTQ * 256 + 2 * W * 32 * 4;
     const hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_rows_kernel<MODE, W>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((attn_bf16_rows_kernel<MODE, W>), dim3(grid), dim3(64 * W), smem, st, a);
@@ -299,7 +330,7 @@ hipError_t launch(const ArgsB& a, unsigned grid, hipStream_t st) {
 template <int W>
 static hipError_t launch_waves(const Shape& sh, const ArgsB& a, unsigned grid, hipStream_t st) {
     if (!a.idx) return launch<2, W>(a, grid, st);
-    return sh.b % 32 == 0 ? launch<1, W>(a, grid, st) : launch<0, W>(a, grid, st);
+    return sh.b % 16 == 0 ? launch<1, W>(a, grid, st) : launch<0, W>(a, grid, st);
 }
 
 // Row tiles that exist: a segment's last tile may be short.
@@ -310,37 +341,42 @@ static long long row_tiles(const Shape& sh, bool sparse, int rows) {
 
 static long long listed_keys(const Shape& sh) { return std::min((long long)sh.n, (long long)sh.list_len * sh.b); }
 
-// Few query rows: 256 of them to a workgroup leave compute units idle, 32 do not.  The lines lie where the two kernels meet (256-row against
-// 32-row kernel).
-//   block-sparse, blocks of 64 or 16: 16384 rows: 32 heads x 512 20.4 / 13.9 to 22.6 / 15.4 us, 8 x 2048 25.7 / 21.1 to 55 / 35, 1 x 16K
-//   26.3 / 22.3 to 69 / 56; 24576 rows: 26.5 / 26.7 and 26.9 / 25.5, 26.1 / 30.2 to 69 / 59, 27.6 / 33.7 to 72 / 85.
-//   dense, 32768 rows: 32 x 1024 30.9 / 30.5, 8 x 4096 98 / 86, 1 x 32K 722 / 590; 40960 rows: 37 / 40, 123 / 126, 903 / 938.
-// Two 32-row workgroups fit a compute unit, and segments that are no multiple of 32 rows make more of them out of 16384 rows than the 512
-// that fit the chip.  A second round costs as much as the first where all lists are as long, and more than the 256-row kernel takes
-// where they are short: 16384 x 1 head, segments of 240 (552 workgroups), 6 blocks of 48 24.0 / 30.4, 10 of 40 27.4 / 33.7, 20 of
-// 24 29.0 / 34.4, 40 of 48 67 / 62; 290 x 56 (616) 16.2 / 18.5; but 680 x 24 (552) 23.0 / 18.5, 2720 x 6 (546), 40 of 48 65 / 42; up
-// to 540 workgroups (a short last tile per head) the 32-row kernel is never slower.  Segments of 48: more than 256 workgroups of
-// 256 rows, 46 / 30.
+// Few query rows: 256 of them to a workgroup leave compute units idle, 32 do not; where 256 fill the chip that kernel reads the keys once for eight
+// row tiles and takes two thirds of the time.  The lines lie where the two kernels meet (us, 256-row / 32-row kernel; t: row tiles of 32).
+//   block-sparse, up to t = 540 always: 32 heads x 500 17.6 / 12.1, 1 x 16K (960, 2624, 4672 keys) 28 / 20, 65 / 40, 112 / 61.
+//   t = 576 to 657, keys few beside the sequence lose: 1 x 19000 (800, 1312 keys) 26.1 / 28.2, 38 / 37, 2 x 9500 27.8 / 30.1 (960), 37.8 / 35.1 (1312), but 4
+//   x 4700, 960 keys 27.9 / 24.4, 8 x 2300 27.3 / 21.2.
+//   t = 700 to 880: 8 x 3500, 960 keys 28.8 / 30.4, 1 x 24000 (1312) 39.1 / 40.0, 2 x 14000 (1312) 39.4 / 41.1, but 4 x 7000 (1312) 39.9 / 38.7, 8 x 3500 (2624) 65 / 50,
+//   2 x 14000 (2624) 67 / 64, 32 x 850 26.4 / 23.5.
+//   t = 1024: 8 x 4096 (960, 1312, 2624) 30 / 34, 40.2 / 39.3, 70 / 60, 4 x 8192 (2624) 72 / 67, 2 x 16384 (2624, 4672) 70 / 73, 119 / 115, 32 x 1000 30.2 / 27.7;
+//   t = 1500: 32 x 1500 32 / 41, 8 x 6000 (4672) 122 / 125.
+//   segments of 128 rows and less leave half of a 256-row workgroup empty, at any length: 32 heads x 8192, segments of 128 (416, 1184, 4256 keys) 143 /
+//   148, 302 / 266, 877 / 612, of 64 (592) 368 / 171; 4 x 9000 (416) 35 / 28; segments of 192 220 / 272.
+//   dense, 49152 rows: 32 x 1500 40 / 36, 8 x 6000 147 / 109, 4 x 12000 280 / 208; 65536 rows: 32 x 2000 53 / 57, 8 x 8192 205 / 192, 2 x 32768 745 /
+//   720; 32 x 1750 48.9 / 49.5; 96000 rows: 8 x 12000 323 / 389.
 bool attn_bf16_rows_better(const Shape& sh, bool sparse) {
     const long long rows = (long long)sh.batch * sh.hq * sh.n;
-    if (!sparse) return rows <= 32768;
-    if (rows > 16384) return false;
-    const long long keys = listed_keys(sh);
-    return row_tiles(sh, true, kRowsTQ) <= 540 || row_tiles(sh, true, 256) > 256 || keys >= 1536 || (keys >= 340 && sh.n <= 2 * keys);
+    if (!sparse) return rows <= 49152 || (rows <= 65536 && sh.n >= 4096);
+    const long long keys = listed_keys(sh), tiles = row_tiles(sh, true, kRowsTQ), wide = row_tiles(sh, true, 256);
+    if (tiles <= 540) return true;
+    if (8 * wide >= 4 * tiles) return true;
+    if (8 * wide >= 2 * tiles) return tiles <= 1200 || keys >= 512;
+    if (tiles <= 660) return keys >= 1300 || sh.n <= 5 * keys;
+    if (tiles <= 900) return sh.n <= 2 * keys || (keys >= 1300 && sh.n <= 8 * keys);
+    return tiles <= 1024 && (5ll * sh.n <= 6 * keys || (keys >= 2400 && 2ll * sh.n <= 7 * keys));
 }
 
-// Eight waves where the workgroups are too few to give every compute unit two, and for dense rows of thousands of keys; four
-// otherwise, two workgroups to a unit.  Eight against four waves: block-sparse, 8 heads x 1024 tokens 13.6 / 14.4 us (blocks of
-// 32) and 15.3 / 17.1 (64), 2 x 8192 58 / 54 and 26 / 22; more than 256 workgroups out of 8192 rows: 8192 x 1, segments of 240, 60 blocks of 40
-// 32 / 42, but 256 x 32 16.0 / 13.2; dense, one head x 16K 160 / 211, 2 x 8192 88 / 109, 2 x 16K 306 / 315, 8 x 2048 29 / 33, 8 x
-// 4096 91 / 86, 32 x 512 15.3 / 13.1.
+// Eight waves where the workgroups are too few to give every compute unit two, and for long rows of unequal length; four otherwise, two workgroups to
+// a unit.  Four against eight waves: block-sparse, t = 256 8 x 1000 13.3 / 10.7 us, 1 x 8192 (1312, 4672 keys) 18.6 / 13.9, 48 / 32; t = 375
+// 1 x 12000 (1312, 4672) 22.5 / 24.9, 52 / 56, 8 x 1500 (960, 1312) 15.2 / 17.5, 17.9 / 17.3, 4 x 3000 (2624) 30 / 25, 2 x 6000 (4672) 49 / 35; t = 500 8 x 2000
+// 18.5 / 22.1; dense, 32 x 256 6.4 / 6.8, 8 x 1000 12.0 / 10.2, 1 x 16K 140 / 99, 8 x 2000 21.5 / 19.9, 32 x 500 9.2 / 11.5, 8 x 3000 32 / 38.
 hipError_t launch_attn_bf16_rows(const Shape& sh, ArgsB a, hipStream_t st) {
     const int longest = a.idx ? std::min(sh.s, sh.n) : sh.n;          // a segment may be set longer than the sequence
     a.qtiles = (longest + kRowsTQ - 1) / kRowsTQ;
     const unsigned grid = (unsigned)((long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1));
-    const long long rows = (long long)sh.batch * sh.hq * sh.n;
-    const bool eight = a.idx ? rows <= 8192 && (row_tiles(sh, true, kRowsTQ) <= 270 || listed_keys(sh) >= 340)
-                             : rows <= 8192 || (sh.n >= 2048 && rows <= 16384) || sh.n >= 8192;
+    const long long tiles = row_tiles(sh, a.idx != nullptr, kRowsTQ), keys = listed_keys(sh);
+    const bool eight = a.idx ? tiles <= 270 || (tiles <= 400 && 10ll * sh.n <= 13 * keys)
+                             : (tiles <= 270 && sh.n >= 512) || (tiles <= 520 && sh.n >= 1024);
     return eight ? launch_waves<8>(sh, a, grid, st) : launch_waves<4>(sh, a, grid, st);
 }
 

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("b,s", [(64, 256), (128, 256), (192, 384), (32, 256), (96, 288)], ids=["b64", "b128", "b192", "b32", "b96"])
 def test_blocks_behind_the_count(b, s):
-    w, q, k, v = make(1, 20, 4, 1201, s, b, 5, 1)
+    w, q, k, v = make(1, 40, 4, 1201, s, b, 5, 1)                 # enough rows for the 256-row kernel
     idx, cnt = lists(w, w.n_q_heads)
     ref, ref_cnt = idx.copy(), cnt.copy()
     for h in range(w.n_q_heads):
@@ -22,14 +22,14 @@ def test_blocks_behind_the_count(b, s):
             ref_cnt[0, h, j] = keep
             idx[0, h, j, keep:] = (h + np.arange(idx.shape[3] - keep)) % max(1, j * w.blocks_per_segment)    # blocks that the rows would see
     out, lse = H.gpu_sparse(w, *dev(q, k, v, idx, ref_cnt))
-    todo = [(0, h, j) for h in (0, 1, 2, 3, 4, 19) for j in range(w.n_segments)]
+    todo = [(0, h, j) for h in (0, 1, 2, 3, 4, 39) for j in range(w.n_segments)]
     check(w, out, lse, q, k, v, ref, ref_cnt, todo)
 
 
 @pytest.mark.parametrize("b", [32, 64])
 def test_lists_of_more_than_512_entries(b):
-    w, q, k, v = make(1, 1, 1, 520 * b + 64, 512, b, 515, 1)
-    idx, cnt = lists(w, 1)
+    w, q, k, v = make(1, 2 if b == 32 else 1, 1, 520 * b + 64, 512, b, 515, 1)
+    idx, cnt = lists(w, w.n_q_heads)
     assert cnt.max() > 512
     out, lse = H.gpu_sparse(w, *dev(q, k, v, idx, cnt))
     check(w, out, lse, q, k, v, idx, cnt, [(0, 0, j) for j in (0, 1, w.n_segments - 2, w.n_segments - 1)])
