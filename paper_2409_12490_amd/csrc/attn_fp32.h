@@ -7,6 +7,26 @@ namespace cp {
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef const __attribute__((address_space(4))) int32_t* scalar_list;   // read through scalar loads: wave-uniform addresses
 
+namespace {
+
+// Eight copies of 16 bytes per lane from memory (one base) to LDS at (lds_base + lane * 16) + 1 KiB * i: see the bf16 kernels.  A load needs one wait
+// state after m0 and five after a vector instruction that writes its scalar address, which the compiler does not see in here.  One block of
+// eight instead of a base, m0 and waits for each: dense 8 x 8192 583 -> 574 us, block-sparse 8 x 8192 (704 keys) 134 -> 127, 4 x 4096 42.4 -> 41.4.
+__device__ __forceinline__ void copy16x8(const void* sbase, const unsigned (&voff)[8], unsigned lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %9\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %9\n\t"
+                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %9\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %9\n\t"
+                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %5, %9\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %6, %9\n\t"
+                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %7, %9\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %8, %9"
+                 ::"s"(lds_base), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "v"(voff[4]), "v"(voff[5]), "v"(voff[6]), "v"(voff[7]), "s"(sbase)
+                 : "memory", "scc");
+}
+// one, from an address per lane
+__device__ __forceinline__ void copy16_far(const void* src, unsigned lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(src) : "memory");
+}
+
+}  // namespace
+
 struct Args32 {
     const float* q; const float* k; const float* v; const int32_t* idx; const int32_t* cnt;
     float* out; float* lse;

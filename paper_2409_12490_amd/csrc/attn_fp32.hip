@@ -46,7 +46,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
     constexpr int TQ = 16 * RT, TK = 16;
     constexpr int kNoToken = 0x7fffffff;                            // a key that does not exist: after every query
     const bool dense = MODE == 2 || (MODE == 0 && !a.idx);
-    __shared__ __attribute__((aligned(16))) float part_o[W * TQ * kHeadDim];   // 16-byte chunks XOR-swizzled by the row
+    __shared__ __attribute__((aligned(1024))) float part_o[W * TQ * kHeadDim];   // 16-byte chunks XOR-swizzled by the row
     __shared__ float part_m[W * TQ], part_l[W * TQ];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -74,12 +74,27 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
         count = min(max(((scalar_list)(unsigned long long)a.cnt)[lrow], 0), a.list_len);
     }
     f32x4 qf[RT][8];
+    // MODE 1/2: Q comes by whole rows to LDS, once per workgroup, 16-byte chunks XOR-swizzled by the row, and into registers from there: a lane per row
+    // straight from memory, by every wave for itself, asks the address unit for 512 * W pieces of 16 bytes, one a cycle.  One head x 2048
+    // tokens, block-sparse (384 keys) 12.1 -> 11.6 us, dense 42.2 -> 40.6, x 512 dense 14.1 -> 13.1.  (K and V the same way, with a tile of
+    // each in LDS, 14.8: with one wave to a SIMD the way through LDS costs more than the address unit did.)
+    const unsigned lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)part_o;
+    if (RUN) {
+        static_assert(!RUN || RT == 1, "16 rows of Q take the place of the first partial O");
+        const int l32 = lane & 31, hh = lane >> 5;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        const int row = q_lo + 16 * rt + c16;
-        const float* src = a.q + bb * a.qs0 + h * a.qs1 + (long long)min(row, q_last) * a.qs2 + 4 * g;
+        for (int x = 0; x < 8 / W; ++x) {
+            const int i = wave * (8 / W) + x;
+            copy16_far((const char*)(a.q + bb * a.qs0 + h * a.qs1 + (long long)min(q_lo + 2 * i + hh, q_last) * a.qs2) + (((unsigned)(l32 ^ hh) << 4) ^ (32 * i)), lds + i * 1024);
+        }
+    } else {
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) qf[rt][kk] = *(const f32x4*)(src + 16 * kk);
+        for (int rt = 0; rt < RT; ++rt) {
+            const int row = q_lo + 16 * rt + c16;
+            const float* src = a.q + bb * a.qs0 + h * a.qs1 + (long long)min(row, q_last) * a.qs2 + 4 * g;
+#pragma unroll
+            for (int kk = 0; kk < 8; ++kk) qf[rt][kk] = *(const f32x4*)(src + 16 * kk);
+        }
     }
     // positions 0 .. total-1 of the listed blocks laid end to end (host checks list_len * b < 2^31)
     const unsigned total = dense ? (unsigned)q_last + 1u : (unsigned)count * (unsigned)a.b;
@@ -159,7 +174,13 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
     }
 
     int base = -1, tok = kNoToken;
-    if (RUN) { base = next_base(wave); load_k_run(base); }
+    if (RUN) {
+        base = next_base(wave); load_k_run(base);
+        asm volatile("s_waitcnt vmcnt(8)" ::: "memory");            // the wave's share of Q has landed; K is younger
+        __syncthreads();
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) qf[0][kk] = *(__attribute__((address_space(3))) const f32x4*)(uintptr_t)(lds + c16 * 512 + (((4 * kk + g) ^ c16) << 4));
+    }
     else { tok = key_token(wave); load_k_token(tok); }
     // ascending lists: nothing is visible from the tile on whose first token is past the last row
     auto more = [&](int t) -> bool {
@@ -250,6 +271,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
         base = nbase;
     }
 
+    if (RUN) __syncthreads();                                       // everybody has read Q
     // ---- merge the W partial results: out = sum_w 2^(m_w - M) O_w / sum_w 2^(m_w - M) l_w ----------------------
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {

@@ -89,14 +89,6 @@ __device__ __forceinline__ bool fit(float most, int least, int max, int& e, floa
     low = fminf(low, most > 0.f ? most : INFINITY);
     return __ballot(low * pow2(e) < kBottom) == 0;
 }
-// 16 bytes per lane from memory to LDS at (lds_base + lane * 16): see the bf16 kernels.  The load needs one wait state after m0 and five after
-// a vector instruction that writes its scalar address, which the compiler does not see in here.
-__device__ __forceinline__ void copy16(const void* sbase, unsigned voff, unsigned lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(voff), "s"(sbase) : "memory");
-}
-__device__ __forceinline__ void copy16_far(const void* src, unsigned lds_base) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(src) : "memory");
-}
 __device__ __forceinline__ float half_max(float x) {                // over lanes l and l ^ 32
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
@@ -171,6 +163,9 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
     // the wave's K tile by copies of two rows each, the lane's 16 bytes being chunk (lane & 31) ^ (row & 15) of its row
     const unsigned k_tile = k_tile0 + wave * (TK * 512);
     const unsigned k_chunk = (unsigned)(l32 ^ hh) << 4, k_row = hh * row_bytes;
+    unsigned run_off[8];                                            // byte offsets of the lane's pieces of a run
+#pragma unroll
+    for (int i = 0; i < 8; ++i) run_off[i] = (unsigned)(2 * i) * row_bytes + k_row + (k_chunk ^ (32 * i));
     auto copy_k = [&](int b0, int b1) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // the reads of the tile before are done
 #pragma unroll
@@ -178,9 +173,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
             const int base = run ? b1 : b0;
             if (base >= 0 && base + 16 <= a.n) {
                 const char* rows = (const char*)(kp + (long long)base * a.ks2);
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    copy16((const void*)(rows + (unsigned long long)(2 * i) * row_bytes), k_row + (k_chunk ^ (32 * i)), k_tile + run * 8192 + i * 1024);
+                copy16x8(rows, run_off, k_tile + run * 8192);
             } else {                                                // rows without a token copy an existing one, masked later
 #pragma unroll
                 for (int i = 0; i < 8; ++i) {
