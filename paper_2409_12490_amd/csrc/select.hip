@@ -6,7 +6,8 @@
 // by an MSB-first radix search (one wave-wide count per bit: a compare per key, the lane masks counted on the
 // scalar unit) that stops at the first bit whose count is exactly k; everything above it is taken, ties at
 // the threshold go to the smallest indices, and the result is compacted in index order, so the
-// list comes out ascending.  Long rows are first thinned to the few keys that can be among the k largest.
+// list comes out ascending.  Long rows are first thinned to the few keys that can be among the k largest; the longest are
+// not held in registers but read twice.
 #include "kernels.h"
 
 namespace cp {
@@ -146,6 +147,34 @@ __device__ __forceinline__ int select_row(const SelectArgs& a, long long row, in
     return take_largest<PER_LANE>(key, thr, kj, (n_cand + 63) / 64, lane, out, [&](int m) { return m * 64 + lane; });
 }
 
+// The group's scores of a list's first n blocks, merged by max, to LDS, by the whole workgroup: several loads of a head's row in flight
+__device__ __forceinline__ void merge_group(const SelectArgs& a, long long row, int j, int n, uint32_t* merged) {
+    const float* src = a.scores + ((row / a.n1 * a.group) * a.n1 + j) * a.n2;
+    const long long step = (long long)a.n1 * a.n2;             // to the next head's row
+    for (int i = threadIdx.x; i < n; i += 256) {
+        uint32_t kx = 0;
+        int g2 = 0;
+        for (; g2 + 4 <= a.group; g2 += 4) {
+            float x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = src[(g2 + u) * step + i];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) kx = max(kx, ordered_key(x[u]));
+        }
+        for (; g2 < a.group; ++g2) kx = max(kx, ordered_key(src[g2 * step + i]));
+        merged[i] = kx;
+    }
+}
+
+// behind the `written` chosen blocks: the local blocks, then the segment's own, then -1
+__device__ __forceinline__ void finish_row(const SelectArgs& a, long long row, int n_cand, int diag_hi, int written, int lane, int32_t* out) {
+    const int fixed = diag_hi - n_cand;
+    for (int x = lane; x < fixed; x += 64) out[written + x] = n_cand + x;
+    const int total = written + fixed;
+    for (int x = total + lane; x < a.list_len; x += 64) out[x] = -1;
+    if (lane == 0) a.cnt[row] = total;
+}
+
 // SHARED: a workgroup per list: its four waves merge the scores of the group's query heads into LDS,
 // several loads of a head's row in flight, then one of them searches.  With one wave per list, its loads head after head,
 // 32 query heads x 128K tokens in blocks of 64 took 44 us for 8 KV heads and 71 us for 4; now 15 and 14 (67 MB of scores).
@@ -167,21 +196,7 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
     uint2* cand = cand_all[SHARED ? 0 : threadIdx.x >> 6];
     __shared__ uint32_t merged[SHARED ? 64 * MAX_PER_LANE : 1];
     if (SHARED) {                                              // the whole workgroup merges the group's scores, one wave searches
-        const float* src = a.scores + ((row / a.n1 * a.group) * a.n1 + j) * a.n2;
-        const long long step = (long long)a.n1 * a.n2;         // to the next head's row
-        for (int i = threadIdx.x; i < n_cand && kj > 0; i += 256) {
-            uint32_t kx = 0;
-            int g2 = 0;
-            for (; g2 + 4 <= a.group; g2 += 4) {
-                float x[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) x[u] = src[(g2 + u) * step + i];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) kx = max(kx, ordered_key(x[u]));
-            }
-            for (; g2 < a.group; ++g2) kx = max(kx, ordered_key(src[g2 * step + i]));
-            merged[i] = kx;
-        }
+        merge_group(a, row, j, kj > 0 ? n_cand : 0, merged);
         __syncthreads();
         if (threadIdx.x >= 64) return;
     }
@@ -201,16 +216,11 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
             default: written = select_row<8 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
         }
     }
-    // local blocks then the segment's own blocks
-    const int fixed = diag_hi - n_cand;
-    for (int x = lane; x < fixed; x += 64) out[written + x] = n_cand + x;
-    const int total = written + fixed;
-    for (int x = total + lane; x < a.list_len; x += 64) out[x] = -1;
-    if (lane == 0) a.cnt[row] = total;
+    finish_row(a, row, n_cand, diag_hi, written, lane, out);
 }
 
 
-// Rows longer than 4096 blocks: one 256-thread workgroup per row, thread t owns blocks t, t+256, ...; the same
+// Rows longer than 4096 blocks, k > kStreamMaxK: one 256-thread workgroup per row, thread t owns blocks t, t+256, ...; the same
 // radix search with the wave counts added up through LDS, and a compaction whose prefix runs over the four waves.
 constexpr int kWideThreads = 256, kWidePerThread = 32;       // 8192 blocks
 template <bool SHARED>
@@ -293,7 +303,205 @@ __global__ __launch_bounds__(kWideThreads) void select_wide_kernel(SelectArgs a)
     if (tid == 0) a.cnt[row] = total;
 }
 
+// ---------------------------------------------------------------------------------------------
+// Long rows: the same search, the row streamed instead of held in registers.
+//
+// A wave reads its row twice, 16 bytes to a lane and load.  First pass: the maxima of 64 * NB buckets (lane, load mod NB/4, key of the
+// load); their k-th largest, T, has at least k keys at or above it.  Second pass: the keys >= T, in index order, to the wave's LDS
+// region, where the exact search runs on at most 2 * NB of them per lane.  With k at most half of the buckets they fit unless many
+// scores are equal or the large ones share few buckets.  Then those above T are tried (many scores of 0: fewer than k are left, and T is
+// the k-th largest), and at last the row is searched where it lies, pass after pass from the L2 cache.
+//
+// Bound by the vector unit (about 25 instructions per four keys in both passes) and, for few rows, by the latency of the loads.  In
+// registers a row of 4096 blocks holds 64 keys per lane: few waves to a SIMD, and a count or a compaction step for every one of them.
+// Per-head lists of 32 heads, in registers / streamed: 128K tokens in blocks of 32, k = 64, 78 / 45 us (with many zeros 186 / 52), k = 128 79 / 46;
+// in blocks of 16 (a workgroup per row, a barrier per bit), k = 128, 136 / 62, k = 256 136 / 69; 94505 tokens, segments of 128, 78 / 55.
+// Shared lists of 4 KV heads 36 / 25 (blocks of 32), 8 KV heads 134 / 50 (16).
+// Eight loads in flight: 65 instead of 62 and 61 instead of 55 us.
+// ---------------------------------------------------------------------------------------------
+constexpr int kStreamAhead = 4;                         // loads in flight
+constexpr int kStreamMaxK = 256;                        // the largest k that is streamed
+typedef __attribute__((ext_vector_type(4), aligned(4))) float f32x4_row;    // four scores of a row, which starts anywhere
+
+// f(u, i, key) for every four keys of the lane, in index order, until it returns false (the same for the whole wave): key[e] belongs
+// to block i + e, and is 0 past the candidates; u numbers the loads in flight
+template <bool SHARED, typename F>
+__device__ __forceinline__ void for_keys(const float* src, const uint32_t* merged, int n2, int n_cand, int lane, F f) {
+    for (int c0 = 0; c0 < n_cand; c0 += 256 * kStreamAhead) {
+        uint32_t key[kStreamAhead][4];
+        int at[kStreamAhead];
+#pragma unroll
+        for (int u = 0; u < kStreamAhead; ++u) {
+            at[u] = min(c0 + 256 * u + 4 * lane, SHARED ? (n2 + 3) / 4 * 4 - 4 : n2 - 4);   // the last four of the row, if it ends before
+            if (SHARED) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) key[u][e] = merged[at[u] + e];
+            } else {
+                const f32x4_row x = *(const f32x4_row*)(src + at[u]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) key[u][e] = __float_as_uint(x[e]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kStreamAhead; ++u) {
+            const int i = c0 + 256 * u + 4 * lane;
+            if (c0 + 256 * u >= n_cand) break;          // wave-uniform
+            if (!SHARED) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) key[u][e] = ordered_key(__uint_as_float(key[u][e]));
+            }
+            if (c0 + 256 * u + 256 > n_cand) {          // keys below i are another lane's
+#pragma unroll
+                for (int e = 0; e < 4; ++e) key[u][e] = at[u] + e >= i && at[u] + e < n_cand ? key[u][e] : 0u;
+            }
+            if (!f(u, at[u], key[u])) return;
+        }
+    }
+}
+
+// Appends, in index order, what `in` says of the wave's 256 keys; put(position, e) stores one.  Returns how many.
+template <typename Put>
+__device__ __forceinline__ int append(const bool (&in)[4], Put put) {
+    int before = 0, all = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const unsigned long long mask = __ballot(in[e]);
+        before = __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, before));
+        all += (int)__popcll(mask);
+    }
+    if (all == 0) return 0;                             // wave-uniform
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (in[e]) put(before++, e);
+    return all;
+}
+
+// The kj largest of the `total` <= 64 * N keys in the wave's LDS region, which hold them
+template <int N>
+__device__ __forceinline__ int search_candidates(const uint2* cand, int total, int kj, int lane, int32_t* out) {
+    uint32_t key[N]; int at[N];
+#pragma unroll
+    for (int c = 0; c < N; ++c) {
+        const uint2 e = cand[c * 64 + lane];
+        key[c] = c * 64 + lane < total ? e.x : 0u; at[c] = (int)e.y;
+    }
+    const uint32_t thr = kth_largest<N>(key, kj);
+    return take_largest<N>(key, thr, kj, (total + 63) / 64, lane, out, [&](int c) { return at[c]; });
+}
+
+template <int NB, bool SHARED>
+__device__ __forceinline__ int select_streamed(const float* src, const uint32_t* merged, int n2, int n_cand, int kj, int lane,
+                                               int32_t* out, uint2* cand) {
+    constexpr int kRoom = 2 * 64 * NB;
+    uint32_t top[NB];
+#pragma unroll
+    for (int x = 0; x < NB; ++x) top[x] = 0u;
+    for_keys<SHARED>(src, merged, n2, n_cand, lane, [&](int u, int, const uint32_t (&key)[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) top[u % (NB / 4) * 4 + e] = max(top[u % (NB / 4) * 4 + e], key[e]);
+        return true;
+    });
+    const uint32_t T = kth_largest<NB>(top, kj);
+    uint32_t largest = 0u;
+#pragma unroll
+    for (int x = 0; x < NB; ++x) largest = max(largest, top[x]);
+    for (int o = 32; o > 0; o >>= 1) largest = max(largest, (uint32_t)__shfl_xor((int)largest, o));
+    auto count = [&](uint32_t a, uint32_t b, uint32_t c, int (&n)[3]) {      // keys >= a, b, c; none of them 0
+        n[0] = n[1] = n[2] = 0;
+        for_keys<SHARED>(src, merged, n2, n_cand, lane, [&](int, int, const uint32_t (&key)[4]) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                n[0] += (int)__popcll(__ballot(key[e] >= a));
+                n[1] += (int)__popcll(__ballot(key[e] >= b));
+                n[2] += (int)__popcll(__ballot(key[e] >= c));
+            }
+            return true;
+        });
+    };
+    int n[3] = {0, 0, 0};
+    uint32_t least = max(T, 1u), thr = T;
+    for (int tries = 0; tries < 2; ++tries) {
+        int total = 0;
+        for_keys<SHARED>(src, merged, n2, n_cand, lane, [&](int, int i, const uint32_t (&key)[4]) {
+            bool in[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) in[e] = key[e] >= least;
+            const int base = total;
+            total += append(in, [&](int pos, int e) { if (base + pos < kRoom) cand[base + pos] = make_uint2(key[e], (unsigned)(i + e)); });
+            return total <= kRoom;
+        });
+        if (total <= kRoom) {                           // wave-uniform
+            // the wave reads back what its own lanes wrote: LDS operations of a wave complete in order
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            return total <= 64 * NB ? search_candidates<NB>(cand, total, kj, lane, out) : search_candidates<2 * NB>(cand, total, kj, lane, out);
+        }
+        // Too many.  Without those equal to T they may fit; if fewer than k are left then, the k-th largest is T itself
+        if (T != largest && tries == 0) count(T + 1, T + 1, T + 1, n);
+        if (n[0] < kj || n[0] > kRoom) break;
+        least = T + 1;
+    }
+    if (n[0] >= kj) {                                   // two bits of the k-th largest per pass, from the highest that T, below it, and the largest differ in
+        int bit = (31 - __clz(T ^ largest)) | 1;        // of the pair
+        thr = (largest >> bit >> 1) << bit << 1;
+        for (; bit > 0; bit -= 2) {
+            const uint32_t one = 1u << (bit - 1);
+            count(thr + one, thr + 2 * one, thr + 3 * one, n);
+            const int digit = n[2] >= kj ? 3 : n[1] >= kj ? 2 : n[0] >= kj ? 1 : 0;
+            thr += digit * one;
+            if (digit > 0 && n[digit - 1] == kj) break; // exactly the list
+        }
+        n[0] = 0;
+        if (thr != largest) count(thr + 1, thr + 1, thr + 1, n);
+    }
+    int ties_left = kj - n[0], written = 0;             // n[0]: keys above thr
+    for_keys<SHARED>(src, merged, n2, n_cand, lane, [&](int, int i, const uint32_t (&key)[4]) {
+        bool in[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) in[e] = key[e] > thr;
+        if (ties_left > 0) {                            // wave-uniform
+            bool tie[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) tie[e] = key[e] == thr && key[e] != 0u;
+            const int ties = append(tie, [&](int pos, int e) { in[e] = pos < ties_left; });
+            ties_left -= min(ties_left, ties);
+        }
+        const int base = written;
+        written += append(in, [&](int pos, int e) { out[base + pos] = i + e; });
+        return written < kj;
+    });
+    return written;
+}
+
+// PER_LANE: 64 * PER_LANE >= n2 (SHARED: the merged scores in LDS)
+template <int NB, bool SHARED, int PER_LANE>
+__global__ __launch_bounds__(256) void select_stream_kernel(SelectArgs a) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const long long row = SHARED ? (long long)blockIdx.x : (long long)blockIdx.x * 4 + wave;
+    if (row >= a.rows) return;
+    const int j = (int)(row % a.n1);
+    const int diag_lo = j * a.r, diag_hi = min(a.n2, diag_lo + a.r);
+    const int n_cand = diag_lo - min(a.local, diag_lo), kj = min(a.budget, n_cand);
+    int32_t* out = a.idx + row * a.list_len;
+    __shared__ uint2 cand_all[SHARED ? 1 : 4][2 * 64 * NB];
+    __shared__ uint32_t merged[SHARED ? 64 * PER_LANE : 1];
+    if (SHARED) {
+        merge_group(a, row, j, kj > 0 ? n_cand : 0, merged);
+        __syncthreads();
+        if (threadIdx.x >= 64) return;
+    }
+    int written = 0;
+    if (kj > 0) written = select_streamed<NB, SHARED>(a.scores + row * a.n2, merged, a.n2, n_cand, kj, lane, out, cand_all[SHARED ? 0 : wave]);
+    finish_row(a, row, n_cand, diag_hi, written, lane, out);
+}
+
 }  // namespace
+
+template <bool SHARED, int PER_LANE>
+static hipError_t launch_stream(const SelectArgs& a, unsigned grid, hipStream_t st) {
+    if (a.budget <= 128) hipLaunchKernelGGL((select_stream_kernel<4, SHARED, PER_LANE>), dim3(grid), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((select_stream_kernel<8, SHARED, PER_LANE>), dim3(grid), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
 
 template <bool SHARED>
 hipError_t launch_select_impl(const Shape& sh, const float* scores, int32_t* idx, int32_t* cnt, hipStream_t st) {
@@ -303,9 +511,14 @@ hipError_t launch_select_impl(const Shape& sh, const float* scores, int32_t* idx
     a.group = sh.hq / sh.hkv;
     a.n1 = sh.n1; a.n2 = sh.n2; a.r = sh.r; a.budget = sh.budget; a.local = sh.local; a.list_len = sh.list_len;
     const unsigned grid = (unsigned)(SHARED ? a.rows : (a.rows + 3) / 4);
+    // Streamed: rows of more than 2048 blocks.  Up to there a wave holds its row without losing the company of others (per-head lists in
+    // registers / streamed, 32 heads x 128K tokens in blocks of 64: 18.8 / 24.2 us; shared ones 17.4 / 16.1, but 20000 tokens in blocks of 16
+    // 9.6 / 10.3).  k above 256 would need 1024 buckets (k = 300 of 2063 blocks: 34 / 34 us, with many zeros 43 / 67).
     if (sh.n2 <= 64 * 8) hipLaunchKernelGGL((select_kernel<8, SHARED>), dim3(grid), dim3(256), 0, st, a);
     else if (sh.n2 <= 64 * 32) hipLaunchKernelGGL((select_kernel<32, SHARED>), dim3(grid), dim3(256), 0, st, a);
-    else if (sh.n2 <= 64 * 64) hipLaunchKernelGGL((select_kernel<64, SHARED>), dim3(grid), dim3(256), 0, st, a);
+    else if (sh.budget <= kStreamMaxK) {
+        return sh.n2 <= 64 * 64 ? launch_stream<SHARED, 64>(a, grid, st) : launch_stream<SHARED, 128>(a, grid, st);
+    } else if (sh.n2 <= 64 * 64) hipLaunchKernelGGL((select_kernel<64, SHARED>), dim3(grid), dim3(256), 0, st, a);
     else {
         if (a.rows > 0x7fffffffLL || sh.n2 > kWideThreads * kWidePerThread) return hipErrorInvalidValue;
         hipLaunchKernelGGL(select_wide_kernel<SHARED>, dim3((unsigned)a.rows), dim3(kWideThreads), 0, st, a);
@@ -313,11 +526,11 @@ hipError_t launch_select_impl(const Shape& sh, const float* scores, int32_t* idx
     return hipGetLastError();
 }
 
-// A KV head with one query head has that head's list: the per-head kernel, four rows to a workgroup, unless the lists are long and so few that
-// a workgroup each fits the chip twice (128K tokens in blocks of 32, a workgroup / a wave per list: 256 lists 13 / 17 us, 512 14 /
-// 17, 2048 34 / 25, 8192 129 / 83; in blocks of 64: 256 lists 8.7 / 7.8, 8192 42 / 20).
+// A KV head with one query head has that head's list: the per-head kernel, four rows to a workgroup, unless the rows are held in registers, long and
+// so few that a workgroup each fits the chip twice (128K tokens in blocks of 32, k > 256, a workgroup / a wave per list: 256 lists 13 / 17 us,
+// 512 14 / 17, 2048 34 / 25, 8192 129 / 83).  Streamed, a wave per list is the faster one there too (512 lists 14 / 12).
 hipError_t launch_select(const Shape& sh, const float* scores, int32_t* idx, int32_t* cnt, bool shared, hipStream_t st) {
-    const bool few = sh.n2 > 64 * 32 && sh.n2 <= 64 * 64 && (long long)sh.batch * sh.hkv * sh.n1 <= 512;
+    const bool few = sh.budget > kStreamMaxK && sh.n2 > 64 * 32 && sh.n2 <= 64 * 64 && (long long)sh.batch * sh.hkv * sh.n1 <= 512;
     return shared && (sh.hq != sh.hkv || few) ? launch_select_impl<true>(sh, scores, idx, cnt, st)
                                               : launch_select_impl<false>(sh, scores, idx, cnt, st);
 }
