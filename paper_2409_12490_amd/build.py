@@ -9,7 +9,7 @@ from concurrent.futures import ThreadPoolExecutor
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libcritiprefill.so")
-SOURCES = ["api.hip", "estimate.hip", "select.hip", "attn_fp32.hip", "attn_fp32_split.hip", "attn_bf16.hip", "attn_bf16_rows.hip"]
+SOURCES = ["api.hip", "estimate.hip", "select.hip", "attn_fp32.hip", "attn_fp32_split.hip", "attn_bf16.hip", "attn_bf16_rows.hip", "attn_bf16_half.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
@@ -17,7 +17,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # operands that only MFMA touches live in AGPRs), and fmaxf needs no NaN-quieting pre-pass (the kernel
 # never produces NaN: masked logits are -inf and the running max is guarded).
 _BF16_ATTN = ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-fno-honor-nans", "-mno-amdgpu-ieee"]
-EXTRA = {"attn_bf16.hip": _BF16_ATTN, "attn_bf16_rows.hip": _BF16_ATTN}
+EXTRA = {"attn_bf16.hip": _BF16_ATTN, "attn_bf16_rows.hip": _BF16_ATTN, "attn_bf16_half.hip": _BF16_ATTN}
 
 
 def _compile(src: str, objdir: str) -> str:

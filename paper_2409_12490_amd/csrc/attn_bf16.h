@@ -1,4 +1,4 @@
-// What the two bf16 attention kernels share: vector types, argument block, lane exchanges, the copy from memory to LDS.
+// What the three bf16 attention kernels share: vector types, argument block, lane exchanges, the copy from memory to LDS.
 #pragma once
 #include "kernels.h"
 
@@ -11,7 +11,7 @@ struct ArgsB {
     int group;                            // G = hq / hkv
     int shared_lists;                     // lists are per (batch, KV head, segment) instead of per query head
     float scale_log2e, scale;
-    FastDiv div_order[3], div_group, div_hkv, div_b;   // 256-row kernel: see its workgroup order; G; hkv; b
+    FastDiv div_order[3], div_group, div_hkv, div_b;   // 256-row and 128-row kernel: see the workgroup order; G; hkv; b
     long long qs0, qs1, qs2, ks0, ks1, ks2, os0, os1, os2;
 };
 
@@ -93,8 +93,15 @@ __device__ __forceinline__ float half_sum(float x) {
 
 }  // namespace
 
-// Attention with 32-row workgroups whose waves split the keys, and whether it is the better one here.
+// Workgroups of `rows` query rows that a launch needs: a segment's last one may be short.
+long long attn_bf16_row_tiles(const Shape& sh, bool sparse, int rows);
+
+// Attention with 32-row workgroups whose waves split the keys, and whether it is better here than 256-row workgroups.
 bool attn_bf16_rows_better(const Shape& sh, bool sparse);
 hipError_t launch_attn_bf16_rows(const Shape& sh, ArgsB a, hipStream_t st);
+
+// Attention over lists with 128-row workgroups, two to a compute unit, and whether it is better here than either.
+bool attn_bf16_half_better(const Shape& sh);
+hipError_t launch_attn_bf16_half(const Shape& sh, ArgsB a, hipStream_t st);
 
 }  // namespace cp

@@ -709,6 +709,7 @@ hipError_t launch_attn_bf16(const Shape& sh, const void* q, const void* k, const
     a.ks0 = sh.kvs[0]; a.ks1 = sh.kvs[1]; a.ks2 = sh.kvs[2];
     a.os0 = sh.os[0]; a.os1 = sh.os[1]; a.os2 = sh.os[2];
     a.group = sh.hq / sh.hkv;
+    if (idx && attn_bf16_half_better(sh)) return launch_attn_bf16_half(sh, a, st);
     if (attn_bf16_rows_better(sh, idx != nullptr)) return launch_attn_bf16_rows(sh, a, st);
     const uint32_t bkv = (uint32_t)sh.batch * sh.hkv;
     a.div_group = FastDiv(a.group); a.div_hkv = FastDiv(sh.hkv); a.div_b = FastDiv(sh.b);

@@ -334,7 +334,7 @@ static hipError_t launch_waves(const Shape& sh, const ArgsB& a, unsigned grid, h
 }
 
 // Row tiles that exist: a segment's last tile may be short.
-static long long row_tiles(const Shape& sh, bool sparse, int rows) {
+long long attn_bf16_row_tiles(const Shape& sh, bool sparse, int rows) {
     const int s = sparse ? sh.s : sh.n, rest = sh.n % s;
     return (long long)sh.batch * sh.hq * ((long long)(sh.n / s) * ((s + rows - 1) / rows) + (rest + rows - 1) / rows);
 }
@@ -357,7 +357,7 @@ static long long listed_keys(const Shape& sh) { return std::min((long long)sh.n,
 bool attn_bf16_rows_better(const Shape& sh, bool sparse) {
     const long long rows = (long long)sh.batch * sh.hq * sh.n;
     if (!sparse) return rows <= 49152 || (rows <= 65536 && sh.n >= 4096);
-    const long long keys = listed_keys(sh), tiles = row_tiles(sh, true, kRowsTQ), wide = row_tiles(sh, true, 256);
+    const long long keys = listed_keys(sh), tiles = attn_bf16_row_tiles(sh, true, kRowsTQ), wide = attn_bf16_row_tiles(sh, true, 256);
     if (tiles <= 540) return true;
     if (8 * wide >= 4 * tiles) return true;
     if (8 * wide >= 2 * tiles) return tiles <= 1200 || keys >= 512;
@@ -374,7 +374,7 @@ hipError_t launch_attn_bf16_rows(const Shape& sh, ArgsB a, hipStream_t st) {
     const int longest = a.idx ? std::min(sh.s, sh.n) : sh.n;          // a segment may be set longer than the sequence
     a.qtiles = (longest + kRowsTQ - 1) / kRowsTQ;
     const unsigned grid = (unsigned)((long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1));
-    const long long tiles = row_tiles(sh, a.idx != nullptr, kRowsTQ), keys = listed_keys(sh);
+    const long long tiles = attn_bf16_row_tiles(sh, a.idx != nullptr, kRowsTQ), keys = listed_keys(sh);
     const bool eight = a.idx ? tiles <= 270 || (tiles <= 400 && 10ll * sh.n <= 13 * keys)
                              : (tiles <= 270 && sh.n >= 512) || (tiles <= 520 && sh.n >= 1024);
     return eight ? launch_waves<8>(sh, a, grid, st) : launch_waves<4>(sh, a, grid, st);
