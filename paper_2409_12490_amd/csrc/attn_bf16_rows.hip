@@ -1,5 +1,5 @@
-// bf16 MFMA flash attention for launches that cannot fill the chip with 256-row workgroups (attn_bf16.hip): few heads, short
-// sequences, short segments.  The same arithmetic (bf16 operands, fp32 sums, P rounded to bf16 and the row sum taken over the
+// bf16 MFMA flash attention for launches that cannot fill the chip with 256-row workgroups (attn_bf16.hip) or 128-row ones (attn_bf16_half.hip): few
+// heads, short sequences, segments of up to 64 rows.  The same arithmetic (bf16 operands, fp32 sums, P rounded to bf16 and the row sum taken over the
 // rounded values) in another split: a workgroup owns 32 query rows and its W waves split the KEYS.  Wave w takes tiles w, w + W, ...
 // of 32 keys, with a running max, sum and output of its own, and the W partial results are merged through LDS at the end.
 //
@@ -350,7 +350,8 @@ static long long listed_keys(const Shape& sh) { return std::min((long long)sh.n,
 //   2 x 14000 (2624) 67 / 64, 32 x 850 26.4 / 23.5.
 //   t = 1024: 8 x 4096 (960, 1312, 2624) 30 / 34, 40.2 / 39.3, 70 / 60, 4 x 8192 (2624) 72 / 67, 2 x 16384 (2624, 4672) 70 / 73, 119 / 115, 32 x 1000 30.2 / 27.7;
 //   t = 1500: 32 x 1500 32 / 41, 8 x 6000 (4672) 122 / 125.
-//   segments of 128 rows and less leave half of a 256-row workgroup empty, at any length: 32 heads x 8192, segments of 128 (416, 1184, 4256 keys) 143 /
+//   segments of 128 rows and less leave half of a 256-row workgroup empty, at any length (most of those of 65 to 128 rows are the 128-row kernel's, which is asked
+//   first, attn_bf16_half_better): 32 heads x 8192, segments of 128 (416, 1184, 4256 keys) 143 /
 //   148, 302 / 266, 877 / 612, of 64 (592) 368 / 171; 4 x 9000 (416) 35 / 28; segments of 192 220 / 272.
 //   dense, 49152 rows: 32 x 1500 40 / 36, 8 x 6000 147 / 109, 4 x 12000 280 / 208; 65536 rows: 32 x 2000 53 / 57, 8 x 8192 205 / 192, 2 x 32768 745 /
 //   720; 32 x 1750 48.9 / 49.5; 96000 rows: 8 x 12000 323 / 389.
