@@ -321,7 +321,7 @@ hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// 16 rows to a workgroup: what is left to this kernel are launches that 32 rows would not fill the chip with (attn_fp32_split_better).  Eight waves
+// 16 rows to a workgroup: what is left to this kernel are launches that 32 rows would not fill the chip with, or not evenly (attn_fp32_split_better).  Eight waves
 // split a long row further, four are better where rows are short.  Attention alone, us, four / eight waves (workgroups of 32 rows in brackets): dense 1 head
 // x 2048 tokens (64) 43 / 41; block-sparse 1 x 2048, 416 keys (64) 13.9 / 14.7.
 template <int MODE>

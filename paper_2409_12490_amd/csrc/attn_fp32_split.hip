@@ -1,33 +1,32 @@
 // fp32 attention on the 16-bit matrix instructions, for launches with enough query rows: the same walk over a block list (Algorithm 2) or all
-// keys (Eq. 2) as attn_fp32.hip, with every fp32 factor split into two fp16 values and three products of them in the place of one.
+// keys (Eq. 2) as attn_fp32.hip, with every fp32 factor split into three bf16 values and six products of them in the place of one.
 //
-//   x * 2^e = h + l + r    h = fp16(x * 2^e), l = fp16(x * 2^e - h), |r| <= 2^-24 |x * 2^e| or 2^-25: what fp32 itself rounds away
-//   x y 2^(e+f) = h_x h_y + h_x l_y + l_x h_y, products exact in fp32, sums in fp32; l_x l_y is left out (at most 2^-22, 2^-24 on average)
+//   x = h + m + l      h = bf16(x), m = bf16(x - h), l = x - h - m: all 24 bits, exactly, with fp32's own range of exponents
+//   x y = h_x h_y + (h_x m_y + m_x h_y) + m_x m_y + (h_x l_y + l_x h_y), products exact, sums in fp32; left out are m_x l_y + l_x m_y + l_x l_y, of
+//         either sign, at most 2^-24 of x y (2^-26.5 in the root mean square): half of what one rounding of the sum may be
 //
 // A workgroup owns 32 query rows of one segment (sparse) or of the sequence (dense); its W waves split the KEYS: wave w takes tiles w, w + W, ...
 // of 32 keys (two runs of 16 tokens), with a running reference, sum and output of its own, merged through LDS at the end.  Per wave and tile:
 //
 //   S^T[key][q]  = K . Q^T      32x32x16 MFMA.  K comes by global_load_lds as whole rows (a lane per row straight from memory costs the
 //                               address unit a request per lane and bound the kernel) into 16 KiB of LDS of the wave's own and is split
-//                               on its way to the MFMAs; Q is split once per workgroup and read from LDS
+//                               on its way to the MFMAs; Q is split once per workgroup: h and m in LDS, l in registers
 //   softmax                     one query per lane column
 //   O^T[ch][q]  += V^T . P^T    a lane holds 8 keys of one channel, loaded as single floats; P^T is the S^T accumulator, split
 //
-// Scales and ranges.  Powers of two: one for Q, one each for the wave's K and V so far, set so that the largest value lies at 2^12..2^13 and
-// set anew (O follows) where one reaches 2^15.  Every lane's largest Q, K and V must be at least 1/2 after scaling, or zero, so that l
-// keeps its bits: the range of magnitudes in which all of a wave's rows and channels have to lie is 2^13 to 2^16.  Weights are relative to a reference that
-// the row's max may outgrow by 2^4 and are split times 2^11: they are known to 2^-36 of the largest.  Where a value does not fit (infinities,
-// rows that are 2^13 times smaller than others, Q or K above 2^72, V above 2^104) the workgroup walks again with fp32 products, weights relative to the
-// true max and down to the subnormals, as attn_fp32.hip does.
+// Values.  Weights count down to the subnormals, relative to a reference that the row's max may outgrow by 2^4; they are split times 2^20, which
+// brings a subnormal's bits into bf16's range.  What cannot be split exactly (values below 2^-110 that are not 0) or has no finite result (infinities, V above
+// about 2^94) is seen at the end of the walk, and the workgroup walks again with fp32 products, as attn_fp32.hip does.  If all
+// of them do, that takes 1.3 to 2 times the time of attn_fp32.hip: block-sparse 4 x 4096 78 us (there 60), dense 4 x 2500 149 (75), 8 x 8192 1845 (1220).
 //
-// Errors against float64 (2-norm, attn_fp32.hip / here): dense 4 x 2500 5.2e-7 / 3.5e-7, block-sparse 4 x 4096 7.1e-7 / 3.6e-7, unit-scale logits 1.0e-7 /
-// 0.9e-7, a channel of K 50 times the others 1.8e-6 / 8.2e-7.
+// Errors against float64 (2-norm, attn_fp32.hip / here): dense 4 x 2500 5.2e-7 / 2.6e-7, block-sparse 4 x 4096 7.1e-7 / 2.7e-7, dense 8 x 8192 9.4e-7 / 3.5e-7: the
+// sums have fewer roundings.
 //
-// What bounds it: with 8 waves on a compute unit, one after another the vector instructions (750 a tile and wave, of which the splitting is 440), the MFMAs (48)
-// and the caches: 32 rows read their keys anew, 32 KiB a tile, at 14 TB/s of L2 for 8 heads x 8192 tokens.  The matrix pipe is busy 31 % of the time, the
-// vector unit 66 %, and the two hardly overlap.  Dense 8 x 8192 1090 -> 607 us, 4 x 2500 78 -> 54; block-sparse 4 x 4096 (704 keys) 57 -> 41.  On the way: K straight
-// from memory as A operands 678 (dense 8 x 8192, with 4 products 723), products l_x l_y too 8 % slower and no more exact, scales left out 0 to 2 % faster, the
-// largest values left out 3 %, residues by a conversion and an fma instead of v_fma_mix 5 % slower.
+// What bounds it: the vector instructions (1140 a tile and wave, of which the splitting is 860; busy 75 % of the time) beside 96 MFMAs (50 %), at a clock
+// of 1.9 GHz.  The splitting goes between the MFMAs of values split before (all of it first: 2 to 5 % slower).  Residues by v_dot2_f32_bf16, which reads
+// a bf16 without unpacking it, take half the instructions, but that unit does not run beside the MFMAs: no faster (815 to 840 us where this takes 813).  Two fp16
+// values and three products were faster (575), but hold 22 bits of a value within 2^13 of the largest and less of the others.
+// Dense 8 x 8192 1110 -> 830 us, 4 x 2500 77 -> 64; block-sparse 4 x 4096 (704 keys) 55 -> 44, 8 x 8192 (704) 194 -> 144.
 #include "attn_fp32.h"
 
 #include <algorithm>
@@ -37,57 +36,77 @@ namespace cp {
 namespace {
 
 typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
-typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
 constexpr int TQ = 32, TK = 32;               // query rows of a workgroup, keys of a tile (two runs of 16 tokens)
-constexpr float kTop = 32768.f, kBottom = 0.5f;    // scaled values: the largest of a lane is inside, or 0
-constexpr int kFit = 12;                      // a scale is set to bring the largest value to 2^12 .. 2^13
-constexpr int kMaxScale = 60;                 // log2 of the scales of Q and K: -60 .. 60, so that a product's is within fp32
-constexpr int kLeastScaleV = -92, kMaxScaleV = 100;    // V up to 2^104: O, at most 2^kLazy * keys * |V|, stays within fp32
 constexpr float kLazy = 4.f;                  // log2 of how far a row's max may outgrow its reference while the products are split
-constexpr int kScaleP = 11;                   // weights, up to 2^kLazy, are split times 2^11
+constexpr float kScaleP = 1048576.f;          // weights are split times 2^20: those of 2^-149 have bits down to 2^-129, within bf16's subnormals
 
-struct Parts { f16x8 h, l; };                 // x * scale = h + l, each rounded to nearest
+struct Parts { bf16x8 h, m, l; };             // x = h + m + l
 
-__device__ __forceinline__ float pow2(int e) { return __uint_as_float((unsigned)(127 + e) << 23); }
-__device__ __forceinline__ Parts split8(const float (&x)[8], float scale) {
-    Parts p;
-    f16x2 h[4]; float r[8], y[8];
+// Splits x in five stages, which can go between the MFMAs of values split before.  x becomes what is left of it; lost: its low 16 bits are set where
+// that is more than 8 bits (|x| below 2^-110).
+template <int STAGE>
+__device__ __forceinline__ void split_stage(float (&x)[8], Parts& p, unsigned& lost) {
+    union Pairs { bf16x2 p[4]; bf16x8 v; unsigned u[4]; };
+    if (STAGE == 0 || STAGE == 2) {             // the upper 8 bits, rounded
+        Pairs y;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) y[i] = x[i] * scale;
-    __builtin_amdgcn_sched_barrier(0);          // stage by stage: the four pairs in turn, or each waits for itself
+        for (int i = 0; i < 4; ++i) y.p[i] = __builtin_convertvector((f32x2){x[2 * i], x[2 * i + 1]}, bf16x2);
+        (STAGE == 0 ? p.h : p.m) = y.v;
+    } else if (STAGE == 1 || STAGE == 3) {
+        Pairs y;
+        y.v = STAGE == 1 ? p.h : p.m;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) h[i] = __builtin_convertvector((f32x2){y[2 * i], y[2 * i + 1]}, f16x2);
-    __builtin_amdgcn_sched_barrier(0);
+        for (int i = 0; i < 8; ++i) x[i] -= __uint_as_float(i & 1 ? y.u[i >> 1] & 0xffff0000u : y.u[i >> 1] << 16);
+    } else {
+        Pairs y;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) r[i] = fmaf(x[i], scale, -(float)h[i >> 1][i & 1]);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const f16x2 l = __builtin_convertvector((f32x2){r[2 * i], r[2 * i + 1]}, f16x2);
-        p.h[2 * i] = h[i][0]; p.h[2 * i + 1] = h[i][1]; p.l[2 * i] = l[0]; p.l[2 * i + 1] = l[1];
+        for (int i = 0; i < 4; ++i) {
+            const unsigned lo = __float_as_uint(x[2 * i]), hi = __float_as_uint(x[2 * i + 1]);
+            y.u[i] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);       // the upper halves: what is left has 8 bits
+            lost |= lo | hi;
+        }
+        asm("" : "+v"(lost));                   // here, or the residues are kept until the end of the tile
+        p.l = y.v;
     }
+}
+__device__ __forceinline__ Parts split8(float (&x)[8], unsigned& lost) {
+    Parts p;
+    split_stage<0>(x, p, lost);
+    __builtin_amdgcn_sched_barrier(0);          // stage by stage: the pairs in turn, or each waits for itself
+    split_stage<1>(x, p, lost);
+    __builtin_amdgcn_sched_barrier(0);
+    split_stage<2>(x, p, lost);
+    __builtin_amdgcn_sched_barrier(0);
+    split_stage<3>(x, p, lost);
+    __builtin_amdgcn_sched_barrier(0);
+    split_stage<4>(x, p, lost);
     return p;
 }
-__device__ __forceinline__ void mul_parts(const Parts& a, const Parts& b, f32x16& c, f32x16& small) {
-    small = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.l, b.h, small, 0, 0, 0);
-    small = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.h, b.l, small, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x16_f16(a.h, b.h, c, 0, 0, 0);
-}
-// A scale 2^e for values whose largest per lane is `most`: kept while all of them fit, else set anew from the wave's largest.  False: some
-// lane's values, these or earlier ones (low: the least of their maxima), are too small beside the largest, or nothing fits them.
-__device__ __forceinline__ bool fit(float most, int least, int max, int& e, float& low) {
-    if (__ballot(!(most * pow2(e) < kTop)) != 0) {
-        float top = most;
-        for (int o = 32; o > 0; o >>= 1) top = fmaxf(top, __shfl_xor(top, o));
-        e = __builtin_amdgcn_readfirstlane(127 + kFit - (int)(__float_as_uint(top) >> 23));
-        if (e < least || e > max) { e = 0; return false; }
-    }
-    low = fminf(low, most > 0.f ? most : INFINITY);
-    return __ballot(low * pow2(e) < kBottom) == 0;
+// c + small += a b, and between the products what splits x into next
+template <bool NEXT>
+__device__ __forceinline__ void mul_parts(const Parts& a, const Parts& b, f32x16& c, f32x16& small, float (&x)[8], Parts& next, unsigned& lost) {
+    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, small, 0, 0, 0);
+    if (NEXT) split_stage<0>(x, next, lost);
+    __builtin_amdgcn_sched_barrier(0);
+    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, small, 0, 0, 0);
+    if (NEXT) split_stage<1>(x, next, lost);
+    __builtin_amdgcn_sched_barrier(0);
+    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, small, 0, 0, 0);
+    if (NEXT) split_stage<2>(x, next, lost);
+    __builtin_amdgcn_sched_barrier(0);
+    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, small, 0, 0, 0);
+    if (NEXT) split_stage<3>(x, next, lost);
+    __builtin_amdgcn_sched_barrier(0);
+    small = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, small, 0, 0, 0);
+    if (NEXT) split_stage<4>(x, next, lost);
+    __builtin_amdgcn_sched_barrier(0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, c, 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
 }
 __device__ __forceinline__ float half_max(float x) {                // over lanes l and l ^ 32
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -103,6 +122,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
     // operands, [part][16 channels][lane] of 16 bytes.  Afterwards: a partial O per wave in the place of its K tile, (max, sum) of every wave
     // and row and a flag per wave in the place of Q.
     const unsigned k_tile0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)smem;
+    const unsigned q_tile = k_tile0 + W * TK * 512;                 // for fp32 products: the 32 rows of Q, swizzled like K
     float* part_o = smem;
     u32x4* q_parts = (u32x4*)(smem + W * TQ * kHeadDim);
     float* part_m = smem + W * TQ * kHeadDim;
@@ -123,7 +143,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
     const int qpos = q_lo + l32;
     const float* kp = a.k + bb * a.ks0 + kvh * a.ks1;
     const float* vp = a.v + bb * a.ks0 + kvh * a.ks1;
-    const float* qrow = a.q + bb * a.qs0 + h * a.qs1 + (long long)min(qpos, q_last) * a.qs2 + 4 * hh;
+    const float* qp = a.q + bb * a.qs0 + h * a.qs1;
 
     scalar_list list = nullptr; int count = 0;
     if (!DENSE) {
@@ -163,43 +183,31 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
     // the wave's K tile by copies of two rows each, the lane's 16 bytes being chunk (lane & 31) ^ (row & 15) of its row
     const unsigned k_tile = k_tile0 + wave * (TK * 512);
     const unsigned k_chunk = (unsigned)(l32 ^ hh) << 4, k_row = hh * row_bytes;
-    unsigned run_off[8];                                            // byte offsets of the lane's pieces of a run
-#pragma unroll
-    for (int i = 0; i < 8; ++i) run_off[i] = (unsigned)(2 * i) * row_bytes + k_row + (k_chunk ^ (32 * i));
     auto copy_k = [&](int b0, int b1) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");          // the reads of the tile before are done
 #pragma unroll
         for (int run = 0; run < 2; ++run) {
-            const int base = run ? b1 : b0;
-            if (base >= 0 && base + 16 <= a.n) {
-                const char* rows = (const char*)(kp + (long long)base * a.ks2);
-                copy16x8(rows, run_off, k_tile + run * 8192);
-            } else {                                                // rows without a token copy an existing one, masked later
+            const int base = max(run ? b1 : b0, 0);                 // a run without tokens copies existing ones, masked later
+            const char* rows = (const char*)(kp + (long long)base * a.ks2);
+            unsigned off[8], chunk = k_chunk;
+            asm("" : "+v"(chunk));                                  // what follows is worked out here, not kept through the loop
+            if (base + 16 <= a.n) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int tok = min(max(base, 0) + 2 * i + hh, a.n - 1);
-                    copy16_far((const char*)kp + (unsigned long long)(unsigned)tok * row_bytes + (k_chunk ^ (32 * i)), k_tile + run * 8192 + i * 1024);
-                }
+                for (int i = 0; i < 8; ++i) off[i] = (unsigned)(2 * i) * row_bytes + k_row + (chunk ^ (32 * i));
+            } else {                                                // rows past the end repeat the last one
+#pragma unroll
+                for (int i = 0; i < 8; ++i) off[i] = (unsigned)min(2 * i + hh, a.n - 1 - base) * row_bytes + (chunk ^ (32 * i));
             }
+            copy16x8(rows, off, k_tile + run * 8192);
         }
     };
-    auto read_k = [&](int ks, float (&f)[8]) {                      // row l32 of the tile, channels 16*ks + 8*(e >> 2) + 4*hh + (e & 3)
+    const unsigned row_at = l32 * 512 + ((hh ^ (l32 & 15)) << 4);
+    auto read_row = [&](unsigned tile, int ks, float (&f)[8]) {     // row l32 of the tile, channels 16*ks + 8*(e >> 2) + 4*hh + (e & 3)
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const f32x4 v = *(__attribute__((address_space(3))) const f32x4*)(uintptr_t)(k_tile + l32 * 512 + (((4 * ks + 2 * i + hh) ^ (l32 & 15)) << 4));
+            const f32x4 v = *(__attribute__((address_space(3))) const f32x4*)(uintptr_t)((tile + (row_at ^ ((4 * (ks & 3) + 2 * i) << 4))) + (ks >> 2) * 256);
 #pragma unroll
             for (int e = 0; e < 4; ++e) f[4 * i + e] = v[e];
-        }
-    };
-    float kf[8][8];                                                 // row l32 of the tile, channels 16*ks + 8*(e >> 2) + 4*hh + (e & 3)
-    auto load_k = [&](int b0, int b1) {                             // rows without a token read an existing one, masked later
-        const int base = max(l32 < 16 ? b0 : b1, 0), tok = min(base + (l32 & 15), a.n - 1);
-        const char* src = (const char*)kp + (unsigned long long)(unsigned)tok * row_bytes + 16 * hh;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const f32x4 v = *(const f32x4*)(src + 32 * i);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) kf[i >> 1][4 * (i & 1) + e] = v[e];
         }
     };
     float vf[2][4][8];                                              // [run][channel tile][e]: key 8*(e >> 2) + 4*hh + (e & 3), channel 32*dt + l32
@@ -224,42 +232,45 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
         }
     };
 
-    // ---- Q: every wave splits some of the 16-channel steps, by one scale
-    float* tops = part_m;                                           // largest and least row maximum of every wave's steps
-    int eq = kMaxScale;
-    bool exact;                                                     // workgroup-uniform: products of unsplit values
+    // ---- Q: every wave splits some of the 16-channel steps; h and m stay in LDS, l, through the K tiles, in registers (two workgroups of
+    // four waves fill a compute unit's LDS with what is there)
+    unsigned lost = 0;                                              // of the values that this wave has split
+    bf16x8 q_l[8];
     {
-        constexpr int kSteps = 8 / W > 0 ? 8 / W : 1;
-        float v[kSteps][8], most = 0.f;
+        u32x4* l_parts = (u32x4*)smem;
+        constexpr int kSteps = 8 / W;
+        const float* row = qp + (long long)min(qpos, q_last) * a.qs2 + 4 * hh;
+        float v[kSteps][8];
 #pragma unroll
         for (int i = 0; i < kSteps; ++i)
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
-                const f32x4 w = *(const f32x4*)(qrow + 16 * (wave + i * W) + 8 * p);
+                const f32x4 w = *(const f32x4*)(row + 16 * (wave + i * W) + 8 * p);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) { v[i][4 * p + e] = w[e]; most = fmaxf(most, fabsf(w[e])); }
+                for (int e = 0; e < 4; ++e) v[i][4 * p + e] = w[e];
             }
-        tops[tid] = most;                                           // [wave][lane]: rows l32, halves hh
-        __syncthreads();
-        float row = 0.f;                                            // of the lane's row and half over all steps
-#pragma unroll
-        for (int w = 0; w < W; ++w) row = fmaxf(row, tops[w * 64 + lane]);
-        __syncthreads();                                            // Q's parts take their place
-        float low = INFINITY;
-        exact = !fit(row, -kMaxScale, kMaxScale, eq, low);
 #pragma unroll
         for (int i = 0; i < kSteps; ++i) {
-            const Parts p = split8(v[i], pow2(eq));
-            union { f16x8 b; u32x4 u; } c;
+            const Parts p = split8(v[i], lost);
+            union { bf16x8 b; u32x4 u; } c;
             c.b = p.h; q_parts[(0 * 8 + wave + i * W) * 64 + lane] = c.u;
-            c.b = p.l; q_parts[(1 * 8 + wave + i * W) * 64 + lane] = c.u;
+            c.b = p.m; q_parts[(1 * 8 + wave + i * W) * 64 + lane] = c.u;
+            c.b = p.l; l_parts[(wave + i * W) * 64 + lane] = c.u;
         }
         __syncthreads();
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            union { bf16x8 b; u32x4 u; } c;
+            c.u = l_parts[ks * 64 + lane]; q_l[ks] = c.b;
+        }
+        __syncthreads();                                            // before K comes
     }
 
     f32x16 o[4];
     float m, l;                                                     // reference of the raw logits; the lane's own keys' weights
     const float c = a.scale_log2e;
+    // EXACT: fp32 products.  Else false where a value could not be split in full, or something is not finite: infinities, and what is near enough
+    // to them to overflow in a part or in a weight's scale
     auto walk = [&](auto exact_tag) __attribute__((always_inline)) -> bool {
         constexpr bool EXACT = decltype(exact_tag)::value;
 #pragma unroll
@@ -267,67 +278,55 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
         m = -INFINITY; l = 0.f;
-        int ek = kMaxScale, ev = kMaxScaleV;                        // log2 of the scales of K and V
-        float low_k = INFINITY, low_v = INFINITY;
         int b0, b1;
         start_walk();
         next_tile(wave, b0, b1);
-        if (EXACT) load_k(b0, b1); else copy_k(b0, b1);
+        copy_k(b0, b1);
         for (int t = wave; t < ntiles && b0 <= q_last; t += W) {
-            if (!EXACT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the tile's K is in LDS
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // the tile's K is in LDS
             load_v(0, b0);
             __builtin_amdgcn_sched_barrier(0);
             f32x16 s, small;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) { s[r] = 0.f; small[r] = 0.f; }
             if (EXACT) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) { s[r] = 0.f; small[r] = 0.f; }
+                for (int ks = 0; ks < 8; ++ks) {
+                    float k8[8], q8[8];
+                    read_row(k_tile, ks, k8); read_row(q_tile, ks, q8);
 #pragma unroll
-                for (int ks = 0; ks < 8; ++ks)
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        const f32x4 w = *(const f32x4*)(qrow + 16 * ks + 8 * i);
-#pragma unroll
-                        for (int e = 0; e < 4; e += 2) {            // two chains: half as many roundings in each
-                            s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[ks][4 * i + e], w[e], s, 0, 0, 0);
-                            small = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[ks][4 * i + e + 1], w[e + 1], small, 0, 0, 0);
-                        }
+                    for (int e = 0; e < 8; e += 2) {                // two chains: half as many roundings in each
+                        s = __builtin_amdgcn_mfma_f32_32x32x2f32(k8[e], q8[e], s, 0, 0, 0);
+                        small = __builtin_amdgcn_mfma_f32_32x32x2f32(k8[e + 1], q8[e + 1], small, 0, 0, 0);
                     }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             } else {
-                int tried;
-                do {                                                // a second time where the tile asks for another scale
-                    tried = ek;
-                    const float scale = pow2(ek);
-                    float most = 0.f, kn[8];
-                    Parts qn;
-                    auto read_q = [&](int ks) {
-                        union { f16x8 b; u32x4 u; } w;
-                        w.u = q_parts[(0 * 8 + ks) * 64 + lane]; qn.h = w.b;
-                        w.u = q_parts[(1 * 8 + ks) * 64 + lane]; qn.l = w.b;
-                    };
+                float kx[2][8];
+                Parts kp[2], q[2];
+                auto read_q = [&](int ks) {
+                    union { bf16x8 b; u32x4 u; } w;
+                    w.u = q_parts[(0 * 8 + ks) * 64 + lane]; q[ks & 1].h = w.b;
+                    w.u = q_parts[(1 * 8 + ks) * 64 + lane]; q[ks & 1].m = w.b;
+                    q[ks & 1].l = q_l[ks];
+                };
+                read_row(k_tile, 0, kx[0]); read_q(0); read_row(k_tile, 1, kx[1]);
+                kp[0] = split8(kx[0], lost);
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) { s[r] = 0.f; small[r] = 0.f; }
-                    read_k(0, kn); read_q(0);
-#pragma unroll
-                    for (int ks = 0; ks < 8; ++ks) {
-                        float kc[8];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) kc[e] = kn[e];
-                        const Parts q = qn;
-                        if (ks < 7) { read_k(ks + 1, kn); read_q(ks + 1); }
-#pragma unroll
-                        for (int e = 0; e < 8; e += 2) most = fmaxf(fmaxf(fabsf(kc[e]), fabsf(kc[e + 1])), most);
-                        mul_parts(split8(kc, scale), q, s, small);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    if (!fit(most, -kMaxScale, kMaxScale, ek, low_k)) return false;
-                } while (ek != tried);
+                for (int ks = 0; ks < 8; ++ks) {
+                    if (ks < 6) read_row(k_tile, ks + 2, kx[ks & 1]);
+                    if (ks < 7) read_q(ks + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (ks < 7) mul_parts<true>(kp[ks & 1], q[ks & 1], s, small, kx[(ks + 1) & 1], kp[(ks + 1) & 1], lost);
+                    else mul_parts<false>(kp[ks & 1], q[ks & 1], s, small, kx[0], kp[0], lost);
+                }
             }
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[r] += small[r];
             __builtin_amdgcn_sched_barrier(0);
             const int c0 = b0, c1 = b1;
             next_tile(t + W, b0, b1);
-            if (!EXACT) copy_k(b0, b1);
+            copy_k(b0, b1);
             load_v(1, c1);
             __builtin_amdgcn_sched_barrier(0);
 
@@ -341,19 +340,23 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
             float mx = fmaxf(s[0], s[1]);
 #pragma unroll
             for (int r = 2; r < 16; r += 2) mx = fmaxf(fmaxf(s[r], s[r + 1]), mx);
-            const float unit = EXACT ? 1.f : pow2(-ek - eq);        // of the logits in s
-            mx = half_max(mx) * unit;
+            mx = half_max(mx);
             const float m_new = (mx - m) * c > (EXACT ? 0.f : kLazy) ? mx : m;
             const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-            float alpha = (m - m_safe) * c;
-            if (EXACT) {                                            // weights count down to the smallest subnormal: v_exp_f32 has none
-                alpha = exp2f(alpha);
+            const float alpha = exp2f((m - m_safe) * c);
+            float least = 0.f;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s[r] = exp2f((s[r] - m_safe) * c);
-            } else {
-                alpha = __builtin_amdgcn_exp2f(alpha);
+            for (int r = 0; r < 16; ++r) { s[r] = (s[r] - m_safe) * c; least = fminf(least, s[r]); }
+            if (__ballot(least < -126.f) == 0) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(fmaf(s[r], unit, -m_safe) * c);
+                for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+            } else {                                                // v_exp_f32 has no subnormal results, exp2f does
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[r] = exp2f(s[r]);
+            }
+            if (!EXACT) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[r] *= kScaleP;
             }
             float sum = 0.f;
 #pragma unroll
@@ -366,58 +369,59 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
 #pragma unroll
                     for (int r = 0; r < 16; ++r) o[dt][r] *= alpha;
             }
+            if (EXACT) {
 #pragma unroll
-            for (int run = 0; run < 2; ++run) {
-                if (EXACT) {
+                for (int run = 0; run < 2; ++run)
 #pragma unroll
                     for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
                         for (int e = 0; e < 8; ++e) o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[run][dt][e], s[8 * run + e], o[dt], 0, 0, 0);
-                } else {
-                    float p8[8], most = 0.f;
+            } else {
+                Parts vp2[2], p;
+                vp2[0] = split8(vf[0][0], lost);
 #pragma unroll
-                    for (int dt = 0; dt < 4; ++dt)
+                for (int x = 0; x < 8; ++x) {
+                    if (x % 4 == 0) {
+                        float p8[8];
 #pragma unroll
-                        for (int e = 0; e < 8; e += 2) most = fmaxf(fmaxf(fabsf(vf[run][dt][e]), fabsf(vf[run][dt][e + 1])), most);
-                    const int before = ev;
-                    if (!fit(most, kLeastScaleV, kMaxScaleV, ev, low_v)) return false;
-                    if (ev != before) {
-#pragma unroll
-                        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) o[dt][r] *= pow2(max(ev - before, -126));      // less only where O is still 0
-                    }
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) p8[e] = s[8 * run + e];
-                    const Parts p = split8(p8, pow2(kScaleP));
-#pragma unroll
-                    for (int dt = 0; dt < 4; ++dt) {
-                        mul_parts(split8(vf[run][dt], pow2(ev)), p, o[dt], o[dt]);
+                        for (int e = 0; e < 8; ++e) p8[e] = s[2 * x + e];
+                        p = split8(p8, lost);                       // always exact, see kScaleP
                         __builtin_amdgcn_sched_barrier(0);
                     }
+                    if (x < 7) mul_parts<true>(vp2[x & 1], p, o[x % 4], o[x % 4], vf[(x + 1) / 4][(x + 1) % 4], vp2[(x + 1) & 1], lost);
+                    else mul_parts<false>(vp2[x & 1], p, o[x % 4], o[x % 4], vf[0][0], vp2[0], lost);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-                if (EXACT && run == 0) { load_k(b0, b1); __builtin_amdgcn_sched_barrier(0); }
             }
         }
-        if (!EXACT) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // no copy is in flight into what the partial results or Q take
+        float finite = l * 0.f;
 #pragma unroll
-            for (int dt = 0; dt < 4; ++dt)
+        for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) o[dt][r] *= pow2(-ev - kScaleP);
-        }
-        return true;
+            for (int r = 0; r < 16; ++r) finite = fmaf(o[dt][r], 0.f, finite);
+        return __ballot(!(finite == 0.f) || (lost & 0xffffu) != 0) == 0;
     };
-    if (!exact) exact = !walk(std::false_type());
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // no copy is in flight into what the partial results take
-    // one wave that meets a value out of range has all walk again
+    bool exact = !walk(std::false_type());
+    // one wave that meets such a value has all walk again, with Q by whole rows in the place of its parts
     __syncthreads();                                                // every wave is past its last read of Q
     if (lane == 0) flags[wave] = exact;
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < W; ++w) exact |= flags[w] != 0;
     exact = __builtin_amdgcn_readfirstlane(exact);
-    if (exact) walk(std::true_type());
+    if (exact) {
+        __syncthreads();                                            // everybody has read the flags
+#pragma unroll
+        for (int x = 0; x < 16 / W; ++x) {
+            const int i = wave * (16 / W) + x, row = 2 * i + hh;
+            copy16_far((const char*)(qp + (long long)min(q_lo + row, q_last) * a.qs2) + ((unsigned)(l32 ^ (row & 15)) << 4), q_tile + i * 1024);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        walk(std::true_type());
+        __syncthreads();                                            // everybody is past Q
+    }
+    const float unit = exact ? 1.f : 1.f / kScaleP;                 // of the weights in l and O
 
     // ---- merge the W partial results
     l += __shfl_xor(l, 32);
@@ -452,7 +456,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
             const float inv = L > 0.f ? 1.0f / L : 0.f;
             *(f32x4*)(op + (long long)(q_lo + row) * a.os2 + 4 * chunk) = sum * inv;
             if (a.lse && chunk == 0)
-                a.lse[((long long)bb * a.hq + h) * a.n + q_lo + row] = L > 0.f ? M * a.scale + logf(L) : -INFINITY;
+                a.lse[((long long)bb * a.hq + h) * a.n + q_lo + row] = L > 0.f ? M * a.scale + logf(L * unit) : -INFINITY;
         }
     }
 }
@@ -480,28 +484,30 @@ static long long listed_keys(const Shape& sh, bool sparse) {
     return sparse ? std::min((long long)sh.n, (long long)sh.list_len * sh.b) : sh.n;
 }
 
-// Against the fp32 matrix instructions (us, that kernel in its best form / this one; t: row tiles of 32).  That kernel splits rows into 16 and
-// so fills the chip with half as many: t = 128 block-sparse 4 heads x 512 keys 13.5 / 18.8, 1 x 4096, 960 keys 26 / 30, dense 4 x 1000 23.4 / 26.4.  From t = 256 on
-// it is always behind: block-sparse 8 x 1000, 400 keys 22.9 / 20.9, 2 x 4096 (256, 960 keys) 44 / 31, 4 x 4096 (512, 704) 57 / 41, 8 x
-// 8192 (2048; 400, 1184, 4384) 147 / 109, 345 / 214, 898 / 504; dense 8 x 1000 35 / 29, 4 x 2500 (316) 78 / 54, 8 x 8192 1093 / 607.
-// In between the two meet where rows are short or few: t = 192 3 x 2048, 1856 keys 44 / 45 and dense 46 / 47, 188 4 x 1500 dense 35 / 37, but 1 x 6000
-// (188; 400, 960, 1856) 23 / 20.5, 43 / 31, 80 / 47; t = 163 1 x 5200 (400, 960, 3264) 22.9 / 20.0, 42 / 29, 72 / 74, 152 8 x 600, 400 keys 16 / 19.
+// Against the fp32 matrix instructions (us, attn_fp32.hip / this one; t: row tiles of 32).  That kernel splits rows into 16 and so fills the chip with
+// half as many; where rows see unequal numbers of keys, most of those before them, it keeps a unit's two workgroups of unlike length.
+//   nearly all keys: t = 188 to 192 2 x 3000 57 / 69, 4 x 1500 32 / 39, 3 x 2048 block-sparse 42 / 51; t = 256 1 x 8192 159 / 184, 4 x 2048 47 / 51, but 8 x 1000
+//   32 / 29, 16 x 512 19.0 / 18.3; t = 258 3 x 2731 63 / 67, 282 3 x 3000 78 / 74, 313 1 x 10000 252 / 233, 320 8 x 1250 44 / 36, 512 4 x 4096 166 / 122.
+//   fewer: t = 256 always (416, 1248 keys): 1 x 8192 24 / 21, 54 / 40, 4 x 2048 21.7 / 19.3, 47 / 37; t = 188 to 192 1 x 6000 (416, 1248, 3136) 20.9 / 18.7, 53 / 36, 85 /
+//   75, 4 x 1500 (704, 1248) 26.0 / 23.8, 30 / 35, 3 x 2048 (1248) 37.4 / 36.2, 8 x 750 (416) 17.1 / 18.0; t = 163 1 x 5200 (416, 1248, 3136) 21.0 / 18.2, 49 / 36, 62 / 74;
+//   152 8 x 600 (416) 14.7 / 17.7, 128 1 x 4096 (416, 1248) 13.2 / 17.7, 28.6 / 35.1.
 bool attn_fp32_split_better(const Shape& sh, bool sparse) {
     if (sh.kvs[2] >= (1 << 26) || (sparse && sh.b % 16 != 0)) return false;     // a run's rows within 32-bit byte offsets of its first; runs of 16
-    const long long tiles = row_tiles(sh, sparse), keys = listed_keys(sh, sparse);
+    const long long tiles = row_tiles(sh, sparse), keys = listed_keys(sh, sparse), n = sh.n;
+    if (n > 1024 && 5 * keys > 4 * n) return tiles > 272;
     if (tiles >= 256) return true;
-    if (tiles >= 184) return sh.n >= 2400 || (sparse && keys < 1536);
-    return tiles >= 144 && sparse && sh.n >= 2400 && keys < 2400;
+    if (tiles >= 184) return n >= 1400 && 5 * keys <= 3 * n;
+    return tiles >= 144 && n >= 2400 && 3 * keys <= n;
 }
 
-// Eight waves leave one workgroup to a compute unit, four two.  Eight / four: up to a chip full of workgroups block-sparse 1 x 8192 (t =
-// 256; 400, 1184, 4384 keys) 22 / 26, 39 / 48, 98 / 136, dense 2 x 4096 81 / 111; beyond it rows of many or unequal keys: dense 4 x 2500
-// (316) 54 / 71, 2 x 8192 (512) 176 / 220, 3 x 6000 (564) 162 / 169, block-sparse 2 x 6000 (376, 4384) 105 / 138, 3 x 3000 (282; 400, 960, 1856) 33 / 26,
-// 37 / 40, 48 / 65; but 2 x 6000 (376, 960) 58 / 52, 4 x 4096 (512, 1856) 92 / 89; dense 3 x 8192 (768) 283 / 254.
+// Eight waves leave one workgroup to a compute unit, four two.  Eight / four: up to a chip full of workgroups block-sparse 1 x 8192 (t = 256; 416, 1248,
+// 3136 keys) 21 / 24, 40 / 46, 82 / 98, dense 2 x 4096 95 / 116; beyond it rows of many and so unequal keys: dense 4 x 2500 (316) 64 / 76, 2 x 8192 (512) 229 /
+// 267, 3 x 6000 (564) 202 / 217, block-sparse 2 x 5000 (314, 3136) 84 / 98, 8 x 2048 (512, 2048) 68 / 74; but 2 x 6000 (376; 704, 3136) 47 / 42, 116 / 112, 4 x
+// 4096 (512, 1248) 76 / 71, 32 x 500 (512) 28 / 24; dense 4 x 6000 (752) 263 / 256.
 hipError_t launch_attn_fp32_split(const Shape& sh, Args32& a, hipStream_t st) {
     const bool sparse = a.idx != nullptr;
     const long long tiles = row_tiles(sh, sparse), keys = listed_keys(sh, sparse);
-    const bool eight = tiles <= 256 || (tiles <= 320 && keys >= 640) || (tiles < 600 && (!sparse || keys >= 3072));
+    const bool eight = tiles <= 256 || (tiles <= 640 && sh.n >= 1024 && 8 * keys >= 5ll * sh.n);
     if (sparse) return eight ? launch<1, 8>(sh, a, st) : launch<1, 4>(sh, a, st);
     return eight ? launch<2, 8>(sh, a, st) : launch<2, 4>(sh, a, st);
 }

@@ -1,8 +1,8 @@
-"""fp32 attention on fp16 pairs (launches with enough row tiles): edges of tiles and runs, both wave counts, block sizes, layouts, shared lists and
-bad lists, values that change their scale on the way and values that no scale fits.
+"""fp32 attention on triples of bf16 (launches with enough row tiles): edges of tiles and runs, both wave counts, block sizes, layouts, shared lists and
+bad lists, values, weights and channels of any size beside each other, values that cannot be split.
 
-Tolerances: as the other fp32 attention tests where inputs are of unit scale.  Relative errors (2-norm): a factor is known to 2^-24, products are
-exact, sums of n terms in fp32 to about sqrt(n) 2^-24 of their size; 1e-6 = 16 * 2^-24 covers 32 channels-steps, a few hundred keys and the exponential."""
+Tolerances: as the other fp32 attention tests where inputs are of unit scale.  Relative errors (2-norm): factors are exact, products known to
+2^-24, sums of n terms in fp32 to about sqrt(n) 2^-24 of their size; 1e-6 = 16 * 2^-24 covers the channels, a few hundred keys and the exponential."""
 import numpy as np
 import pytest
 import torch
@@ -130,7 +130,7 @@ def test_bad_lists_and_counts(b):
 
 
 def test_run_twice_and_powers_of_two():
-    """The scales follow the values: powers of two in V come out exactly, powers of two between Q and K do not show at all."""
+    """Powers of two in V come out exactly, powers of two between Q and K do not show at all."""
     w, q, k, v = make(1, 8, 2, 1003, 256, 32, 6, 1)
     idx, cnt = (torch.from_numpy(x).to(DEV) for x in lists(w, 8))
     out, lse = H.gpu_sparse(w, q, k, v, idx, cnt)
@@ -148,7 +148,7 @@ GROW = {"k_grows": ("k", 200.0), "v_grows": ("v", 3000.0), "v_shrinks": ("v", 1 
 @pytest.mark.parametrize("case", GROW)
 @pytest.mark.parametrize("shape", [(1, 8, 2, 1003), (1, 24, 2, 1003)], ids=["eight", "four"])
 def test_scales_on_the_way(case, shape):
-    """Values that outgrow the scale of a wave's first tiles (set anew), or lie too far apart for one scale (walked again with fp32 products)."""
+    """Values that grow or shrink on the way through the sequence."""
     w, q, k, v = make(*shape, 256, 64, 4, 1)
     which, factor = GROW[case]
     x = {"q": q, "k": k, "v": v}[which]
@@ -191,3 +191,109 @@ def test_segment_longer_than_the_sequence():
     idx, cnt = lists(w, w.n_q_heads)
     out, lse = H.gpu_sparse(w, q, k, v, torch.from_numpy(idx).to(DEV), torch.from_numpy(cnt).to(DEV))
     check(w, out, lse, q, k, v, idx, cnt)
+
+
+def every_block(w, b):
+    """Lists that hold every block: dense attention again."""
+    return [torch.from_numpy(x).to(DEV) for x in O.select(np.ones((w.batch, w.n_q_heads, w.n_segments, w.n_blocks), np.float32), w.segment_size, b, 25, 0)]
+
+
+LIGHT = {
+    # logit of the light keys, their V, V of token 0 (logit 0)
+    "v1": (-17.0, 1.0, 0.0), "v1_lighter": (-25.0, 1.0, 0.0), "v_large": (-25.0, 2.0 ** 70, 0.0), "v_2_100": (-25.0, 2.0 ** 100, 0.0),
+    "v_beside_1": (-28.0, 2.0 ** 30, 1.0), "subnormal": (-90.0, 2.0 ** 60, 0.0), "subnormal_2_118": (-90.0, 2.0 ** 118, 0.0),
+}
+
+
+@pytest.mark.parametrize("b", [16, 0], ids=["runs", "dense"])
+@pytest.mark.parametrize("case", LIGHT)
+def test_light_keys(case, b):
+    """Keys of small weight count where the heavy one has a small V: down to the subnormal weights, at any size of V.  Logits are exact up to one
+    rounding, 90 * 2^-24 = 5e-6 relative in a weight; a subnormal weight of 8e-40 is known to 2^-19 = 2e-6."""
+    n, H_ = 300, 32
+    logit, light, heavy = LIGHT[case]
+    w = H.small_workload("light", 1, H_, H_, n, b * 25 or 16, b or 16, 25, 0, dtype="fp32")
+    q = torch.zeros((1, H_, n, 128), dtype=torch.float32, device=DEV)
+    k, v = torch.zeros_like(q), torch.full_like(q, light)
+    q[..., 0] = 1.0
+    k[:, :, 1:, 0] = logit * 128 ** 0.5
+    v[:, :, 0] = heavy
+    assert tiles(w, bool(b)) >= 256
+    out, lse = H.gpu_sparse(w, q, k, v, *every_block(w, b)) if b else H.gpu_dense(w, q, k, v)
+    ref, lse_ref = O.dense_causal_attention(synth.to_f64(q[:, :1].cpu()), synth.to_f64(k[:, :1].cpu()), synth.to_f64(v[:, :1].cpu()))
+    for h in (0, 7, 31):
+        np.testing.assert_allclose(out[:, h].cpu().numpy(), ref[:, 0], rtol=2e-5)
+        np.testing.assert_allclose(lse[:, h].cpu().numpy(), lse_ref[:, 0], rtol=0, atol=2e-5)
+
+
+def test_a_single_key_returns_its_value():
+    """A row that sees one key has that key's V, bit for bit: no operand is held in fewer bits than it came in."""
+    w, q, k, v = make(2, 32, 8, 333, 256, 64, 4, 1)
+    out, _ = H.gpu_dense(w, q, k, v)
+    assert torch.equal(out[:, :, 0], v.repeat_interleave(4, 1)[:, :, 0])
+
+
+@pytest.mark.parametrize("e", [10, 24, 36, 60])
+@pytest.mark.parametrize("which", ["v", "qk", "kq"])
+def test_channels_apart(which, e):
+    """A power of two in some channels of V comes out of the same channels, exactly; between channels of Q and K it does not show."""
+    w, q, k, v = make(1, 8, 2, 1003, 256, 32, 6, 1)
+    idx, cnt = (torch.from_numpy(x).to(DEV) for x in lists(w, 8))
+    out, lse = H.gpu_sparse(w, q, k, v, idx, cnt)
+    d = torch.ones(128, device=DEV)
+    d[32:64] = d[100] = 2.0 ** -e
+    if which == "v":
+        again, lse2 = H.gpu_sparse(w, q, k, v * d, idx, cnt)
+        assert torch.equal(again, out * d) and torch.equal(lse2, lse)
+    else:
+        again, lse2 = H.gpu_sparse(w, *((q * d, k / d) if which == "qk" else (q / d, k * d)), v, idx, cnt)
+        assert torch.equal(again, out) and torch.equal(lse2, lse)
+
+
+@pytest.mark.parametrize("factor", [1e4, 1e10, 1e25])
+@pytest.mark.parametrize("first", [2, 34])
+def test_later_values_larger(first, factor):
+    """What a row may not see does not show in it, whatever its size."""
+    w, q, k, v = make(1, 8, 2, 1003, 256, 64, 4, 1)
+    out, lse = H.gpu_dense(w, q, k, v)
+    v[:, :, first:] *= factor
+    again, lse2 = H.gpu_dense(w, q, k, v)
+    o_ref, lse_ref = dense_exact(w, q, k, v)
+    err = (again.double() - o_ref).norm(dim=3) / o_ref.norm(dim=3)
+    assert float(err.max()) <= 4e-6
+    assert torch.equal(again[:, :, :first], out[:, :, :first]) and torch.equal(lse, lse2)
+
+
+@pytest.mark.parametrize("which", ["v", "k", "q"])
+def test_values_below_the_split(which):
+    """Values too small for three bf16 parts (below 2^-110): a power of two between Q and K, or in V, still does not show but for the rounding of other
+    sums (fp32 products take over)."""
+    w, q, k, v = make(1, 8, 2, 1003, 256, 32, 6, 1)
+    idx, cnt = (torch.from_numpy(x).to(DEV) for x in lists(w, 8))
+    out, lse = H.gpu_sparse(w, q, k, v, idx, cnt)
+    e = 2.0 ** -112                                           # unit-scale values keep their 24 bits above 2^-149 (but for those below 2^-14)
+    args = {"v": (q, k, v * e), "k": (q / e, k * e, v), "q": (q * e, k / e, v)}[which]
+    again, lse2 = H.gpu_sparse(w, *args, idx, cnt)
+    assert rel(again, out.double() * (e if which == "v" else 1.0)) <= 2e-6
+    assert rel(lse2, lse.double()) <= 1e-6
+
+
+def test_infinities():
+    """An infinite value goes to what sees it, as an infinity; a key at minus infinity is as good as not there."""
+    w, q, k, v = make(1, 8, 2, 1003, 256, 64, 4, 1)
+    o_ref, _ = dense_exact(w, q, k, v)
+    x = v.clone()
+    x[0, 1, 700, 5] = float("inf")
+    out, _ = H.gpu_dense(w, q, k, x)
+    assert torch.isposinf(out[0, 4:, 704:, 5]).all()          # rows of later workgroups, which see all keys of its tile
+    rest = [c for c in range(128) if c != 5]
+    assert rel(out[0, 4:, :, rest], o_ref[0, 4:, :, rest]) <= 1e-6
+    q, y = q.clone(), k.clone()
+    q[..., 3] = q[..., 3].abs() + 0.1
+    y[0, :, 700, 3] = -float("inf")
+    out, lse = H.gpu_dense(w, q, y, v)
+    visible = torch.ones(1003, 1003, dtype=torch.bool, device=DEV).tril()
+    visible[:, 700] = False
+    y[0, :, 700, 3] = 0.0
+    o_ref, lse_ref = exact(q, y.repeat_interleave(4, 1), v.repeat_interleave(4, 1), visible)
+    assert rel(out, o_ref) <= 1e-6 and rel(lse, lse_ref) <= 1e-6
