@@ -175,6 +175,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
         b0 = run_at(walk_e, walk_off);
         const bool next = walk_off + 16 >= (unsigned)a.b;
         b1 = run_at(walk_e + (next ? 1 : 0), next ? 0 : walk_off + 16);
+        if (b1 > q_last) b1 = -1;                                   // behind every row: 0 * V must be 0, whatever V holds
         walk_e += step_e; walk_off += step_off;
         if (walk_off >= (unsigned)a.b) { walk_off -= a.b; ++walk_e; }
     };

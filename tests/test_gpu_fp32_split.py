@@ -297,3 +297,16 @@ def test_infinities():
     y[0, :, 700, 3] = 0.0
     o_ref, lse_ref = exact(q, y.repeat_interleave(4, 1), v.repeat_interleave(4, 1), visible)
     assert rel(out, o_ref) <= 1e-6 and rel(lse, lse_ref) <= 1e-6
+
+
+def test_runs_behind_the_last_row():
+    """A tile's second run that lies behind the workgroup's last row is not touched: segments of three runs behind an odd number of blocks, so that the
+    second and third of a segment share a tile, of which the rows of its first 32 see one."""
+    w, q, k, v = make(1, 8, 2, 1203, 48, 16, 5, 0)
+    idx, cnt = (torch.from_numpy(x).to(DEV) for x in lists(w, 8))
+    out, lse = H.gpu_sparse(w, q, k, v, idx, cnt)
+    first = 10 * 48 + 32
+    k[:, :, first:first + 16, 7] = float("inf")
+    v[:, :, first:first + 16] = float("inf")
+    again, lse2 = H.gpu_sparse(w, q, k, v, idx, cnt)
+    assert torch.equal(again[:, :, :first], out[:, :, :first]) and torch.equal(lse2[:, :, :first], lse[:, :, :first])
