@@ -315,7 +315,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
 
 template <int MODE, int RT, int W>
 hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
-    a.qtiles = ((a.idx ? sh.s : sh.n) + 16 * RT - 1) / (16 * RT);
+    a.qtiles = ((a.idx ? min(sh.s, sh.n) : sh.n) + 16 * RT - 1) / (16 * RT);    // a segment may be set longer than the sequence
     const long long grid = (long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1);
     hipLaunchKernelGGL((attn_fp32_kernel<MODE, RT, W>), dim3((unsigned)grid), dim3(64 * W), 0, st, a);
     return hipGetLastError();

@@ -125,3 +125,17 @@ def test_batches(b, s):
     for (o_ref, lse_ref), (out, lse) in runs:
         assert H.max_abs(out.cpu().numpy(), o_ref) <= H.TOL_OUT["fp32"]
         assert H.max_abs(lse.cpu().numpy(), lse_ref) <= 1e-4
+
+
+def test_segment_far_longer_than_the_sequence():
+    """A segment set longer than the sequence launches no workgroups past its end: with 2^28 tokens to a segment they would be 2^24, more
+    than a launch takes."""
+    n = 100
+    w = H.small_workload("longseg", 1, 1, 1, n, 1 << 28, 1 << 14, 1, 0, dtype="fp32", unit_variance=True)
+    q, k, v = synth.make_qkv(w)
+    qd, kd, vd = q.to(DEV), k.to(DEV), v.to(DEV)
+    idx = torch.full((1, 1, 1, (1 << 14) + 1), -1, dtype=torch.int32, device=DEV)
+    idx[..., 0] = 0
+    out, _ = H.gpu_sparse(w, qd, kd, vd, idx, torch.ones((1, 1, 1), dtype=torch.int32, device=DEV))
+    d_ref, _ = O.dense_causal_attention(synth.to_f64(q), synth.to_f64(k), synth.to_f64(v))
+    assert H.max_abs(out.cpu().numpy(), d_ref) <= H.TOL_OUT["fp32"]
