@@ -2,6 +2,8 @@
 through the CPU checker, and the comparison rules.  No arithmetic of the method lives here."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -118,3 +120,29 @@ def check_selection(S_dec, idx_o, cnt_o, idx_g, cnt_g, w: synth.Workload, exact:
 
 def max_abs(a, b):
     return float(np.max(np.abs(np.asarray(a, dtype=np.float64) - np.asarray(b, dtype=np.float64))))
+
+
+class _Shape(ctypes.Structure):                  # cp::Shape of csrc/kernels.h
+    _fields_ = ([(x, ctypes.c_int) for x in ("batch", "hq", "hkv", "n", "s", "b", "r", "n1", "n2", "budget", "local", "list_len", "dtype")]
+                + [(x, ctypes.c_float) for x in ("attn_scale", "score_scale", "alpha")] + [("softmax_domain", ctypes.c_int)]
+                + [(x, ctypes.c_int64 * 3) for x in ("qs", "kvs", "os")])
+
+
+def attention_kernel(w: synth.Workload, sparse: bool = True) -> str:
+    """Which kernel the library's own rules give this attention: "32", "128" or "256" rows in bf16, "split" or "fp32".  For tests that are
+    written for one of them."""
+    r = w.segment_size // w.block_size
+    sh = _Shape(w.batch, w.n_q_heads, w.n_kv_heads, w.seq_len, w.segment_size, w.block_size, r, w.n_segments, w.n_blocks, w.budget_blocks,
+                w.local_blocks, w.budget_blocks + w.local_blocks + r)
+    sh.kvs[2] = 128
+
+    def rule(name, *args):
+        f = getattr(B.load(), f"_ZN2cp{len(name)}{name}ERKNS_5ShapeE" + "b" * len(args))
+        f.restype = ctypes.c_bool
+        return f(ctypes.byref(sh), *(ctypes.c_bool(a) for a in args))
+
+    if w.dtype == "fp32":
+        return "split" if rule("attn_fp32_split_better", sparse) else "fp32"
+    if sparse and rule("attn_bf16_half_better"):
+        return "128"
+    return "32" if rule("attn_bf16_rows_better", sparse) else "256"

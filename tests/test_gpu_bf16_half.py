@@ -27,6 +27,8 @@ SHAPES = [
     (1, 32, 8, 3300, 256, 16, 20, 1),        # two 128-row tiles, runs of 16
     (1, 16, 4, 4100, 320, 64, 3, 1), (1, 8, 2, 4000, 512, 64, 4, 1),
     (2, 8, 2, 3999, 208, 16, 7, 0),          # 13 blocks of 16 to a segment: lists that end inside a tile
+    (1, 8, 1, 8300, 128, 32, 3, 1),          # 520 (query head, segment) pairs of a KV head: a round of 512 and a part of one
+    (1, 16, 1, 8400, 256, 16, 4, 0),         # 528, of two row tiles each
 ]
 
 
@@ -34,14 +36,43 @@ SHAPES = [
 @pytest.mark.parametrize("gain", [1.0, 6.0])
 def test_sparse(shape, gain):
     w, q, k, v = make(*shape, gain)
+    assert H.attention_kernel(w) == "128"
     idx, cnt = lists(w, w.n_q_heads)
     out, lse = H.gpu_sparse(w, *dev(q, k, v, idx, cnt))
     check(w, out, lse, q, k, v, idx, cnt, sample(w))
 
 
+@pytest.mark.parametrize("k,kernel", [(382, "128"), (383, "32")])
+def test_longest_lists(k, kernel):
+    """Lists of 49152 keys, the most that the kernel's table of tiles holds; one block more is for the 32-row kernel."""
+    w, q, k_, v = make(1, 1, 1, 49200, 128, 128, k, 1)
+    assert H.attention_kernel(w) == kernel
+    idx, cnt = lists(w, 1)
+    assert cnt.max() == min(k + 2, w.n_blocks)
+    out, lse = H.gpu_sparse(w, *dev(q, k_, v, idx, cnt))
+    check(w, out, lse, q, k_, v, idx, cnt, [(0, 0, j) for j in (0, 100, w.n_segments - 2, w.n_segments - 1)])
+
+
+@pytest.mark.parametrize("shape", [(8, 2, 4000, 512, 64, 4, 1), (8, 2, 4000, 512, 32, 30, 1), (8, 2, 4000, 512, 16, 80, 1), (7, 1, 4100, 480, 48, 30, 1)],
+                         ids=["b64", "b32", "b16", "b48"])
+@pytest.mark.parametrize("gain", [1.0, 6.0])
+def test_same_bits_as_256_rows(shape, gain):
+    """The same sequences once in a launch of this kernel and once, twice over, in one that the 256-row kernel takes."""
+    one, q, k, v = make(1, *shape, gain)
+    two = make(2, *shape)[0]
+    assert (H.attention_kernel(one), H.attention_kernel(two)) == ("128", "256")
+    idx, cnt = lists(one, one.n_q_heads)
+    args = dev(q, k, v, idx, cnt)
+    out, lse = H.gpu_sparse(one, *args)
+    out2, lse2 = H.gpu_sparse(two, *(x.repeat(2, *[1] * (x.dim() - 1)) for x in args))
+    for i in (0, 1):
+        assert torch.equal(out2[i], out[0]) and torch.equal(lse2[i], lse[0])
+
+
 @pytest.mark.parametrize("shape", [(1, 16, 4, 2950, 128, 32, 10, 1), (1, 32, 8, 3300, 256, 16, 20, 1)], ids=["b32", "b16"])
 def test_shared_lists_token_major(shape):
     w, q, k, v = make(*shape)
+    assert H.attention_kernel(w) == "128"
     idx, cnt = lists(w, w.n_kv_heads)
     dq, dk, dv = (x.transpose(1, 2).contiguous().transpose(1, 2).to("cuda") for x in (q, k, v))
     out, lse = H.gpu_sparse_shared(w, dq, dk, dv, *dev(idx, cnt))
@@ -53,6 +84,7 @@ def test_bad_lists(b):
     """Entries outside the sequence have no tokens, entries behind the count are not read, counts outside the list are clamped."""
     s = 128
     w, q, k, v = make(1, 16, 4, 2950, s, b, 7, 1)
+    assert H.attention_kernel(w) == "128"
     idx, cnt = lists(w, w.n_q_heads)
     bad, bad_cnt, ref, ref_cnt = idx.copy(), cnt.copy(), idx.copy(), cnt.copy()
     for h in range(w.n_q_heads):

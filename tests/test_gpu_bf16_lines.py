@@ -1,6 +1,6 @@
-"""The two bf16 attention kernels on both sides of the lines between them as they lie with K and Q copied by whole rows: 32-row workgroups for segments of
-up to 128 rows at any length and for rows that leave 256-row workgroups idle, blocks that are odd multiples of 16 as pairs of runs (also an odd
-number of runs, and runs that end inside a tile), four and eight waves; and the 256-row kernel's special cases at row counts that still are its own.
+"""The bf16 attention kernels on both sides of the lines between them: 32-row workgroups for rows that leave 256-row ones idle and for segments of up
+to 64, blocks that are odd multiples of 16 as pairs of runs (also an odd number of runs, and runs that end inside a tile), four and eight waves; 128-row
+ones for segments of up to 128 and a few short lists; and the 256-row kernel's special cases at row counts that are its own.
 Against the checker on sampled segments and rows, with the bars of the other bf16 attention tests."""
 import numpy as np
 import pytest
@@ -21,25 +21,28 @@ def make(Bt, Hq, Hkv, n, s, b, k, L, gain=1.0):
 
 
 SPARSE = [
-    # Bt Hq Hkv  n     s    b    k   L
-    (1, 2, 1, 1003, 112, 16, 9, 1),          # runs of 16, odd numbers of them; segments of 112: a last row tile of 16
-    (1, 3, 3, 777, 240, 48, 6, 1), (2, 5, 5, 901, 160, 80, 4, 1), (1, 4, 2, 2050, 96, 32, 20, 0),
-    (1, 8, 2, 1500, 512, 64, 20, 1),         # 376 row tiles, nearly all keys: eight waves; and four:
-    (1, 8, 2, 1500, 512, 64, 2, 1),
-    (1, 16, 4, 4100, 128, 32, 40, 1),        # segments of 128 far beyond 16384 rows: 32-row
-    (1, 32, 8, 1300, 64, 16, 30, 2),         # segments of 64
-    (1, 16, 4, 4100, 128, 32, 8, 0),         # 2064 row tiles of short lists: 256-row
-    (1, 9, 3, 2051, 256, 32, 40, 1),         # 585 row tiles, 1.4 times the keys: 32-row
-    (1, 2, 1, 9501, 512, 64, 3, 1),          # 594 row tiles of few keys: 256-row
-    (1, 7, 7, 3301, 256, 32, 60, 1),         # 728 row tiles, keys enough: 32-row
-    (1, 16, 4, 2001, 512, 64, 30, 1),        # 1008 row tiles, all keys: 32-row
-    (1, 17, 17, 2001, 512, 64, 30, 1),       # 1071: 256-row
+    # Bt Hq Hkv  n     s    b    k   L, rows of a workgroup
+    (1, 2, 1, 1003, 112, 16, 9, 1, "32"),          # runs of 16, odd numbers of them; segments of 112: a last row tile of 16
+    (1, 3, 3, 777, 240, 48, 6, 1, "32"), (2, 5, 5, 901, 160, 80, 4, 1, "32"), (1, 4, 2, 2050, 96, 32, 20, 0, "32"),
+    (1, 8, 2, 1500, 512, 64, 20, 1, "32"),         # 376 row tiles, nearly all keys: eight waves; and four:
+    (1, 8, 2, 1500, 512, 64, 2, 1, "32"),
+    (1, 16, 4, 4100, 128, 32, 40, 1, "128"),       # segments of 128, 2064 row tiles
+    (1, 16, 4, 4100, 128, 32, 8, 0, "128"),
+    (1, 4, 2, 3001, 128, 32, 40, 1, "32"),         # 376 row tiles
+    (1, 32, 8, 1300, 64, 16, 30, 2, "32"),         # segments of 64
+    (1, 9, 3, 2051, 256, 32, 40, 1, "32"),         # 585 row tiles, 1.4 times the keys
+    (1, 2, 1, 9501, 512, 64, 3, 1, "128"),         # 594 row tiles of few keys
+    (1, 7, 7, 3301, 256, 32, 60, 1, "32"),         # 728 row tiles, keys enough
+    (1, 16, 4, 2001, 512, 64, 30, 1, "32"),        # 1008 row tiles, all keys
+    (1, 17, 17, 2001, 512, 64, 30, 1, "256"),      # 1071
+    (1, 17, 17, 2001, 512, 64, 3, 1, "256"),       # of few keys
 ]
 
 
-@pytest.mark.parametrize("shape", SPARSE, ids=lambda t: "x".join(map(str, t)))
+@pytest.mark.parametrize("shape", SPARSE, ids=lambda t: "x".join(map(str, t[:8])))
 def test_sparse(shape):
-    w, q, k, v = make(*shape)
+    w, q, k, v = make(*shape[:8])
+    assert H.attention_kernel(w) == shape[8]
     idx, cnt = lists(w, w.n_q_heads)
     out, lse = H.gpu_sparse(w, *dev(q, k, v, idx, cnt))
     check(w, out, lse, q, k, v, idx, cnt, sample(w))
@@ -93,6 +96,7 @@ def test_dense(shape, gain):
 @pytest.mark.parametrize("b", [64, 32, 16])
 def test_256_rows_many_trailing_tiles(b):
     w, q, k, v = make(1, 5, 1, 9001, 8192, b, 4, 0)
+    assert H.attention_kernel(w) == "256"
     idx, cnt = lists(w, w.n_q_heads)
     out, lse = H.gpu_sparse(w, *dev(q, k, v, idx, cnt))
     check(w, out, lse, q, k, v, idx, cnt, [(0, 2, 0), (0, 0, 1), (0, 4, 1)])
@@ -101,6 +105,7 @@ def test_256_rows_many_trailing_tiles(b):
 @pytest.mark.parametrize("b", [64, 32, 16])
 def test_256_rows_negative_and_zero_counts(b):
     w, q, k, v = make(1, 40, 2, 1000, 256, b, 3, 1)
+    assert H.attention_kernel(w) == "256"
     idx, cnt = lists(w, w.n_q_heads)
     bad, ref = cnt.copy(), cnt.copy()
     bad[0, 0, 1], bad[0, 39, 2], bad[0, 10, 3] = -3, -(1 << 31), 0

@@ -1,6 +1,5 @@
-"""The two bf16 attention kernels on both sides of the line between them (16384 query rows block-sparse, 32768 dense), each in all its
-tile modes: 32-row workgroups whose waves split the keys (4 or 8 waves; blocks of 32 and of other sizes; dense), and 256-row
-workgroups (blocks of 64, of 32, of other sizes; dense).  Ragged lengths, last tiles of one token, segments shorter than a row
+"""The bf16 attention kernels with 32-row workgroups whose waves split the keys (4 or 8 waves; blocks of multiples of 16 and of other sizes; dense) and
+with 256-row workgroups (blocks of 64, of 32, of other sizes; dense).  Ragged lengths, last tiles of one token, segments shorter than a row
 tile, lists that hold bad entries.  Bars of the other bf16 attention tests."""
 import numpy as np
 import pytest
@@ -14,25 +13,29 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 SHAPES = [
-    # Hq Hkv    n    s    b   k  L
-    (1, 1, 1, 16, 16, 1, 0),             # one query, one key
-    (2, 1, 33, 32, 32, 2, 0),            # 32 rows, blocks of 32: a last tile of one token
-    (4, 2, 2047, 256, 64, 5, 1),         # 8188 rows: eight waves
-    (4, 2, 2049, 96, 96, 4, 0),          # 8196 rows: four waves, blocks of 96
-    (2, 2, 1003, 24, 8, 9, 1),           # 32 rows, a token per key; segments of 24
-    (3, 1, 1500, 144, 48, 6, 1),         # 32 rows, blocks of 48
-    (16, 4, 1024, 512, 128, 2, 1),       # 16384 rows: the last 32-row block-sparse launch
-    (16, 4, 1025, 512, 128, 2, 1),       # 16400 rows: 256-row kernel, blocks of 64s
-    (24, 8, 777, 256, 32, 6, 0),         # 256-row kernel, blocks of 32; dense in 32-row workgroups, four waves
-    (24, 8, 1399, 64, 16, 5, 2),         # 256-row kernel, a token per key; 33576 rows: 256-row dense
-    (32, 8, 2100, 192, 96, 3, 1),        # 256-row kernel, blocks of 96
-    (2, 1, 8200, 512, 64, 4, 1),         # 16400 rows of 8200 keys: dense with eight waves
-    (1, 1, 16001, 240, 48, 5, 1),        # 534 row tiles of 32: 32-row
-    (1, 1, 16321, 240, 48, 5, 1),        # 545 row tiles, short lists: 256-row kernel below 16384 rows
-    (1, 1, 16321, 240, 48, 40, 0),       # 545 row tiles, long lists: 32-row
-    (32, 8, 250, 240, 48, 6, 0),         # 8000 rows in 288 tiles, 250 keys: 32-row, four waves
-    (3, 1, 77, 4096, 64, 2, 1),          # a segment longer than the sequence
-    (24, 8, 800, 4096, 16, 2, 1),        # the same in the 256-row kernel
+    # Hq Hkv    n    s    b   k  L, rows of a workgroup: block-sparse, dense
+    (1, 1, 1, 16, 16, 1, 0, "32", "32"),             # one query, one key
+    (2, 1, 33, 32, 32, 2, 0, "32", "32"),            # a last tile of one token
+    (4, 2, 2047, 256, 64, 5, 1, "32", "32"),         # 256 row tiles: eight waves
+    (4, 2, 2049, 96, 96, 4, 0, "32", "32"),          # 260: blocks of 96
+    (2, 2, 1003, 24, 8, 9, 1, "32", "32"),           # a token per key; segments of 24
+    (3, 1, 1500, 144, 48, 6, 1, "32", "32"),         # blocks of 48
+    (16, 4, 1024, 512, 128, 2, 1, "32", "32"),
+    (16, 4, 1025, 512, 128, 2, 1, "32", "32"),       # 528 row tiles
+    (40, 8, 1025, 512, 128, 2, 1, "256", "32"),      # blocks of 64s
+    (24, 8, 777, 256, 32, 6, 0, "32", "32"),         # four waves
+    (48, 8, 777, 256, 32, 6, 0, "256", "32"),        # blocks of 32
+    (24, 8, 1399, 64, 16, 5, 2, "32", "32"),
+    (40, 8, 1399, 240, 24, 5, 2, "256", "256"),      # a token per key
+    (32, 8, 2100, 192, 96, 3, 1, "256", "256"),      # blocks of 96
+    (2, 1, 8200, 512, 64, 4, 1, "32", "32"),         # dense with eight waves
+    (1, 1, 16001, 240, 48, 5, 1, "32", "32"),        # 534 row tiles
+    (1, 1, 16321, 240, 48, 5, 1, "128", "32"),       # 545 row tiles, short lists
+    (1, 1, 16321, 240, 48, 40, 0, "32", "32"),       # long ones
+    (32, 8, 250, 240, 48, 6, 0, "32", "32"),         # 8000 rows in 288 tiles, 250 keys: four waves
+    (3, 1, 77, 4096, 64, 2, 1, "32", "32"),          # a segment longer than the sequence
+    (24, 8, 800, 4096, 16, 2, 1, "32", "32"),
+    (48, 16, 800, 4096, 16, 2, 1, "256", "32"),
 ]
 
 
@@ -41,10 +44,11 @@ def lists(w, seed):
     return O.select(S, w.segment_size, w.block_size, w.budget_blocks, w.local_blocks)
 
 
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda c: "x".join(map(str, c[:7])))
 def test_both_kernels_against_checker(shape):
-    Hq, Hkv, n, s, b, k, L = shape
+    Hq, Hkv, n, s, b, k, L, sparse, dense = shape
     w = H.small_workload("rows", 1, Hq, Hkv, n, s, b, k, L, unit_variance=n > 1)
+    assert (H.attention_kernel(w), H.attention_kernel(w, False)) == (sparse, dense)
     q, k_, v = synth.make_qkv(w, threads=8)
     qf, kf, vf = (synth.to_f64(t) for t in (q, k_, v))
     # token-major storage, as a model's projections leave it
@@ -70,10 +74,11 @@ def test_both_kernels_against_checker(shape):
 
 
 @pytest.mark.parametrize("b", [64, 32, 16])
-@pytest.mark.parametrize("heads", [2, 20], ids=["32_rows", "256_rows"])
+@pytest.mark.parametrize("heads", [2, 20, 40], ids=["32_rows", "32_rows_more", "256_rows"])
 def test_bad_and_empty_lists(heads, b):
     """Empty lists, a count past the row, negative and too large entries: masked, as in the tests of the 256-row kernel."""
     w = H.small_workload("badrows", 1, heads, 1, 1000, 256, b, 3, 1)
+    assert H.attention_kernel(w) == ("256" if heads == 40 else "32")
     q, k, v = synth.make_qkv(w, threads=4)
     idx, cnt = lists(w, b)
     bad, bad_cnt, ref, ref_cnt = idx.copy(), cnt.copy(), idx.copy(), cnt.copy()

@@ -1,6 +1,6 @@
-"""The 256-row bf16 attention kernel beyond the row counts that the 32-row kernel takes (16384 block-sparse, 32768 dense): shared lists,
-logits far from the unit scale, several batches with head counts that are no powers of two, repeated runs, segments with more trailing
-tiles than a wave looks at in one go, negative counts; in every tile mode (blocks of 64, of 32, of other sizes, dense).  Against the
+"""The 256-row bf16 attention kernel: shared lists, logits far from the unit scale, repeated runs; and the 32-row kernel at some 17000 to 34000
+rows: segments far longer than a workgroup, negative counts, several dense batches with head counts that are no powers of two (the same of the 256-row
+kernel is in test_gpu_bf16_lines.py); in every tile mode (blocks of 64, of 32, of other sizes, dense).  Against the
 checker on sampled segments and rows, with the bars of the other bf16 attention tests."""
 import numpy as np
 import pytest
@@ -50,6 +50,7 @@ def dev(*arrays):
 @pytest.mark.parametrize("b,s", [(64, 512), (32, 256), (24, 240)], ids=["b64", "b32", "b24"])
 def test_shared_lists(b, s):
     w, q, k, v = make(2, 12, 3, 1403, s, b, 5, 1)
+    assert H.attention_kernel(w) == "256"
     idx, cnt = lists(w, w.n_kv_heads)
     out, lse = H.gpu_sparse_shared(w, *dev(q, k, v, idx, cnt))
     check(w, out, lse, q, k, v, *O.expand_shared_lists(idx, cnt, w.n_q_heads), sample(w))
@@ -60,6 +61,7 @@ def test_shared_lists(b, s):
 def test_peaked_and_flat_logits(b, gain):
     """Logits 36 and 0.0025 times as large: the reference point of a row moves again and again, or never after the first tile."""
     w, q, k, v = make(1, 20, 5, 1701, 256, b, 6, 1, gain)
+    assert H.attention_kernel(w) == "256"
     idx, cnt = lists(w, w.n_q_heads)
     out, lse = H.gpu_sparse(w, *dev(q, k, v, idx, cnt))
     check(w, out, lse, q, k, v, idx, cnt, sample(w))
@@ -68,6 +70,7 @@ def test_peaked_and_flat_logits(b, gain):
 @pytest.mark.parametrize("gain", [6.0, 1.0, 0.05])
 def test_dense_batches(gain):
     w, q, k, v = make(2, 12, 3, 1403, 512, 64, 5, 1, gain)
+    assert H.attention_kernel(w, False) == "32"
     assert w.batch * w.n_q_heads * w.seq_len > 32768
     out, lse = (t.float().cpu().numpy() for t in H.gpu_dense(w, *dev(q, k, v)))
     assert np.isfinite(out).all() and np.isfinite(lse).all()
@@ -81,6 +84,7 @@ def test_dense_batches(gain):
 def test_long_segments_drop_many_trailing_tiles(b):
     """Segments of 8192 tokens: the first query tile of one sees 4 of its own 128 tiles of 64 keys."""
     w, q, k, v = make(1, 3, 1, 9001, 8192, b, 4, 0)
+    assert H.attention_kernel(w) == "32"
     idx, cnt = lists(w, w.n_q_heads)
     out, lse = H.gpu_sparse(w, *dev(q, k, v, idx, cnt))
     check(w, out, lse, q, k, v, idx, cnt, [(0, 2, 0), (0, 0, 1), (0, 2, 1)])
@@ -89,6 +93,7 @@ def test_long_segments_drop_many_trailing_tiles(b):
 @pytest.mark.parametrize("b", [64, 32, 16])
 def test_negative_and_zero_counts(b):
     w, q, k, v = make(1, 20, 1, 1000, 256, b, 3, 1)
+    assert H.attention_kernel(w) == "32"
     idx, cnt = lists(w, w.n_q_heads)
     bad, ref = cnt.copy(), cnt.copy()
     bad[0, 0, 1], bad[0, 19, 2], bad[0, 10, 3] = -3, -(1 << 31), 0
@@ -104,6 +109,7 @@ def test_negative_and_zero_counts(b):
 @pytest.mark.parametrize("b", [64, 32, 16])
 def test_run_twice_bit_identical(b):
     w, q, k, v = make(1, 20, 5, 1701, 256, b, 6, 1)
+    assert H.attention_kernel(w) == "256"
     args = dev(q, k, v, *lists(w, w.n_q_heads))
     first, second = H.gpu_sparse(w, *args), H.gpu_sparse(w, *args)
     assert all(torch.equal(x, y) for x, y in zip(first, second))

@@ -1,5 +1,5 @@
 """A whole layer captured into a graph and replayed several times on new inputs, eager work in between: every replay equals the eager
-result bit for bit.  Shapes on both sides of the attention kernels' line, one and several score chunks, shared lists, fp32."""
+result bit for bit.  Every attention kernel, one and several score chunks, rows that are streamed by the selection, shared lists."""
 import pytest
 import torch
 
@@ -11,17 +11,21 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 CASES = [
-    # Hq Hkv    n    s    b   k  dtype
-    (4, 2, 2100, 256, 64, 5, "bf16"),      # 32-row attention, one score chunk
-    (8, 2, 4500, 256, 16, 9, "bf16"),      # 256-row attention, several chunks
-    (4, 1, 1200, 128, 32, 4, "fp32"),
+    # Hq Hkv    n    s    b   k  dtype, kernel of the block-sparse attention
+    (4, 2, 2100, 256, 64, 5, "bf16", "32"),      # one score chunk
+    (8, 2, 4500, 256, 16, 9, "bf16", "256"),     # several chunks
+    (16, 4, 2950, 128, 32, 10, "bf16", "128"),
+    (2, 1, 33100, 512, 16, 9, "bf16", "128"),    # 2069 blocks
+    (4, 1, 1200, 128, 32, 4, "fp32", "fp32"),
+    (8, 2, 1003, 256, 64, 3, "fp32", "split"),
 ]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
 def test_replays_equal_eager(case):
-    Hq, Hkv, n, s, b, k, dtype = case
+    Hq, Hkv, n, s, b, k, dtype, kernel = case
     w = H.small_workload("capture", 1, Hq, Hkv, n, s, b, k, 1, dtype=dtype, unit_variance=True)
+    assert H.attention_kernel(w) == kernel
     sets = [[t.to(DEV) for t in synth.make_qkv(w.replace(seed=w.seed + i), threads=4)] for i in range(3)]
     q, k_, v = (t.clone() for t in sets[0])
     out = torch.empty_like(q)

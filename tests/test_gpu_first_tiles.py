@@ -10,9 +10,11 @@ from tests import helpers as H
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("b,s", [(64, 256), (128, 256), (192, 384), (32, 256), (96, 288)], ids=["b64", "b128", "b192", "b32", "b96"])
-def test_blocks_behind_the_count(b, s):
-    w, q, k, v = make(1, 40, 4, 1201, s, b, 5, 1)                 # enough rows for the 256-row kernel
+@pytest.mark.parametrize("b,s,kernel", [(64, 256, "256"), (128, 256, "256"), (192, 768, "256"), (32, 256, "256"), (96, 768, "256"), (192, 384, "128"), (96, 288, "128")],
+                         ids=["b64", "b128", "b192", "b32", "b96", "b192_128_rows", "b96_128_rows"])
+def test_blocks_behind_the_count(b, s, kernel):
+    w, q, k, v = make(1, 40, 4, 1201, s, b, 5, 1)
+    assert H.attention_kernel(w) == kernel
     idx, cnt = lists(w, w.n_q_heads)
     ref, ref_cnt = idx.copy(), cnt.copy()
     for h in range(w.n_q_heads):
@@ -29,6 +31,7 @@ def test_blocks_behind_the_count(b, s):
 @pytest.mark.parametrize("b", [32, 64])
 def test_lists_of_more_than_512_entries(b):
     w, q, k, v = make(1, 2 if b == 32 else 1, 1, 520 * b + 64, 512, b, 515, 1)
+    assert H.attention_kernel(w) == "256"
     idx, cnt = lists(w, w.n_q_heads)
     assert cnt.max() > 512
     out, lse = H.gpu_sparse(w, *dev(q, k, v, idx, cnt))

@@ -26,12 +26,6 @@ def lists(w, heads, seed=3):
     return O.select(S, w.segment_size, w.block_size, w.budget_blocks, w.local_blocks)
 
 
-def tiles(w, sparse):
-    s = w.segment_size if sparse else w.seq_len
-    rest = w.seq_len % s
-    return w.batch * w.n_q_heads * (w.seq_len // s * -(-s // 32) + -(-rest // 32))
-
-
 def exact(q, k, v, visible):
     """softmax(q k^T / sqrt(d)) v in float64; visible [.., rows, keys]."""
     z = torch.matmul(q.double(), k.double().transpose(-1, -2).contiguous()) / q.shape[-1] ** 0.5
@@ -70,7 +64,7 @@ def check(w, out, lse, q, k, v, idx, cnt):
 SPARSE = [
     # Bt, Hq, Hkv, n, s, b, k, L: runs of 16 that pair up across blocks, odd numbers of them, ragged ends inside a run
     (1, 8, 2, 1003, 128, 16, 5, 1), (1, 8, 2, 1400, 144, 16, 20, 0), (1, 8, 4, 1601, 112, 16, 9, 1), (2, 5, 5, 900, 256, 32, 7, 1), (1, 12, 3, 1111, 240, 48, 6, 2),
-    (1, 16, 1, 1000, 320, 80, 4, 1), (1, 10, 2, 1025, 512, 64, 3, 1), (1, 3, 1, 2900, 256, 128, 6, 0), (2, 4, 2, 2100, 512, 64, 24, 1), (1, 2, 1, 4100, 4096, 64, 8, 0),
+    (1, 16, 1, 1000, 320, 80, 4, 1), (1, 10, 2, 1025, 512, 64, 3, 1), (1, 3, 1, 2900, 256, 128, 6, 0), (2, 4, 2, 2100, 512, 64, 24, 1), (1, 3, 1, 4100, 4096, 64, 8, 0),
 ]
 
 
@@ -78,7 +72,7 @@ SPARSE = [
 @pytest.mark.parametrize("token_major", [False, True])
 def test_sparse(shape, token_major):
     w, q, k, v = make(*shape)
-    assert tiles(w, True) >= 256
+    assert H.attention_kernel(w) == "split"
     idx, cnt = lists(w, w.n_q_heads)
     if token_major:
         q, k, v = (x.transpose(1, 2).contiguous().transpose(1, 2) for x in (q, k, v))
@@ -86,11 +80,11 @@ def test_sparse(shape, token_major):
     check(w, out, lse, q, k, v, idx, cnt)
 
 
-@pytest.mark.parametrize("shape", [(1, 8, 2, 1000), (1, 8, 2, 1003), (2, 5, 5, 833), (1, 4, 2, 2065), (1, 20, 4, 1031), (1, 32, 8, 257), (1, 300, 300, 17), (1, 260, 1, 33)],
+@pytest.mark.parametrize("shape", [(1, 8, 2, 1000), (1, 8, 2, 1003), (2, 5, 5, 833), (1, 6, 2, 2065), (1, 20, 4, 1031), (1, 32, 8, 257), (1, 300, 300, 17), (1, 260, 1, 33)],
                          ids=lambda t: "x".join(map(str, t)))
 def test_dense(shape):
     w, q, k, v = make(*shape, 256, 64, 4, 1)
-    assert tiles(w, False) >= 256
+    assert H.attention_kernel(w, False) == "split"
     out, lse = H.gpu_dense(w, q, k, v)
     o_ref, lse_ref = dense_exact(w, q, k, v)
     assert rel(out, o_ref) <= 1e-6 and rel(lse, lse_ref) <= 1e-6
@@ -218,7 +212,7 @@ def test_light_keys(case, b):
     q[..., 0] = 1.0
     k[:, :, 1:, 0] = logit * 128 ** 0.5
     v[:, :, 0] = heavy
-    assert tiles(w, bool(b)) >= 256
+    assert H.attention_kernel(w, bool(b)) == "split"
     out, lse = H.gpu_sparse(w, q, k, v, *every_block(w, b)) if b else H.gpu_dense(w, q, k, v)
     ref, lse_ref = O.dense_causal_attention(synth.to_f64(q[:, :1].cpu()), synth.to_f64(k[:, :1].cpu()), synth.to_f64(v[:, :1].cpu()))
     for h in (0, 7, 31):
@@ -303,6 +297,7 @@ def test_runs_behind_the_last_row():
     """A tile's second run that lies behind the workgroup's last row is not touched: segments of three runs behind an odd number of blocks, so that the
     second and third of a segment share a tile, of which the rows of its first 32 see one."""
     w, q, k, v = make(1, 8, 2, 1203, 48, 16, 5, 0)
+    assert H.attention_kernel(w) == "split"
     idx, cnt = (torch.from_numpy(x).to(DEV) for x in lists(w, 8))
     out, lse = H.gpu_sparse(w, q, k, v, idx, cnt)
     first = 10 * 48 + 32

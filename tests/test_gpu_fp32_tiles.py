@@ -1,5 +1,5 @@
-"""The fp32 attention kernel at the borders of its variants: 16 or 32 rows per workgroup, keys split over 4 or 8 waves,
-tiles of 16 consecutive tokens or one token per key.  Against the fp64 checker with the fp32 bars of the other tests
+"""The fp32 attention kernels at the borders of their variants: fp32 products or split ones, keys divided between 4 or 8 waves,
+tiles of consecutive tokens or one token per key.  Against the fp64 checker with the fp32 bars of the other tests
 (unit-variance inputs, so logits of a few units: 128 products and the weighted sum round to about 1e-6)."""
 import numpy as np
 import pytest
@@ -18,9 +18,9 @@ SHAPES = [
     (1, 1, 1, 16, 16, 1, 0),              # one query, one key
     (2, 1, 271, 128, 16, 3, 1),           # 16 rows, 4 waves, most of them without a tile; a last tile of 15 tokens
     (2, 2, 1553, 288, 48, 40, 0),         # 16 rows, 8 waves; 48 does not divide 8 x 16 keys
-    (8, 4, 1601, 128, 32, 60, 1),         # 32 rows, 8 waves; a last row tile of one row
-    (8, 2, 2064, 256, 64, 4, 1),          # 32 rows: 4 waves for the short lists, 8 for dense
-    (16, 4, 3120, 512, 128, 16, 0),       # 32 rows, 4 waves: many workgroups
+    (8, 4, 1601, 128, 32, 60, 1),         # split products, 8 waves; a last row tile of one row
+    (8, 2, 2064, 256, 64, 4, 1),          # split: 4 waves for the short lists, 8 for dense
+    (16, 4, 3120, 512, 128, 16, 0),       # split, 4 waves: many workgroups
     (3, 1, 500, 72, 24, 4, 1),            # blocks of 24: one token per key; segments no multiple of a row tile
 ]
 

@@ -112,7 +112,7 @@ def test_select_negative_and_large_budget():
 
 @pytest.mark.parametrize("n_blocks,budget", [(4096, 32), (8192, 100)])
 def test_select_long_rows_with_ties(n_blocks, budget):
-    """Rows of 4096 blocks (64 per lane) and 8192 blocks (one workgroup per row), scores quantised to a handful of
+    """Rows of 4096 and 8192 blocks (streamed for these budgets), scores quantised to a handful of
     levels so that the k-th score is shared by hundreds of blocks and the smallest-index tie rule decides."""
     b = 16
     w = H.small_workload("long", 1, 2, 1, n_blocks * b, 512, b, budget, 2)

@@ -1,5 +1,5 @@
-"""Lists from rows that are streamed: more than 2048 blocks, per head and shared, with row ends that no load
-divides, at the edges of both bucket counts, bit-exact against the checker's rule on the same scores.  The score layouts reach every way out
+"""Lists from rows of more than 2048 blocks, per head and shared: streamed for budgets up to 256, held in registers (up to 4096 blocks) or
+searched by a workgroup each above.  With row ends that no load divides, at the edges of both bucket counts, bit-exact against the checker's rule on the same scores.  The score layouts reach every way out
 of the search: few candidates, more than one search's worth, too many equal to the threshold (found again above it, or ties to be
 counted out), and large scores that share their buckets (searched in the row itself)."""
 import numpy as np
@@ -57,3 +57,22 @@ def test_rows_of_a_group(n_blocks, budget, kind):
     q = torch.empty((1, 6, w.seq_len, 128), dtype=torch.bfloat16, device=DEV)
     k = torch.empty((1, 2, w.seq_len, 128), dtype=torch.bfloat16, device=DEV)
     H.check_selection(Sg, idx_o, cnt_o, *H.gpu_select_shared(w, q, k, torch.from_numpy(S).to(DEV)), w, exact=True)
+
+
+@pytest.mark.parametrize("kind", ["spread", "zeros", "few_values", "constant"])
+@pytest.mark.parametrize("n_blocks,budget", [(2049, 257), (3001, 300), (4096, 257), (4096, 1000), (4099, 257), (8192, 300), (8192, 2000)])
+def test_budgets_above_the_stream(n_blocks, budget, kind):
+    """Per head; shared between two query heads; and shared with one query head to a KV head, of up to 512 lists (a workgroup each) and of more."""
+    b, s = 16, 1024
+    for heads, kv, seg in [(2, 1, s), (2, 2, s), (2, 2, 128)] if n_blocks == 4096 else [(2, 1, s), (2, 2, s)]:
+        w = H.small_workload("above", 1, heads, kv, n_blocks * b, seg, b, budget, 1)
+        print(n_blocks, budget, kind, heads, kv, w.n_segments, flush=True)
+        S = scores(kind, (1, heads, w.n_segments, w.n_blocks), np.random.default_rng(n_blocks + budget))
+        q = torch.empty((1, heads, w.seq_len, 128), dtype=torch.bfloat16, device=DEV)
+        k = torch.empty((1, kv, w.seq_len, 128), dtype=torch.bfloat16, device=DEV)
+        if kv == 1:
+            idx_o, cnt_o = O.select(S, seg, b, budget, 1)
+            H.check_selection(S, idx_o, cnt_o, *H.gpu_select(w, q, k, torch.from_numpy(S).to(DEV)), w, exact=True)
+        Sg = O.shared_group_scores(S, kv)
+        idx_o, cnt_o = O.select(Sg, seg, b, budget, 1)
+        H.check_selection(Sg, idx_o, cnt_o, *H.gpu_select_shared(w, q, k, torch.from_numpy(S).to(DEV)), w, exact=True)
