@@ -100,8 +100,9 @@ constexpr int kPrefilterMaxK = 128;                     // and is used for k up 
 // in index order into the wave's LDS region (at most 4 per lane) and the exact search runs on them: the same list,
 // ties included, with a fraction of the compares.  A row with more than 256 keys >= T (many equal scores) is
 // searched in full.
+// THIN: not for rows of more than 2048 blocks, which come here with k above 256 only (without it, 32 heads x 128K tokens in blocks of 32, k = 300 177 -> 89 us).
 // merged: the row's keys in LDS (SHARED), else they come from the scores.
-template <int PER_LANE, bool SHARED>
+template <int PER_LANE, bool SHARED, bool THIN>
 __device__ __forceinline__ int select_row(const SelectArgs& a, long long row, int n_cand, int kj, int lane,
                                           int32_t* out, uint2* cand, const uint32_t* merged) {
     uint32_t key[PER_LANE];
@@ -111,7 +112,7 @@ __device__ __forceinline__ int select_row(const SelectArgs& a, long long row, in
         const uint32_t kx = SHARED ? merged[min(i, n_cand - 1)] : row_key<false>(a, row, 0, min(i, a.n2 - 1));   // unconditional load: no per-element exec masks to keep
         key[m] = (i < n_cand) ? kx : 0u;                   // 0 is below every trial threshold: never counted
     }
-    if (PER_LANE > kCandPerLane && kj <= kPrefilterMaxK) {
+    if (THIN && PER_LANE > kCandPerLane && kj <= kPrefilterMaxK) {
         uint32_t top[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int m = 0; m < PER_LANE; ++m) top[m & 3] = max(top[m & 3], key[m]);
@@ -192,7 +193,8 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
     const int n_cand = diag_lo - n_local;
     const int kj = min(a.budget, n_cand);
     int32_t* out = a.idx + row * a.list_len;
-    __shared__ uint2 cand_all[SHARED ? 1 : 4][64 * kCandPerLane];
+    constexpr bool THIN = MAX_PER_LANE <= 32;
+    __shared__ uint2 cand_all[SHARED ? 1 : 4][THIN ? 64 * kCandPerLane : 1];
     uint2* cand = cand_all[SHARED ? 0 : threadIdx.x >> 6];
     __shared__ uint32_t merged[SHARED ? 64 * MAX_PER_LANE : 1];
     if (SHARED) {                                              // the whole workgroup merges the group's scores, one wave searches
@@ -206,14 +208,14 @@ __global__ __launch_bounds__(256) void select_kernel(SelectArgs a) {
         constexpr int E = MAX_PER_LANE / 8;
         const int eighths = (n_cand + 64 * E - 1) / (64 * E);          // wave-uniform, 1 .. 8
         switch (eighths) {
-            case 1: written = select_row<1 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
-            case 2: written = select_row<2 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
-            case 3: written = select_row<3 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
-            case 4: written = select_row<4 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
-            case 5: written = select_row<5 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
-            case 6: written = select_row<6 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
-            case 7: written = select_row<7 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
-            default: written = select_row<8 * E, SHARED>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            case 1: written = select_row<1 * E, SHARED, THIN>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            case 2: written = select_row<2 * E, SHARED, THIN>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            case 3: written = select_row<3 * E, SHARED, THIN>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            case 4: written = select_row<4 * E, SHARED, THIN>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            case 5: written = select_row<5 * E, SHARED, THIN>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            case 6: written = select_row<6 * E, SHARED, THIN>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            case 7: written = select_row<7 * E, SHARED, THIN>(a, row, n_cand, kj, lane, out, cand, merged); break;
+            default: written = select_row<8 * E, SHARED, THIN>(a, row, n_cand, kj, lane, out, cand, merged); break;
         }
     }
     finish_row(a, row, n_cand, diag_hi, written, lane, out);
@@ -513,7 +515,7 @@ hipError_t launch_select_impl(const Shape& sh, const float* scores, int32_t* idx
     const unsigned grid = (unsigned)(SHARED ? a.rows : (a.rows + 3) / 4);
     // Streamed: rows of more than 2048 blocks.  Up to there a wave holds its row without losing the company of others (per-head lists in
     // registers / streamed, 32 heads x 128K tokens in blocks of 64: 18.8 / 24.2 us; shared ones 17.4 / 16.1, but 20000 tokens in blocks of 16
-    // 9.6 / 10.3).  k above 256 would need 1024 buckets (k = 300 of 2063 blocks: 34 / 34 us, with many zeros 43 / 67).
+    // 9.6 / 10.3).  k above 256 would need 1024 buckets (32 heads, k = 300 of 2063 blocks: 22 / 34 us, with many zeros 30 / 67).
     if (sh.n2 <= 64 * 8) hipLaunchKernelGGL((select_kernel<8, SHARED>), dim3(grid), dim3(256), 0, st, a);
     else if (sh.n2 <= 64 * 32) hipLaunchKernelGGL((select_kernel<32, SHARED>), dim3(grid), dim3(256), 0, st, a);
     else if (sh.budget <= kStreamMaxK) {
@@ -526,13 +528,10 @@ hipError_t launch_select_impl(const Shape& sh, const float* scores, int32_t* idx
     return hipGetLastError();
 }
 
-// A KV head with one query head has that head's list: the per-head kernel, four rows to a workgroup, unless the rows are held in registers, long and
-// so few that a workgroup each fits the chip twice (128K tokens in blocks of 32, k > 256, a workgroup / a wave per list: 256 lists 13 / 17 us,
-// 512 14 / 17, 2048 34 / 25, 8192 129 / 83).  Streamed, a wave per list is the faster one there too (512 lists 14 / 12).
+// A KV head with one query head has that head's list: the per-head kernel, four rows to a workgroup.  (A workgroup per list, where rows are held in registers, 128K
+// tokens in blocks of 32, k = 300, a wave / a workgroup: 256 lists 35 / 35 us, 512 35 / 38, 8192 88 / 123.)
 hipError_t launch_select(const Shape& sh, const float* scores, int32_t* idx, int32_t* cnt, bool shared, hipStream_t st) {
-    const bool few = sh.budget > kStreamMaxK && sh.n2 > 64 * 32 && sh.n2 <= 64 * 64 && (long long)sh.batch * sh.hkv * sh.n1 <= 512;
-    return shared && (sh.hq != sh.hkv || few) ? launch_select_impl<true>(sh, scores, idx, cnt, st)
-                                              : launch_select_impl<false>(sh, scores, idx, cnt, st);
+    return shared && sh.hq != sh.hkv ? launch_select_impl<true>(sh, scores, idx, cnt, st) : launch_select_impl<false>(sh, scores, idx, cnt, st);
 }
 
 }  // namespace cp

@@ -62,7 +62,7 @@ def test_rows_of_a_group(n_blocks, budget, kind):
 @pytest.mark.parametrize("kind", ["spread", "zeros", "few_values", "constant"])
 @pytest.mark.parametrize("n_blocks,budget", [(2049, 257), (3001, 300), (4096, 257), (4096, 1000), (4099, 257), (8192, 300), (8192, 2000)])
 def test_budgets_above_the_stream(n_blocks, budget, kind):
-    """Per head; shared between two query heads; and shared with one query head to a KV head, of up to 512 lists (a workgroup each) and of more."""
+    """Per head; shared between two query heads; and shared with one query head to a KV head, few lists and many."""
     b, s = 16, 1024
     for heads, kv, seg in [(2, 1, s), (2, 2, s), (2, 2, 128)] if n_blocks == 4096 else [(2, 1, s), (2, 2, s)]:
         w = H.small_workload("above", 1, heads, kv, n_blocks * b, seg, b, budget, 1)
