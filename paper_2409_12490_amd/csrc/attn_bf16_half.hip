@@ -12,9 +12,10 @@
 // they delay it: 32 heads x 8192 tokens (segments of 128, 416 keys) 83.0 against 75.5 us, 2 x 8 x 93184 (672 keys) 614 against 603; only for long
 // lists it is the better place (4256 keys 427 against 442).
 //
-// What bounds it: like the 256-row kernel the matrix pipe and the vector unit under a power-bound clock, with twice its reads from the caches; where that kernel
-// has no empty waves it is 7 to 15 % slower.  2 x 8 x 93184 tokens: 466 GFLOP in 581 us, 0.80 PFLOP/s; the 32-row kernel, which reads the
-// keys four times as often, took 988.
+// What bounds it: neither the matrix pipe (37 % busy) nor the vector unit (35 %) nor the caches (6.8 TB/s) alone, at a power-bound clock of 2.0 GHz: two waves to a SIMD take
+// turns at phases that depend on each other, and short items start and end often.  It reads the keys twice as often as the 256-row kernel and is 7 to 15 %
+// slower where that has no empty waves.  2 x 8 x 93184 tokens: 466 GFLOP in 581 us, 0.80 PFLOP/s; the 32-row kernel, which reads the keys four
+// times as often, took 988.
 #include "attn_bf16.h"
 
 #include <algorithm>
@@ -27,7 +28,8 @@ constexpr int kWaves = TQ / WQ;
 constexpr int kTileBytes = TK * 256;
 constexpr int kKOff = 0, kVOff = 2 * kTileBytes;  // two slots each
 constexpr int kTabOff = 4 * kTileBytes;           // sparse: first tokens of the four runs of every tile
-constexpr int kTabMax = 12 * 1024;                // of 80 KiB
+constexpr int kTabMax = 12 * 1024;                // of 80 KiB: lists of up to 49152 keys.  Longer ones are for the other two kernels, with segments of 65 to 128
+                                                  // rows for the 32-row one, which takes 1.3 times the time (4256 keys)
 constexpr int kOutPitch = 272;                    // epilogue staging: one output row + 16 B, in bytes
 constexpr unsigned kRound = 512;                  // workgroups that the chip holds
 constexpr int kLook = 3;                          // LDS fragments read ahead of their MFMAs
@@ -335,7 +337,7 @@ long long table_bytes(const Shape& sh) { return ((long long)sh.list_len * sh.b +
 //   Up to 64 rows half of this kernel is empty too: 32 x 8192, segments of 64 158 / 173.
 //   Segments that fill a quarter less of its workgroups: of 384 225 / 177, 1291 / 1158, of 320 252 / 202; as much of either: of 192 145 / 140, 265 / 279, 997 / 1064.
 //   Else it reads the keys twice as often and loses (32 x 16384, segments of 512, 1600 keys 356 / 385, 32 x 50000 1058 / 1216), but not where 256-row
-//   workgroups leave half of the chip idle (w = 128: 8 x 4000 21.0 / 19.7, 37.8 / 36.5, 25.6 / 24.3, 42.2 / 40.9; w = 250: 8 x 8000 25.2 / 26.2) and for short
+//   workgroups leave half of the chip idle (w = 128: 8 x 4000 21.0 / 19.7, 37.8 / 36.5, 25.6 / 24.3, 42.2 / 40.9; w = 188 to 256: 8 x 6000 21.0 / 22.0, 32 x 1500 35.8 / 37.3, 8 x 8000 25.2 / 26.2, 41.0 / 43.1, 32 x 2000 39.1 / 41.4, 16 x 4000 40.2 / 42.6) and for short
 //   lists of blocks of an odd multiple of 16, whose keys that kernel takes one by one (528, 784, 1296 keys: w = 500 50.7 / 46.2, 62.7 / 59.3, 89 / 85, w = 2048 189 / 174,
 //   247 / 236, 346 / 355; w = 6272 (784) 639 / 632).
 bool attn_bf16_half_better(const Shape& sh) {

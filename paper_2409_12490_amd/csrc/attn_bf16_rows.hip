@@ -11,10 +11,10 @@
 // for when QK has read this one, V when PV has; each has half a tile's time to land, and loads return in order, so the other may be on its way.
 //
 // What bounds it: K as A operands straight from memory, a lane per row, asked the address unit of a compute unit for 512 pieces of 16 bytes a tile and Q for 512
-// more per wave, one a cycle: that bound the kernel (640 of them a tile, 2560 of the 3000 cycles that four waves take).  By whole rows it is 256 pieces of 64
+// more per wave, one a cycle: that bound the kernel.  By whole rows it is 256 pieces of 64
 // bytes: dense 2 heads x 600 tokens 9.9 -> 7.3 us, 4 x 3000 32.4 -> 20.5, 2 x 8192 88 -> 53; block-sparse 4 x 4000 (blocks of 16) 28.7 -> 18.6, 2 x 5632 24.7 ->
-// 17.5, 8 x 1024 14.4 -> 10.6.  What is left is latency up to a few hundred workgroups, beyond that the caches: every 32 rows read their keys
-// anew, eight times the bytes of the 256-row kernel.
+// 17.5, 8 x 1024 14.4 -> 10.6.  What is left is latency up to a few hundred workgroups, beyond that the caches (19 TB/s for dense 2 x 8192): every 32
+// rows read their keys anew, eight times the bytes of the 256-row kernel.
 #include "attn_bf16.h"
 
 #include <algorithm>
