@@ -36,6 +36,9 @@ struct Args32 {
     long long qs0, qs1, qs2, ks0, ks1, ks2, os0, os1, os2;
 };
 
+// Row tiles of `rows` that exist: a segment's last one may be short.
+long long attn_fp32_row_tiles(const Shape& sh, bool sparse, int rows);
+
 // Attention with fp32 factors split into three bf16 values, and whether it is the better one here.
 bool attn_fp32_split_better(const Shape& sh, bool sparse);
 hipError_t launch_attn_fp32_split(const Shape& sh, Args32& a, hipStream_t st);

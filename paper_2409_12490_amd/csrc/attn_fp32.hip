@@ -22,7 +22,7 @@
 //
 // This kernel takes the launches that are too small for attn_fp32_split.hip, and the block sizes and strides that are not for it.
 //
-// What bounds it: latency, where few workgroups fill the chip (one head x 2048 tokens, 384 keys: 13.7 us, against 85 of a vector-FMA loop over
+// What bounds it: latency, where few workgroups fill the chip (one head x 2048 tokens, 384 keys: 10.2 us, against 85 of a vector-FMA loop over
 // 32 x 32 tiles in LDS), and the fp32 matrix instructions, which share their units with the vector instructions (measured: a wave's softmax and address
 // arithmetic add their time to the MFMAs of all waves of the SIMD).  So the key loop keeps them few: tiles of 16 consecutive tokens with their
 // addresses on the scalar unit (MODE 1/2), O rescaled only in tiles where some row's max moves.
@@ -38,15 +38,19 @@ __device__ __forceinline__ float group_max(float x) {               // over the 
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// C workgroups (blockIdx.y) share a row tile, each with its part of the channels of V and O: see launch_tiled.
 // MODE 0: any block size and any stride (dense if there is no list): every key of a tile has a token of its own.  MODE 1: sparse, block size a multiple of
 // 16: a tile is 16 consecutive tokens, described by its first token on the scalar unit.  MODE 2: dense.
-template <int MODE, int RT, int W>
+template <int MODE, int RT, int W, int C>
 __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kernel(Args32 a) {
     constexpr bool RUN = MODE != 0;
     constexpr int TQ = 16 * RT, TK = 16;
     constexpr int kNoToken = 0x7fffffff;                            // a key that does not exist: after every query
     const bool dense = MODE == 2 || (MODE == 0 && !a.idx);
-    __shared__ __attribute__((aligned(1024))) float part_o[W * TQ * kHeadDim];   // 16-byte chunks XOR-swizzled by the row
+    constexpr int CH = kHeadDim / C, CHUNKS = CH / 4;               // channels of the output
+    const int part = C > 1 ? blockIdx.y : 0;
+    constexpr int PIECES = C == 1 ? 2 : 1, E = CH / (16 * PIECES);  // a lane's floats of a row of V: PIECES of E, 16 E apart
+    __shared__ __attribute__((aligned(1024))) float part_o[W * TQ * CH];     // 16-byte chunks XOR-swizzled by the row
     __shared__ float part_m[W * TQ], part_l[W * TQ];
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -65,7 +69,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
     if (q_lo >= q_end) return;                                     // uniform: tile past a short segment
     const int q_last = min(q_end, q_lo + TQ) - 1;
     const float* kp = a.k + bb * a.ks0 + kvh * a.ks1;
-    const float* vp = a.v + bb * a.ks0 + kvh * a.ks1;
+    const float* vp = a.v + bb * a.ks0 + kvh * a.ks1 + part * CH;
 
     scalar_list list = nullptr; int count = 0;
     if (!dense) {
@@ -80,7 +84,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
     // each in LDS, 14.8: with one wave to a SIMD the way through LDS costs more than the address unit did.)
     const unsigned lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) float*)part_o;
     if (RUN) {
-        static_assert(!RUN || RT == 1, "16 rows of Q take the place of the first partial O");
+        static_assert(!RUN || (RT == 1 && W * CH >= kHeadDim), "16 rows of Q take the place of partial Os");
         const int l32 = lane & 31, hh = lane >> 5;
 #pragma unroll
         for (int x = 0; x < 8 / W; ++x) {
@@ -127,14 +131,15 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
         return t < ntiles && e < (unsigned)count && blk >= 0 && tk < a.n ? (int)tk : kNoToken;
     };
 
-    f32x4 kf[8], vf[4][2];
+    typedef __attribute__((ext_vector_type(E))) float f32xE;
+    f32x4 kf[8]; f32xE vf[4][PIECES];
     auto load_k = [&](const float* rows, unsigned off) {            // 32-bit byte offset from a wave-uniform address (MODE 1/2)
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) kf[kk] = *(const f32x4*)((const char*)rows + off + 64 * kk);
     };
     auto load_v = [&](int r, const float* rows, unsigned off) {
-        vf[r][0] = *(const f32x4*)((const char*)rows + off);
-        vf[r][1] = *(const f32x4*)((const char*)rows + off + 256);
+#pragma unroll
+        for (int hf = 0; hf < PIECES; ++hf) vf[r][hf] = *(const f32xE*)((const char*)rows + off + 256 * hf);
     };
     // MODE 1/2: the lane's offsets inside a tile of 16 existing tokens.  In the last, ragged tile of the sequence the rows
     // past its end repeat the last token; they lie after every query and are masked.
@@ -142,7 +147,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
     const unsigned k_full = c16 * row_bytes + 16 * g;
     unsigned v_full[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) v_full[r] = (4 * g + r) * row_bytes + 16 * c16;
+    for (int r = 0; r < 4; ++r) v_full[r] = (4 * g + r) * row_bytes + 4 * E * c16;
     auto load_k_run = [&](int base) {
         const int b0 = max(base, 0);
         unsigned off = k_full;
@@ -155,22 +160,22 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
         for (int r = 0; r < 4; ++r) off[r] = v_full[r];
         if (base + TK > a.n) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) off[r] = min(4 * g + r, a.n - 1 - base) * row_bytes + 16 * c16;
+            for (int r = 0; r < 4; ++r) off[r] = min(4 * g + r, a.n - 1 - base) * row_bytes + 4 * E * c16;
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) load_v(r, vp + (long long)base * a.ks2, off[r]);
     };
     auto load_k_token = [&](int tok) { load_k(kp + (long long)(tok == kNoToken ? 0 : tok) * a.ks2 + 4 * g, 0u); };
 
-    f32x4 o[RT][2][4];
+    f32x4 o[RT][PIECES][E];
     float m[RT], l[RT];                                             // m: running max of the raw logits
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         m[rt] = -INFINITY; l[rt] = 0.f;
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf)
+        for (int hf = 0; hf < PIECES; ++hf)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[rt][hf][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int e = 0; e < E; ++e) o[rt][hf][e] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
     int base = -1, tok = kNoToken;
@@ -196,7 +201,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 ktok[r] = __shfl(tok, 4 * g + r);
-                load_v(r, vp + (long long)(ktok[r] == kNoToken ? 0 : ktok[r]) * a.ks2 + 4 * c16, 0u);
+                load_v(r, vp + (long long)(ktok[r] == kNoToken ? 0 : ktok[r]) * a.ks2 + E * c16, 0u);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -249,22 +254,25 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
             m[rt] = m_new;
             if (__ballot(alpha != 1.0f) != 0) {
 #pragma unroll
-                for (int hf = 0; hf < 2; ++hf)
+                for (int hf = 0; hf < PIECES; ++hf)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) o[rt][hf][e] *= alpha;
+                    for (int e = 0; e < E; ++e) o[rt][hf][e] *= alpha;
             }
         }
         if (missing) {                                              // 0 * V must be 0, whatever token 0 holds
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (ktok[r] == kNoToken) { vf[r][0] = f32x4{0.f, 0.f, 0.f, 0.f}; vf[r][1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+                if (ktok[r] == kNoToken) {
+#pragma unroll
+                    for (int hf = 0; hf < PIECES; ++hf) vf[r][hf] = 0.f;
+                }
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int hf = 0; hf < 2; ++hf)
+            for (int hf = 0; hf < PIECES; ++hf)
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
+                for (int e = 0; e < E; ++e)
 #pragma unroll
                     for (int rt = 0; rt < RT; ++rt)
                         o[rt][hf][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][hf][e], s[rt][0][r], o[rt][hf][e], 0, 0, 0);
@@ -278,20 +286,24 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
         l[rt] += __shfl_xor(l[rt], 16); l[rt] += __shfl_xor(l[rt], 32);
         const int row = 16 * rt + c16;
         if (g == 0) { part_m[wave * TQ + row] = m[rt]; part_l[wave * TQ + row] = l[rt]; }
-        float* dst = part_o + (wave * TQ + row) * kHeadDim;
+        float* dst = part_o + (wave * TQ + row) * CH;
 #pragma unroll
-        for (int hf = 0; hf < 2; ++hf)
+        for (int hf = 0; hf < PIECES; ++hf)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {                           // channels 64*hf + 16*g + 4*r .. +3
-                const int chunk = (16 * hf + 4 * g + r) ^ c16;
-                *(f32x4*)(dst + 4 * chunk) = f32x4{o[rt][hf][0][r], o[rt][hf][1][r], o[rt][hf][2][r], o[rt][hf][3][r]};
+            for (int r = 0; r < E; ++r) {                           // channels 64*hf + 4*E*g + 4*r .. +3: from E to a matrix row
+                const int chunk = (16 * hf + E * g + r) ^ (c16 & (CHUNKS - 1));
+                f32x4 w;
+#pragma unroll
+                for (int x = 0; x < 4; ++x) w[x] = o[rt][hf][x % E][(4 * r + x) / E];
+                *(f32x4*)(dst + 4 * chunk) = w;
             }
     }
     __syncthreads();
-    float* op = a.out + bb * a.os0 + h * a.os1;
+    float* op = a.out + bb * a.os0 + h * a.os1 + part * CH;
 #pragma unroll
-    for (int c = 0; c < TQ * 32 / (64 * W); ++c) {
-        const int row = (c * 64 * W + tid) >> 5, chunk = tid & 31;
+    for (int c = 0; c < (TQ * CHUNKS + 64 * W - 1) / (64 * W); ++c) {
+        const int row = (c * 64 * W + tid) / CHUNKS, chunk = tid % CHUNKS;
+        if (row >= TQ) break;
         float M = -INFINITY, L = 0.f;
 #pragma unroll
         for (int w = 0; w < W; ++w) M = fmaxf(M, part_m[w * TQ + row]);
@@ -301,33 +313,41 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
         for (int w = 0; w < W; ++w) {
             const float f = exp2f((part_m[w * TQ + row] - M_safe) * a.scale_log2e);
             L += f * part_l[w * TQ + row];
-            sum += f * *(const f32x4*)(part_o + (w * TQ + row) * kHeadDim + 4 * (chunk ^ (row & 15)));
+            sum += f * *(const f32x4*)(part_o + (w * TQ + row) * CH + 4 * (chunk ^ (row & 15 & (CHUNKS - 1))));
         }
         const int qpos = q_lo + row;
         if (qpos < q_end) {
             const float inv = L > 0.f ? 1.0f / L : 0.f;
             *(f32x4*)(op + (long long)qpos * a.os2 + 4 * chunk) = sum * inv;
-            if (a.lse && chunk == 0)
+            if (a.lse && chunk == 0 && part == 0)
                 a.lse[((long long)bb * a.hq + h) * a.n + qpos] = L > 0.f ? M * a.scale + logf(L) : -INFINITY;
         }
     }
 }
 
-template <int MODE, int RT, int W>
+template <int MODE, int RT, int W, int C>
 hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
     a.qtiles = ((a.idx ? min(sh.s, sh.n) : sh.n) + 16 * RT - 1) / (16 * RT);    // a segment may be set longer than the sequence
     const long long grid = (long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1);
-    hipLaunchKernelGGL((attn_fp32_kernel<MODE, RT, W>), dim3((unsigned)grid), dim3(64 * W), 0, st, a);
+    hipLaunchKernelGGL((attn_fp32_kernel<MODE, RT, W, C>), dim3((unsigned)grid, C), dim3(64 * W), 0, st, a);
     return hipGetLastError();
 }
 
 // 16 rows to a workgroup: what is left to this kernel are launches that 32 rows would not fill the chip with, or not evenly (attn_fp32_split_better).  Eight waves
-// split a long row further, four are better where rows are short.  Attention alone, us, four / eight waves (workgroups of 32 rows in brackets): dense 1 head
-// x 2048 tokens (64) 43 / 41; block-sparse 1 x 2048, 416 keys (64) 13.9 / 14.7.
+// split a long row further, four are better where rows are short.  Attention alone, us, four / eight waves (row tiles in brackets): dense 8 heads x 512 tokens (256)
+// 13.5 / 14.6, 1 x 3000 (188) 57.5 / 56.2; block-sparse 1 x 2100 (132; 384 keys) 12.0 / 12.4, 1 x 3000 (188; 1056) 25.4 / 24.0, 1 x 4000 (250; 1216) 28.3 / 27.2, 2 x 1500
+// (188; all keys) 34.1 / 31.8.
+// Up to kHalfTiles row tiles two workgroups take a tile, each with half of its channels of V and O: the products of Q and K are made twice, 48 matrix instructions
+// a tile of keys instead of 64, on compute units that would be idle.  One / two workgroups (row tiles), the same bits: block-sparse 1 x 2048 (128; 384 keys) 11.6 / 10.2, 1 x 915 (58, all keys)
+// 22.4 / 18.8, 2 x 1000 (126; 640) 16.5 / 13.9, 1 x 1500 (94; 768) 18.9 / 16.1; dense 1 x 512 (32) 13.0 / 11.0, 3 x 600 (114) 15.4 / 13.1, 1 x 2048 (128) 39.7 / 34.8 with
+// four waves (36.2 with eight).  Above, some units get two: 3 x 1300 (246) 23.8 / 36.2, 2 x 1500 (188) 31.4 / 44.4.  Four workgroups gain no more on 64 tiles and less (1 x 915
+// 18.6, dense 1 x 1000 19.4 against 19.0).
+constexpr int kHalfTiles = 128;
 template <int MODE>
 hipError_t launch_tiled(const Shape& sh, Args32& a, hipStream_t st) {
+    if (attn_fp32_row_tiles(sh, a.idx != nullptr, 16) <= kHalfTiles) return launch<MODE, 1, 4, 2>(sh, a, st);
     const long long keys = a.idx ? min((long long)sh.n, (long long)sh.list_len * sh.b) : sh.n;
-    return keys > 1024 ? launch<MODE, 1, 8>(sh, a, st) : launch<MODE, 1, 4>(sh, a, st);
+    return keys > 1024 ? launch<MODE, 1, 8, 1>(sh, a, st) : launch<MODE, 1, 4, 1>(sh, a, st);
 }
 
 }  // namespace
@@ -347,7 +367,7 @@ hipError_t launch_attn_fp32(const Shape& sh, const void* q, const void* k, const
     if (attn_fp32_split_better(sh, idx != nullptr)) return launch_attn_fp32_split(sh, a, st);
     if (!idx && near) return launch_tiled<2>(sh, a, st);
     if (idx && near && sh.b % 16 == 0) return launch_tiled<1>(sh, a, st);
-    return launch<0, 2, 4>(sh, a, st);
+    return launch<0, 2, 4, 1>(sh, a, st);
 }
 
 }  // namespace cp

@@ -475,10 +475,9 @@ hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
 }
 }  // namespace
 
-// Row tiles that exist: a segment's last tile may be short.
-static long long row_tiles(const Shape& sh, bool sparse) {
+long long attn_fp32_row_tiles(const Shape& sh, bool sparse, int rows) {
     const int s = sparse ? sh.s : sh.n, rest = sh.n % s;
-    return (long long)sh.batch * sh.hq * ((long long)(sh.n / s) * ((s + TQ - 1) / TQ) + (rest + TQ - 1) / TQ);
+    return (long long)sh.batch * sh.hq * ((long long)(sh.n / s) * ((s + rows - 1) / rows) + (rest + rows - 1) / rows);
 }
 
 static long long listed_keys(const Shape& sh, bool sparse) {
@@ -494,7 +493,7 @@ static long long listed_keys(const Shape& sh, bool sparse) {
 //   152 8 x 600 (416) 14.7 / 17.7, 128 1 x 4096 (416, 1248) 13.2 / 17.7, 28.6 / 35.1.
 bool attn_fp32_split_better(const Shape& sh, bool sparse) {
     if (sh.kvs[2] >= (1 << 26) || (sparse && sh.b % 16 != 0)) return false;     // a run's rows within 32-bit byte offsets of its first; runs of 16
-    const long long tiles = row_tiles(sh, sparse), keys = listed_keys(sh, sparse), n = sh.n;
+    const long long tiles = attn_fp32_row_tiles(sh, sparse, TQ), keys = listed_keys(sh, sparse), n = sh.n;
     if (n > 1024 && 5 * keys > 4 * n) return tiles > 272;
     if (tiles >= 256) return true;
     if (tiles >= 184) return n >= 1400 && 5 * keys <= 3 * n;
@@ -507,7 +506,7 @@ bool attn_fp32_split_better(const Shape& sh, bool sparse) {
 // 4096 (512, 1248) 76 / 71, 32 x 500 (512) 28 / 24; dense 4 x 6000 (752) 263 / 256.
 hipError_t launch_attn_fp32_split(const Shape& sh, Args32& a, hipStream_t st) {
     const bool sparse = a.idx != nullptr;
-    const long long tiles = row_tiles(sh, sparse), keys = listed_keys(sh, sparse);
+    const long long tiles = attn_fp32_row_tiles(sh, sparse, TQ), keys = listed_keys(sh, sparse);
     const bool eight = tiles <= 256 || (tiles <= 640 && sh.n >= 1024 && 8 * keys >= 5ll * sh.n);
     if (sparse) return eight ? launch<1, 8>(sh, a, st) : launch<1, 4>(sh, a, st);
     return eight ? launch<2, 8>(sh, a, st) : launch<2, 4>(sh, a, st);

@@ -21,6 +21,10 @@ SHAPES = [
     (8, 4, 1601, 128, 32, 60, 1),         # split products, 8 waves; a last row tile of one row
     (8, 2, 2064, 256, 64, 4, 1),          # split: 4 waves for the short lists, 8 for dense
     (16, 4, 3120, 512, 128, 16, 0),       # split, 4 waves: many workgroups
+    (1, 1, 2048, 128, 32, 8, 0),          # 128 row tiles: two workgroups to a tile, each with half of the channels
+    (2, 1, 1009, 255, 51, 9, 1),          # the same dense; block-sparse a token per key
+    (2, 2, 1001, 256, 16, 70, 1),         # 126 row tiles, long lists; a last tile of nine rows
+    (3, 1, 688, 344, 43, 9, 1),           # dense 129 row tiles: one workgroup to a tile
     (3, 1, 500, 72, 24, 4, 1),            # blocks of 24: one token per key; segments no multiple of a row tile
 ]
 
