@@ -1,6 +1,7 @@
 // What the three bf16 attention kernels share: vector types, argument block, lane exchanges, the copy from memory to LDS.
 #pragma once
 #include "kernels.h"
+#include "work_order.h"
 
 namespace cp {
 
@@ -11,8 +12,14 @@ struct ArgsB {
     int group;                            // G = hq / hkv
     int shared_lists;                     // lists are per (batch, KV head, segment) instead of per query head
     float scale_log2e, scale;
-    FastDiv div_order[3], div_group, div_hkv, div_b;   // 256-row and 128-row kernel: see the workgroup order; G; hkv; b
     long long qs0, qs1, qs2, ks0, ks1, ks2, os0, os1, os2;
+};
+
+// Index arithmetic of the 256-row and the 128-row kernel, an argument of its own and their first: it is the first thing that they need, and the 32-row kernel
+// reads fewer lines of arguments without it (behind the other arguments 0.4 us more for launches of one round, among them 0.15 us more for the smallest of the 32-row kernel).
+struct ArgsIndex {
+    WorkOrder order;
+    FastDiv div_hkv, div_b;
 };
 
 namespace {
@@ -92,6 +99,8 @@ __device__ __forceinline__ float half_sum(float x) {
 }
 
 }  // namespace
+
+inline long long attn_bf16_kv_bytes(const Shape& sh) { return 4ll * sh.batch * sh.hkv * sh.n * kHeadDim; }
 
 // Workgroups of `rows` query rows that a launch needs: a segment's last one may be short.
 long long attn_bf16_row_tiles(const Shape& sh, bool sparse, int rows);

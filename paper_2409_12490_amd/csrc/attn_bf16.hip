@@ -29,6 +29,8 @@
 // hand-placed ones that pace the ring.
 #include "attn_bf16.h"
 
+#include <algorithm>
+
 namespace cp {
 namespace {
 
@@ -41,7 +43,7 @@ constexpr int kTokOff = 0;                            // [NBUF][TK] token positi
 constexpr int kVOff = 1024;                           // [NBUF] V tiles
 constexpr int kKOff = kVOff + NBUF * kTileBytes;      // [NBUF] K tiles
 constexpr int kListOff = kKOff + NBUF * kTileBytes;   // the segment's block list (sparse only)
-constexpr unsigned kRound = 256;                      // workgroups of a round, see the workgroup order
+constexpr unsigned kRound = 256;                      // workgroups that the chip holds
 constexpr int kOutPitch = 272;                        // epilogue staging: one output row + 16 B, in bytes
 static_assert(kListOff + kMaxListBf16 * 4 <= 160 * 1024, "LDS budget");
 static_assert(8 * WQ * kOutPitch <= 2 * NBUF * kTileBytes, "epilogue staging reuses the tile rings");
@@ -52,7 +54,7 @@ static_assert(8 * WQ * kOutPitch <= 2 * NBUF * kTileBytes, "epilogue staging reu
 // of 32 consecutive tokens, described by their two first tokens.
 constexpr int kFragLook = 3;               // depth of the LDS fragment ring, see the matrix phase
 template <int MODE, int KLOOK = kFragLook>
-__global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
+__global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsIndex ix, ArgsB a) {
     constexpr bool DENSE = MODE == 2, FAST = MODE != 0, HALF = MODE == 3;
     constexpr bool EARLY = MODE == 1 || HALF;                    // the first tiles are asked for before the list is in LDS
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -68,44 +70,20 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     // list is asked for after 120 instead of 290 instructions: 32 x 16K tokens (16 blocks of 64) 388 -> 376 us, 2 x 32 x 64K (32
     // of 32) 2640 -> 2597, 32 x 128K (32 of 64, shared lists) 4.97 -> 4.75 ms, same outputs.
     asm volatile("" ::"s"(a.q), "s"(a.k), "s"(a.v), "s"(a.idx), "s"(a.cnt), "s"(a.n), "s"(a.s), "s"(a.qs0), "s"(a.qs1), "s"(a.qs2), "s"(a.ks0),
-                 "s"(a.ks1), "s"(a.ks2), "s"(a.list_len), "s"(a.scale_log2e), "s"(a.div_b.mul));
+                 "s"(a.ks1), "s"(a.ks2), "s"(a.list_len), "s"(a.scale_log2e), "s"(ix.div_b.mul), "s"(ix.order.set_kv), "s"(ix.order.by_kv.shift));
     // ---- which (batch, head, segment, query tile) this workgroup owns --------------------------
     const unsigned wg = workgroup_id();
     int bb, h, g, j = 0, qt;
     if (DENSE) {
         // heaviest query tiles first; consecutive workgroups walk the KV heads so that the query
         // heads sharing one KV head land on the same XCD (workgroup id mod 8) at the same time.
-        // div_order: batch * hq, batch * hkv
-        const unsigned y = a.div_order[0].div(wg), x = wg - y * (unsigned)(a.batch * a.hq);
+        const unsigned y = ix.order.by_heads.div(wg), x = wg - y * ix.order.set_heads;
         qt = a.qtiles - 1 - (int)y;
-        const unsigned gq = a.div_order[1].div(x), bkvh = x - gq * (unsigned)(a.batch * a.hkv);
-        bb = (int)a.div_hkv.div(bkvh); g = (int)bkvh - bb * a.hkv; h = g * a.group + (int)gq;
+        const unsigned gq = ix.order.by_kv.div(x), bkvh = x - gq * ix.order.set_kv;
+        bb = (int)ix.div_hkv.div(bkvh); g = (int)bkvh - bb * a.hkv; h = g * a.group + (int)gq;
     } else {
-        // (batch, KV head) groups run one after another.  Workgroups reach the compute units round-robin and in
-        // order: workgroup x + 256 follows workgroup x on the same unit and starts only after every workgroup
-        // before it has started, so a round of 256 workgroups lasts as long as its slowest member.  The first
-        // query tile of a segment sees fewer keys than the last (the plain order, both tiles in every round, left
-        // the units with the short tiles idle 6 us per item; measured with per-wave time stamps), so a round
-        // takes 256 (query head, segment) pairs at ONE query tile and the next round the same pairs at the next
-        // tile.  Inside a round every XCD (workgroup id mod 8) gets 32 consecutive pairs: the query heads of a
-        // few neighbouring segments.
-        // div_order: items of a group, items of a round, pairs that fill no whole round
-        const unsigned pairs = a.group * a.n1, qtiles = a.qtiles;
-        const unsigned grp = a.div_order[0].div(wg), x = wg - grp * pairs * qtiles;
-        const unsigned full = pairs / kRound * kRound;           // pairs that fill whole rounds
-        unsigned u;
-        if (x < full * qtiles) {
-            const unsigned rd = a.div_order[1].div(x), y = x - rd * kRound * qtiles, pos = y % kRound;
-            qt = (int)(y / kRound);
-            u = rd * kRound + (pos & 7) * (kRound / 8) + (pos >> 3);
-        } else {
-            const unsigned rest = pairs - full, y = x - full * qtiles;
-            qt = (int)a.div_order[2].div(y);
-            u = full + y - (unsigned)qt * rest;
-        }
-        j = (int)a.div_group.div(u);
-        const int gq = (int)u - j * a.group;
-        bb = (int)a.div_hkv.div(grp); g = (int)grp - bb * a.hkv; h = g * a.group + gq;
+        const WorkOrder::Item item = ix.order.item(wg, kRound, (unsigned)a.n1, (unsigned)a.qtiles);
+        bb = (int)ix.div_hkv.div((unsigned)item.bkv); g = item.bkv - bb * a.hkv; h = g * a.group + item.gq; j = item.segment; qt = item.tile;
     }
     const int q_lo = DENSE ? qt * TQ : j * a.s + qt * TQ;
     const int q_end = DENSE ? a.n : min(a.n, (j + 1) * a.s);
@@ -139,7 +117,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
             const scalar_list entries = (scalar_list)(unsigned long long)list;
 #pragma unroll
             for (int x = 0; x < kFirst; ++x) {
-                at[x] = a.div_b.div((unsigned)(x * kRun));
+                at[x] = ix.div_b.div((unsigned)(x * kRun));
                 entry[x] = entries[min(at[x], (unsigned)a.list_len - 1u)];
             }
         }
@@ -567,7 +545,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     // behind the list (8 bytes per tile), so that the key loop reads a tile's description instead of walking the list
     if (HALF) {
         for (int x = tid; x < ntiles; x += 512) {
-            const unsigned p0 = (unsigned)x * TK, e0 = a.div_b.div(p0), p1 = p0 + 32, e1 = a.div_b.div(p1);
+            const unsigned p0 = (unsigned)x * TK, e0 = ix.div_b.div(p0), p1 = p0 + 32, e1 = ix.div_b.div(p1);
             const int lo = *LDS_PTR(const int, lds0 + kListOff + e0 * 4) * a.b + (int)(p0 - e0 * ub);
             const int hi = e1 < (unsigned)count ? *LDS_PTR(const int, lds0 + kListOff + e1 * 4) * a.b + (int)(p1 - e1 * ub) : -1;
             i32x2 d; d[0] = lo; d[1] = hi;
@@ -581,7 +559,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
             int tok;
             if (HALF) tok = *LDS_PTR(const int, tab0 + x * 8);
             else {
-                const unsigned p = (unsigned)x * TK, e = a.div_b.div(p);
+                const unsigned p = (unsigned)x * TK, e = ix.div_b.div(p);
                 tok = *LDS_PTR(const int, lds0 + kListOff + e * 4) * a.b + (int)(p - e * ub);
             }
             const unsigned long long seen = __builtin_amdgcn_ballot_w64(tok <= q_last && lane < ntiles);
@@ -599,7 +577,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsB a) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // and K0, V0, K1
     __syncthreads();                                                 // everybody's, and nobody reads Q in LDS any more
     if (HALF) walk_t = 4;
-    else if (EARLY) { walk_e = (int)a.div_b.div(4 * TK); walk_off = 4 * TK - walk_e * a.b; }
+    else if (EARLY) { walk_e = (int)ix.div_b.div(4 * TK); walk_off = 4 * TK - walk_e * a.b; }
     else if (DENSE) dense_tile = 4;
     describe_first(2);
     if (ntiles > 0) { issue_v(1, false); issue_k(2); }
@@ -711,39 +689,37 @@ hipError_t launch_attn_bf16(const Shape& sh, const void* q, const void* k, const
     a.group = sh.hq / sh.hkv;
     if (idx && attn_bf16_half_better(sh)) return launch_attn_bf16_half(sh, a, st);
     if (attn_bf16_rows_better(sh, idx != nullptr)) return launch_attn_bf16_rows(sh, a, st);
-    const uint32_t bkv = (uint32_t)sh.batch * sh.hkv;
-    a.div_group = FastDiv(a.group); a.div_hkv = FastDiv(sh.hkv); a.div_b = FastDiv(sh.b);
+    ArgsIndex ix;
+    ix.div_hkv = FastDiv(sh.hkv); ix.div_b = FastDiv(sh.b);
     hipError_t e;
     if (idx) {
         if (sh.list_len > kMaxListBf16) return hipErrorInvalidValue;
-        a.qtiles = (sh.s + TQ - 1) / TQ;
+        a.qtiles = (std::min(sh.s, sh.n) + TQ - 1) / TQ;          // a segment may be set longer than the sequence
         const long long grid = (long long)sh.batch * sh.hq * sh.n1 * a.qtiles;
-        const uint32_t pairs = (uint32_t)a.group * sh.n1;        // (query head, segment) pairs of a KV head
-        a.div_order[0] = FastDiv(pairs * a.qtiles); a.div_order[1] = FastDiv(kRound * a.qtiles);
-        a.div_order[2] = FastDiv(pairs % kRound ? pairs % kRound : 1);
+        ix.order = WorkOrder(sh.batch * sh.hkv, a.group, sh.n1, a.qtiles, kRound, attn_bf16_kv_bytes(sh));
         const int smem = kListOff + ((sh.list_len * 4 + 1023) & ~1023);
         const int tab_bytes = (int)(((long long)sh.list_len * sh.b + TK - 1) / TK) * 8;     // MODE 3: tile descriptions
         if (sh.b % TK == 0) {
             e = hipFuncSetAttribute((const void*)attn_bf16_kernel<1>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(attn_bf16_kernel<1>, dim3((unsigned)grid), dim3(512), smem, st, a);
+            hipLaunchKernelGGL(attn_bf16_kernel<1>, dim3((unsigned)grid), dim3(512), smem, st, ix, a);
         } else if (sh.b % 32 == 0 && smem + tab_bytes <= 160 * 1024) {
             e = hipFuncSetAttribute((const void*)attn_bf16_kernel<3>, hipFuncAttributeMaxDynamicSharedMemorySize, smem + tab_bytes);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(attn_bf16_kernel<3>, dim3((unsigned)grid), dim3(512), smem + tab_bytes, st, a);
+            hipLaunchKernelGGL(attn_bf16_kernel<3>, dim3((unsigned)grid), dim3(512), smem + tab_bytes, st, ix, a);
         } else {
             e = hipFuncSetAttribute((const void*)attn_bf16_kernel<0>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
             if (e != hipSuccess) return e;
-            hipLaunchKernelGGL(attn_bf16_kernel<0>, dim3((unsigned)grid), dim3(512), smem, st, a);
+            hipLaunchKernelGGL(attn_bf16_kernel<0>, dim3((unsigned)grid), dim3(512), smem, st, ix, a);
         }
     } else {
         a.qtiles = (sh.n + TQ - 1) / TQ;
         const long long grid = (long long)sh.batch * sh.hq * a.qtiles;
-        a.div_order[0] = FastDiv((uint32_t)sh.batch * sh.hq); a.div_order[1] = FastDiv(bkv);
+        ix.order = WorkOrder(sh.batch * sh.hkv, a.group, 1, a.qtiles, kRound, 0);
         e = hipFuncSetAttribute((const void*)attn_bf16_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 kListOff);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(attn_bf16_kernel<2>, dim3((unsigned)grid), dim3(512), kListOff, st, a);
+        hipLaunchKernelGGL(attn_bf16_kernel<2>, dim3((unsigned)grid), dim3(512), kListOff, st, ix, a);
     }
     return hipGetLastError();
 }

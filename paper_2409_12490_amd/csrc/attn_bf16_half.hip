@@ -43,31 +43,17 @@ __device__ __forceinline__ void dma16_runs(const void* b0, const void* b1, const
                  : "memory", "scc");
 }
 
-__global__ __launch_bounds__(64 * kWaves, 2) void attn_bf16_half_kernel(ArgsB a) {
+__global__ __launch_bounds__(64 * kWaves, 2) void attn_bf16_half_kernel(ArgsIndex ix, ArgsB a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
     const int tid = thread_id(), lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // ---- which (batch, head, segment, query tile): the order of the 256-row kernel -----------------------------------
-    const unsigned wg = workgroup_id();
-    int qt;
-    const unsigned pairs = a.group * a.n1, qtiles = a.qtiles;
-    const unsigned grp = a.div_order[0].div(wg), x = wg - grp * pairs * qtiles;
-    const unsigned full = pairs / kRound * kRound;
-    unsigned u;
-    if (x < full * qtiles) {
-        const unsigned rd = a.div_order[1].div(x), y = x - rd * kRound * qtiles, pos = y % kRound;
-        qt = (int)(y / kRound);
-        u = rd * kRound + (pos & 7) * (kRound / 8) + (pos >> 3);
-    } else {
-        const unsigned rest = pairs - full, y = x - full * qtiles;
-        qt = (int)a.div_order[2].div(y);
-        u = full + y - (unsigned)qt * rest;
-    }
-    const int j = (int)a.div_group.div(u);
-    const int gq = (int)u - j * a.group;
-    const int bb = (int)a.div_hkv.div(grp), g = (int)grp - bb * a.hkv, h = g * a.group + gq;
+    // every argument in one go, as in the 256-row kernel
+    asm volatile("" ::"s"(ix.order.full), "s"(ix.order.by_kv.shift), "s"(ix.div_hkv.mul), "s"(ix.div_b.mul), "s"(a.q), "s"(a.k), "s"(a.v), "s"(a.idx), "s"(a.cnt), "s"(a.n),
+                 "s"(a.s), "s"(a.qs0), "s"(a.qs1), "s"(a.qs2), "s"(a.ks0), "s"(a.ks1), "s"(a.ks2), "s"(a.list_len), "s"(a.scale_log2e));
+    const WorkOrder::Item item = ix.order.item(workgroup_id(), kRound, (unsigned)a.n1, (unsigned)a.qtiles);
+    const int bb = (int)ix.div_hkv.div((unsigned)item.bkv), g = item.bkv - bb * a.hkv, h = g * a.group + item.gq, j = item.segment, qt = item.tile;
     const int q_lo = j * a.s + qt * TQ;
     const int q_end = min(a.n, (j + 1) * a.s);
     if (q_lo >= q_end) return;                                   // uniform: tile past a short segment
@@ -95,9 +81,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bf16_half_kernel(ArgsB a)
     const int cnt = *(scalar_list)(unsigned long long)uniform_ptr(a.cnt + lrow);
     const int count = min(max(cnt, 0), a.list_len);
     int ntiles = (int)(((unsigned)count * (unsigned)a.b + TK - 1) / TK);
-    const int blocks = (int)a.div_b.div((unsigned)(a.n + a.b - 1));
+    const int blocks = (int)ix.div_b.div((unsigned)(a.n + a.b - 1));
     for (int x = tid; x < 4 * ntiles; x += 64 * kWaves) {
-        const unsigned p = 16u * (unsigned)x, e = a.div_b.div(p);
+        const unsigned p = 16u * (unsigned)x, e = ix.div_b.div(p);
         const int blk = list[min(e, (unsigned)a.list_len - 1u)];
         const int tok = blk * a.b + (int)(p - e * (unsigned)a.b);
         // entries outside the sequence have no tokens
@@ -352,15 +338,14 @@ bool attn_bf16_half_better(const Shape& sh) {
 }
 
 hipError_t launch_attn_bf16_half(const Shape& sh, ArgsB a, hipStream_t st) {
-    a.div_group = FastDiv(a.group); a.div_hkv = FastDiv(sh.hkv); a.div_b = FastDiv(sh.b);
+    ArgsIndex ix;
+    ix.div_hkv = FastDiv(sh.hkv); ix.div_b = FastDiv(sh.b);
     a.qtiles = (std::min(sh.s, sh.n) + TQ - 1) / TQ;              // a segment may be set longer than the sequence
-    const uint32_t pairs = (uint32_t)a.group * sh.n1;
-    a.div_order[0] = FastDiv(pairs * a.qtiles); a.div_order[1] = FastDiv(kRound * a.qtiles);
-    a.div_order[2] = FastDiv(pairs % kRound ? pairs % kRound : 1);
+    ix.order = WorkOrder(sh.batch * sh.hkv, a.group, sh.n1, a.qtiles, kRound, attn_bf16_kv_bytes(sh));
     const int smem = kTabOff + (int)((table_bytes(sh) + 1023) & ~1023ll);
     const hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_half_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(attn_bf16_half_kernel, dim3((unsigned)((long long)sh.batch * sh.hq * sh.n1 * a.qtiles)), dim3(64 * kWaves), smem, st, a);
+    hipLaunchKernelGGL(attn_bf16_half_kernel, dim3((unsigned)((long long)sh.batch * sh.hq * sh.n1 * a.qtiles)), dim3(64 * kWaves), smem, st, ix, a);
     return hipGetLastError();
 }
 

@@ -1,0 +1,54 @@
+"""The order of workgroups of block-sparse attention (WorkOrder), compiled for the CPU from the header the kernels include: every (KV head, query head,
+segment, row tile) exactly once, whatever the numbers of heads and segments leave over after whole rounds, and the heaviest first."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2409_12490_amd", "csrc")
+PROGRAM = """
+#define __host__
+#define __device__
+#define __forceinline__ inline
+#include "work_order.h"
+extern "C" void order(unsigned bkv, unsigned group, unsigned n1, unsigned qtiles, unsigned round, long long kv_bytes, int* out) {
+    const cp::WorkOrder o(bkv, group, n1, qtiles, round, kv_bytes);
+    for (unsigned wg = 0; wg < bkv * group * n1 * qtiles; ++wg) {
+        const auto t = o.item(wg, round, n1, qtiles);
+        out[4 * wg] = t.bkv; out[4 * wg + 1] = t.gq; out[4 * wg + 2] = t.segment; out[4 * wg + 3] = t.tile;
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def order(tmp_path_factory):
+    compiler = shutil.which("g++") or shutil.which("clang++") or shutil.which("c++")
+    if compiler is None:
+        pytest.skip("no C++ compiler")
+    where = tmp_path_factory.mktemp("work_order")
+    (where / "f.cpp").write_text(PROGRAM)
+    subprocess.run([compiler, "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(where / "f.cpp"), "-o", str(where / "f.so")], check=True)
+    f = ctypes.CDLL(str(where / "f.so")).order
+    f.argtypes = [ctypes.c_uint] * 5 + [ctypes.c_longlong, np.ctypeslib.ndpointer(np.int32)]
+    f.restype = None
+    return f
+
+
+@pytest.mark.parametrize("round_", [256, 512])
+@pytest.mark.parametrize("kv_bytes", [1 << 26, (1 << 26) + 1])
+def test_each_item_once(order, round_, kv_bytes):
+    for bkv, group, n1, qtiles in [(1, 1, 1, 1), (1, 1, 1, 3), (8, 4, 8, 1), (8, 4, 8, 2), (8, 4, 33, 2), (16, 4, 129, 1), (24, 1, 11, 5), (17, 1, 31, 2), (6, 3, 57, 4), (16, 8, 4, 2), (2, 1, 257, 1)]:
+        out = np.full((bkv * group * n1 * qtiles, 4), -1, np.int32)
+        order(bkv, group, n1, qtiles, round_, kv_bytes, out)
+        what = (bkv, group, n1, qtiles)
+        assert (out >= 0).all() and (out < np.array([bkv, group, n1, qtiles])).all(), what
+        assert len(np.unique(out, axis=0)) == len(out), what
+        at_a_time = 8 if bkv % 8 == 0 and kv_bytes > 1 << 26 else bkv
+        last_tile = out[out[:, 3] == qtiles - 1]
+        for first in range(0, bkv, at_a_time):                # the segments of a set of KV heads, from the last to the first
+            segments = last_tile[last_tile[:, 0] // at_a_time == first // at_a_time, 2]
+            assert (np.diff(segments) <= 0).all(), what
