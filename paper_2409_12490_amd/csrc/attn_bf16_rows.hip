@@ -30,6 +30,7 @@ constexpr int kNoToken = 0x7fffffff;              // a key that does not exist: 
 template <int MODE, int W>
 __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a) {
     constexpr bool DENSE = MODE == 2, RUN = MODE != 0;
+    ask_for(a.q, a.k, a.v, a.idx, a.cnt, a.batch, a.n, a.qtiles, a.group, a.scale_log2e, a.qs0, a.qs1, a.qs2, a.ks0, a.ks1, a.ks2);
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
     constexpr unsigned kQ = W * 2 * kSlotBytes;                     // behind the waves' K and V slots: Q

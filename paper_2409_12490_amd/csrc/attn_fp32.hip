@@ -43,6 +43,7 @@ __device__ __forceinline__ float group_max(float x) {               // over the 
 // 16: a tile is 16 consecutive tokens, described by its first token on the scalar unit.  MODE 2: dense.
 template <int MODE, int RT, int W, int C>
 __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kernel(Args32 a) {
+    ask_for(a.q, a.k, a.v, a.idx, a.cnt, a.batch, a.n, a.qtiles, a.shared_lists, a.scale_log2e, a.qs0, a.qs1, a.qs2, a.ks0, a.ks1, a.ks2);
     constexpr bool RUN = MODE != 0;
     constexpr int TQ = 16 * RT, TK = 16;
     constexpr int kNoToken = 0x7fffffff;                            // a key that does not exist: after every query

@@ -116,6 +116,7 @@ __device__ __forceinline__ float half_max(float x) {                // over lane
 // MODE 1: sparse, block size a multiple of 16; MODE 2: dense.
 template <int MODE, int W>
 __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
+    ask_for(a.q, a.k, a.v, a.idx, a.cnt, a.batch, a.n, a.qtiles, a.shared_lists, a.scale_log2e, a.qs0, a.qs1, a.qs2, a.ks0, a.ks1, a.ks2);
     constexpr bool DENSE = MODE == 2;
     extern __shared__ __attribute__((aligned(1024))) float smem[];
     // While keys are walked: a K tile of 16 KiB per wave (32 rows of 512 B, 16-byte chunks XOR-swizzled by the row), then the parts of Q as B

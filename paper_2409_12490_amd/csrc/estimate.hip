@@ -70,6 +70,7 @@ template <typename T>
 __global__ __launch_bounds__(64 * kPoolWaves) void pool_kernel(PoolArgs a) {
     constexpr int E = PoolVec<T>::kElems, kLanes = kHeadDim / E, kRows = 64 / kLanes, kLoads = 8, kBatch = kLoads * kRows;
     __shared__ __attribute__((aligned(16))) float part[kPoolWaves][2][kHeadDim];
+    ask_for(a.q, a.k, a.qrep, a.krep, a.q_wgs, a.q_split, a.k_split, a.q_across, a.k_across, a.div_n1.mul, a.div_hkv.shift, a.qs0, a.qs1, a.qs2, a.ks0, a.ks1, a.ks2);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const bool is_q = blockIdx.x < a.q_wgs;
@@ -188,6 +189,7 @@ __global__ __launch_bounds__(64 * kScore32Waves) void score_fp32_kernel(ScoreArg
     constexpr float kLog2e = 1.4426950408889634f;
     const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    ask_for(a.qrep, a.krep, a.prev, a.scores, a.hq, a.n1, a.n2, a.segs, a.scale, a.alpha);
     const int segs = a.segs, pitch = score32_pitch(a.n2);
     float* z = smem;                                        // [2 * segs][pitch]
     float* inv = smem + 2 * segs * pitch;                   // [2 * segs][2]
@@ -336,6 +338,7 @@ __global__ __launch_bounds__(64 * kScoreWaves, 2) void score_kernel(ScoreArgs a)
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)score_lds;
     constexpr unsigned kRed = kChunkTiles * kTileBytes;     // behind the tiles: (max, sum) [wave][product][column], PASS 0 and 2
     constexpr float kLog2e = 1.4426950408889634f;
+    ask_for(a.qrep, a.krep, a.prev, a.scores, a.stats, a.hq, a.n1, a.n2, a.nchunk, a.group, a.share_least, a.share_more, a.div_chunks.mul, a.div_groups.mul, a.scale);
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // grid (x, shares, z): unit x + X z is a chunk of a (batch, KV head)
