@@ -28,9 +28,11 @@ constexpr int kNoToken = 0x7fffffff;              // a key that does not exist: 
 // MODE 0: sparse, any block size: every key of a tile has a token of its own.  MODE 1: sparse, block size a multiple of 16: a
 // tile is two runs of 16 consecutive tokens, described by their first tokens on the scalar unit.  MODE 2: dense.
 template <int MODE, int W>
-__global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a) {
+__global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a, TileOrder order) {
     constexpr bool DENSE = MODE == 2, RUN = MODE != 0;
     ask_for(a.q, a.k, a.v, a.idx, a.cnt, a.batch, a.n, a.qtiles, a.group, a.scale_log2e, a.qs0, a.qs1, a.qs2, a.ks0, a.ks1, a.ks2);
+    if (W == 4) ask_for(order.turn);
+    if (!DENSE) ask_for(order.full, order.past, order.most, order.by_full.mul, order.by_level.mul, order.by_tiles.shift);
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
     constexpr unsigned kQ = W * 2 * kSlotBytes;                     // behind the waves' K and V slots: Q
@@ -38,17 +40,18 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a) {
 
     const int tid = thread_id(), lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Consecutive workgroups walk the KV heads, so that a head's keys stay with few XCDs (workgroup id mod 8); inside one the row
-    // tiles of a segment and head follow each other, and the segments with most keys, those at the end, come first.
+    // Consecutive workgroups walk the KV heads, so that a head's keys stay with few XCDs (workgroup id mod 8); then the query heads of a group, and inside a
+    // head the tiles that see most keys come first.
     const int G = a.group, bkv = a.batch * a.hkv;
-    const int wg = (int)workgroup_id(), x = wg % bkv, y = wg / bkv;
+    const int wg = (int)(W == 4 ? order.place(workgroup_id()) : workgroup_id()), x = wg % bkv, y = wg / bkv;
     const int bb = x / a.hkv, kvh = x % a.hkv;
     int h, j = 0, q_lo;
     if (DENSE) { h = kvh * G + y % G; q_lo = (a.qtiles - 1 - y / G) * kRowsTQ; }
     else {
-        h = kvh * G + y / a.qtiles % G;
-        j = a.n1 - 1 - y / a.qtiles / G;
-        q_lo = j * a.s + y % a.qtiles * kRowsTQ;
+        h = kvh * G + y % G;
+        const TileOrder::Item item = order.item(y / G, a.n1, a.qtiles);
+        j = item.segment;
+        q_lo = j * a.s + item.tile * kRowsTQ;
     }
     const int q_end = DENSE ? a.n : min(a.n, (j + 1) * a.s);       // rows >= q_end do not exist
     if (q_lo >= q_end) return;                                     // uniform: tile past a short segment
@@ -318,11 +321,11 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a) {
 }
 
 template <int MODE, int W>
-hipError_t launch(const ArgsB& a, unsigned grid, hipStream_t st) {
+hipError_t launch(const ArgsB& a, TileOrder order, unsigned grid, hipStream_t st) {
     constexpr int smem = W * 2 * kSlotBytes + kRowsTQ * 256 + 2 * W * 32 * 4;
     const hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_rows_kernel<MODE, W>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((attn_bf16_rows_kernel<MODE, W>), dim3(grid), dim3(64 * W), smem, st, a);
+    hipLaunchKernelGGL((attn_bf16_rows_kernel<MODE, W>), dim3(grid), dim3(64 * W), smem, st, a, order);
     return hipGetLastError();
 }
 
@@ -330,8 +333,11 @@ hipError_t launch(const ArgsB& a, unsigned grid, hipStream_t st) {
 
 template <int W>
 static hipError_t launch_waves(const Shape& sh, const ArgsB& a, unsigned grid, hipStream_t st) {
-    if (!a.idx) return launch<2, W>(a, grid, st);
-    return sh.b % 16 == 0 ? launch<1, W>(a, grid, st) : launch<0, W>(a, grid, st);
+    // up to a chip full of workgroups the order is of no matter: segments from the last to the first
+    TileOrder order(sh.n1, sh.r, grid > 256 ? sh.budget : sh.n1 * sh.r, sh.local, sh.b, a.qtiles);
+    if (W == 4) order.of_four(grid);
+    if (!a.idx) return launch<2, W>(a, order, grid, st);
+    return sh.b % 16 == 0 ? launch<1, W>(a, order, grid, st) : launch<0, W>(a, order, grid, st);
 }
 
 // Row tiles that exist: a segment's last tile may be short.

@@ -1,6 +1,7 @@
 // What the two fp32 attention kernels share.
 #pragma once
 #include "kernels.h"
+#include "work_order.h"
 
 namespace cp {
 
@@ -31,6 +32,7 @@ struct Args32 {
     const float* q; const float* k; const float* v; const int32_t* idx; const int32_t* cnt;
     float* out; float* lse;
     int batch, hq, hkv, n, s, b, n1, list_len, qtiles;   // qtiles: per segment (sparse) or per sequence (dense)
+    TileOrder order;                              // attn_fp32_split_kernel, sparse
     int shared_lists;                             // lists are per (batch, KV head, segment) instead of per query head
     float scale_log2e, scale;
     long long qs0, qs1, qs2, ks0, ks1, ks2, os0, os1, os2;

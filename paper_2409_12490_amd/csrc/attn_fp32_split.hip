@@ -132,12 +132,12 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
 
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int G = a.hq / a.hkv, bkv = a.batch * a.hkv;              // order of the workgroups: see attn_fp32_kernel
-    const int x = blockIdx.x % bkv, y = blockIdx.x / bkv;
+    const int G = a.hq / a.hkv, bkv = a.batch * a.hkv;              // consecutive workgroups walk the KV heads, see attn_fp32_kernel; then TileOrder
+    const unsigned wg = W == 4 ? a.order.place(blockIdx.x) : blockIdx.x;
+    const int x = wg % bkv, y = wg / bkv;
     const int bb = x / a.hkv, kvh = x % a.hkv, h = kvh * G + y % G;
-    const int item = (DENSE ? a.qtiles : a.n1 * a.qtiles) - 1 - y / G;
-    const int j = DENSE ? 0 : item / a.qtiles;
-    const int q_lo = DENSE ? item * TQ : j * a.s + item % a.qtiles * TQ;
+    const TileOrder::Item item = DENSE ? TileOrder::Item{0, a.qtiles - 1 - y / G} : a.order.item(y / G, a.n1, a.qtiles);
+    const int j = item.segment, q_lo = j * a.s + item.tile * TQ;
     const int q_end = DENSE ? a.n : min(a.n, (j + 1) * a.s);        // rows >= q_end do not exist
     if (q_lo >= q_end) return;                                      // uniform: tile past a short segment
     const int q_last = min(q_end, q_lo + TQ) - 1;
@@ -467,6 +467,9 @@ template <int MODE, int W>
 hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
     a.qtiles = ((a.idx ? min(sh.s, sh.n) : sh.n) + TQ - 1) / TQ;    // a segment may be set longer than the sequence
     const long long grid = (long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1);
+    // eight waves, or more workgroups than the chip holds: segments from the last to the first (by keys: 8/2 x 3000 94 -> 101, 2 x 8/2 x 8000 352 -> 359)
+    a.order = TileOrder(sh.n1, sh.r, a.idx && W == 4 && grid <= 512 ? sh.budget : sh.n1 * sh.r, sh.local, sh.b, a.qtiles);
+    if (W == 4) a.order.of_four(grid);
     constexpr int smem = W * TQ * kHeadDim * 4 + 2 * 8 * 64 * 16;   // W = 4: half of a compute unit's LDS
     static_assert(2 * W * TQ * 4 + W * 4 <= 2 * 8 * 64 * 16, "what takes the place of Q");
     const hipError_t e = hipFuncSetAttribute((const void*)attn_fp32_split_kernel<MODE, W>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);

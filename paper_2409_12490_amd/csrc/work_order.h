@@ -50,4 +50,45 @@ struct WorkOrder {
     }
 };
 
+// The order of the 32-row kernels (attn_bf16_rows.hip, attn_fp32_split.hip) inside a head: row tiles by the keys that they see, most first, where the segments came from the
+// last to the first.  A segment whose list is full sees `past` tiles' worth of keys before it and those up to the tile; the others, at the start of the sequence, see all
+// keys up to the tile.  The lists on the GPU may say otherwise: the order decides the time alone.  Before / now (us): bf16 32 heads x 900 tokens (512, 64; 4 blocks) 22.1 / 18.8, 32 x
+// 700 (256, 32; 16) 16.9 / 15.4, 8 x 4000 (512, 64; 40) 54.9 / 52.2, and with the turn below 4 x 4000 (512, 16; 64) 20.8 / 19.1, 2 x 8000 (512, 64; 40) 36.7 / 33.8; fp32 4 x 4096 (256,
+// 64; 6) 43.7 / 39.4, (512, 64; 20) 97 / 84, 4 x 3000 (256, 64; 4) 34.4 / 28.2, 2 x 6000 (512, 64; 4) 45.2 / 34.8, 2 x 7000 (16) 83 / 73.
+struct TileOrder {
+    struct Item { int segment, tile; };
+    unsigned turn;                        // workgroups at the front that come in the opposite order, see of_four
+    unsigned full, past, most;            // segments with full lists; 32 keys each; what the last tile of the others sees
+    FastDiv by_full, by_level, by_tiles;  // full, full + 1, qtiles
+
+    TileOrder() = default;
+    TileOrder(int n1, int r, int budget, int local, int b, int qtiles) : turn(0) {
+        const long long blocks = (long long)budget + local, keys = blocks * b / 32;
+        const unsigned early = blocks > (long long)n1 * r ? n1 : (unsigned)((blocks + r - 1) / r);
+        full = n1 - early; most = early * qtiles;
+        past = full == 0 || keys > most ? most : (unsigned)(keys + qtiles < most ? most - qtiles : keys);    // for segments of no multiple of 32 rows
+        by_full = FastDiv(full ? full : 1); by_level = FastDiv(full + 1); by_tiles = FastDiv(qtiles);
+    }
+    // Workgroups of four waves, two to a compute unit.  Where the chip holds all of them, the one that comes 256 after another joins it on its unit: the first 256 with the longest
+    // last, so that long and short share one (the longest first in both halves: fp32 4 x 4096 41.6 instead of 40.2, 8 x 1300 33.5 instead of 29.3).
+    void of_four(long long wgs) { turn = wgs > 256 && wgs <= 512 ? 256 : 0; }
+    __host__ __device__ __forceinline__ unsigned place(unsigned id) const { return id < turn ? turn - 1 - id : id; }
+    __host__ __device__ __forceinline__ Item item(unsigned rank, unsigned n1, unsigned qtiles) const {
+        const unsigned above = (past + qtiles - most) * full;    // of full segments, with more keys than all others
+        unsigned seen, x;                 // tiles' worth of keys; which of those that see as many
+        if (rank < above) {
+            const unsigned level = by_full.div(rank);
+            x = rank - level * full; seen = past + qtiles - level;
+        } else if (rank -= above; rank < (most - past) * (full + 1)) {
+            const unsigned level = by_level.div(rank);
+            x = rank - level * (full + 1); seen = most - level;
+        } else {
+            x = full; seen = past - (rank - (most - past) * (full + 1));
+        }
+        if (x < full) return {(int)(n1 - 1 - x), (int)(seen - past - 1)};
+        const unsigned segment = by_tiles.div(seen - 1);
+        return {(int)segment, (int)(seen - 1 - segment * qtiles)};
+    }
+};
+
 }  // namespace cp

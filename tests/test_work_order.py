@@ -1,4 +1,4 @@
-"""The order of workgroups of block-sparse attention (WorkOrder), compiled for the CPU from the header the kernels include: every (KV head, query head,
+"""The order of workgroups of block-sparse attention (WorkOrder, TileOrder), compiled for the CPU from the header the kernels include: every (KV head, query head,
 segment, row tile) exactly once, whatever the numbers of heads and segments leave over after whole rounds, and the heaviest first."""
 import ctypes
 import os
@@ -21,21 +21,36 @@ extern "C" void order(unsigned bkv, unsigned group, unsigned n1, unsigned qtiles
         out[4 * wg] = t.bkv; out[4 * wg + 1] = t.gq; out[4 * wg + 2] = t.segment; out[4 * wg + 3] = t.tile;
     }
 }
+extern "C" void tiles(int n1, int r, int budget, int local, int b, int qtiles, long long wgs, int four, int* out) {
+    cp::TileOrder o(n1, r, budget, local, b, qtiles);
+    if (four) o.of_four(wgs);
+    for (long long wg = 0; wg < wgs; ++wg) {
+        const unsigned heads = (unsigned)(wgs / (n1 * qtiles)), place = o.place((unsigned)wg);
+        const auto t = o.item(place / heads, n1, qtiles);
+        out[3 * wg] = place % heads; out[3 * wg + 1] = t.segment; out[3 * wg + 2] = t.tile;
+    }
+}
 """
 
 
 @pytest.fixture(scope="module")
-def order(tmp_path_factory):
+def lib(tmp_path_factory):
     compiler = shutil.which("g++") or shutil.which("clang++") or shutil.which("c++")
     if compiler is None:
         pytest.skip("no C++ compiler")
     where = tmp_path_factory.mktemp("work_order")
     (where / "f.cpp").write_text(PROGRAM)
     subprocess.run([compiler, "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(where / "f.cpp"), "-o", str(where / "f.so")], check=True)
-    f = ctypes.CDLL(str(where / "f.so")).order
-    f.argtypes = [ctypes.c_uint] * 5 + [ctypes.c_longlong, np.ctypeslib.ndpointer(np.int32)]
-    f.restype = None
-    return f
+    lib = ctypes.CDLL(str(where / "f.so"))
+    lib.order.argtypes = [ctypes.c_uint] * 5 + [ctypes.c_longlong, np.ctypeslib.ndpointer(np.int32)]
+    lib.tiles.argtypes = [ctypes.c_int] * 6 + [ctypes.c_longlong, ctypes.c_int, np.ctypeslib.ndpointer(np.int32)]
+    lib.order.restype = lib.tiles.restype = None
+    return lib
+
+
+@pytest.fixture(scope="module")
+def order(lib):
+    return lib.order
 
 
 @pytest.mark.parametrize("round_", [256, 512])
@@ -52,3 +67,23 @@ def test_each_item_once(order, round_, kv_bytes):
         for first in range(0, bkv, at_a_time):                # the segments of a set of KV heads, from the last to the first
             segments = last_tile[last_tile[:, 0] // at_a_time == first // at_a_time, 2]
             assert (np.diff(segments) <= 0).all(), what
+
+
+@pytest.mark.parametrize("heads", [1, 3, 8])
+@pytest.mark.parametrize("s,b", [(16, 16), (96, 32), (128, 128), (255, 51), (256, 32), (512, 64)])
+def test_each_row_tile_once(lib, heads, s, b):
+    r, qtiles = s // b, (s + 31) // 32
+    for n1 in (1, 2, 5, 16, 33):
+        for budget, local in [(0, 0), (1, 0), (3, 2), (6, 1), (17, 0), (40, 1), (2000, 2), (2**30, 2**30)]:
+            for four in (0, 1):
+                out = np.full((heads * n1 * qtiles, 3), -1, np.int32)
+                lib.tiles(n1, r, budget, local, b, qtiles, len(out), four, out)
+                what = (n1, budget, local, four)
+                assert (out >= 0).all() and (out < np.array([heads, n1, qtiles])).all(), what
+                assert len(np.unique(out, axis=0)) == len(out), what
+                if s % 32 or (budget + local) * b % 32:
+                    continue
+                keys = np.minimum((budget + local) * b, out[:, 1].astype(np.int64) * s) + 32 * (out[:, 2] + 1)
+                if four and 256 < len(out) <= 512:                # the longest 256 with the longest last
+                    keys[:256] = keys[:256][::-1].copy()
+                assert (np.diff(keys) <= 0).all(), what
