@@ -333,9 +333,9 @@ hipError_t launch(const ArgsB& a, TileOrder order, unsigned grid, hipStream_t st
 
 template <int W>
 static hipError_t launch_waves(const Shape& sh, const ArgsB& a, unsigned grid, hipStream_t st) {
-    // up to a chip full of workgroups the order is of no matter: segments from the last to the first
-    TileOrder order(sh.n1, sh.r, grid > 256 ? sh.budget : sh.n1 * sh.r, sh.local, sh.b, a.qtiles);
-    if (W == 4) order.of_four(grid);
+    const bool pairs = W == 4 && TileOrder::in_pairs(grid, attn_bf16_row_tiles(sh, a.idx != nullptr, kRowsTQ));
+    TileOrder order(sh.n1, sh.r, sh.budget, sh.local, sh.b, a.qtiles, kRowsTQ, pairs || grid > (W == 4 ? 512 : 256));   // what the chip holds at once needs no order but pairs
+    if (pairs) order.turn = 256;
     if (!a.idx) return launch<2, W>(a, order, grid, st);
     return sh.b % 16 == 0 ? launch<1, W>(a, order, grid, st) : launch<0, W>(a, order, grid, st);
 }

@@ -61,11 +61,19 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
     // Consecutive workgroups walk the KV heads, so that a head's keys stay with few XCDs (workgroup id mod 8); the tiles
     // with most keys, those at the end of the sequence, come first.
     const int G = a.hq / a.hkv, bkv = a.batch * a.hkv;
-    const int x = blockIdx.x % bkv, y = blockIdx.x / bkv;
+    constexpr bool PAIRS = W == 4 && C == 1 && MODE != 0;           // two workgroups to a compute unit: see TileOrder
+    const unsigned wg = PAIRS ? a.order.place(blockIdx.x) : blockIdx.x;
+    const int x = wg % bkv, y = wg / bkv;
     const int bb = x / a.hkv, kvh = x % a.hkv, h = kvh * G + y % G;
-    const int item = (dense ? a.qtiles : a.n1 * a.qtiles) - 1 - y / G;
-    const int j = dense ? 0 : item / a.qtiles;
-    const int q_lo = dense ? item * TQ : j * a.s + item % a.qtiles * TQ;
+    int j, q_lo;
+    if (PAIRS && !dense) {
+        const TileOrder::Item item = a.order.item(y / G, a.n1, a.qtiles);
+        j = item.segment; q_lo = j * a.s + item.tile * TQ;
+    } else {
+        const int item = (dense ? a.qtiles : a.n1 * a.qtiles) - 1 - y / G;
+        j = dense ? 0 : item / a.qtiles;
+        q_lo = dense ? item * TQ : j * a.s + item % a.qtiles * TQ;
+    }
     const int q_end = dense ? a.n : min(a.n, (j + 1) * a.s);       // rows >= q_end do not exist
     if (q_lo >= q_end) return;                                     // uniform: tile past a short segment
     const int q_last = min(q_end, q_lo + TQ) - 1;
@@ -330,6 +338,9 @@ template <int MODE, int RT, int W, int C>
 hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
     a.qtiles = ((a.idx ? min(sh.s, sh.n) : sh.n) + 16 * RT - 1) / (16 * RT);    // a segment may be set longer than the sequence
     const long long grid = (long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1);
+    const bool pairs = W == 4 && C == 1 && TileOrder::in_pairs(grid, attn_fp32_row_tiles(sh, a.idx != nullptr, 16 * RT));
+    a.order = TileOrder(sh.n1, sh.r, sh.budget, sh.local, sh.b, a.qtiles, 16 * RT, pairs);
+    if (pairs) a.order.turn = 256;
     hipLaunchKernelGGL((attn_fp32_kernel<MODE, RT, W, C>), dim3((unsigned)grid, C), dim3(64 * W), 0, st, a);
     return hipGetLastError();
 }

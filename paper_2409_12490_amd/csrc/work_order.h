@@ -50,28 +50,32 @@ struct WorkOrder {
     }
 };
 
-// The order of the 32-row kernels (attn_bf16_rows.hip, attn_fp32_split.hip) inside a head: row tiles by the keys that they see, most first, where the segments came from the
+// The order of the 32-row and 16-row kernels (attn_bf16_rows.hip, attn_fp32_split.hip, attn_fp32.hip) inside a head: row tiles by the keys that they see, most first, where the segments came from the
 // last to the first.  A segment whose list is full sees `past` tiles' worth of keys before it and those up to the tile; the others, at the start of the sequence, see all
 // keys up to the tile.  The lists on the GPU may say otherwise: the order decides the time alone.  Before / now (us): bf16 32 heads x 900 tokens (512, 64; 4 blocks) 22.1 / 18.8, 32 x
 // 700 (256, 32; 16) 16.9 / 15.4, 8 x 4000 (512, 64; 40) 54.9 / 52.2, and with the turn below 4 x 4000 (512, 16; 64) 20.8 / 19.1, 2 x 8000 (512, 64; 40) 36.7 / 33.8; fp32 4 x 4096 (256,
-// 64; 6) 43.7 / 39.4, (512, 64; 20) 97 / 84, 4 x 3000 (256, 64; 4) 34.4 / 28.2, 2 x 6000 (512, 64; 4) 45.2 / 34.8, 2 x 7000 (16) 83 / 73.
+// 64; 6) 43.7 / 39.4, (512, 64; 20) 97 / 84, 4 x 3000 (256, 64; 4) 34.4 / 28.2, 2 x 6000 (512, 64; 4) 45.2 / 34.8, 2 x 7000 (16) 83 / 73; 16-row
+// tiles 8 x 700 (256, 32; 4) 15.6 / 13.5, 8 x 900 (512, 64; 4) 25.4 / 22.7, dense 8 x 800 25.2 / 19.4, 16 x 400 15.5 / 12.2, 12 x 600 21.5 / 16.8.
 struct TileOrder {
+    // Workgroups of four waves, two to a compute unit.  Where the chip holds all of them, the one that comes 256 after another joins it on its unit: the first 256 come with the
+    // longest last (turn = 256), so that long and short share one (the longest first in both halves: fp32 4 x 4096 41.6 instead of 40.2, 8 x 1300 33.5 instead of 29.3).  Not where many of
+    // them find no rows, past the end of a short last segment, and leave their places to others (fp32 8 x 600, 208 of 512: 15.5 -> 21.2, 8 x 1300, 56 of 328: 29.0 -> 29.4; 8 x 900, 56 of 512: 25.4 -> 22.7).
+    static bool in_pairs(long long wgs, long long with_rows) { return wgs > 256 && wgs <= 512 && 8 * (wgs - with_rows) <= wgs; }
+
     struct Item { int segment, tile; };
-    unsigned turn;                        // workgroups at the front that come in the opposite order, see of_four
-    unsigned full, past, most;            // segments with full lists; 32 keys each; what the last tile of the others sees
+    unsigned turn;                        // workgroups at the front that come in the opposite order, see in_pairs
+    unsigned full, past, most;            // segments with full lists; a tile's rows of keys each; what the last tile of the others sees
     FastDiv by_full, by_level, by_tiles;  // full, full + 1, qtiles
 
     TileOrder() = default;
-    TileOrder(int n1, int r, int budget, int local, int b, int qtiles) : turn(0) {
-        const long long blocks = (long long)budget + local, keys = blocks * b / 32;
-        const unsigned early = blocks > (long long)n1 * r ? n1 : (unsigned)((blocks + r - 1) / r);
+    // by_keys: else the segments from the last to the first, tile by tile
+    TileOrder(int n1, int r, int budget, int local, int b, int qtiles, int rows, bool by_keys) : turn(0) {
+        const long long blocks = (long long)budget + local, keys = blocks * b / rows;
+        const unsigned early = !by_keys || blocks > (long long)n1 * r ? n1 : (unsigned)((blocks + r - 1) / r);
         full = n1 - early; most = early * qtiles;
-        past = full == 0 || keys > most ? most : (unsigned)(keys + qtiles < most ? most - qtiles : keys);    // for segments of no multiple of 32 rows
+        past = full == 0 || keys > most ? most : (unsigned)(keys + qtiles < most ? most - qtiles : keys);    // for segments of no multiple of a tile's rows
         by_full = FastDiv(full ? full : 1); by_level = FastDiv(full + 1); by_tiles = FastDiv(qtiles);
     }
-    // Workgroups of four waves, two to a compute unit.  Where the chip holds all of them, the one that comes 256 after another joins it on its unit: the first 256 with the longest
-    // last, so that long and short share one (the longest first in both halves: fp32 4 x 4096 41.6 instead of 40.2, 8 x 1300 33.5 instead of 29.3).
-    void of_four(long long wgs) { turn = wgs > 256 && wgs <= 512 ? 256 : 0; }
     __host__ __device__ __forceinline__ unsigned place(unsigned id) const { return id < turn ? turn - 1 - id : id; }
     __host__ __device__ __forceinline__ Item item(unsigned rank, unsigned n1, unsigned qtiles) const {
         const unsigned above = (past + qtiles - most) * full;    // of full segments, with more keys than all others

@@ -21,9 +21,9 @@ extern "C" void order(unsigned bkv, unsigned group, unsigned n1, unsigned qtiles
         out[4 * wg] = t.bkv; out[4 * wg + 1] = t.gq; out[4 * wg + 2] = t.segment; out[4 * wg + 3] = t.tile;
     }
 }
-extern "C" void tiles(int n1, int r, int budget, int local, int b, int qtiles, long long wgs, int four, int* out) {
-    cp::TileOrder o(n1, r, budget, local, b, qtiles);
-    if (four) o.of_four(wgs);
+extern "C" void tiles(int n1, int r, int budget, int local, int b, int qtiles, int rows, long long wgs, int by_keys, int pairs, int* out) {
+    cp::TileOrder o(n1, r, budget, local, b, qtiles, rows, by_keys);
+    if (pairs) o.turn = 256;
     for (long long wg = 0; wg < wgs; ++wg) {
         const unsigned heads = (unsigned)(wgs / (n1 * qtiles)), place = o.place((unsigned)wg);
         const auto t = o.item(place / heads, n1, qtiles);
@@ -43,7 +43,7 @@ def lib(tmp_path_factory):
     subprocess.run([compiler, "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(where / "f.cpp"), "-o", str(where / "f.so")], check=True)
     lib = ctypes.CDLL(str(where / "f.so"))
     lib.order.argtypes = [ctypes.c_uint] * 5 + [ctypes.c_longlong, np.ctypeslib.ndpointer(np.int32)]
-    lib.tiles.argtypes = [ctypes.c_int] * 6 + [ctypes.c_longlong, ctypes.c_int, np.ctypeslib.ndpointer(np.int32)]
+    lib.tiles.argtypes = [ctypes.c_int] * 7 + [ctypes.c_longlong, ctypes.c_int, ctypes.c_int, np.ctypeslib.ndpointer(np.int32)]
     lib.order.restype = lib.tiles.restype = None
     return lib
 
@@ -70,20 +70,25 @@ def test_each_item_once(order, round_, kv_bytes):
 
 
 @pytest.mark.parametrize("heads", [1, 3, 8])
+@pytest.mark.parametrize("rows", [16, 32])
 @pytest.mark.parametrize("s,b", [(16, 16), (96, 32), (128, 128), (255, 51), (256, 32), (512, 64)])
-def test_each_row_tile_once(lib, heads, s, b):
-    r, qtiles = s // b, (s + 31) // 32
+def test_each_row_tile_once(lib, heads, rows, s, b):
+    r, qtiles = s // b, (s + rows - 1) // rows
     for n1 in (1, 2, 5, 16, 33):
+        wgs = heads * n1 * qtiles
         for budget, local in [(0, 0), (1, 0), (3, 2), (6, 1), (17, 0), (40, 1), (2000, 2), (2**30, 2**30)]:
-            for four in (0, 1):
-                out = np.full((heads * n1 * qtiles, 3), -1, np.int32)
-                lib.tiles(n1, r, budget, local, b, qtiles, len(out), four, out)
-                what = (n1, budget, local, four)
+            for by_keys, pairs in [(0, 0), (1, 0), (1, 1)]:
+                if pairs and not 256 < wgs <= 512:
+                    continue
+                out = np.full((wgs, 3), -1, np.int32)
+                lib.tiles(n1, r, budget, local, b, qtiles, rows, wgs, by_keys, pairs, out)
+                what = (n1, budget, local, by_keys, pairs)
                 assert (out >= 0).all() and (out < np.array([heads, n1, qtiles])).all(), what
                 assert len(np.unique(out, axis=0)) == len(out), what
-                if s % 32 or (budget + local) * b % 32:
-                    continue
-                keys = np.minimum((budget + local) * b, out[:, 1].astype(np.int64) * s) + 32 * (out[:, 2] + 1)
-                if four and 256 < len(out) <= 512:                # the longest 256 with the longest last
-                    keys[:256] = keys[:256][::-1].copy()
-                assert (np.diff(keys) <= 0).all(), what
+                if pairs:                                     # the longest 256 with the longest last
+                    out[:256] = out[:256][::-1].copy()
+                if not by_keys:
+                    assert (np.diff(out[:, 1] * qtiles + out[:, 2]) <= 0).all(), what
+                elif s % rows == 0 and (budget + local) * b % rows == 0:
+                    keys = np.minimum((budget + local) * b, out[:, 1].astype(np.int64) * s) + rows * (out[:, 2] + 1)
+                    assert (np.diff(keys) <= 0).all(), what
