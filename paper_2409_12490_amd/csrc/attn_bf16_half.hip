@@ -315,6 +315,7 @@ long long table_bytes(const Shape& sh) { return ((long long)sh.list_len * sh.b +
 
 }  // namespace
 
+// (Times before the heaviest tiles came first, work_order.h, which takes 3 to 13 % off this kernel and 3 to 37 % off the 256-row one where they take two rounds or more.)
 // The line lies where this kernel meets the other two (us, the better one of those / this one, runs of both in turn; t: row tiles of 32, w: 256-row workgroups).
 //   Segments of 65 to 128 rows: 2 x 8 heads x 93184 tokens (672 keys) 988 / 581; 32 x 8192 (416, 1184, 4256) 138 / 75, 248 / 157, 595 / 443; blocks of 16, 32 x 20000
 //   592 / 383, 32 x 60000 (3300) 4701 / 3136; segments of 96 165 / 128; t = 1400 to 1500: 16 x 2800 (1184) 43 / 38, 32 x 1500 37.4 / 36.6.  Below, lists that are short

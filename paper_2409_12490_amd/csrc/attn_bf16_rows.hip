@@ -348,6 +348,7 @@ long long attn_bf16_row_tiles(const Shape& sh, bool sparse, int rows) {
 
 static long long listed_keys(const Shape& sh) { return std::min((long long)sh.n, (long long)sh.list_len * sh.b); }
 
+// (Times before the orders of work_order.h, which take up to 15 % off this kernel.)
 // Few query rows: 256 of them to a workgroup leave compute units idle, 32 do not; where 256 fill the chip that kernel reads the keys once for eight
 // row tiles and takes two thirds of the time.  The lines lie where the two kernels meet (us, 256-row / 32-row kernel; t: row tiles of 32).
 //   block-sparse, up to t = 540 always: 32 heads x 500 17.6 / 12.1, 1 x 16K (960, 2624, 4672 keys) 28 / 20, 65 / 40, 112 / 61.

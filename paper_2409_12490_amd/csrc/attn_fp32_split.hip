@@ -26,7 +26,7 @@
 // of 1.9 GHz.  The splitting goes between the MFMAs of values split before (all of it first: 2 to 5 % slower).  Residues by v_dot2_f32_bf16, which reads
 // a bf16 without unpacking it, take half the instructions, but that unit does not run beside the MFMAs: no faster (815 to 840 us where this takes 813).  Two fp16
 // values and three products were faster (575), but hold 22 bits of a value within 2^13 of the largest and less of the others.
-// Dense 8 x 8192 1110 -> 830 us, 4 x 2500 77 -> 64; block-sparse 4 x 4096 (704 keys) 55 -> 44, 8 x 8192 (704) 194 -> 144.
+// Dense 8 x 8192 1110 -> 830 us, 4 x 2500 77 -> 64; block-sparse 4 x 4096 (704 keys) 55 -> 39, 8 x 8192 (704) 194 -> 144.
 #include "attn_fp32.h"
 
 #include <algorithm>
@@ -505,6 +505,7 @@ bool attn_fp32_split_better(const Shape& sh, bool sparse) {
     return tiles >= 144 && n >= 2400 && 3 * keys <= n;
 }
 
+// (Times before TileOrder, which takes up to 22 % off four waves with at most 512 workgroups.)
 // Eight waves leave one workgroup to a compute unit, four two.  Eight / four: up to a chip full of workgroups block-sparse 1 x 8192 (t = 256; 416, 1248,
 // 3136 keys) 21 / 24, 40 / 46, 82 / 98, dense 2 x 4096 95 / 116; beyond it rows of many and so unequal keys: dense 4 x 2500 (316) 64 / 76, 2 x 8192 (512) 229 /
 // 267, 3 x 6000 (564) 202 / 217, block-sparse 2 x 5000 (314, 3136) 84 / 98, 8 x 2048 (512, 2048) 68 / 74; but 2 x 6000 (376; 704, 3136) 47 / 42, 116 / 112, 4 x
