@@ -25,6 +25,9 @@ SHAPES = [
     (2, 1, 1009, 255, 51, 9, 1),          # the same dense; block-sparse a token per key
     (2, 2, 1001, 256, 16, 70, 1),         # 126 row tiles, long lists; a last tile of nine rows
     (3, 1, 688, 344, 43, 9, 1),           # dense 129 row tiles: one workgroup to a tile
+    (8, 2, 700, 256, 32, 4, 1),           # 352 row tiles of 16, two workgroups to a compute unit: long and short in pairs
+    (8, 2, 600, 512, 64, 4, 0),           # block-sparse: too many of 512 past the end of the last segment for that
+    (4, 2, 3000, 256, 64, 4, 1),          # 376 split tiles of 32 rows in pairs
     (3, 1, 500, 72, 24, 4, 1),            # blocks of 24: one token per key; segments no multiple of a row tile
 ]
 
