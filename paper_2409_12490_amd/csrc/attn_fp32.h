@@ -41,6 +41,10 @@ struct Args32 {
 // Row tiles of `rows` that exist: a segment's last one may be short.
 long long attn_fp32_row_tiles(const Shape& sh, bool sparse, int rows);
 
+// Where 16 rows go to a workgroup: waves of a workgroup, and workgroups that share a row tile.
+int attn_fp32_tile_waves(const Shape& sh, bool sparse);
+int attn_fp32_tile_parts(const Shape& sh, bool sparse);
+
 // Attention with fp32 factors split into three bf16 values, and whether it is the better one here.
 bool attn_fp32_split_better(const Shape& sh, bool sparse);
 hipError_t launch_attn_fp32_split(const Shape& sh, Args32& a, hipStream_t st);

@@ -128,21 +128,27 @@ class _Shape(ctypes.Structure):                  # cp::Shape of csrc/kernels.h
                 + [(x, ctypes.c_int64 * 3) for x in ("qs", "kvs", "os")])
 
 
-def attention_kernel(w: synth.Workload, sparse: bool = True) -> str:
-    """Which kernel the library's own rules give this attention: "32", "128" or "256" rows in bf16, "split" or "fp32".  For tests that are
-    written for one of them."""
+def _rule(w: synth.Workload, name: str, *args, restype=ctypes.c_bool):
+    """One of the library's own dispatch rules, a function of cp::Shape and truth values."""
     r = w.segment_size // w.block_size
     sh = _Shape(w.batch, w.n_q_heads, w.n_kv_heads, w.seq_len, w.segment_size, w.block_size, r, w.n_segments, w.n_blocks, w.budget_blocks,
                 w.local_blocks, w.budget_blocks + w.local_blocks + r)
     sh.kvs[2] = 128
+    f = getattr(B.load(), f"_ZN2cp{len(name)}{name}ERKNS_5ShapeE" + "b" * len(args))
+    f.restype = restype
+    return f(ctypes.byref(sh), *(ctypes.c_bool(a) for a in args))
 
-    def rule(name, *args):
-        f = getattr(B.load(), f"_ZN2cp{len(name)}{name}ERKNS_5ShapeE" + "b" * len(args))
-        f.restype = ctypes.c_bool
-        return f(ctypes.byref(sh), *(ctypes.c_bool(a) for a in args))
 
+def attention_kernel(w: synth.Workload, sparse: bool = True) -> str:
+    """Which kernel the library's own rules give this attention: "32", "128" or "256" rows in bf16, "split" or "fp32".  For tests that are
+    written for one of them."""
     if w.dtype == "fp32":
-        return "split" if rule("attn_fp32_split_better", sparse) else "fp32"
-    if sparse and rule("attn_bf16_half_better"):
+        return "split" if _rule(w, "attn_fp32_split_better", sparse) else "fp32"
+    if sparse and _rule(w, "attn_bf16_half_better"):
         return "128"
-    return "32" if rule("attn_bf16_rows_better", sparse) else "256"
+    return "32" if _rule(w, "attn_bf16_rows_better", sparse) else "256"
+
+
+def fp32_tiling(w: synth.Workload, sparse: bool = True):
+    """Workgroups that share a row tile of 16 and waves of each, by the library's own rules, where the "fp32" kernel takes tokens in runs or none listed."""
+    return tuple(_rule(w, name, sparse, restype=ctypes.c_int) for name in ("attn_fp32_tile_parts", "attn_fp32_tile_waves"))

@@ -146,3 +146,27 @@ def test_segment_far_longer_than_the_sequence():
     out, _ = H.gpu_sparse(w, qd, kd, vd, idx, torch.ones((1, 1, 1), dtype=torch.int32, device=DEV))
     d_ref, _ = O.dense_causal_attention(synth.to_f64(q), synth.to_f64(k), synth.to_f64(v))
     assert H.max_abs(out.cpu().numpy(), d_ref) <= H.TOL_OUT["fp32"]
+
+
+@pytest.mark.parametrize("n,others", [(600, 8), (1024, 3), (1025, 2), (1333, 2), (2048, 2)])
+@pytest.mark.parametrize("b", [16, 0], ids=["runs", "dense"])
+def test_a_shared_row_tile_has_the_same_bits(n, others, b):
+    """Two workgroups share the row tiles of small launches, each with half of the channels.  That changes no sum: the head's result is, bit for bit, that of the same
+    head among others, where a tile has one workgroup and its keys are split between as many waves (four, or eight for more than 1024 keys)."""
+    one = H.small_workload("alone", 1, 1, 1, n, 512, b or 64, 130 if b else 40, 1, dtype="fp32", unit_variance=True)
+    many = H.small_workload("among", 1, others, others, n, 512, b or 64, 130 if b else 40, 1, dtype="fp32", unit_variance=True)
+    assert H.attention_kernel(one, bool(b)) == H.attention_kernel(many, bool(b)) == "fp32"
+    waves = 8 if n > 1024 else 4
+    assert H.fp32_tiling(one, bool(b)) == (2, waves) and H.fp32_tiling(many, bool(b)) == (1, waves)
+    q, k, v = (t.to(DEV) for t in synth.make_qkv(many, threads=8))
+    Sd = np.random.default_rng(n).random((1, others, many.n_segments, many.n_blocks), dtype=np.float32)
+    idx, cnt = (torch.from_numpy(x).to(DEV) for x in O.select(Sd, 512, b or 64, many.budget_blocks, 1))
+    for h in (0, others - 1):
+        q1, k1, v1 = (t[:, h:h + 1].clone() for t in (q, k, v))
+        if b:
+            lists = [t[:, h:h + 1].clone() for t in (idx, cnt)]
+            pair = H.gpu_sparse(many, q, k, v, idx, cnt), H.gpu_sparse(one, q1, k1, v1, *lists)
+        else:
+            pair = H.gpu_dense(many, q, k, v), H.gpu_dense(one, q1, k1, v1)
+        for all_heads, alone in zip(*pair):
+            assert torch.equal(all_heads[:, h:h + 1], alone)
