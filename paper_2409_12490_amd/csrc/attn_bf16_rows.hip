@@ -41,7 +41,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a, Tile
     const int tid = thread_id(), lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // Consecutive workgroups walk the KV heads, so that a head's keys stay with few XCDs (workgroup id mod 8); then the query heads of a group, and inside a
-    // head the tiles that see most keys come first.
+    // head TileOrder.
     const int G = a.group, bkv = a.batch * a.hkv;
     const int wg = (int)(W == 4 ? order.place(workgroup_id()) : workgroup_id()), x = wg % bkv, y = wg / bkv;
     const int bb = x / a.hkv, kvh = x % a.hkv;
@@ -333,9 +333,7 @@ hipError_t launch(const ArgsB& a, TileOrder order, unsigned grid, hipStream_t st
 
 template <int W>
 static hipError_t launch_waves(const Shape& sh, const ArgsB& a, unsigned grid, hipStream_t st) {
-    const bool pairs = W == 4 && TileOrder::in_pairs(grid, attn_bf16_row_tiles(sh, a.idx != nullptr, kRowsTQ));
-    TileOrder order(sh.n1, sh.r, sh.budget, sh.local, sh.b, a.qtiles, kRowsTQ, pairs || grid > (W == 4 ? 512 : 256));   // what the chip holds at once needs no order but pairs
-    if (pairs) order.turn = 256;
+    const TileOrder order = TileOrder::of_launch(W, grid, attn_bf16_row_tiles(sh, a.idx != nullptr, kRowsTQ), sh.n1, sh.r, sh.budget, sh.local, sh.b, a.qtiles, kRowsTQ);
     if (!a.idx) return launch<2, W>(a, order, grid, st);
     return sh.b % 16 == 0 ? launch<1, W>(a, order, grid, st) : launch<0, W>(a, order, grid, st);
 }

@@ -338,9 +338,7 @@ template <int MODE, int RT, int W, int C>
 hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
     a.qtiles = ((a.idx ? min(sh.s, sh.n) : sh.n) + 16 * RT - 1) / (16 * RT);    // a segment may be set longer than the sequence
     const long long grid = (long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1);
-    const bool pairs = W == 4 && C == 1 && TileOrder::in_pairs(grid, attn_fp32_row_tiles(sh, a.idx != nullptr, 16 * RT));
-    a.order = TileOrder(sh.n1, sh.r, sh.budget, sh.local, sh.b, a.qtiles, 16 * RT, pairs);
-    if (pairs) a.order.turn = 256;
+    a.order = TileOrder::of_launch(W, grid, attn_fp32_row_tiles(sh, a.idx != nullptr, 16 * RT), sh.n1, sh.r, sh.budget, sh.local, sh.b, a.qtiles, 16 * RT);
     hipLaunchKernelGGL((attn_fp32_kernel<MODE, RT, W, C>), dim3((unsigned)grid, C), dim3(64 * W), 0, st, a);
     return hipGetLastError();
 }

@@ -467,10 +467,7 @@ template <int MODE, int W>
 hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
     a.qtiles = ((a.idx ? min(sh.s, sh.n) : sh.n) + TQ - 1) / TQ;    // a segment may be set longer than the sequence
     const long long grid = (long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1);
-    // eight waves, or more workgroups than the chip holds: segments from the last to the first (by keys: 8/2 x 3000 94 -> 101, 2 x 8/2 x 8000 352 -> 359)
-    const bool pairs = W == 4 && TileOrder::in_pairs(grid, attn_fp32_row_tiles(sh, a.idx != nullptr, TQ));
-    a.order = TileOrder(sh.n1, sh.r, sh.budget, sh.local, sh.b, a.qtiles, TQ, pairs);
-    if (pairs) a.order.turn = 256;
+    a.order = TileOrder::of_launch(W, grid, attn_fp32_row_tiles(sh, a.idx != nullptr, TQ), sh.n1, sh.r, sh.budget, sh.local, sh.b, a.qtiles, TQ);
     constexpr int smem = W * TQ * kHeadDim * 4 + 2 * 8 * 64 * 16;   // W = 4: half of a compute unit's LDS
     static_assert(2 * W * TQ * 4 + W * 4 <= 2 * 8 * 64 * 16, "what takes the place of Q");
     const hipError_t e = hipFuncSetAttribute((const void*)attn_fp32_split_kernel<MODE, W>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);

@@ -50,16 +50,28 @@ struct WorkOrder {
     }
 };
 
-// The order of the 32-row and 16-row kernels (attn_bf16_rows.hip, attn_fp32_split.hip, attn_fp32.hip) inside a head: row tiles by the keys that they see, most first, where the segments came from the
-// last to the first.  A segment whose list is full sees `past` tiles' worth of keys before it and those up to the tile; the others, at the start of the sequence, see all
-// keys up to the tile.  The lists on the GPU may say otherwise: the order decides the time alone.  Before / now (us): bf16 32 heads x 900 tokens (512, 64; 4 blocks) 22.1 / 18.8, 32 x
-// 700 (256, 32; 16) 16.9 / 15.4, 8 x 4000 (512, 64; 40) 54.9 / 52.2, and with the turn below 4 x 4000 (512, 16; 64) 20.8 / 19.1, 2 x 8000 (512, 64; 40) 36.7 / 33.8; fp32 4 x 4096 (256,
-// 64; 6) 43.7 / 39.4, (512, 64; 20) 97 / 84, 4 x 3000 (256, 64; 4) 34.4 / 28.2, 2 x 6000 (512, 64; 4) 45.2 / 34.8, 2 x 7000 (16) 83 / 73; 16-row
-// tiles 8 x 700 (256, 32; 4) 15.6 / 13.5, 8 x 900 (512, 64; 4) 25.4 / 22.7, dense 8 x 800 25.2 / 19.4, 16 x 400 15.5 / 12.2, 12 x 600 21.5 / 16.8.
+// The order of the kernels with 32 and 16 rows to a workgroup (attn_bf16_rows.hip, attn_fp32_split.hip, attn_fp32.hip) inside a head.
+//
+// Every launch but those of in_pairs: segments from the last to the first, and the row tiles of a segment, which read the same keys, after one
+// another.
+//
+// In pairs: workgroups of four waves, two to a compute unit, where the chip holds all of them.  Row tiles come by the keys that they see, most
+// first, and the workgroup that comes 256 after another joins it on its unit, so the first 256 come with the longest last (turn = 256) and long and
+// short ones share a unit.  A segment whose list is full sees `past` tiles' worth of keys before it and those up to the tile; the others, at the
+// start of the sequence, see all keys up to the tile.  The lists on the GPU may say otherwise: the order decides the time alone.
+//
+// Attention alone, us (segment, block; blocks listed).  Segments from the last to the first / by keys without the turn / in pairs: bf16 4 heads x
+// 4000 tokens (512, 16; 64) 21.1 / 19.5 / 19.3, 2 x 8000 (512, 64; 40) 37.9 / 34.4 / 34.1; fp32 4 x 4096 (256, 64; 6) 44.9 / 42.6 / 41.1, (512, 64; 20)
+// 98 / 89 / 85, 4 x 3000 (256, 64; 4) 35.2 / 28.8 / 28.6, 2 x 6000 (512, 64; 4) 46 / 38 / 35; 16-row tiles 8 x 700 (256, 32; 4) 15.6 / 16.7 / 13.5, 8 x 900
+// (512, 64; 4) 25.5 / 25.0 / 22.7, dense 8 x 800 25.5 / 25.5 / 19.5, 16 x 400 15.7 / 15.7 / 12.3, 12 x 600 21.5 / 21.5 / 16.7.
+// More workgroups than the chip holds, by keys / segments from the last to the first.  The tiles of a segment come half a launch apart by keys, and
+// its keys from memory again: bf16 batch 4 x 8/8 x 30000 (128, 8; 100) 1083 / 999, 12/12 x 60000 800 / 759, 32/8 x 32768 (64, 16; 10) 418 / 408; just
+// above the chip long ones share a unit: 16/4 x 1100 (512, 64; 4) 18.4 / 13.5, 4/2 x 4700 (14) 28.5 / 23.4, 32/8 x 900 (4) 18.3 / 17.7; fp32 8/2 x 3000
+// 101 / 94.  By keys is better for few KV heads of short lists, 8/2 x 60000 (64, 16; 20) 242 / 253, 2/1 x 12000 (256, 64; 30) 46.4 / 48.8; over 215
+// launches it is 0.8 % behind.
 struct TileOrder {
-    // Workgroups of four waves, two to a compute unit.  Where the chip holds all of them, the one that comes 256 after another joins it on its unit: the first 256 come with the
-    // longest last (turn = 256), so that long and short share one (the longest first in both halves: fp32 4 x 4096 41.6 instead of 40.2, 8 x 1300 33.5 instead of 29.3).  Not where many of
-    // them find no rows, past the end of a short last segment, and leave their places to others (fp32 8 x 600, 208 of 512: 15.5 -> 21.2, 8 x 1300, 56 of 328: 29.0 -> 29.4; 8 x 900, 56 of 512: 25.4 -> 22.7).
+    // Not where many workgroups find no rows, past the end of a short last segment, and leave their places to others: fp32 8 x 600 (512, 64; 4; 208 of
+    // 512) would take 20.0 instead of 14.7, but 8 x 900 (56 of 512) gains as above.
     static bool in_pairs(long long wgs, long long with_rows) { return wgs > 256 && wgs <= 512 && 8 * (wgs - with_rows) <= wgs; }
 
     struct Item { int segment, tile; };
@@ -75,6 +87,13 @@ struct TileOrder {
         full = n1 - early; most = early * qtiles;
         past = full == 0 || keys > most ? most : (unsigned)(keys + qtiles < most ? most - qtiles : keys);    // for segments of no multiple of a tile's rows
         by_full = FastDiv(full ? full : 1); by_level = FastDiv(full + 1); by_tiles = FastDiv(qtiles);
+    }
+    // The order of a launch of `wgs` workgroups, of which `with_rows` have rows.
+    static TileOrder of_launch(int waves, long long wgs, long long with_rows, int n1, int r, int budget, int local, int b, int qtiles, int rows) {
+        const bool pairs = waves == 4 && in_pairs(wgs, with_rows);
+        TileOrder o(n1, r, budget, local, b, qtiles, rows, pairs);
+        if (pairs) o.turn = 256;
+        return o;
     }
     __host__ __device__ __forceinline__ unsigned place(unsigned id) const { return id < turn ? turn - 1 - id : id; }
     __host__ __device__ __forceinline__ Item item(unsigned rank, unsigned n1, unsigned qtiles) const {

@@ -30,6 +30,14 @@ extern "C" void tiles(int n1, int r, int budget, int local, int b, int qtiles, i
         out[3 * wg] = place % heads; out[3 * wg + 1] = t.segment; out[3 * wg + 2] = t.tile;
     }
 }
+extern "C" int launched(int waves, long long wgs, long long with_rows, int n1, int r, int budget, int local, int b, int qtiles, int rows, int* out) {
+    const cp::TileOrder o = cp::TileOrder::of_launch(waves, wgs, with_rows, n1, r, budget, local, b, qtiles, rows);
+    for (int rank = 0; rank < n1 * qtiles; ++rank) {
+        const auto t = o.item(rank, n1, qtiles);
+        out[2 * rank] = t.segment; out[2 * rank + 1] = t.tile;
+    }
+    return o.turn;
+}
 """
 
 
@@ -45,6 +53,7 @@ def lib(tmp_path_factory):
     lib.order.argtypes = [ctypes.c_uint] * 5 + [ctypes.c_longlong, np.ctypeslib.ndpointer(np.int32)]
     lib.tiles.argtypes = [ctypes.c_int] * 7 + [ctypes.c_longlong, ctypes.c_int, ctypes.c_int, np.ctypeslib.ndpointer(np.int32)]
     lib.order.restype = lib.tiles.restype = None
+    lib.launched.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_longlong] + [ctypes.c_int] * 7 + [np.ctypeslib.ndpointer(np.int32)]
     return lib
 
 
@@ -92,3 +101,16 @@ def test_each_row_tile_once(lib, heads, rows, s, b):
                 elif s % rows == 0 and (budget + local) * b % rows == 0:
                     keys = np.minimum((budget + local) * b, out[:, 1].astype(np.int64) * s) + rows * (out[:, 2] + 1)
                     assert (np.diff(keys) <= 0).all(), what
+
+
+@pytest.mark.parametrize("waves,wgs,with_rows,pairs", [(4, 256, 256, 0), (4, 257, 257, 1), (4, 512, 512, 1), (4, 513, 513, 0), (4, 4096, 4096, 0), (4, 1 << 20, 1 << 20, 0), (8, 257, 257, 0),
+                                                       (8, 512, 512, 0), (8, 4096, 4096, 0), (4, 512, 448, 1), (4, 512, 447, 0), (4, 384, 336, 1), (4, 384, 335, 0)])
+def test_order_of_a_launch(lib, waves, wgs, with_rows, pairs):
+    """Long and short row tiles in pairs where the chip holds all workgroups of four waves, two to a compute unit, and one in eight at most is past the end.  In every other launch the row tiles of
+    a segment stay together: they read the same keys."""
+    for n1, s, b, rows, budget in [(64, 64, 16, 32, 20), (200, 48, 16, 32, 60), (33, 128, 8, 32, 100), (16, 512, 64, 32, 6), (9, 256, 32, 16, 4)]:
+        qtiles = -(-s // rows)
+        out = np.full((n1 * qtiles, 2), -1, np.int32)
+        assert lib.launched(waves, wgs, with_rows, n1, s // b, budget, 1, b, qtiles, rows, out) == (256 if pairs else 0)
+        together = (out.reshape(n1, qtiles, 2)[:, :, 0] == np.arange(n1)[::-1, None]).all()
+        assert together == (not pairs), (n1, s, b)
