@@ -1,16 +1,22 @@
-// Which (batch, query head, segment, row tile) a workgroup of block-sparse attention takes (256-row and 128-row bf16 kernels).
+// Which (batch, query head, segment, row tile) a workgroup of block-sparse attention takes.  The orders decide the time alone.
 //
-// A compute unit takes the next workgroup in order when it is free, and each of the 8 XCDs every eighth workgroup, so the order decides how evenly the units finish and
-// what the caches hold.  The heaviest come first: segments from the last to the first, all heads of one, and (head, segment) pairs in rounds that fill the chip once, a
-// round at its last row tile, which sees most keys, then the same pairs at the one before.  With the tiles of a segment in one round the units that get first tiles get
-// them again in the next, and with segments in ascending order the long ones of the last heads are left over.  Heads of one KV head after another, ascending segments -> this order (us):
-// 32/8 heads x 3000 tokens (512, 64; 32 blocks) 112 -> 73, 4000 (16) 86 -> 81, 4096 (64) 188 -> 123, 7000 (256, 32; 32) 150 -> 143, 8000 (32) 265 -> 255, 16384 (16) 360 -> 351, 32/4 x
-// 24000 (32) 825 -> 805, 2 x 32/8 x 12340 (512, 32; 67) 880 -> 838; 128-row workgroups 32/8 x 8192 (128, 32; 128) 443 -> 394.  A model of units that take the next workgroup
-// when they are free (5.5 us and 1.65 per tile of 64 keys) gives the same gains; what it leaves at 32/8 x 16384 is 3 % above an even split.
+// WorkOrder: the kernels with 256 and 128 rows to a workgroup (attn_bf16.hip, attn_bf16_half.hip).
 //
-// Consecutive workgroups walk the KV heads, so that one's keys stay with one XCD or two.  More than 64 MiB of keys and values are walked eight KV heads at a time, one to
-// an XCD (16 / 8 at a time: 2 x 32/8 x 12340 815 / 809, 34000 (256, 32; 32) 1319 / 1303, 65536 2480 / 2435).  Smaller ones are walked all together: fewer
-// rounds that are not full.
+// A compute unit takes the next workgroup in order when it is free, and each of the 8 XCDs every eighth workgroup, so the order decides how evenly
+// the units finish and what the caches hold.  The heaviest come first: segments from the last to the first, all heads of one, and (head, segment)
+// pairs in rounds that fill the chip once, a round at its last row tile, which sees most keys, then the same pairs at the one before.  With the tiles
+// of a segment in one round the units that get first tiles get them again in the next, and with segments in ascending order the long ones of the last
+// heads are left over.  One KV head after another, ascending segments -> this order (us; (segment, block; blocks listed)): 32/8 heads x 3000 tokens
+// (512, 64; 32) 113 -> 74, 4000 (16) 86 -> 81, 4096 (64) 188 -> 128, 7000 (256, 32; 32) 149 -> 142, 8000 (512, 64; 32) 267 -> 253, 16384 (16) 363 -> 349,
+// 32/4 x 24000 (32) 828 -> 808, 2 x 32/8 x 12340 (512, 32; 67) 879 -> 832; 128-row workgroups 32/8 x 8192 (128, 32; 128) 440 -> 389, (32) 158 -> 153.  A
+// model of units that take the next workgroup when they are free (5.5 us and 1.65 per tile of 64 keys) gives the same gains; what it leaves at
+// 32/8 x 16384 is 3 % above an even split.
+//
+// Consecutive workgroups walk the KV heads of a set.  Up to 64 MiB of keys and values all KV heads are one set, which leaves fewer rounds that are not
+// full (36/12 x 10000 in sets of 4 376 instead of 366).  More of them are walked 8, 4, 2 or 1 at a time, the largest of these that divides their
+// number, so that every eighth workgroup, an XCD's, reads the keys of one KV head: all together / in sets, 2 x 32/8 x 34000 (256, 32; 32) 1371 / 1336
+// (sets of 4 1333), 65536 2668 / 2581 (2583); 36/12 x 14000 (512, 64; 32) 535 / 529, 49152 1976 / 1912; 40/10 x 65536 2906 / 2810.  An odd number goes one
+// at a time, which is better than together but 1 to 2 % behind neighbouring segments on one XCD: 25/5 x 65536 1856 / 1810, where that takes 1770.
 #pragma once
 #include "fast_div.h"
 
@@ -24,7 +30,8 @@ struct WorkOrder {
     WorkOrder() = default;
     // bkv = batch * hkv, group = query heads of a KV head, n1 segments of qtiles row tiles, workgroups that fill the chip, bytes of K and V
     WorkOrder(unsigned bkv, unsigned group, unsigned n1, unsigned qtiles, unsigned round, long long kv_bytes) {
-        set_kv = bkv % 8 == 0 && kv_bytes > (64ll << 20) ? 8 : bkv;
+        const unsigned least = bkv & (0u - bkv);        // the largest power of two that divides it
+        set_kv = kv_bytes <= (64ll << 20) ? bkv : least < 8 ? least : 8;
         set_heads = set_kv * group;
         const unsigned pairs = bkv * group * n1;
         rest = pairs % round; full = pairs - rest;

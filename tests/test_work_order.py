@@ -1,6 +1,7 @@
 """The order of workgroups of block-sparse attention (WorkOrder, TileOrder), compiled for the CPU from the header the kernels include: every (KV head, query head,
 segment, row tile) exactly once, whatever the numbers of heads and segments leave over after whole rounds, and the heaviest first."""
 import ctypes
+import math
 import os
 import shutil
 import subprocess
@@ -65,17 +66,19 @@ def order(lib):
 @pytest.mark.parametrize("round_", [256, 512])
 @pytest.mark.parametrize("kv_bytes", [1 << 26, (1 << 26) + 1])
 def test_each_item_once(order, round_, kv_bytes):
-    for bkv, group, n1, qtiles in [(1, 1, 1, 1), (1, 1, 1, 3), (8, 4, 8, 1), (8, 4, 8, 2), (8, 4, 33, 2), (16, 4, 129, 1), (24, 1, 11, 5), (17, 1, 31, 2), (6, 3, 57, 4), (16, 8, 4, 2), (2, 1, 257, 1)]:
+    for bkv, group, n1, qtiles in [(1, 1, 1, 1), (1, 1, 1, 3), (8, 4, 8, 1), (8, 4, 8, 2), (8, 4, 33, 2), (16, 4, 129, 1), (24, 1, 11, 5), (17, 1, 31, 2), (6, 3, 57, 4), (12, 3, 40, 2), (5, 1, 9, 2), (16, 8, 4, 2), (2, 1, 257, 1)]:
         out = np.full((bkv * group * n1 * qtiles, 4), -1, np.int32)
         order(bkv, group, n1, qtiles, round_, kv_bytes, out)
         what = (bkv, group, n1, qtiles)
         assert (out >= 0).all() and (out < np.array([bkv, group, n1, qtiles])).all(), what
         assert len(np.unique(out, axis=0)) == len(out), what
-        at_a_time = 8 if bkv % 8 == 0 and kv_bytes > 1 << 26 else bkv
+        at_a_time = math.gcd(bkv, 8) if kv_bytes > 1 << 26 else bkv
         last_tile = out[out[:, 3] == qtiles - 1]
         for first in range(0, bkv, at_a_time):                # the segments of a set of KV heads, from the last to the first
             segments = last_tile[last_tile[:, 0] // at_a_time == first // at_a_time, 2]
             assert (np.diff(segments) <= 0).all(), what
+        assert (np.diff(last_tile[:, 0] // at_a_time) >= 0).all(), what       # set after set; in each an XCD, every eighth workgroup, has one KV head to read
+        assert (last_tile[:, 0] % at_a_time == np.arange(len(last_tile)) % at_a_time).all(), what
 
 
 @pytest.mark.parametrize("heads", [1, 3, 8])
