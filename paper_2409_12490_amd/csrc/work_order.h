@@ -12,11 +12,16 @@
 // model of units that take the next workgroup when they are free (5.5 us and 1.65 per tile of 64 keys) gives the same gains; what it leaves at
 // 32/8 x 16384 is 3 % above an even split.
 //
+// Launches of less than two rounds and one workgroup more to each of the 256 units take all pairs at their last row tile before any at the one before: by
+// rounds the units that take a third workgroup have two long ones.  By rounds / all pairs: 8/2 x 18523 (512, 32; 16) 88.8 / 84.2, 20443 (512, 64; 16)
+// 124.9 / 120.1, 16/16 x 8283 (512, 32; 16) 83.3 / 72.2, 128-row workgroups 4/2 x 37083 (256, 16; 4) 41.5 / 39.7.  With more, the tiles of a segment come too
+// far apart: 16/16 x 47963 (1024, 64; 32) 942 / 969, 128-row 32/8 x 6123 (256, 16; 4) 44.4 / 46.7, 8/2 x 20443 (256, 16; 30) 71.8 / 73.5.
+//
 // Consecutive workgroups walk the KV heads of a set.  Up to 64 MiB of keys and values all KV heads are one set, which leaves fewer rounds that are not
 // full (36/12 x 10000 in sets of 4 376 instead of 366).  More of them are walked 8, 4, 2 or 1 at a time, the largest of these that divides their
 // number, so that every eighth workgroup, an XCD's, reads the keys of one KV head: all together / in sets, 2 x 32/8 x 34000 (256, 32; 32) 1371 / 1336
 // (sets of 4 1333), 65536 2668 / 2581 (2583); 36/12 x 14000 (512, 64; 32) 535 / 529, 49152 1976 / 1912; 40/10 x 65536 2906 / 2810.  An odd number goes one
-// at a time, which is better than together but 1 to 2 % behind neighbouring segments on one XCD: 25/5 x 65536 1856 / 1810, where that takes 1770.
+// at a time, which is better than together but 1 to 2 % behind neighbouring segments on one XCD: 25/5 x 65536 1856 / 1810, where that takes 1754.
 #pragma once
 #include "fast_div.h"
 
@@ -34,7 +39,8 @@ struct WorkOrder {
         set_kv = kv_bytes <= (64ll << 20) ? bkv : least < 8 ? least : 8;
         set_heads = set_kv * group;
         const unsigned pairs = bkv * group * n1;
-        rest = pairs % round; full = pairs - rest;
+        rest = pairs * qtiles < 2 * round + 256 ? pairs : pairs % round;
+        full = pairs - rest;
         by_round = FastDiv(round * qtiles); by_rest = FastDiv(rest ? rest : 1);
         by_set = FastDiv(set_heads * n1); by_heads = FastDiv(set_heads); by_kv = FastDiv(set_kv);
     }
