@@ -315,18 +315,21 @@ long long table_bytes(const Shape& sh) { return ((long long)sh.list_len * sh.b +
 
 }  // namespace
 
-// (Times before the heaviest tiles came first, work_order.h, which takes 3 to 13 % off this kernel and 3 to 37 % off the 256-row one where they take two rounds or more.)
-// The line lies where this kernel meets the other two (us, the better one of those / this one, runs of both in turn; t: row tiles of 32, w: 256-row workgroups).
-//   Segments of 65 to 128 rows: 2 x 8 heads x 93184 tokens (672 keys) 988 / 581; 32 x 8192 (416, 1184, 4256) 138 / 75, 248 / 157, 595 / 443; blocks of 16, 32 x 20000
-//   592 / 383, 32 x 60000 (3300) 4701 / 3136; segments of 96 165 / 128; t = 1400 to 1500: 16 x 2800 (1184) 43 / 38, 32 x 1500 37.4 / 36.6.  Below, lists that are short
-//   beside the sequence: t = 750 to 1024: 8 x 3000 (672, 1184) 22.5 / 20.9, 28.5 / 31.4, 4 x 6000 (416, 1440) 17.5 / 15.7, 38.2 / 38.7, 8 x 4096 (416,
-//   2208) 20.7 / 17.0, 51 / 56; t = 560 to 660: 2 x 9000 (672) 23.2 / 21.4, 4 x 4500 (416, 672) 16.9 / 15.6, 20.0 / 21.1, 2 x 10500 (2208) 53 / 55.
-//   Up to 64 rows half of this kernel is empty too: 32 x 8192, segments of 64 158 / 173.
-//   Segments that fill a quarter less of its workgroups: of 384 225 / 177, 1291 / 1158, of 320 252 / 202; as much of either: of 192 145 / 140, 265 / 279, 997 / 1064.
-//   Else it reads the keys twice as often and loses (32 x 16384, segments of 512, 1600 keys 356 / 385, 32 x 50000 1058 / 1216), but not where 256-row
-//   workgroups leave half of the chip idle (w = 128: 8 x 4000 21.0 / 19.7, 37.8 / 36.5, 25.6 / 24.3, 42.2 / 40.9; w = 188 to 256: 8 x 6000 21.0 / 22.0, 32 x 1500 35.8 / 37.3, 8 x 8000 25.2 / 26.2, 41.0 / 43.1, 32 x 2000 39.1 / 41.4, 16 x 4000 40.2 / 42.6) and for short
-//   lists of blocks of an odd multiple of 16, whose keys that kernel takes one by one (528, 784, 1296 keys: w = 500 50.7 / 46.2, 62.7 / 59.3, 89 / 85, w = 2048 189 / 174,
-//   247 / 236, 346 / 355; w = 6272 (784) 639 / 632).
+// The line lies where this kernel meets the other two (us, the better one of those / this one, all in the orders of work_order.h; t: row tiles of 32, w: 256-row
+// workgroups).
+//   Segments of 65 to 128 rows: 2 x 8 heads x 93184 tokens (672 keys) 978 / 580; 32 x 8192 (416, 1184, 4256) 122 / 71, 235 / 151, 589 / 393; blocks of 16,
+//   32 x 20000 (672) 413 / 249, 32 x 60000 (3296) 4679 / 2942; segments of 96 157 / 122; t = 1400 to 1500: 16 x 2800 (1184) 40 / 34, 32 x 1500 29 / 22.  Below, lists
+//   that are short beside the sequence: t = 750 to 1024: 8 x 3000 (672, 1184) 21.4 / 20.3, 27.2 / 31.1, 4 x 6000 (416, 1440) 16.9 / 14.9, 34.8 / 36.6, 8 x 4096
+//   (416, 2208) 17.7 / 15.3, 47 / 53; t = 560 to 660: 2 x 9000 (672) 21.8 / 20.2, 4 x 4500 (416, 672) 16.0 / 14.7, 18.3 / 20.1, 2 x 10500 (2208) 50 / 53.
+//   Up to 64 rows half of this kernel is empty too: 32 x 8192, segments of 64 156 / 167.
+//   Segments that fill a quarter less of its workgroups: of 384 32 x 4096, 8192, 32768 (1440) 109 / 82, 205 / 168, 879 / 717, of 320 114 / 94, 239 / 196, 1010 / 816, of
+//   288 118 / 108, 249 / 208, 1055 / 897; as much of either: of 192 32 x 8192 (480, 1248) 103 / 97, 193 / 198, 32 x 32768 (736) 527 / 545.
+//   Else it reads the keys twice as often and loses (32 x 16384, segments of 512, 1600 keys 345 / 368, 32 x 50000 1069 / 1157), but not where 256-row
+//   workgroups leave half of the chip idle (w = 128: 8 x 4000 (832, 1600) 24.0 / 23.0, 37.3 / 39.4, the better one of 256 rows 39.8; w = 188 to 256: 8 x 6000 25.7 / 26.3,
+//   41.6 / 44.8, 32 x 1500 24.5 / 25.1, 8 x 8000 27.5 / 27.8, 45.3 / 47.8, 32 x 2000 26.2 / 26.8, 41.8 / 45.2, 16 x 4000 27.2 / 27.7, 44.0 / 47.1) and for short
+//   lists of blocks of an odd multiple of 16, whose keys that kernel takes one by one: w = 512 (528, 784 keys) 46.0 / 41.2, 58.3 / 54.0, w = 2048 188 / 164, 240 / 221,
+//   w = 6272 (336, 528) 419 / 360, 539 / 487; 1232 to 1296 keys, w = 512 to 1504 83 / 79, 171 / 160, 238 / 227, but w = 6272 1043 / 1054 and heads of
+//   their own KV head 16/16 x 30000 (w = 2400; 400, 80; 1280) 377 / 388, x 131072 (w = 8752; 480, 48; 912) 1009 / 1020.
 bool attn_bf16_half_better(const Shape& sh) {
     if (sh.b % 16 != 0 || table_bytes(sh) > kTabMax) return false;
     const long long tiles = attn_bf16_row_tiles(sh, true, WQ), wide = attn_bf16_row_tiles(sh, true, 256), halves = attn_bf16_row_tiles(sh, true, TQ);
@@ -335,7 +338,7 @@ bool attn_bf16_half_better(const Shape& sh) {
         return 8 * wide < 4 * tiles && (tiles >= 1400 || (tiles > 700 && 5ll * sh.n >= 22 * keys) || (tiles > 540 && sh.n >= 10 * keys));
     if (attn_bf16_rows_better(sh, true)) return false;
     if (wide <= 256) return halves <= 256;
-    return 8 * wide >= 5 * halves || (sh.b % 32 != 0 && keys <= 1100 && wide <= 4200);
+    return 8 * wide >= 5 * halves || (sh.b % 32 != 0 && (keys <= 768 || (keys <= 1100 && wide <= 4200) || (keys <= 1300 && wide <= 1600)));
 }
 
 hipError_t launch_attn_bf16_half(const Shape& sh, ArgsB a, hipStream_t st) {
