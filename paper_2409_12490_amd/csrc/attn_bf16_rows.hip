@@ -346,19 +346,20 @@ long long attn_bf16_row_tiles(const Shape& sh, bool sparse, int rows) {
 
 static long long listed_keys(const Shape& sh) { return std::min((long long)sh.n, (long long)sh.list_len * sh.b); }
 
-// (Times before the orders of work_order.h, which take up to 15 % off this kernel.)
 // Few query rows: 256 of them to a workgroup leave compute units idle, 32 do not; where 256 fill the chip that kernel reads the keys once for eight
-// row tiles and takes two thirds of the time.  The lines lie where the two kernels meet (us, 256-row / 32-row kernel; t: row tiles of 32).
-//   block-sparse, up to t = 540 always: 32 heads x 500 17.6 / 12.1, 1 x 16K (960, 2624, 4672 keys) 28 / 20, 65 / 40, 112 / 61.
-//   t = 576 to 657, keys few beside the sequence lose: 1 x 19000 (800, 1312 keys) 26.1 / 28.2, 38 / 37, 2 x 9500 27.8 / 30.1 (960), 37.8 / 35.1 (1312), but 4
-//   x 4700, 960 keys 27.9 / 24.4, 8 x 2300 27.3 / 21.2.
-//   t = 700 to 880: 8 x 3500, 960 keys 28.8 / 30.4, 1 x 24000 (1312) 39.1 / 40.0, 2 x 14000 (1312) 39.4 / 41.1, but 4 x 7000 (1312) 39.9 / 38.7, 8 x 3500 (2624) 65 / 50,
-//   2 x 14000 (2624) 67 / 64, 32 x 850 26.4 / 23.5.
-//   t = 1024: 8 x 4096 (960, 1312, 2624) 30 / 34, 40.2 / 39.3, 70 / 60, 4 x 8192 (2624) 72 / 67, 2 x 16384 (2624, 4672) 70 / 73, 119 / 115, 32 x 1000 30.2 / 27.7;
-//   t = 1500: 32 x 1500 32 / 41, 8 x 6000 (4672) 122 / 125.
+// row tiles and takes two thirds of the time.  The lines lie where this kernel meets the other two (us, the better one of those / this one, all in the orders of
+// work_order.h; segments of 512, blocks of 64; keys listed in brackets; t: row tiles of 32).
+//   block-sparse, up to t = 540 always: 32 heads x 500 15.9 / 9.8, 1 x 16384 (960, 2624, 4672) 25.3 / 19.0, 61 / 37, 104 / 58.
+//   t = 576 to 657, keys few beside the sequence lose: 1 x 19000 (832, 1344) 23.3 / 25.4, 34.3 / 34.2, 2 x 9500 (960, 1344) 26.0 / 26.2, 34.1 / 29.6, but 4 x 4700
+//   (960) 25.3 / 19.8, 8 x 2300 25.4 / 16.4.
+//   t = 700 to 880: 8 x 3500 (960) 25.6 / 25.3, 1 x 24000 (1344) 34.8 / 35.1, 2 x 14000 (1344) 34.5 / 37.1, 4 x 7000 (1344) 33.9 / 34.6, but 8 x 3500 (2624) 61 / 43,
+//   2 x 14000 (2624) 62 / 57, 32 x 850 (832) 20.3 / 17.5.
+//   t = 900 to 1024: 8 x 4096 (960, 1344, 2624) 25.7 / 27.2, 33.9 / 33.6, 61 / 49, 4 x 8192 (2624) 62 / 58, 2 x 16384 (2624, 4672) 62 / 64, 105 / 101, 32 x 1000 (832)
+//   23.2 / 20.5, 16 x 2000 (1600) 39.5 / 31.0; of 178 launches at most twice as long as their keys (eight numbers of heads) this kernel takes 0.64 to 0.90 of
+//   the time on average, 0.53 to 1.04 in each; t = 1500: 32 x 1500 (1344) 35.1 / 36.1, 8 x 6000 (4672) 105.4 / 104.9.
 //   segments of 128 rows and less leave half of a 256-row workgroup empty, at any length (most of those of 65 to 128 rows are the 128-row kernel's, which is asked
-//   first, attn_bf16_half_better): 32 heads x 8192, segments of 128 (416, 1184, 4256 keys) 143 /
-//   148, 302 / 266, 877 / 612, of 64 (592) 368 / 171; 4 x 9000 (416) 35 / 28; segments of 192 220 / 272.
+//   first, attn_bf16_half_better): against 256 rows 32 heads x 8192, segments of 128 (416, 1184, 4256) 127 / 122, 269 / 235, 676 / 589, of 64 (592) 312 / 156; segments
+//   of 192 (480) 103 / 128.
 //   dense, 49152 rows: 32 x 1500 40 / 36, 8 x 6000 147 / 109, 4 x 12000 280 / 208; 65536 rows: 32 x 2000 53 / 57, 8 x 8192 205 / 192, 2 x 32768 745 /
 //   720; 32 x 1750 48.9 / 49.5; 96000 rows: 8 x 12000 323 / 389.
 bool attn_bf16_rows_better(const Shape& sh, bool sparse) {
@@ -369,8 +370,7 @@ bool attn_bf16_rows_better(const Shape& sh, bool sparse) {
     if (8 * wide >= 4 * tiles) return true;
     if (8 * wide >= 2 * tiles) return tiles <= 1200 || keys >= 512;
     if (tiles <= 660) return keys >= 1300 || sh.n <= 5 * keys;
-    if (tiles <= 900) return sh.n <= 2 * keys || (keys >= 1300 && sh.n <= 8 * keys);
-    return tiles <= 1024 && (5ll * sh.n <= 6 * keys || (keys >= 2400 && 2ll * sh.n <= 7 * keys));
+    return tiles <= 1024 && (sh.n <= 2 * keys || (tiles <= 900 ? keys >= 1300 && sh.n <= 8 * keys : keys >= 2400 && 2ll * sh.n <= 7 * keys));
 }
 
 // Eight waves where the workgroups are too few to give every compute unit two, and for long rows of unequal length; four otherwise, two workgroups to

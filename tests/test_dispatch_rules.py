@@ -17,3 +17,13 @@ def workload(dtype, heads, kv_heads, n, s, b, k, L=1):
 ])
 def test_blocks_of_odd_multiples_of_16(n, s, b, k, kernel):
     assert H.attention_kernel(workload("bf16", 32, 8, n, s, b, k)) == kernel
+
+
+@pytest.mark.parametrize("heads,n,s,b,k,kernel", [
+    ((32, 8), 1000, 512, 64, 4, "32"), ((32, 8), 1024, 512, 64, 4, "32"), ((32, 8), 1025, 512, 64, 4, "256"),    # 1024 row tiles, 832 keys; 1056
+    ((16, 4), 1664, 512, 64, 4, "32"), ((16, 4), 1665, 512, 64, 4, "128"),                                       # at most twice the keys
+    ((16, 4), 2000, 512, 64, 16, "32"), ((8, 2), 4000, 512, 64, 32, "32"), ((8, 2), 4000, 512, 64, 16, "128"), ((8, 2), 4096, 512, 64, 32, "32"),
+    ((1, 1), 32768, 512, 64, 247, "32"), ((1, 1), 32768, 512, 64, 160, "32"), ((1, 1), 32768, 512, 64, 100, "128"), ((1, 1), 32769, 512, 64, 247, "256"),
+])
+def test_rows_of_32_up_to_1024_row_tiles(heads, n, s, b, k, kernel):
+    assert H.attention_kernel(workload("bf16", *heads, n, s, b, k)) == kernel
