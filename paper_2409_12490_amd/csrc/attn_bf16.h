@@ -105,8 +105,10 @@ inline long long attn_bf16_kv_bytes(const Shape& sh) { return 4ll * sh.batch * s
 // Workgroups of `rows` query rows that a launch needs: a segment's last one may be short.
 long long attn_bf16_row_tiles(const Shape& sh, bool sparse, int rows);
 
-// Attention with 32-row workgroups whose waves split the keys, and whether it is better here than 256-row workgroups.
+// Attention with 32-row workgroups whose waves split the keys, whether it is better here than the others, the waves, and the order of the workgroups.
 bool attn_bf16_rows_better(const Shape& sh, bool sparse);
+int attn_bf16_rows_waves(const Shape& sh, bool sparse);
+TileOrder attn_bf16_rows_order(const Shape& sh, bool sparse, int waves);
 hipError_t launch_attn_bf16_rows(const Shape& sh, ArgsB a, hipStream_t st);
 
 // Attention over lists with 128-row workgroups, two to a compute unit, and whether it is better here than either.

@@ -333,7 +333,7 @@ hipError_t launch(const ArgsB& a, TileOrder order, unsigned grid, hipStream_t st
 
 template <int W>
 static hipError_t launch_waves(const Shape& sh, const ArgsB& a, unsigned grid, hipStream_t st) {
-    const TileOrder order = TileOrder::of_launch(W, grid, attn_bf16_row_tiles(sh, a.idx != nullptr, kRowsTQ), sh.n1, sh.r, sh.budget, sh.local, sh.b, a.qtiles, kRowsTQ);
+    const TileOrder order = attn_bf16_rows_order(sh, a.idx != nullptr, W);
     if (!a.idx) return launch<2, W>(a, order, grid, st);
     return sh.b % 16 == 0 ? launch<1, W>(a, order, grid, st) : launch<0, W>(a, order, grid, st);
 }
@@ -342,6 +342,17 @@ static hipError_t launch_waves(const Shape& sh, const ArgsB& a, unsigned grid, h
 long long attn_bf16_row_tiles(const Shape& sh, bool sparse, int rows) {
     const int s = sparse ? sh.s : sh.n, rest = sh.n % s;
     return (long long)sh.batch * sh.hq * ((long long)(sh.n / s) * ((s + rows - 1) / rows) + (rest + rows - 1) / rows);
+}
+
+static int rows_qtiles(const Shape& sh, bool sparse) {
+    return ((sparse ? std::min(sh.s, sh.n) : sh.n) + kRowsTQ - 1) / kRowsTQ;      // a segment may be set longer than the sequence
+}
+
+static long long rows_grid(const Shape& sh, bool sparse) { return (long long)sh.batch * sh.hq * rows_qtiles(sh, sparse) * (sparse ? sh.n1 : 1); }
+
+TileOrder attn_bf16_rows_order(const Shape& sh, bool sparse, int waves) {
+    return TileOrder::of_launch(waves, rows_grid(sh, sparse), attn_bf16_row_tiles(sh, sparse, kRowsTQ), sh.n1, sh.r, sh.budget, sh.local, sh.b,
+                                rows_qtiles(sh, sparse), kRowsTQ);
 }
 
 static long long listed_keys(const Shape& sh) { return std::min((long long)sh.n, (long long)sh.list_len * sh.b); }
@@ -377,14 +388,18 @@ bool attn_bf16_rows_better(const Shape& sh, bool sparse) {
 // a unit.  Four against eight waves: block-sparse, t = 256 8 x 1000 13.3 / 10.7 us, 1 x 8192 (1312, 4672 keys) 18.6 / 13.9, 48 / 32; t = 375
 // 1 x 12000 (1312, 4672) 22.5 / 24.9, 52 / 56, 8 x 1500 (960, 1312) 15.2 / 17.5, 17.9 / 17.3, 4 x 3000 (2624) 30 / 25, 2 x 6000 (4672) 49 / 35; t = 500 8 x 2000
 // 18.5 / 22.1; dense, 32 x 256 6.4 / 6.8, 8 x 1000 12.0 / 10.2, 1 x 16K 140 / 99, 8 x 2000 21.5 / 19.9, 32 x 500 9.2 / 11.5, 8 x 3000 32 / 38.
+int attn_bf16_rows_waves(const Shape& sh, bool sparse) {
+    const long long tiles = attn_bf16_row_tiles(sh, sparse, kRowsTQ), keys = listed_keys(sh);
+    const bool eight = sparse ? tiles <= 270 || (tiles <= 400 && 10ll * sh.n <= 13 * keys)
+                              : (tiles <= 270 && sh.n >= 512) || (tiles <= 520 && sh.n >= 1024);
+    return eight ? 8 : 4;
+}
+
 hipError_t launch_attn_bf16_rows(const Shape& sh, ArgsB a, hipStream_t st) {
-    const int longest = a.idx ? std::min(sh.s, sh.n) : sh.n;          // a segment may be set longer than the sequence
-    a.qtiles = (longest + kRowsTQ - 1) / kRowsTQ;
-    const unsigned grid = (unsigned)((long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1));
-    const long long tiles = attn_bf16_row_tiles(sh, a.idx != nullptr, kRowsTQ), keys = listed_keys(sh);
-    const bool eight = a.idx ? tiles <= 270 || (tiles <= 400 && 10ll * sh.n <= 13 * keys)
-                             : (tiles <= 270 && sh.n >= 512) || (tiles <= 520 && sh.n >= 1024);
-    return eight ? launch_waves<8>(sh, a, grid, st) : launch_waves<4>(sh, a, grid, st);
+    const bool sparse = a.idx != nullptr;
+    a.qtiles = rows_qtiles(sh, sparse);
+    const unsigned grid = (unsigned)rows_grid(sh, sparse);
+    return attn_bf16_rows_waves(sh, sparse) == 8 ? launch_waves<8>(sh, a, grid, st) : launch_waves<4>(sh, a, grid, st);
 }
 
 }  // namespace cp

@@ -32,21 +32,25 @@ struct Args32 {
     const float* q; const float* k; const float* v; const int32_t* idx; const int32_t* cnt;
     float* out; float* lse;
     int batch, hq, hkv, n, s, b, n1, list_len, qtiles;   // qtiles: per segment (sparse) or per sequence (dense)
-    TileOrder order;                              // attn_fp32_split_kernel, sparse
+    TileOrder order;                              // which row tile a workgroup takes; attn_fp32_kernel: in launches of kPairs
     int shared_lists;                             // lists are per (batch, KV head, segment) instead of per query head
     float scale_log2e, scale;
     long long qs0, qs1, qs2, ks0, ks1, ks2, os0, os1, os2;
 };
 
-// Row tiles of `rows` that exist: a segment's last one may be short.
+// Row tiles of `rows`: those that exist, a segment's last one may be short; of the longest segment; workgroups launched for them; their order.
 long long attn_fp32_row_tiles(const Shape& sh, bool sparse, int rows);
+int attn_fp32_qtiles(const Shape& sh, bool sparse, int rows);
+long long attn_fp32_grid(const Shape& sh, bool sparse, int rows);
+TileOrder attn_fp32_order(const Shape& sh, bool sparse, int rows, int waves);
 
 // Where 16 rows go to a workgroup: waves of a workgroup, and workgroups that share a row tile.
 int attn_fp32_tile_waves(const Shape& sh, bool sparse);
 int attn_fp32_tile_parts(const Shape& sh, bool sparse);
 
-// Attention with fp32 factors split into three bf16 values, and whether it is the better one here.
+// Attention with fp32 factors split into three bf16 values, whether it is the better one here, and the waves of a workgroup.
 bool attn_fp32_split_better(const Shape& sh, bool sparse);
+int attn_fp32_split_waves(const Shape& sh, bool sparse);
 hipError_t launch_attn_fp32_split(const Shape& sh, Args32& a, hipStream_t st);
 
 }  // namespace cp

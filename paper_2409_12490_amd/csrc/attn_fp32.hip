@@ -41,6 +41,10 @@ __device__ __forceinline__ float group_max(float x) {               // over the 
 // C workgroups (blockIdx.y) share a row tile, each with its part of the channels of V and O: see launch_tiled.
 // MODE 0: any block size and any stride (dense if there is no list): every key of a tile has a token of its own.  MODE 1: sparse, block size a multiple of
 // 16: a tile is 16 consecutive tokens, described by its first token on the scalar unit.  MODE 2: dense.
+// Two workgroups to a compute unit, row tiles in TileOrder.
+template <int MODE, int W, int C>
+constexpr bool kPairs = MODE != 0 && W == 4 && C == 1;
+
 template <int MODE, int RT, int W, int C>
 __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kernel(Args32 a) {
     ask_for(a.q, a.k, a.v, a.idx, a.cnt, a.batch, a.n, a.qtiles, a.shared_lists, a.scale_log2e, a.qs0, a.qs1, a.qs2, a.ks0, a.ks1, a.ks2);
@@ -50,7 +54,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
     const bool dense = MODE == 2 || (MODE == 0 && !a.idx);
     constexpr int CH = kHeadDim / C, CHUNKS = CH / 4;               // channels of the output
     const int part = C > 1 ? blockIdx.y : 0;
-    constexpr int PIECES = C == 1 ? 2 : 1, E = CH / (16 * PIECES);  // a lane's floats of a row of V: PIECES of E, 16 E apart
+    constexpr int PIECES = CH / 64;                                 // a lane's floats of a row of V: PIECES of four, 64 apart
     __shared__ __attribute__((aligned(1024))) float part_o[W * TQ * CH];     // 16-byte chunks XOR-swizzled by the row
     __shared__ float part_m[W * TQ], part_l[W * TQ];
 
@@ -61,7 +65,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
     // Consecutive workgroups walk the KV heads, so that a head's keys stay with few XCDs (workgroup id mod 8); the tiles
     // with most keys, those at the end of the sequence, come first.
     const int G = a.hq / a.hkv, bkv = a.batch * a.hkv;
-    constexpr bool PAIRS = W == 4 && C == 1 && MODE != 0;           // two workgroups to a compute unit: see TileOrder
+    constexpr bool PAIRS = kPairs<MODE, W, C>;
     const unsigned wg = PAIRS ? a.order.place(blockIdx.x) : blockIdx.x;
     const int x = wg % bkv, y = wg / bkv;
     const int bb = x / a.hkv, kvh = x % a.hkv, h = kvh * G + y % G;
@@ -140,15 +144,14 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
         return t < ntiles && e < (unsigned)count && blk >= 0 && tk < a.n ? (int)tk : kNoToken;
     };
 
-    typedef __attribute__((ext_vector_type(E))) float f32xE;
-    f32x4 kf[8]; f32xE vf[4][PIECES];
+    f32x4 kf[8], vf[4][PIECES];
     auto load_k = [&](const float* rows, unsigned off) {            // 32-bit byte offset from a wave-uniform address (MODE 1/2)
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) kf[kk] = *(const f32x4*)((const char*)rows + off + 64 * kk);
     };
     auto load_v = [&](int r, const float* rows, unsigned off) {
 #pragma unroll
-        for (int hf = 0; hf < PIECES; ++hf) vf[r][hf] = *(const f32xE*)((const char*)rows + off + 256 * hf);
+        for (int hf = 0; hf < PIECES; ++hf) vf[r][hf] = *(const f32x4*)((const char*)rows + off + 256 * hf);
     };
     // MODE 1/2: the lane's offsets inside a tile of 16 existing tokens.  In the last, ragged tile of the sequence the rows
     // past its end repeat the last token; they lie after every query and are masked.
@@ -156,7 +159,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
     const unsigned k_full = c16 * row_bytes + 16 * g;
     unsigned v_full[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) v_full[r] = (4 * g + r) * row_bytes + 4 * E * c16;
+    for (int r = 0; r < 4; ++r) v_full[r] = (4 * g + r) * row_bytes + 16 * c16;
     auto load_k_run = [&](int base) {
         const int b0 = max(base, 0);
         unsigned off = k_full;
@@ -169,14 +172,14 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
         for (int r = 0; r < 4; ++r) off[r] = v_full[r];
         if (base + TK > a.n) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) off[r] = min(4 * g + r, a.n - 1 - base) * row_bytes + 4 * E * c16;
+            for (int r = 0; r < 4; ++r) off[r] = min(4 * g + r, a.n - 1 - base) * row_bytes + 16 * c16;
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) load_v(r, vp + (long long)base * a.ks2, off[r]);
     };
     auto load_k_token = [&](int tok) { load_k(kp + (long long)(tok == kNoToken ? 0 : tok) * a.ks2 + 4 * g, 0u); };
 
-    f32x4 o[RT][PIECES][E];
+    f32x4 o[RT][PIECES][4];
     float m[RT], l[RT];                                             // m: running max of the raw logits
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
@@ -184,7 +187,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
 #pragma unroll
         for (int hf = 0; hf < PIECES; ++hf)
 #pragma unroll
-            for (int e = 0; e < E; ++e) o[rt][hf][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int e = 0; e < 4; ++e) o[rt][hf][e] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
     int base = -1, tok = kNoToken;
@@ -210,7 +213,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 ktok[r] = __shfl(tok, 4 * g + r);
-                load_v(r, vp + (long long)(ktok[r] == kNoToken ? 0 : ktok[r]) * a.ks2 + E * c16, 0u);
+                load_v(r, vp + (long long)(ktok[r] == kNoToken ? 0 : ktok[r]) * a.ks2 + 4 * c16, 0u);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -265,7 +268,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
 #pragma unroll
                 for (int hf = 0; hf < PIECES; ++hf)
 #pragma unroll
-                    for (int e = 0; e < E; ++e) o[rt][hf][e] *= alpha;
+                    for (int e = 0; e < 4; ++e) o[rt][hf][e] *= alpha;
             }
         }
         if (missing) {                                              // 0 * V must be 0, whatever token 0 holds
@@ -281,7 +284,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
 #pragma unroll
             for (int hf = 0; hf < PIECES; ++hf)
 #pragma unroll
-                for (int e = 0; e < E; ++e)
+                for (int e = 0; e < 4; ++e)
 #pragma unroll
                     for (int rt = 0; rt < RT; ++rt)
                         o[rt][hf][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][hf][e], s[rt][0][r], o[rt][hf][e], 0, 0, 0);
@@ -299,12 +302,9 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
 #pragma unroll
         for (int hf = 0; hf < PIECES; ++hf)
 #pragma unroll
-            for (int r = 0; r < E; ++r) {                           // channels 64*hf + 4*E*g + 4*r .. +3: from E to a matrix row
-                const int chunk = (16 * hf + E * g + r) ^ (c16 & (CHUNKS - 1));
-                f32x4 w;
-#pragma unroll
-                for (int x = 0; x < 4; ++x) w[x] = o[rt][hf][x % E][(4 * r + x) / E];
-                *(f32x4*)(dst + 4 * chunk) = w;
+            for (int r = 0; r < 4; ++r) {                           // channels 64*hf + 16*g + 4*r .. +3
+                const int chunk = (16 * hf + 4 * g + r) ^ (c16 & (CHUNKS - 1));
+                *(f32x4*)(dst + 4 * chunk) = f32x4{o[rt][hf][0][r], o[rt][hf][1][r], o[rt][hf][2][r], o[rt][hf][3][r]};
             }
     }
     __syncthreads();
@@ -312,7 +312,7 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
 #pragma unroll
     for (int c = 0; c < (TQ * CHUNKS + 64 * W - 1) / (64 * W); ++c) {
         const int row = (c * 64 * W + tid) / CHUNKS, chunk = tid % CHUNKS;
-        if (row >= TQ) break;
+        if (row >= TQ) break;                                       // eight waves, half of the channels
         float M = -INFINITY, L = 0.f;
 #pragma unroll
         for (int w = 0; w < W; ++w) M = fmaxf(M, part_m[w * TQ + row]);
@@ -336,9 +336,9 @@ __global__ __launch_bounds__(64 * W, MODE == 0 ? 1 : 4 - RT) void attn_fp32_kern
 
 template <int MODE, int RT, int W, int C>
 hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
-    a.qtiles = ((a.idx ? min(sh.s, sh.n) : sh.n) + 16 * RT - 1) / (16 * RT);    // a segment may be set longer than the sequence
-    const long long grid = (long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1);
-    a.order = TileOrder::of_launch(W, grid, attn_fp32_row_tiles(sh, a.idx != nullptr, 16 * RT), sh.n1, sh.r, sh.budget, sh.local, sh.b, a.qtiles, 16 * RT);
+    a.qtiles = attn_fp32_qtiles(sh, a.idx != nullptr, 16 * RT);
+    const long long grid = attn_fp32_grid(sh, a.idx != nullptr, 16 * RT);
+    if (kPairs<MODE, W, C>) a.order = attn_fp32_order(sh, a.idx != nullptr, 16 * RT, W);
     hipLaunchKernelGGL((attn_fp32_kernel<MODE, RT, W, C>), dim3((unsigned)grid, C), dim3(64 * W), 0, st, a);
     return hipGetLastError();
 }

@@ -465,9 +465,9 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
 
 template <int MODE, int W>
 hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
-    a.qtiles = ((a.idx ? min(sh.s, sh.n) : sh.n) + TQ - 1) / TQ;    // a segment may be set longer than the sequence
-    const long long grid = (long long)sh.batch * sh.hq * a.qtiles * (a.idx ? sh.n1 : 1);
-    a.order = TileOrder::of_launch(W, grid, attn_fp32_row_tiles(sh, a.idx != nullptr, TQ), sh.n1, sh.r, sh.budget, sh.local, sh.b, a.qtiles, TQ);
+    a.qtiles = attn_fp32_qtiles(sh, a.idx != nullptr, TQ);
+    const long long grid = attn_fp32_grid(sh, a.idx != nullptr, TQ);
+    a.order = attn_fp32_order(sh, a.idx != nullptr, TQ, W);
     constexpr int smem = W * TQ * kHeadDim * 4 + 2 * 8 * 64 * 16;   // W = 4: half of a compute unit's LDS
     static_assert(2 * W * TQ * 4 + W * 4 <= 2 * 8 * 64 * 16, "what takes the place of Q");
     const hipError_t e = hipFuncSetAttribute((const void*)attn_fp32_split_kernel<MODE, W>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
@@ -480,6 +480,19 @@ hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
 long long attn_fp32_row_tiles(const Shape& sh, bool sparse, int rows) {
     const int s = sparse ? sh.s : sh.n, rest = sh.n % s;
     return (long long)sh.batch * sh.hq * ((long long)(sh.n / s) * ((s + rows - 1) / rows) + (rest + rows - 1) / rows);
+}
+
+int attn_fp32_qtiles(const Shape& sh, bool sparse, int rows) {
+    return ((sparse ? std::min(sh.s, sh.n) : sh.n) + rows - 1) / rows;    // a segment may be set longer than the sequence
+}
+
+long long attn_fp32_grid(const Shape& sh, bool sparse, int rows) {
+    return (long long)sh.batch * sh.hq * attn_fp32_qtiles(sh, sparse, rows) * (sparse ? sh.n1 : 1);
+}
+
+TileOrder attn_fp32_order(const Shape& sh, bool sparse, int rows, int waves) {
+    return TileOrder::of_launch(waves, attn_fp32_grid(sh, sparse, rows), attn_fp32_row_tiles(sh, sparse, rows), sh.n1, sh.r, sh.budget, sh.local, sh.b,
+                                attn_fp32_qtiles(sh, sparse, rows), rows);
 }
 
 static long long listed_keys(const Shape& sh, bool sparse) {
@@ -507,10 +520,13 @@ bool attn_fp32_split_better(const Shape& sh, bool sparse) {
 // 3136 keys) 21 / 24, 40 / 46, 82 / 98, dense 2 x 4096 95 / 116; beyond it rows of many and so unequal keys: dense 4 x 2500 (316) 64 / 76, 2 x 8192 (512) 229 /
 // 267, 3 x 6000 (564) 202 / 217, block-sparse 2 x 5000 (314, 3136) 84 / 98, 8 x 2048 (512, 2048) 68 / 74; but 2 x 6000 (376; 704, 3136) 47 / 42, 116 / 112, 4 x
 // 4096 (512, 1248) 76 / 71, 32 x 500 (512) 28 / 24; dense 4 x 6000 (752) 263 / 256.
-hipError_t launch_attn_fp32_split(const Shape& sh, Args32& a, hipStream_t st) {
-    const bool sparse = a.idx != nullptr;
+int attn_fp32_split_waves(const Shape& sh, bool sparse) {
     const long long tiles = attn_fp32_row_tiles(sh, sparse, TQ), keys = listed_keys(sh, sparse);
-    const bool eight = tiles <= 256 || (tiles <= 640 && sh.n >= 1024 && 8 * keys >= 5ll * sh.n);
+    return tiles <= 256 || (tiles <= 640 && sh.n >= 1024 && 8 * keys >= 5ll * sh.n) ? 8 : 4;
+}
+
+hipError_t launch_attn_fp32_split(const Shape& sh, Args32& a, hipStream_t st) {
+    const bool sparse = a.idx != nullptr, eight = attn_fp32_split_waves(sh, sparse) == 8;
     if (sparse) return eight ? launch<1, 8>(sh, a, st) : launch<1, 4>(sh, a, st);
     return eight ? launch<2, 8>(sh, a, st) : launch<2, 4>(sh, a, st);
 }

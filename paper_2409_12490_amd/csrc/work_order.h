@@ -92,7 +92,7 @@ struct TileOrder {
     unsigned full, past, most;            // segments with full lists; a tile's rows of keys each; what the last tile of the others sees
     FastDiv by_full, by_level, by_tiles;  // full, full + 1, qtiles
 
-    TileOrder() = default;
+    TileOrder() : turn(0), full(0), past(0), most(0) {}
     // by_keys: else the segments from the last to the first, tile by tile
     TileOrder(int n1, int r, int budget, int local, int b, int qtiles, int rows, bool by_keys) : turn(0) {
         const long long blocks = (long long)budget + local, keys = blocks * b / rows;
