@@ -128,15 +128,19 @@ class _Shape(ctypes.Structure):                  # cp::Shape of csrc/kernels.h
                 + [(x, ctypes.c_int64 * 3) for x in ("qs", "kvs", "os")])
 
 
+class _Order(ctypes.Structure):                  # cp::TileOrder of csrc/work_order.h
+    _fields_ = [(x, ctypes.c_uint32) for x in ("turn", "full", "past", "most")] + [(x, ctypes.c_uint32 * 2) for x in ("by_full", "by_level", "by_tiles")]
+
+
 def _rule(w: synth.Workload, name: str, *args, restype=ctypes.c_bool):
-    """One of the library's own dispatch rules, a function of cp::Shape and truth values."""
+    """One of the library's own dispatch rules, a function of cp::Shape, truth values and numbers."""
     r = w.segment_size // w.block_size
     sh = _Shape(w.batch, w.n_q_heads, w.n_kv_heads, w.seq_len, w.segment_size, w.block_size, r, w.n_segments, w.n_blocks, w.budget_blocks,
                 w.local_blocks, w.budget_blocks + w.local_blocks + r)
     sh.kvs[2] = 128
-    f = getattr(B.load(), f"_ZN2cp{len(name)}{name}ERKNS_5ShapeE" + "b" * len(args))
+    f = getattr(B.load(), f"_ZN2cp{len(name)}{name}ERKNS_5ShapeE" + "".join("b" if isinstance(x, bool) else "i" for x in args))
     f.restype = restype
-    return f(ctypes.byref(sh), *(ctypes.c_bool(a) for a in args))
+    return f(ctypes.byref(sh), *(ctypes.c_bool(x) if isinstance(x, bool) else ctypes.c_int(x) for x in args))
 
 
 def attention_kernel(w: synth.Workload, sparse: bool = True) -> str:
@@ -149,6 +153,18 @@ def attention_kernel(w: synth.Workload, sparse: bool = True) -> str:
     return "32" if _rule(w, "attn_bf16_rows_better", sparse) else "256"
 
 
-def fp32_tiling(w: synth.Workload, sparse: bool = True):
-    """Workgroups that share a row tile of 16 and waves of each, by the library's own rules, where the "fp32" kernel takes tokens in runs or none listed."""
-    return tuple(_rule(w, name, sparse, restype=ctypes.c_int) for name in ("attn_fp32_tile_parts", "attn_fp32_tile_waves"))
+def attention_route(w: synth.Workload, sparse: bool = True) -> str:
+    """The kernel and how the library's rules divide the launch: "split 8", "fp32 2x4" (two workgroups of four waves to a row tile), "fp32 tokens" (a token per key), "32 4",
+    " pairs" behind it where long and short row tiles share a compute unit; "128" and "256" as they are."""
+    kernel = attention_kernel(w, sparse)
+    if kernel in ("128", "256"):
+        return kernel
+    if kernel == "fp32":
+        if sparse and w.block_size % 16:
+            return "fp32 tokens"
+        parts, waves = (_rule(w, name, sparse, restype=ctypes.c_int) for name in ("attn_fp32_tile_parts", "attn_fp32_tile_waves"))
+        turn = parts == 1 and _rule(w, "attn_fp32_order", sparse, 16, waves, restype=_Order).turn
+        return f"fp32 {parts}x{waves}" + " pairs" * bool(turn)
+    waves = _rule(w, "attn_fp32_split_waves" if kernel == "split" else "attn_bf16_rows_waves", sparse, restype=ctypes.c_int)
+    order = _rule(w, "attn_fp32_order", sparse, 32, waves, restype=_Order) if kernel == "split" else _rule(w, "attn_bf16_rows_order", sparse, waves, restype=_Order)
+    return f"{kernel} {waves}" + " pairs" * bool(order.turn)

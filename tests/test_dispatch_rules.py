@@ -27,3 +27,28 @@ def test_blocks_of_odd_multiples_of_16(n, s, b, k, kernel):
 ])
 def test_rows_of_32_up_to_1024_row_tiles(heads, n, s, b, k, kernel):
     assert H.attention_kernel(workload("bf16", *heads, n, s, b, k)) == kernel
+
+
+@pytest.mark.parametrize("heads,n,route", [(1, 2048, "fp32 2x8"), (1, 2049, "fp32 1x8"), (2, 1024, "fp32 2x4"), (2, 1025, "fp32 1x8"), (8, 256, "fp32 2x4"), (8, 257, "fp32 1x4"), (1, 1025, "fp32 2x8"), (1, 1024, "fp32 2x4")])
+def test_shared_row_tiles_up_to_128(heads, n, route):
+    """Dense: 128 and 129 or more row tiles of 16; more than 1024 keys have eight waves."""
+    assert H.attention_route(workload("fp32", heads, heads, n, 512, 64, 4), False) == route
+
+
+@pytest.mark.parametrize("dtype,heads,n,route", [
+    ("fp32", 16, 256, "fp32 1x4"), ("fp32", 16, 257, "fp32 1x4 pairs"), ("fp32", 16, 480, "fp32 1x4 pairs"), ("fp32", 12, 650, "fp32 1x4 pairs"),     # 256, 272, 480 and 492 workgroups
+    ("fp32", 32, 512, "split 4 pairs"), ("fp32", 32, 513, "split 4"), ("fp32", 32, 256, "split 8"), ("fp32", 32, 257, "split 4 pairs"),
+    ("bf16", 32, 256, "32 4"), ("bf16", 32, 257, "32 4 pairs"), ("bf16", 32, 512, "32 4 pairs"), ("bf16", 32, 513, "32 4"), ("bf16", 8, 2048, "32 8"),
+])
+def test_pairs_where_the_chip_holds_all(dtype, heads, n, route):
+    """Dense: more than 256 and at most 512 workgroups of four waves."""
+    assert H.attention_route(workload(dtype, heads, heads, n, 512, 64, 4), False) == route
+
+
+@pytest.mark.parametrize("dtype,heads,n,route", [
+    ("bf16", 16, 896, "32 4 pairs"), ("bf16", 16, 960, "32 4 pairs"), ("bf16", 16, 864, "32 4"),       # 512 workgroups, of which 64, 32 and 80 past the end
+    ("fp32", 8, 896, "fp32 1x4 pairs"), ("fp32", 8, 864, "fp32 1x4"),
+])
+def test_no_pairs_where_many_are_past_the_end(dtype, heads, n, route):
+    """Block-sparse, segments of 512: one workgroup in eight may be past the end of the last one."""
+    assert H.attention_route(workload(dtype, heads, heads, n, 512, 64, 4)) == route

@@ -14,28 +14,30 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 SHAPES = [
-    # Hq Hkv   n     s    b    k  L
-    (1, 1, 1, 16, 16, 1, 0),              # one query, one key
-    (2, 1, 271, 128, 16, 3, 1),           # 16 rows, 4 waves, most of them without a tile; a last tile of 15 tokens
-    (2, 2, 1553, 288, 48, 40, 0),         # 16 rows, 8 waves; 48 does not divide 8 x 16 keys
-    (8, 4, 1601, 128, 32, 60, 1),         # split products, 8 waves; a last row tile of one row
-    (8, 2, 2064, 256, 64, 4, 1),          # split: 4 waves for the short lists, 8 for dense
-    (16, 4, 3120, 512, 128, 16, 0),       # split, 4 waves: many workgroups
-    (1, 1, 2048, 128, 32, 8, 0),          # 128 row tiles: two workgroups to a tile, each with half of the channels
-    (2, 1, 1009, 255, 51, 9, 1),          # the same dense; block-sparse a token per key
-    (2, 2, 1001, 256, 16, 70, 1),         # 126 row tiles, long lists; a last tile of nine rows
-    (3, 1, 688, 344, 43, 9, 1),           # dense 129 row tiles: one workgroup to a tile
-    (8, 2, 700, 256, 32, 4, 1),           # 352 row tiles of 16, two workgroups to a compute unit: long and short in pairs
-    (8, 2, 600, 512, 64, 4, 0),           # block-sparse: too many of 512 past the end of the last segment for that
-    (4, 2, 3000, 256, 64, 4, 1),          # 376 split tiles of 32 rows in pairs
-    (3, 1, 500, 72, 24, 4, 1),            # blocks of 24: one token per key; segments no multiple of a row tile
+    # Hq Hkv   n     s    b    k  L, routes: block-sparse, dense (attention_route)
+    (1, 1, 1, 16, 16, 1, 0, "fp32 2x4", "fp32 2x4"),              # one query, one key
+    (2, 1, 271, 128, 16, 3, 1, "fp32 2x4", "fp32 2x4"),           # 16 rows, 4 waves, most of them without a tile; a last tile of 15 tokens
+    (2, 2, 1553, 288, 48, 40, 0, "fp32 1x8", "fp32 1x8"),         # 16 rows, 8 waves; 48 does not divide 8 x 16 keys
+    (8, 4, 1601, 128, 32, 60, 1, "split 8", "split 8"),         # split products, 8 waves; a last row tile of one row
+    (8, 2, 2064, 256, 64, 4, 1, "split 4", "split 8"),          # split: 4 waves for the short lists, 8 for dense
+    (16, 4, 3120, 512, 128, 16, 0, "split 4", "split 4"),       # split, 4 waves: many workgroups
+    (1, 1, 2048, 128, 32, 8, 0, "fp32 2x4", "fp32 2x8"),          # 128 row tiles: two workgroups to a tile, each with half of the channels
+    (2, 1, 1009, 255, 51, 9, 1, "fp32 tokens", "fp32 2x4"),          # the same dense; block-sparse a token per key
+    (2, 2, 1001, 256, 16, 70, 1, "fp32 2x4", "fp32 2x4"),         # 126 row tiles, long lists; a last tile of nine rows
+    (3, 1, 688, 344, 43, 9, 1, "fp32 tokens", "fp32 1x4"),           # dense 129 row tiles: one workgroup to a tile
+    (8, 2, 700, 256, 32, 4, 1, "fp32 1x4 pairs", "fp32 1x4 pairs"),           # 352 row tiles of 16, two workgroups to a compute unit: long and short in pairs
+    (8, 2, 600, 512, 64, 4, 0, "fp32 1x4", "fp32 1x4 pairs"),           # block-sparse: too many of 512 past the end of the last segment for that
+    (4, 2, 3000, 256, 64, 4, 1, "split 4 pairs", "split 8"),          # 376 split tiles of 32 rows in pairs
+    (3, 1, 500, 72, 24, 4, 1, "fp32 tokens", "fp32 2x4"),            # blocks of 24: one token per key; segments no multiple of a row tile
+    (1, 1, 2048, 256, 64, 20, 0, "fp32 2x8", "fp32 2x8"),          # the same with eight waves: rows of more than 1024 keys
 ]
 
 
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda c: "x".join(map(str, c)))
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda c: "x".join(map(str, c[:7])))
 def test_variants_against_checker(shape):
-    Hq, Hkv, n, s, b, k, L = shape
+    Hq, Hkv, n, s, b, k, L, sparse, dense = shape
     w = H.small_workload("fp32tiles", 1, Hq, Hkv, n, s, b, k, L, dtype="fp32", unit_variance=n > 1)
+    assert (H.attention_route(w), H.attention_route(w, False)) == (sparse, dense)
     q, k_, v = synth.make_qkv(w, threads=8)
     qf, kf, vf = (synth.to_f64(t) for t in (q, k_, v))
     q, k_, v = q.to(DEV), k_.to(DEV), v.to(DEV)
@@ -157,7 +159,7 @@ def test_a_shared_row_tile_has_the_same_bits(n, others, b):
     many = H.small_workload("among", 1, others, others, n, 512, b or 64, 130 if b else 40, 1, dtype="fp32", unit_variance=True)
     assert H.attention_kernel(one, bool(b)) == H.attention_kernel(many, bool(b)) == "fp32"
     waves = 8 if n > 1024 else 4
-    assert H.fp32_tiling(one, bool(b)) == (2, waves) and H.fp32_tiling(many, bool(b)) == (1, waves)
+    assert H.attention_route(one, bool(b)) == f"fp32 2x{waves}" and H.attention_route(many, bool(b)).startswith(f"fp32 1x{waves}")
     q, k, v = (t.to(DEV) for t in synth.make_qkv(many, threads=8))
     Sd = np.random.default_rng(n).random((1, others, many.n_segments, many.n_blocks), dtype=np.float32)
     idx, cnt = (torch.from_numpy(x).to(DEV) for x in O.select(Sd, 512, b or 64, many.budget_blocks, 1))
