@@ -48,9 +48,10 @@ constexpr int kOutPitch = 272;                        // epilogue staging: one o
 static_assert(kListOff + kMaxListBf16 * 4 <= 160 * 1024, "LDS budget");
 static_assert(8 * WQ * kOutPitch <= 2 * NBUF * kTileBytes, "epilogue staging reuses the tile rings");
 
-// Puts what follows N words behind a multiple of 32 bytes.  The key loops are 7 KiB of code, the same in every launch, and take up to 3.5 % longer where their instructions
-// lie badly for the fetch of 32 bytes, which anything written before them used to decide.  All eight places of both loops in turn, 8/2 heads x 6000 tokens
-// (512, 64; 32 blocks): 62.9 us with these, 63.2 to 65.4 with others, 32/8 x 65536 2168 and 2175 to 2219, x 2000 50.8 and 51.0 to 52.7; blocks of 32 and 16 and dense within 1 %.
+// Puts what follows N words behind a multiple of 32 bytes.  The key loops are 7 KiB of code, the same in every launch, and take up to 3.5 % longer where their
+// instructions lie badly for the fetch of 32 bytes, which anything written before them used to decide.  All eight places of both loops in turn, 8/2 heads x
+// 6000 tokens (512, 64; 32 blocks): 62.9 us with these, 63.2 to 65.4 with others, 32/8 x 65536 2168 and 2175 to 2219, x 2000 50.8 and 51.0 to 52.7; blocks of 32
+// and 16 and dense within 1 %.  The places belong to the loops as they are: after an edit inside one, its eight places have to be timed again.
 template <int N>
 __device__ __forceinline__ void align_loop() { asm volatile(".p2align 5\n\t.rept %0\n\ts_nop 0\n\t.endr" ::"n"(N)); }
 
@@ -75,8 +76,7 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsIndex ix, ArgsB a
     // this, the index arithmetic free of divisions, Q loaded without a branch per fragment and the trailing tiles looked at 64 at a time, the
     // list is asked for after 120 instead of 290 instructions: 32 x 16K tokens (16 blocks of 64) 388 -> 376 us, 2 x 32 x 64K (32
     // of 32) 2640 -> 2597, 32 x 128K (32 of 64, shared lists) 4.97 -> 4.75 ms, same outputs.
-    asm volatile("" ::"s"(a.q), "s"(a.k), "s"(a.v), "s"(a.idx), "s"(a.cnt), "s"(a.n), "s"(a.s), "s"(a.qs0), "s"(a.qs1), "s"(a.qs2), "s"(a.ks0),
-                 "s"(a.ks1), "s"(a.ks2), "s"(a.list_len), "s"(a.scale_log2e), "s"(ix.div_b.mul), "s"(ix.order.set_kv), "s"(ix.order.by_kv.shift));
+    ask_for(a.q, a.k, a.v, a.idx, a.cnt, a.n, a.s, a.qs0, a.qs1, a.qs2, a.ks0, a.ks1, a.ks2, a.list_len, a.scale_log2e, ix.div_b.mul, ix.order.set_kv, ix.order.by_kv.shift);
     // ---- which (batch, head, segment, query tile) this workgroup owns --------------------------
     const unsigned wg = workgroup_id();
     int bb, h, g, j = 0, qt;
