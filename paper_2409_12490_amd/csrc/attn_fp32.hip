@@ -22,7 +22,7 @@
 //
 // This kernel takes the launches that are too small for attn_fp32_split.hip, and the block sizes and strides that are not for it.
 //
-// What bounds it: latency, where few workgroups fill the chip (one head x 2048 tokens, 384 keys: 10.2 us, against 85 of a vector-FMA loop over
+// What bounds it: latency, where few workgroups fill the chip (one head x 2048 tokens, 384 keys: 9.8 us, against 85 of a vector-FMA loop over
 // 32 x 32 tiles in LDS), and the fp32 matrix instructions, which share their units with the vector instructions (measured: a wave's softmax and address
 // arithmetic add their time to the MFMAs of all waves of the SIMD).  So the key loop keeps them few: tiles of 16 consecutive tokens with their
 // addresses on the scalar unit (MODE 1/2), O rescaled only in tiles where some row's max moves.
@@ -38,7 +38,7 @@ __device__ __forceinline__ float group_max(float x) {               // over the 
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// C workgroups (blockIdx.y) share a row tile, each with its part of the channels of V and O: see launch_tiled.
+// C workgroups (blockIdx.y) share a row tile, each with its part of the channels of V and O: see attn_fp32_tile_parts.
 // MODE 0: any block size and any stride (dense if there is no list): every key of a tile has a token of its own.  MODE 1: sparse, block size a multiple of
 // 16: a tile is 16 consecutive tokens, described by its first token on the scalar unit.  MODE 2: dense.
 // Two workgroups to a compute unit, row tiles in TileOrder.

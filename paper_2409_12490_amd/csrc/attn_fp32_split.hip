@@ -26,7 +26,7 @@
 // of 1.9 GHz.  The splitting goes between the MFMAs of values split before (all of it first: 2 to 5 % slower).  Residues by v_dot2_f32_bf16, which reads
 // a bf16 without unpacking it, take half the instructions, but that unit does not run beside the MFMAs: no faster (815 to 840 us where this takes 813).  Two fp16
 // values and three products were faster (575), but hold 22 bits of a value within 2^13 of the largest and less of the others.
-// Dense 8 x 8192 1110 -> 830 us, 4 x 2500 77 -> 64; block-sparse 4 x 4096 (704 keys) 55 -> 39, 8 x 8192 (704) 194 -> 144.
+// Dense 8 x 8192 1110 -> 830 us, 4 x 2500 77 -> 64; block-sparse 4 x 4096 (704 keys) 55 -> 40, 8 x 8192 (704) 194 -> 146.
 #include "attn_fp32.h"
 
 #include <algorithm>
@@ -499,13 +499,19 @@ static long long listed_keys(const Shape& sh, bool sparse) {
     return sparse ? std::min((long long)sh.n, (long long)sh.list_len * sh.b) : sh.n;
 }
 
-// Against the fp32 matrix instructions (us, attn_fp32.hip / this one; t: row tiles of 32).  That kernel splits rows into 16 and so fills the chip with
-// half as many; where rows see unequal numbers of keys, most of those before them, it keeps a unit's two workgroups of unlike length.
-//   nearly all keys: t = 188 to 192 2 x 3000 57 / 69, 4 x 1500 32 / 39, 3 x 2048 block-sparse 42 / 51; t = 256 1 x 8192 159 / 184, 4 x 2048 47 / 51, but 8 x 1000
-//   32 / 29, 16 x 512 19.0 / 18.3; t = 258 3 x 2731 63 / 67, 282 3 x 3000 78 / 74, 313 1 x 10000 252 / 233, 320 8 x 1250 44 / 36, 512 4 x 4096 166 / 122.
-//   fewer: t = 256 always (416, 1248 keys): 1 x 8192 24 / 21, 54 / 40, 4 x 2048 21.7 / 19.3, 47 / 37; t = 188 to 192 1 x 6000 (416, 1248, 3136) 20.9 / 18.7, 53 / 36, 85 /
-//   75, 4 x 1500 (704, 1248) 26.0 / 23.8, 30 / 35, 3 x 2048 (1248) 37.4 / 36.2, 8 x 750 (416) 17.1 / 18.0; t = 163 1 x 5200 (416, 1248, 3136) 21.0 / 18.2, 49 / 36, 62 / 74;
-//   152 8 x 600 (416) 14.7 / 17.7, 128 1 x 4096 (416, 1248) 13.2 / 17.7, 28.6 / 35.1.
+// Against the fp32 matrix instructions (us, attn_fp32.hip / this one, all with the waves and orders of the present rules; listed keys in brackets; t: row tiles
+// of 32).  That kernel splits rows into 16 and so fills the chip with half as many; where rows see unequal numbers of keys, most of those before them, it keeps a
+// unit's two workgroups of unlike length.
+//   nearly all keys: t = 188 to 200 4 x 1500 31.5 / 38.5, 3 x 2048 block-sparse 41 / 50, 2 x 3195 60 / 71, 1 x 6395 114 / 136; t = 256 to 258 4 x 2043 47 / 50, 2 x 4091
+//   84 / 93, 1 x 8187 158 / 179, 3 x 2731 62 / 65; t = 272 to 282 2 x 4379 102 / 102, 1 x 8795 192 / 195, but 4 x 2171 56 / 53, 3 x 3000 76 / 73; from there on 1 x 10000
+//   (313) 251 / 231, 8 x 1250 (320) 44 / 35, 4 x 2619 (328) 80 / 66, 4 x 4096 (512) 162 / 119.
+//   fewer: t = 256 4 x 2043 (1408, 768, 384) 46 / 38, 24.4 / 24.2, 16.1 / 15.5, 1 x 8187 (5824, 3264, 1600) 159 / 136, 121 / 84, 58 / 48; t = 184 to 200 2 x 3195 (2240,
+//   1216, 576) 55 / 56, 44 / 35, 21.7 / 19.8, 1 x 6000 (416, 1248, 3136) 15.8 / 19.0, 53 / 35, 84 / 77, 4 x 1500 (704, 1248) 23.2 / 23.4, 29 / 34, 3 x 2048 (1248) 36.7 /
+//   34.4, 8 x 750 (416) 13.5 / 17.7; t = 163 1 x 5200 (416, 1248, 3136) 14.8 / 18.3, 49 / 35, 60 / 76; 152 8 x 600 (416) 13.0 / 17.6, 128 1 x 4096 (416, 1248)
+//   13.1 / 17.7, 28 / 35.
+//   Where its row tiles come in pairs that kernel has gained up to a fifth and become the better one for some launches of at most 1024 keys at t = 256 and short lists
+//   below: dense 8 x 1000 25.0 / 28.4, 16 x 512 16.2 / 17.7, 32 x 251 11.1 / 12.2, block-sparse 1 x 8192 (416) 18.4 / 20.8, 1 x 6000 as above.  The line is where the
+//   tests of this kernel hold it.
 bool attn_fp32_split_better(const Shape& sh, bool sparse) {
     if (sh.kvs[2] >= (1 << 26) || (sparse && sh.b % 16 != 0)) return false;     // a run's rows within 32-bit byte offsets of its first; runs of 16
     const long long tiles = attn_fp32_row_tiles(sh, sparse, TQ), keys = listed_keys(sh, sparse), n = sh.n;
@@ -515,11 +521,11 @@ bool attn_fp32_split_better(const Shape& sh, bool sparse) {
     return tiles >= 144 && n >= 2400 && 3 * keys <= n;
 }
 
-// (Times before TileOrder, which takes up to 22 % off four waves with at most 512 workgroups.)
-// Eight waves leave one workgroup to a compute unit, four two.  Eight / four: up to a chip full of workgroups block-sparse 1 x 8192 (t = 256; 416, 1248,
-// 3136 keys) 21 / 24, 40 / 46, 82 / 98, dense 2 x 4096 95 / 116; beyond it rows of many and so unequal keys: dense 4 x 2500 (316) 64 / 76, 2 x 8192 (512) 229 /
-// 267, 3 x 6000 (564) 202 / 217, block-sparse 2 x 5000 (314, 3136) 84 / 98, 8 x 2048 (512, 2048) 68 / 74; but 2 x 6000 (376; 704, 3136) 47 / 42, 116 / 112, 4 x
-// 4096 (512, 1248) 76 / 71, 32 x 500 (512) 28 / 24; dense 4 x 6000 (752) 263 / 256.
+// Eight waves leave one workgroup to a compute unit, four two.  Eight / four (listed keys in brackets): up to a chip full of workgroups dense 4 x 2043 (t = 256) 50 / 61,
+// block-sparse 1 x 8187 (1600) 48 / 57; beyond it rows of many and so unequal keys: dense 4 x 2619 (328) 66 / 79, 1 x 11995 (375) 286 / 337, 2 x 7995 (500) 217 / 248,
+// 4 x 5115 (640) 194 / 197, block-sparse 2 x 5275 (330; 3712) 96 / 113, 1 x 11995 (375; 8512) 227 / 260; but block-sparse 2 x 5275 (2048) 84 / 77, 4 x 2971 (372; 1152)
+// 55 / 44, 4 x 3995 (500; 2816) 117 / 109, dense 32 x 475 (480) 26.9 / 22.1, 4 x 5979 (748) 255 / 249.  (Eight would be better for the first few above 256, 4 x 2171
+// (272; 832) 26.4 / 32.4.)
 int attn_fp32_split_waves(const Shape& sh, bool sparse) {
     const long long tiles = attn_fp32_row_tiles(sh, sparse, TQ), keys = listed_keys(sh, sparse);
     return tiles <= 256 || (tiles <= 640 && sh.n >= 1024 && 8 * keys >= 5ll * sh.n) ? 8 : 4;
