@@ -27,12 +27,14 @@ constexpr int kNoToken = 0x7fffffff;              // a key that does not exist: 
 
 // MODE 0: sparse, any block size: every key of a tile has a token of its own.  MODE 1: sparse, block size a multiple of 16: a
 // tile is two runs of 16 consecutive tokens, described by their first tokens on the scalar unit.  MODE 2: dense.
-template <int MODE, int W>
+// PAIRS: in the order of TileOrder, else segments from the last to the first.
+template <int MODE, int W, bool PAIRS>
 __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a, TileOrder order) {
     constexpr bool DENSE = MODE == 2, RUN = MODE != 0;
     ask_for(a.q, a.k, a.v, a.idx, a.cnt, a.batch, a.n, a.qtiles, a.group, a.scale_log2e, a.qs0, a.qs1, a.qs2, a.ks0, a.ks1, a.ks2);
-    if (W == 4) ask_for(order.turn);
-    if (!DENSE) ask_for(order.full, order.past, order.most, order.by_full.mul, order.by_level.mul, order.by_tiles.shift);
+    if (PAIRS) ask_for(order.turn);
+    if (PAIRS && !DENSE) ask_for(order.full, order.past, order.by_full.mul, order.by_level.mul);
+    if (!DENSE) ask_for(order.most, order.by_tiles.shift);
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
     constexpr unsigned kQ = W * 2 * kSlotBytes;                     // behind the waves' K and V slots: Q
@@ -43,13 +45,13 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a, Tile
     // Consecutive workgroups walk the KV heads, so that a head's keys stay with few XCDs (workgroup id mod 8); then the query heads of a group, and inside a
     // head TileOrder.
     const int G = a.group, bkv = a.batch * a.hkv;
-    const int wg = (int)(W == 4 ? order.place(workgroup_id()) : workgroup_id()), x = wg % bkv, y = wg / bkv;
+    const int wg = (int)(PAIRS ? order.place(workgroup_id()) : workgroup_id()), x = wg % bkv, y = wg / bkv;
     const int bb = x / a.hkv, kvh = x % a.hkv;
     int h, j = 0, q_lo;
     if (DENSE) { h = kvh * G + y % G; q_lo = (a.qtiles - 1 - y / G) * kRowsTQ; }
     else {
         h = kvh * G + y % G;
-        const TileOrder::Item item = order.item(y / G, a.n1, a.qtiles);
+        const TileOrder::Item item = PAIRS ? order.item(y / G, a.n1, a.qtiles) : order.by_segments(y / G, a.qtiles);
         j = item.segment;
         q_lo = j * a.s + item.tile * kRowsTQ;
     }
@@ -320,22 +322,22 @@ __global__ __launch_bounds__(64 * W, 2) void attn_bf16_rows_kernel(ArgsB a, Tile
     }
 }
 
-template <int MODE, int W>
+template <int MODE, int W, bool PAIRS>
 hipError_t launch(const ArgsB& a, TileOrder order, unsigned grid, hipStream_t st) {
     constexpr int smem = W * 2 * kSlotBytes + kRowsTQ * 256 + 2 * W * 32 * 4;
-    const hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_rows_kernel<MODE, W>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    const hipError_t e = hipFuncSetAttribute((const void*)attn_bf16_rows_kernel<MODE, W, PAIRS>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((attn_bf16_rows_kernel<MODE, W>), dim3(grid), dim3(64 * W), smem, st, a, order);
+    hipLaunchKernelGGL((attn_bf16_rows_kernel<MODE, W, PAIRS>), dim3(grid), dim3(64 * W), smem, st, a, order);
     return hipGetLastError();
 }
 
 }  // namespace
 
-template <int W>
-static hipError_t launch_waves(const Shape& sh, const ArgsB& a, unsigned grid, hipStream_t st) {
-    const TileOrder order = attn_bf16_rows_order(sh, a.idx != nullptr, W);
-    if (!a.idx) return launch<2, W>(a, order, grid, st);
-    return sh.b % 16 == 0 ? launch<1, W>(a, order, grid, st) : launch<0, W>(a, order, grid, st);
+template <int MODE>
+static hipError_t launch_waves(const Shape& sh, const ArgsB& a, int waves, unsigned grid, hipStream_t st) {
+    const TileOrder order = attn_bf16_rows_order(sh, MODE != 2, waves);
+    if (waves == 8) return launch<MODE, 8, false>(a, order, grid, st);
+    return order.turn ? launch<MODE, 4, true>(a, order, grid, st) : launch<MODE, 4, false>(a, order, grid, st);
 }
 
 // Row tiles that exist: a segment's last tile may be short.
@@ -399,7 +401,9 @@ hipError_t launch_attn_bf16_rows(const Shape& sh, ArgsB a, hipStream_t st) {
     const bool sparse = a.idx != nullptr;
     a.qtiles = rows_qtiles(sh, sparse);
     const unsigned grid = (unsigned)rows_grid(sh, sparse);
-    return attn_bf16_rows_waves(sh, sparse) == 8 ? launch_waves<8>(sh, a, grid, st) : launch_waves<4>(sh, a, grid, st);
+    const int waves = attn_bf16_rows_waves(sh, sparse);
+    if (!sparse) return launch_waves<2>(sh, a, waves, grid, st);
+    return sh.b % 16 == 0 ? launch_waves<1>(sh, a, waves, grid, st) : launch_waves<0>(sh, a, waves, grid, st);
 }
 
 }  // namespace cp

@@ -32,7 +32,7 @@ struct Args32 {
     const float* q; const float* k; const float* v; const int32_t* idx; const int32_t* cnt;
     float* out; float* lse;
     int batch, hq, hkv, n, s, b, n1, list_len, qtiles;   // qtiles: per segment (sparse) or per sequence (dense)
-    TileOrder order;                              // which row tile a workgroup takes; attn_fp32_kernel: in launches of kPairs
+    TileOrder order;                              // which row tile a workgroup takes; attn_fp32_kernel: in pairs alone
     int shared_lists;                             // lists are per (batch, KV head, segment) instead of per query head
     float scale_log2e, scale;
     long long qs0, qs1, qs2, ks0, ks1, ks2, os0, os1, os2;

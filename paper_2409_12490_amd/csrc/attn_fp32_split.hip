@@ -114,7 +114,8 @@ __device__ __forceinline__ float half_max(float x) {                // over lane
 }
 
 // MODE 1: sparse, block size a multiple of 16; MODE 2: dense.
-template <int MODE, int W>
+// PAIRS: in the order of TileOrder, else segments from the last to the first.
+template <int MODE, int W, bool PAIRS>
 __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
     ask_for(a.q, a.k, a.v, a.idx, a.cnt, a.batch, a.n, a.qtiles, a.shared_lists, a.scale_log2e, a.qs0, a.qs1, a.qs2, a.ks0, a.ks1, a.ks2);
     constexpr bool DENSE = MODE == 2;
@@ -133,10 +134,12 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int G = a.hq / a.hkv, bkv = a.batch * a.hkv;              // consecutive workgroups walk the KV heads, see attn_fp32_kernel; then TileOrder
-    const unsigned wg = W == 4 ? a.order.place(blockIdx.x) : blockIdx.x;
+    const unsigned wg = PAIRS ? a.order.place(blockIdx.x) : blockIdx.x;
     const int x = wg % bkv, y = wg / bkv;
     const int bb = x / a.hkv, kvh = x % a.hkv, h = kvh * G + y % G;
-    const TileOrder::Item item = DENSE ? TileOrder::Item{0, a.qtiles - 1 - y / G} : a.order.item(y / G, a.n1, a.qtiles);
+    const TileOrder::Item item = DENSE   ? TileOrder::Item{0, a.qtiles - 1 - y / G}
+                                 : PAIRS ? a.order.item(y / G, a.n1, a.qtiles)
+                                         : a.order.by_segments(y / G, a.qtiles);
     const int j = item.segment, q_lo = j * a.s + item.tile * TQ;
     const int q_end = DENSE ? a.n : min(a.n, (j + 1) * a.s);        // rows >= q_end do not exist
     if (q_lo >= q_end) return;                                      // uniform: tile past a short segment
@@ -463,16 +466,14 @@ __global__ __launch_bounds__(64 * W, 2) void attn_fp32_split_kernel(Args32 a) {
     }
 }
 
-template <int MODE, int W>
+template <int MODE, int W, bool PAIRS>
 hipError_t launch(const Shape& sh, Args32& a, hipStream_t st) {
-    a.qtiles = attn_fp32_qtiles(sh, a.idx != nullptr, TQ);
     const long long grid = attn_fp32_grid(sh, a.idx != nullptr, TQ);
-    a.order = attn_fp32_order(sh, a.idx != nullptr, TQ, W);
     constexpr int smem = W * TQ * kHeadDim * 4 + 2 * 8 * 64 * 16;   // W = 4: half of a compute unit's LDS
     static_assert(2 * W * TQ * 4 + W * 4 <= 2 * 8 * 64 * 16, "what takes the place of Q");
-    const hipError_t e = hipFuncSetAttribute((const void*)attn_fp32_split_kernel<MODE, W>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    const hipError_t e = hipFuncSetAttribute((const void*)attn_fp32_split_kernel<MODE, W, PAIRS>, hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((attn_fp32_split_kernel<MODE, W>), dim3((unsigned)grid), dim3(64 * W), smem, st, a);
+    hipLaunchKernelGGL((attn_fp32_split_kernel<MODE, W, PAIRS>), dim3((unsigned)grid), dim3(64 * W), smem, st, a);
     return hipGetLastError();
 }
 }  // namespace
@@ -531,10 +532,18 @@ int attn_fp32_split_waves(const Shape& sh, bool sparse) {
     return tiles <= 256 || (tiles <= 640 && sh.n >= 1024 && 8 * keys >= 5ll * sh.n) ? 8 : 4;
 }
 
+template <int MODE>
+static hipError_t launch_waves(const Shape& sh, Args32& a, int waves, hipStream_t st) {
+    if (waves == 8) return launch<MODE, 8, false>(sh, a, st);
+    return a.order.turn ? launch<MODE, 4, true>(sh, a, st) : launch<MODE, 4, false>(sh, a, st);
+}
+
 hipError_t launch_attn_fp32_split(const Shape& sh, Args32& a, hipStream_t st) {
-    const bool sparse = a.idx != nullptr, eight = attn_fp32_split_waves(sh, sparse) == 8;
-    if (sparse) return eight ? launch<1, 8>(sh, a, st) : launch<1, 4>(sh, a, st);
-    return eight ? launch<2, 8>(sh, a, st) : launch<2, 4>(sh, a, st);
+    const bool sparse = a.idx != nullptr;
+    const int waves = attn_fp32_split_waves(sh, sparse);
+    a.qtiles = attn_fp32_qtiles(sh, sparse, TQ);
+    a.order = attn_fp32_order(sh, sparse, TQ, waves);
+    return sparse ? launch_waves<1>(sh, a, waves, st) : launch_waves<2>(sh, a, waves, st);
 }
 
 }  // namespace cp

@@ -109,6 +109,12 @@ struct TileOrder {
         return o;
     }
     __host__ __device__ __forceinline__ unsigned place(unsigned id) const { return id < turn ? turn - 1 - id : id; }
+    // segments from the last to the first
+    __host__ __device__ __forceinline__ Item by_segments(unsigned rank, unsigned qtiles) const {
+        const unsigned at = most - 1 - rank, segment = by_tiles.div(at);
+        return {(int)segment, (int)(at - segment * qtiles)};
+    }
+    // by the keys that they see
     __host__ __device__ __forceinline__ Item item(unsigned rank, unsigned n1, unsigned qtiles) const {
         const unsigned above = (past + qtiles - most) * full;    // of full segments, with more keys than all others
         unsigned seen, x;                 // tiles' worth of keys; which of those that see as many

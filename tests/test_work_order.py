@@ -34,7 +34,8 @@ extern "C" void tiles(int n1, int r, int budget, int local, int b, int qtiles, i
 extern "C" int launched(int waves, long long wgs, long long with_rows, int n1, int r, int budget, int local, int b, int qtiles, int rows, int* out) {
     const cp::TileOrder o = cp::TileOrder::of_launch(waves, wgs, with_rows, n1, r, budget, local, b, qtiles, rows);
     for (int rank = 0; rank < n1 * qtiles; ++rank) {
-        const auto t = o.item(rank, n1, qtiles);
+        const auto t = o.turn ? o.item(rank, n1, qtiles) : o.by_segments(rank, qtiles), u = o.item(rank, n1, qtiles);
+        if (t.segment != u.segment || t.tile != u.tile) return -1;
         out[2 * rank] = t.segment; out[2 * rank + 1] = t.tile;
     }
     return o.turn;
