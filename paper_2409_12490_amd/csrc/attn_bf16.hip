@@ -83,12 +83,12 @@ __global__ __launch_bounds__(512, 1) void attn_bf16_kernel(ArgsIndex ix, ArgsB a
     if (DENSE) {
         // heaviest query tiles first; consecutive workgroups walk the KV heads so that the query
         // heads sharing one KV head land on the same XCD (workgroup id mod 8) at the same time.
-        const unsigned y = ix.order.by_heads.div(wg), x = wg - y * ix.order.set_heads;
+        const unsigned y = ix.order.by_heads.div(wg), x = wg - y * (ix.order.set_kv * (unsigned)a.group);
         qt = a.qtiles - 1 - (int)y;
         const unsigned gq = ix.order.by_kv.div(x), bkvh = x - gq * ix.order.set_kv;
         bb = (int)ix.div_hkv.div(bkvh); g = (int)bkvh - bb * a.hkv; h = g * a.group + (int)gq;
     } else {
-        const WorkOrder::Item item = ix.order.item(wg, kRound, (unsigned)a.n1, (unsigned)a.qtiles);
+        const WorkOrder::Item item = ix.order.item(wg, kRound, (unsigned)a.group, (unsigned)a.n1, (unsigned)a.qtiles);
         bb = (int)ix.div_hkv.div((unsigned)item.bkv); g = item.bkv - bb * a.hkv; h = g * a.group + item.gq; j = item.segment; qt = item.tile;
     }
     const int q_lo = DENSE ? qt * TQ : j * a.s + qt * TQ;

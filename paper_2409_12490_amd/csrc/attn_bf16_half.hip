@@ -52,7 +52,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_bf16_half_kernel(ArgsInde
     // every argument in one go, as in the 256-row kernel
     ask_for(ix.order.full, ix.order.by_kv.shift, ix.div_hkv.mul, ix.div_b.mul, a.q, a.k, a.v, a.idx, a.cnt, a.n, a.s, a.qs0, a.qs1, a.qs2, a.ks0, a.ks1, a.ks2, a.list_len,
             a.scale_log2e);
-    const WorkOrder::Item item = ix.order.item(workgroup_id(), kRound, (unsigned)a.n1, (unsigned)a.qtiles);
+    const WorkOrder::Item item = ix.order.item(workgroup_id(), kRound, (unsigned)a.group, (unsigned)a.n1, (unsigned)a.qtiles);
     const int bb = (int)ix.div_hkv.div((unsigned)item.bkv), g = item.bkv - bb * a.hkv, h = g * a.group + item.gq, j = item.segment, qt = item.tile;
     const int q_lo = j * a.s + qt * TQ;
     const int q_end = min(a.n, (j + 1) * a.s);

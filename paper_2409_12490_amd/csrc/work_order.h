@@ -17,11 +17,12 @@
 // 124.9 / 120.1, 16/16 x 8283 (512, 32; 16) 83.3 / 72.2, 128-row workgroups 4/2 x 37083 (256, 16; 4) 41.5 / 39.7.  With more, the tiles of a segment come too
 // far apart: 16/16 x 47963 (1024, 64; 32) 942 / 969, 128-row 32/8 x 6123 (256, 16; 4) 44.4 / 46.7, 8/2 x 20443 (256, 16; 30) 71.8 / 73.5.
 //
-// Consecutive workgroups walk the KV heads of a set.  Up to 64 MiB of keys and values all KV heads are one set, which leaves fewer rounds that are not
-// full (36/12 x 10000 in sets of 4 376 instead of 366).  More of them are walked 8, 4, 2 or 1 at a time, the largest of these that divides their
-// number, so that every eighth workgroup, an XCD's, reads the keys of one KV head: all together / in sets, 2 x 32/8 x 34000 (256, 32; 32) 1371 / 1336
-// (sets of 4 1333), 65536 2668 / 2581 (2583); 36/12 x 14000 (512, 64; 32) 535 / 529, 49152 1976 / 1912; 40/10 x 65536 2906 / 2810.  An odd number goes one
-// at a time, which is better than together but 1 to 2 % behind neighbouring segments on one XCD: 25/5 x 65536 1856 / 1810, where that takes 1754.
+// Consecutive workgroups walk the KV heads of a set.  Up to 64 MiB of keys and values all KV heads are one set, which leaves fewer rounds that are
+// not full (36/12 x 10000 in sets of 4 376 instead of 366).  More of them are walked 8, 4, 2 or 1 at a time, the largest of these that divides
+// their number, so that every eighth workgroup, an XCD's, reads the keys of one KV head: all together / in sets, 2 x 32/8 x 34000 (256, 32; 32)
+// 1371 / 1336 (sets of 4 1333), 65536 2668 / 2581 (2583); 36/12 x 14000 (512, 64; 32) 535 / 529, 49152 1976 / 1912; 40/10 x 65536 2906 / 2810.  An
+// odd number goes one at a time, and an XCD gets neighbouring segments of a round, whose lists are alike (every eighth of them / neighbours: 25/5 x
+// 65536 1806 / 1746, 9/3 x 100000 1003 / 975, 15/15 x 40000 704 / 680; not for one KV head alone, 8/1 x 9000 (256, 32; 32) 63.5 -> 67.6).
 #pragma once
 #include "fast_div.h"
 
@@ -29,7 +30,7 @@ namespace cp {
 
 struct WorkOrder {
     struct Item { int bkv, gq, segment, tile; };    // (batch, KV head), query head in its group
-    unsigned full, rest, set_kv, set_heads;    // pairs in whole rounds and behind them; KV heads and heads of a set
+    unsigned full, rest, set_kv, neighbours;   // pairs in whole rounds and behind them; KV heads of a set; whether an XCD gets neighbouring pairs
     FastDiv by_round, by_rest, by_set, by_heads, by_kv;
 
     WorkOrder() = default;
@@ -37,19 +38,22 @@ struct WorkOrder {
     WorkOrder(unsigned bkv, unsigned group, unsigned n1, unsigned qtiles, unsigned round, long long kv_bytes) {
         const unsigned least = bkv & (0u - bkv);        // the largest power of two that divides it
         set_kv = kv_bytes <= (64ll << 20) ? bkv : least < 8 ? least : 8;
-        set_heads = set_kv * group;
+        neighbours = set_kv < bkv && set_kv == 1;
+        const unsigned set_heads = set_kv * group;
         const unsigned pairs = bkv * group * n1;
         rest = pairs * qtiles < 2 * round + 256 ? pairs : pairs % round;
         full = pairs - rest;
         by_round = FastDiv(round * qtiles); by_rest = FastDiv(rest ? rest : 1);
         by_set = FastDiv(set_heads * n1); by_heads = FastDiv(set_heads); by_kv = FastDiv(set_kv);
     }
-    __host__ __device__ __forceinline__ Item item(unsigned wg, unsigned round, unsigned n1, unsigned qtiles) const {    // round as a constant of the kernel
+    __host__ __device__ __forceinline__ Item item(unsigned wg, unsigned round, unsigned group, unsigned n1, unsigned qtiles) const {    // round as a constant of the kernel
         Item t; unsigned u;
+        const unsigned set_heads = set_kv * group;
         if (wg < full * qtiles) {
             const unsigned rd = by_round.div(wg), y = wg - rd * round * qtiles;
             t.tile = (int)(qtiles - 1 - y / round);
-            u = rd * round + y % round;
+            const unsigned p = y % round;
+            u = rd * round + (neighbours ? p % 8 * (round / 8) + p / 8 : p);
         } else {
             const unsigned y = wg - full * qtiles, z = by_rest.div(y);
             t.tile = (int)(qtiles - 1 - z);
