@@ -355,21 +355,22 @@ hipError_t launch_tiled(const Shape& sh, Args32& a, hipStream_t st) {
 
 }  // namespace
 
-// 16 rows to a workgroup: what is left to this kernel are launches that 32 rows would not fill the chip with, or not evenly (attn_fp32_split_better).  Eight waves
-// split a long row further, four are better where rows are short.  Attention alone, us, four / eight waves (row tiles in brackets): dense 8 heads x 512 tokens (256)
-// 13.5 / 14.6, 1 x 3000 (188) 57.5 / 56.2; block-sparse 1 x 2100 (132; 384 keys) 12.0 / 12.4, 1 x 3000 (188; 1056) 25.4 / 24.0, 1 x 4000 (250; 1216) 28.3 / 27.2, 2 x 1500
-// (188; all keys) 34.1 / 31.8.  Rows of more than 1024 keys have eight at any number of tiles, because their sums are longer with four: 1 head x 1025 to 2048
-// tokens is 3.49e-7 from float64 with four, 3.15e-7 with eight (four in the two workgroups of attn_fp32_tile_parts would take up to 6 % less: dense
-// 1 x 1025 19.3 / 20.4, 1 x 2048 34.3 / 35.9; block-sparse 1 x 1500 (94; 1280) 27.6 / 28.1, 1 x 2048 (128; all keys) 36.4 / 36.2).
+// 16 rows to a workgroup: what is left to this kernel are launches that 32 rows would not fill the chip with, or not evenly (attn_fp32_split_better).
+// Eight waves split a long row further, four are better where rows are short.  Attention alone, us, four / eight waves (row tiles in brackets): dense 8
+// heads x 512 tokens (256) 13.5 / 14.6, 1 x 3000 (188) 57.5 / 56.2; block-sparse 1 x 2100 (132; 384 keys) 12.0 / 12.4, 1 x 3000 (188; 1056) 25.4 / 24.0,
+// 1 x 4000 (250; 1216) 28.3 / 27.2, 2 x 1500 (188; all keys) 34.1 / 31.8.  Rows of more than 1024 keys have eight at any number of tiles, because their
+// sums are longer with four: 1 head x 1025 to 2048 tokens is 3.49e-7 from float64 with four, 3.15e-7 with eight (four in the two workgroups of
+// attn_fp32_tile_parts would take up to 6 % less: dense 1 x 1025 19.3 / 20.4, 1 x 2048 34.3 / 35.9; block-sparse 1 x 1500 (94; 1280) 27.6 / 28.1, 1 x
+// 2048 (128; all keys) 36.4 / 36.2).
 int attn_fp32_tile_waves(const Shape& sh, bool sparse) {
     return (sparse ? min((long long)sh.n, (long long)sh.list_len * sh.b) : sh.n) > 1024 ? 8 : 4;
 }
 
-// Up to 128 row tiles two workgroups take a tile, each with half of its channels of V and O: the products of Q and K are made twice, 48 matrix instructions
-// a tile of keys instead of 64, on compute units that would be idle.  One / two workgroups (row tiles), the same bits: block-sparse 1 x 2048 (128; 384 keys) 11.6 / 10.2, 1 x 915 (58, all keys)
-// 22.4 / 18.8, 2 x 1000 (126; 640) 16.5 / 13.9, 1 x 1500 (94; 768) 18.9 / 16.1; dense 1 x 512 (32) 13.0 / 11.0, 3 x 600 (114) 15.4 / 13.1, 1 x 2048 (128) 40.1 / 35.9.
-// Above, some units get two: 3 x 1300 (246) 23.8 / 36.2, 2 x 1500 (188) 31.4 / 44.4.  Four workgroups gain no more on 64 tiles and less (1 x 915
-// 18.6, dense 1 x 1000 19.4 against 19.0).
+// Up to 128 row tiles two workgroups take a tile, each with half of its channels of V and O: the products of Q and K are made twice, 48 matrix
+// instructions a tile of keys instead of 64, on compute units that would be idle.  One / two workgroups (row tiles), the same bits: block-sparse 1 x
+// 2048 (128; 384 keys) 11.6 / 10.2, 1 x 915 (58, all keys) 22.4 / 18.8, 2 x 1000 (126; 640) 16.5 / 13.9, 1 x 1500 (94; 768) 18.9 / 16.1; dense 1 x 512
+// (32) 13.0 / 11.0, 3 x 600 (114) 15.4 / 13.1, 1 x 2048 (128) 40.1 / 35.9. Above, some units get two: 3 x 1300 (246) 23.8 / 36.2, 2 x 1500 (188) 31.4 /
+// 44.4.  Four workgroups gain no more on 64 tiles and less (1 x 915 18.6, dense 1 x 1000 19.4 against 19.0).
 int attn_fp32_tile_parts(const Shape& sh, bool sparse) { return attn_fp32_row_tiles(sh, sparse, 16) <= 128 ? 2 : 1; }
 
 hipError_t launch_attn_fp32(const Shape& sh, const void* q, const void* k, const void* v, const int32_t* idx,

@@ -11,8 +11,9 @@ constexpr int kHeadDim = 128;
 constexpr int kMaxListBf16 = 6144;    // block-list entries the bf16 attention kernel keeps in LDS
 
 // At the start of a kernel, every argument that its first loads need, in one go: the compiler loads an argument where it is used, one latency after
-// another, three to five before the first load of a small kernel.  Layers of 1 x 2048 fp32 21.8 -> 21.3 us, 2 x 600 fp32 20.7 -> 20.0, 8/2 x 1000 22.9 -> 22.1;
-// estimate 4 x 700 12.2 -> 11.6, dense 2 x 512 6.64 -> 6.52.  (Not kept: in the selection 15.7 -> 15.9 us at 32/8 x 128K, with more scalar registers spilled.)
+// another, three to five before the first load of a small kernel.  Layers of 1 x 2048 fp32 21.8 -> 21.3 us, 2 x 600 fp32 20.7 -> 20.0, 8/2 x 1000 22.9
+// -> 22.1; estimate 4 x 700 12.2 -> 11.6, dense 2 x 512 6.64 -> 6.52.  (Not kept: in the selection 15.7 -> 15.9 us at 32/8 x 128K, with more scalar
+// registers spilled.)
 template <typename T>
 __device__ __forceinline__ void ask_for_one(const T& x) { asm volatile("" ::"s"(x)); }
 template <typename... T>
